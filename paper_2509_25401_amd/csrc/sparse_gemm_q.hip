@@ -1,14 +1,19 @@
 // Sparse query projection (GEMM-Q of the paper, Section 3.5, Observation 2 / Equation 2) for gfx950.
 //
-// Q[b,h,i-th block,:] = X[b, i-th block, :] . W_h^T (+ bias_h) for every (b,h,i) whose cache flag
-// is clear; a workgroup whose tile is flagged returns at once (its attention output is reused from
-// the cache, so its queries are never read).  One workgroup per (query block, head) output tile, the
-// same granularity as the flags, written straight into the [B,H,L,D] layout the attention kernel
-// reads.  The product is computed transposed, C^T[d][token] = sum_k W[d][k] X[token][k], with
-// v_mfma_f32_32x32x16_bf16: both operands are "k contiguous" rows (A = weight rows, B = token
-// rows), so both come out of LDS with plain 16-byte reads, and a lane ends up holding 4 consecutive
-// d of one token, which stores as 8 bytes.  X and W tiles stream to LDS with direct-to-LDS loads,
-// 64 channels per stage, double buffered.
+// Q[b,h,i-th block,:] = X[b, i-th block, :] . W_h^T (+ bias_h) for every (b,h,i) whose cache flag is clear; a flagged
+// block is left alone (its attention output is reused from the cache, so its queries are never read).  Without flags
+// the product is tiled like a dense one (256 x 256: two heads at a time); with flags a tile is one head and two (or
+// four) of its computed query blocks, found by ballots over the head's flags.  The product is computed transposed,
+// C^T[d][token] = sum_k W[d][k] X[token][k], with v_mfma_f32_32x32x16_bf16: both operands are "k contiguous" rows (A =
+// weight rows, B = token rows), so both come out of LDS with plain 16-byte reads, and a lane ends up holding 4
+// consecutive d of one token.  The result leaves through LDS as whole rows of the [B,H,L,D] layout that the attention
+// kernel reads.
+//
+// What bounds it (33024 tokens, C = 3072, 24 heads of 128, inputs that are not in the caches).  Dense: power; the
+// matrix pipe is busy 71 % of a round at 1.73 GHz, where one tile alone on the chip runs at 2.4 GHz and 87 %: 632 -> 508
+// us (1227 TFLOP/s), with RMSNorm and RoPE 737 -> 540 us; the 128 x 128 tiles it replaces streamed 64 KB from L2 per
+// 1024 MFMA cycles of a CU, these 32.  Few computed blocks: what leaves L2 (0.9 GB at 80 % cached, 5.6 TB/s: a token
+// block's rows are wanted by heads whose weights live on different XCDs).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -36,6 +41,7 @@ struct GemmQParams {
   const uint8_t* flags;  // [B, H, Tq] or nullptr
   char* Q;             // bf16 [B, H, L, D]
   int H, L, C, Tq;
+  int tok_begin, tok_end;   // tokens of every sequence that this launch works on (whole sequences where flags are given)
   // fused epilogue (NORM_ROPE instantiations only)
   const uint16_t* norm_w;   // bf16 [D] or nullptr (= ones)
   const float* rope_cos;    // fp32 [L, D/2] or nullptr (= no rotation)
@@ -43,24 +49,29 @@ struct GemmQParams {
   float eps;
 };
 
-template <int BQ, int D, bool NORM_ROPE>
-__global__ void __launch_bounds__((BQ / 64) * (D / 64) * 64, 2) gemm_q_kernel(const GemmQParams p) {
-  constexpr int WM = BQ / 64;              // waves along tokens
-  constexpr int WN = D / 64;               // waves along head channels
+// TM tokens x TN channels per workgroup, WM x WN waves, WB / XB LDS buffers.  BQ > 0: the tokens are TM / BQ query
+// blocks of one head (TN = D) whose flags are clear, wherever in the sequence they lie; BQ = 0: TM consecutive tokens.
+template <int TM, int TN, int WM, int WN, int WB, int XB, int D, int BQ, bool NORM_ROPE>
+__global__ void __launch_bounds__(WM * WN * 64, 2) gemm_q_kernel(const GemmQParams p) {
+  using Pipe = sa_gemm::Pipe<TN, TM, WN, WM, WB, XB>;
   constexpr int NWAVES = WM * WN;
-  using Stage = sa_gemm::Stages<D, BQ, NWAVES>;   // weight rows = the head's D channels, token rows = the query block
-  constexpr int TS = D / 2 + 2;            // padded row of the cos / sin tiles in LDS (floats)
-
-  // tile of this workgroup: head fastest, so the 8 XCDs (workgroup n runs on XCD n mod 8) each keep
-  // the weights of a fixed set of heads in their L2
-  const int t = blockIdx.x;
-  const int h = t % p.H;
-  const int i = (t / p.H) % p.Tq;
-  const int b = t / (p.H * p.Tq);
-  if (p.flags && p.flags[((size_t)b * p.H + h) * p.Tq + i]) return;   // spatial-axis symbol says: cached
+  constexpr int NT = NWAVES * 64;
+  constexpr int A = Pipe::kA, C = Pipe::kC;
+  constexpr int CW = TN / WN, TW = TM / WM;       // channels / tokens of a wave's corner
+  constexpr int HPW = CW >= D ? CW / D : 1;       // heads of which a wave holds all channels (or one in part)
+  constexpr int NB = CW >= D ? D / 32 : CW / 32;  // 32-channel blocks of a head in a wave
+  constexpr int BR = BQ > 0 ? BQ : TM;            // consecutive tokens
+  constexpr int NG = TM / BR;                     // runs of them
+  static_assert(CW >= D || (CW * 2 == D && WN == 2), "a head lies in one wave or in two");
+  static_assert(BQ == 0 || (TN == D && TM % BR == 0 && BR % TW == 0), "a gathered tile is whole blocks of one head");
+  // LDS after the reduction loop: cos and sin rows of the tile, later the waves' output corners; behind them the bias
+  // and gain as floats and the row sums of heads that lie in two waves
+  constexpr int TABB = TM * (D / 2) * 4;          // bytes of one table
+  constexpr int kVec = 2 * TABB > TM * TN * 2 ? 2 * TABB : TM * TN * 2;
+  constexpr int kGain = kVec + TN * 4;
+  constexpr int kPart = kGain + D * 4;
 
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  // layout: W stage 0, W stage 1, X stage 0, X stage 1
   const unsigned lds_base = (unsigned)(uintptr_t)(LDS_PTR(char))smem;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -68,169 +79,250 @@ __global__ void __launch_bounds__((BQ / 64) * (D / 64) * 64, 2) gemm_q_kernel(co
   const int wm = wave % WM, wn = wave / WM;
   const int l32 = lane & 31, half = lane >> 5;
 
-  const size_t row_pitch = (size_t)p.C * 2;
-  const char* gW = p.W + (size_t)h * D * row_pitch;
-  const char* gX = p.X + ((size_t)b * p.L + (size_t)i * BQ) * row_pitch;
-  // the last token block may be short: loads of missing rows re-read the last row that exists, their results
-  // are never stored
-  const int rows_valid = min(BQ, p.L - i * BQ);
-
-  Stage st;
-  st.init(lds_base, wave, lane, wn, wm, row_pitch, row_pitch, rows_valid);
-  auto issue = [&](int kstep, auto stage_c) {
-    st.template issue<decltype(stage_c)::value>(gW + (size_t)kstep * kRowB, gX + (size_t)kstep * kRowB);
+  // tile of this workgroup: column tile ct, batch b, and the token runs: first token, tokens that exist
+  int ct, b;
+  int tok0[NG], rows[NG];
+  const int n_col = (p.H * D + TN - 1) / TN;
+  if constexpr (BQ > 0) {
+    // head fastest, so every XCD keeps the weights of a fixed set of heads in its L2; the tiles past a head's last
+    // computed block come last in the grid
+    const int n_tok = (p.Tq + NG - 1) / NG;
+    ct = blockIdx.x % n_col;
+    const int j = (blockIdx.x / n_col) % n_tok;
+    b = blockIdx.x / (n_col * n_tok);
+    // the computed blocks number NG * j .. NG * j + NG - 1 of this head: ballots over the flags, 64 blocks per wave
+    const uint8_t* fr = p.flags + ((size_t)b * p.H + ct) * p.Tq;
+    unsigned long long* const masks = (unsigned long long*)smem;
+    int seen = 0, blk[NG];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) blk[g] = -1;
+    for (int c0 = 0; c0 < p.Tq && blk[NG - 1] < 0; c0 += NT) {
+      const unsigned long long live = __builtin_amdgcn_ballot_w64(c0 + tid < p.Tq && fr[min(c0 + tid, p.Tq - 1)] == 0);
+      if (lane == 0) masks[wave] = live;
+      __syncthreads();
+      for (int w = 0; w < NWAVES; ++w) {
+        const unsigned long long mv = masks[w];
+        // (readfirstlane returns int: through unsigned, or bit 31 would be spread over the upper word)
+        const unsigned m_lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)mv);
+        const unsigned m_hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(mv >> 32));
+        const unsigned long long m = (unsigned long long)m_hi << 32 | m_lo;
+        const int count = __popcll(m);
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+          const int rank = NG * j + g - seen;     // among the set bits of this word
+          if (rank >= 0 && rank < count) {
+            const bool here = ((m >> lane) & 1ull) && __popcll(m & ((1ull << lane) - 1ull)) == rank;
+            blk[g] = c0 + 64 * w + __builtin_ctzll(__builtin_amdgcn_ballot_w64(here));
+          }
+        }
+        seen += count;
+      }
+      __syncthreads();                            // the masks are rewritten, or a stage lands on them
+    }
+    if (blk[0] < 0) return;
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      tok0[g] = (blk[g] < 0 ? blk[0] : blk[g]) * BR;   // a missing block re-reads the first one
+      rows[g] = blk[g] < 0 ? 0 : min(BR, p.L - tok0[g]);
+    }
+  } else {
+    const int n_tok = (p.tok_end - p.tok_begin + TM - 1) / TM;
+    int i;
+    if constexpr (TN > 128) {
+      // The 8 XCDs (workgroup n runs on XCD n mod 8) take a contiguous part each of the tiles in the order: batch,
+      // group of 4 column tiles, token tile, column tile.  The 32 tiles an XCD works on at a time are then 4 column
+      // tiles x 8 token tiles: the stage loads of 12 operand tiles serve 32 workgroups.
+      const int tiles = (int)gridDim.x, x = blockIdx.x % 8, at = blockIdx.x / 8;
+      int n = x * (tiles / 8) + min(x, tiles % 8) + at;
+      b = n / (n_col * n_tok);
+      n -= b * (n_col * n_tok);
+      const int g = n / (4 * n_tok), width = min(4, n_col - 4 * g);
+      n -= g * 4 * n_tok;
+      i = n / width;
+      ct = 4 * g + n % width;
+    } else {
+      // column tile fastest: every XCD keeps the weights of a fixed set of column tiles in its L2
+      ct = blockIdx.x % n_col;
+      i = (blockIdx.x / n_col) % n_tok;
+      b = blockIdx.x / (n_col * n_tok);
+    }
+    tok0[0] = p.tok_begin + i * TM;
+    rows[0] = min(TM, p.tok_end - tok0[0]);       // the last token tile may be short
+  }
+  // first token and rows of the run that tile row r lies in
+  auto pick = [](const int (&v)[NG], int g) {
+    // (all values first: a choice between elements would put the array into scratch memory)
+    const int v0 = v[0], v1 = v[NG > 1 ? 1 : 0], v2 = v[NG > 2 ? 2 : 0], v3 = v[NG > 2 ? 3 : 0];
+    const int lo = NG > 1 && (g & 1) ? v1 : v0, hi = NG > 2 && (g & 1) ? v3 : v2;
+    return NG > 2 && (g & 2) ? hi : lo;
   };
+  static_assert(NG == 1 || NG == 2 || NG == 4, "pick() knows these");
+  auto run_tok0 = [&](int r) { return pick(tok0, r / BR); };
+  auto run_rows = [&](int r) { return pick(rows, r / BR); };
 
-  f32x16 acc[2][2];   // [d block][token block] of this wave's 64x64 corner
+  const size_t row_pitch = (size_t)p.C * 2;
+  const int n0 = ct * TN;                         // first output channel of the tile
+  const int cols_valid = min(TN, p.H * D - n0);   // the last column tile may be short
+  const char* gW = p.W + (size_t)n0 * row_pitch;
+  Pipe st;
+  st.init(lds_base, wave, lane, wn, wm, row_pitch, cols_valid);
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int u = 0; u < Pipe::kXLoad; ++u) {
+    // a load covers 8 rows of one run; rows that do not exist re-read the last one that does and are never stored
+    const int r0 = (wave + u * NWAVES) * 8, r = r0 + lane / 8;
+    st.set_x_rows(u, sa_uniform_ptr(p.X + ((size_t)b * p.L + run_tok0(r0)) * row_pitch),
+                  min(r % BR, max(run_rows(r0), 1) - 1), row_pitch, lane);
+  }
+
+  f32x16 acc[A][C];   // [channel block][token block] of this wave's corner
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
+  for (int a = 0; a < A; ++a)
+#pragma unroll
+    for (int c = 0; c < C; ++c)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[a][c][e] = 0.f;
 
-  auto compute = [&](auto stage_c) { st.template mfma<decltype(stage_c)::value>(smem, acc); };
+  size_t k_off = 0;
+  st.run(
+      smem, acc, p.C / kStepK,
+      [&]() {
+        const char* at = gW;
+        gW += kRowB;
+        return at;
+      },
+      [&]() {
+        const size_t at = k_off;
+        k_off += kRowB;
+        return at;
+      });
+  __syncthreads();                                // every wave is done reading the operand stages
 
-  using S0 = std::integral_constant<int, 0>;
-  using S1 = std::integral_constant<int, 1>;
-  const int nk = p.C / kStepK;
-  issue(0, S0{});
-  int k = 0;
-  for (; k + 1 < nk; k += 2) {   // two stages per trip, one per LDS buffer
-    sa_wait_vmem();   // this wave's part of the stage has landed
-    __syncthreads();
-    issue(k + 1, S1{});
-    compute(S0{});
-    sa_wait_vmem();
-    __syncthreads();
-    if (k + 2 < nk) issue(k + 2, S0{});
-    compute(S1{});
+  // ---- epilogue: lane holds token 32 * c + l32 and, per accumulator quad q4, channels 32 * a + 8 * q4 + 4 * half
+  // + 0..3 of this wave's corner
+  float* const bias_f = (float*)(smem + kVec);
+  float* const gain_f = (float*)(smem + kGain);
+  if (p.bias) {
+    for (int e = tid; e < TN; e += NT) bias_f[e] = __builtin_bit_cast(float, (unsigned)p.bias[min(n0 + e, p.H * D - 1)] << 16);
   }
-  if (k < nk) {                  // odd number of stages: the last one sits in buffer 0
-    sa_wait_vmem();
-    __syncthreads();
-    compute(S0{});
-  }
-
-  // epilogue: lane holds token l32 (+32*c) and, per accumulator quad q4, head channels
-  // 32*a + 8*q4 + 4*half + 0..3 of this wave's corner
-  float inv_rms[2] = {1.f, 1.f};
+  constexpr int CHT = D / 8;                      // 16-byte chunks of a table row
+  auto tab_swizzle = [](int row) { return CHT == 16 ? (row & 15) : ((row >> 1) & 7); };
   if constexpr (NORM_ROPE) {
-    // Equation 2: token-wise RMS normalisation over the head's D channels, then the rotation.  The bias
-    // goes into the accumulators first; a token's sum of squares is spread over this lane's 32 values,
-    // the lane 32 further on, and (D = 128) the wave that holds the other 64 channels.
-    if (p.bias) {
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float bv = __builtin_bit_cast(float, (unsigned)p.bias[h * D + wn * 64 + 32 * a + 8 * q4 + 4 * half + e] << 16);
-            acc[a][0][4 * q4 + e] += bv;
-            acc[a][1][4 * q4 + e] += bv;
-          }
+    if (p.norm_w) {
+      for (int e = tid; e < D; e += NT) gain_f[e] = __builtin_bit_cast(float, (unsigned)p.norm_w[e] << 16);
     }
-    // The tile's cos / sin rows (one contiguous block of the tables) come through LDS: read straight
-    // from memory in the accumulator layout, every lane would fetch 8 bytes from its own 256-byte row,
-    // 64 dependent round trips per lane.  The operand stages are dead by now; rows are padded by two
-    // floats so that 32 lanes reading 8 bytes of 32 rows hit 64 different banks.
-    __syncthreads();                           // every wave is done reading the operand stages
-    float* tab = (float*)smem;                 // cos [BQ][TS], then sin [BQ][TS], then the sums [WN][BQ]
+    // The tile's cos / sin rows come through LDS: read straight from memory in
+    // the accumulator layout, every lane would fetch 8 bytes from its own row.  All loads are requested before the
+    // first is stored; 16-byte chunks are permuted by the token so that the 32 tokens of a read spread over the banks.
     if (p.rope_cos) {
-      constexpr int NV = BQ * (D / 2) / 4;     // 16-byte pieces per table
-      const float4* gc = (const float4*)(p.rope_cos + (size_t)i * BQ * (D / 2));
-      const float4* gs = (const float4*)(p.rope_sin + (size_t)i * BQ * (D / 2));
-      for (int e = tid; e < NV; e += NWAVES * 64) {
-        const bool there = (4 * e) / (D / 2) < rows_valid;          // the tables have L rows
-        const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
-        const float4 vc = there ? gc[e] : zero, vs = there ? gs[e] : zero;
-        const int o = (4 * e) / (D / 2) * TS + (4 * e) % (D / 2);
-        *(float2*)(tab + o) = make_float2(vc.x, vc.y);
-        *(float2*)(tab + o + 2) = make_float2(vc.z, vc.w);
-        *(float2*)(tab + BQ * TS + o) = make_float2(vs.x, vs.y);
-        *(float2*)(tab + BQ * TS + o + 2) = make_float2(vs.z, vs.w);
+      constexpr int PER = TABB / 16 / NT;
+      static_assert(TABB % (16 * NT) == 0, "table pieces must split evenly over the threads");
+      const float4* gc = (const float4*)p.rope_cos;
+      const float4* gs = (const float4*)p.rope_sin;
+      float4 vc[PER], vs[PER];
+#pragma unroll
+      for (int u = 0; u < PER; ++u) {
+        const int e = u * NT + tid, row = e / CHT;
+        const size_t at = (size_t)(run_tok0(row) + min(row % BR, max(run_rows(row), 1) - 1)) * CHT + e % CHT;
+        vc[u] = gc[at];
+        vs[u] = gs[at];
+      }
+#pragma unroll
+      for (int u = 0; u < PER; ++u) {
+        const int e = u * NT + tid, row = e / CHT;
+        const int o = row * CHT * 16 + ((e % CHT) ^ tab_swizzle(row)) * 16;
+        *(float4*)(smem + o) = vc[u];
+        *(float4*)(smem + TABB + o) = vs[u];
       }
     }
-    float ss[2];
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      float v = 0.f;
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) v = fmaf(acc[a][c][e], acc[a][c][e], v);
-      ss[c] = v + __shfl_xor(v, 32);
-    }
-    float* part = tab + 2 * BQ * TS;           // [WN][BQ]
-    if (WN == 2 && half == 0) {
-      part[wn * BQ + wm * 64 + l32] = ss[0];
-      part[wn * BQ + wm * 64 + 32 + l32] = ss[1];
-    }
-    __syncthreads();                           // tables and partial sums are in place
-    if constexpr (WN == 2) {
-      ss[0] = part[wm * 64 + l32] + part[BQ + wm * 64 + l32];
-      ss[1] = part[wm * 64 + 32 + l32] + part[BQ + wm * 64 + 32 + l32];
-    }
-#pragma unroll
-    for (int c = 0; c < 2; ++c) inv_rms[c] = 1.0f / sqrtf(ss[c] * (1.0f / D) + p.eps);
   }
+  __syncthreads();
+  if (p.bias) {
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < A; ++a)
 #pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) {
-      const int d0 = wn * 64 + 32 * a + 8 * q4 + 4 * half;
-      float bv[4] = {0.f, 0.f, 0.f, 0.f};
-      float gain[4] = {1.f, 1.f, 1.f, 1.f};
-      if constexpr (NORM_ROPE) {
-        if (p.norm_w) {
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const float4 bv = *(const float4*)(bias_f + wn * CW + 32 * a + 8 * q4 + 4 * half);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) gain[e] = __builtin_bit_cast(float, (unsigned)p.norm_w[d0 + e] << 16);
+        for (int c = 0; c < C; ++c) {
+          acc[a][c][4 * q4 + 0] += bv.x;
+          acc[a][c][4 * q4 + 1] += bv.y;
+          acc[a][c][4 * q4 + 2] += bv.z;
+          acc[a][c][4 * q4 + 3] += bv.w;
         }
-      } else if (p.bias) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          bv[e] = __builtin_bit_cast(float, (unsigned)p.bias[h * D + d0 + e] << 16);
       }
+  }
+  if constexpr (NORM_ROPE) {
+    // Equation 2: token-wise RMS normalisation over the head's D channels, then the rotation.  A token's sum of
+    // squares is spread over this lane's values, the lane 32 further on, and the other wave of a head in two waves.
+    float inv_rms[C][HPW];
 #pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        float y[4];
+    for (int c = 0; c < C; ++c)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) y[e] = acc[a][c][4 * q4 + e] + bv[e];
-        if constexpr (NORM_ROPE) {
+      for (int hh = 0; hh < HPW; ++hh) {
+        float v = 0.f;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) y[e] = y[e] * inv_rms[c] * gain[e];
+        for (int a = hh * NB; a < (hh + 1) * NB; ++a)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) v = fmaf(acc[a][c][e], acc[a][c][e], v);
+        inv_rms[c][hh] = v + __shfl_xor(v, 32);
+      }
+    if constexpr (CW < D) {
+      float* part = (float*)(smem + kPart);       // [WN][TM]
+#pragma unroll
+      for (int c = 0; c < C; ++c)
+        if (half == 0) part[wn * TM + wm * TW + 32 * c + l32] = inv_rms[c][0];
+      __syncthreads();
+#pragma unroll
+      for (int c = 0; c < C; ++c) inv_rms[c][0] = part[wm * TW + 32 * c + l32] + part[TM + wm * TW + 32 * c + l32];
+    }
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+      for (int hh = 0; hh < HPW; ++hh) inv_rms[c][hh] = 1.0f / sqrtf(inv_rms[c][hh] * (1.0f / D) + p.eps);
+#pragma unroll
+    for (int a = 0; a < A; ++a)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const int d0 = (wn * CW + 32 * a + 8 * q4 + 4 * half) % D;     // channel inside the head
+        float4 gain = make_float4(1.f, 1.f, 1.f, 1.f);
+        if (p.norm_w) gain = *(const float4*)(gain_f + d0);
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+          const float inv = inv_rms[c][a / NB % HPW];
+          float y0 = acc[a][c][4 * q4 + 0] * inv * gain.x, y1 = acc[a][c][4 * q4 + 1] * inv * gain.y;
+          float y2 = acc[a][c][4 * q4 + 2] * inv * gain.z, y3 = acc[a][c][4 * q4 + 3] * inv * gain.w;
           if (p.rope_cos) {
             // channels d0..d0+3 are the pairs d0/2 and d0/2 + 1 of this token
-            const float* tab = (const float*)smem;
-            const int at = (wm * 64 + 32 * c + l32) * TS + d0 / 2;
-            const float2 cs = *(const float2*)(tab + at);
-            const float2 sn = *(const float2*)(tab + BQ * TS + at);
-            const float y0 = y[0] * cs.x - y[1] * sn.x, y1 = y[0] * sn.x + y[1] * cs.x;
-            const float y2 = y[2] * cs.y - y[3] * sn.y, y3 = y[2] * sn.y + y[3] * cs.y;
-            y[0] = y0; y[1] = y1; y[2] = y2; y[3] = y3;
+            const int row = wm * TW + 32 * c + l32;
+            const char* at = smem + row * CHT * 16 + ((d0 / 8) ^ tab_swizzle(row)) * 16 + 8 * half;
+            const float2 cs = *(const float2*)at, sn = *(const float2*)(at + TABB);
+            const float r0 = y0 * cs.x - y1 * sn.x, r1 = y0 * sn.x + y1 * cs.x;
+            const float r2 = y2 * cs.y - y3 * sn.y, r3 = y2 * sn.y + y3 * cs.y;
+            y0 = r0; y1 = r1; y2 = r2; y3 = r3;
           }
+          acc[a][c][4 * q4 + 0] = y0;
+          acc[a][c][4 * q4 + 1] = y1;
+          acc[a][c][4 * q4 + 2] = y2;
+          acc[a][c][4 * q4 + 3] = y3;
         }
-        // the finished values go back into the accumulator registers; they leave through LDS below
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[a][c][4 * q4 + e] = y[e];
       }
-    }
-  // Output side.  A lane holds 4 channels of one token: written from here a store would be 8 bytes per lane, 256
-  // bytes apart.  The tile goes through LDS instead (rows of D bf16, 16-byte chunks XOR-permuted by the token so that
-  // the 32 tokens of a write hit different banks) and leaves as whole rows, 16 bytes per lane, with non-temporal
-  // stores: the projection writes its result once and must not push the weights and token rows out of L2 with it.
-  constexpr int ROWB_OUT = D * 2;            // bytes per token row of the tile
-  constexpr int CH = ROWB_OUT / 16;          // 16-byte chunks per row
-  __syncthreads();                           // every wave is done with the operand stages / the tables
+    __syncthreads();                              // every wave is done with the tables
+  }
+  // Output side.  A lane holds 4 channels of one token: written from here a store would be 8 bytes per lane, a row
+  // apart.  Every wave sends its corner through a piece of LDS of its own (rows of CW bf16, 16-byte chunks permuted by
+  // the token so that the 32 tokens of a write hit different banks) and stores whole rows, 16 bytes per lane, with
+  // non-temporal stores: the projection writes its result once and must not push the weights and token rows out of
+  // L2 with it.
+  constexpr int CHO = CW / 8;                     // 16-byte chunks per row of the corner
+  auto out_swizzle = [](int row) { return CHO == 16 ? (row & 15) : ((row >> 1) & 7); };
+  char* const corner = smem + wave * TW * CW * 2;
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < A; ++a)
 #pragma unroll
     for (int q4 = 0; q4 < 4; ++q4)
 #pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        const int d0 = wn * 64 + 32 * a + 8 * q4 + 4 * half;
-        const int token = wm * 64 + 32 * c + l32;
+      for (int c = 0; c < C; ++c) {
+        const int row = 32 * c + l32;
         bf16x2 lo, hi;
         lo[0] = (__bf16)acc[a][c][4 * q4 + 0];
         lo[1] = (__bf16)acc[a][c][4 * q4 + 1];
@@ -239,37 +331,89 @@ __global__ void __launch_bounds__((BQ / 64) * (D / 64) * 64, 2) gemm_q_kernel(co
         u32x2 pk;
         pk[0] = __builtin_bit_cast(unsigned, lo);
         pk[1] = __builtin_bit_cast(unsigned, hi);
-        *(u32x2*)(smem + token * ROWB_OUT + (((d0 / 8) ^ (token & (CH - 1))) * 16) + (d0 % 8) * 2) = pk;
+        *(u32x2*)(corner + row * CW * 2 + (((4 * a + q4) ^ out_swizzle(row)) * 16) + 8 * half) = pk;
       }
-  __syncthreads();
-  constexpr int NT = NWAVES * 64;
-  char* const out0 = p.Q + (((size_t)b * p.H + h) * p.L + (size_t)i * BQ) * (size_t)ROWB_OUT;
+  // (only this wave touches its corner: LDS accesses of a wave execute in order)
 #pragma unroll
-  for (int it = 0; it < BQ * CH / NT; ++it) {
-    const int token = it * (NT / CH) + tid / CH, ch = tid % CH;
-    const u32x4 v = *(const u32x4*)(smem + token * ROWB_OUT + ((ch ^ (token & (CH - 1))) * 16));
-    if (token < rows_valid) __builtin_nontemporal_store(v, (u32x4*)(out0 + (size_t)token * ROWB_OUT + ch * 16));
+  for (int it = 0; it < TW * CHO / 64; ++it) {
+    const int row = it * (64 / CHO) + lane / CHO, ch = lane % CHO;
+    const u32x4 v = *(const u32x4*)(corner + row * CW * 2 + ((ch ^ out_swizzle(row)) * 16));
+    const int r = wm * TW + row, n = wn * CW + ch * 8;                 // inside the tile
+    const int h = (n0 + n) / D, d = (n0 + n) % D;
+    char* const out = p.Q + ((((size_t)b * p.H + h) * p.L + run_tok0(wm * TW) + r % BR) * D + d) * 2;
+    if (r % BR < run_rows(wm * TW) && n < cols_valid) __builtin_nontemporal_store(v, (u32x4*)out);
   }
 }
 
-template <int BQ, int D, bool NORM_ROPE>
-int launch(const GemmQParams& p, int tiles, hipStream_t stream) {
-  constexpr size_t stage_lds = sa_gemm::Stages<D, BQ, (BQ / 64) * (D / 64)>::kLdsBytes;
-  constexpr size_t epi_lds = NORM_ROPE ? (size_t)(2 * BQ * (D / 2 + 2) + 2 * BQ) * 4 : 0;   // cos, sin tiles + row sums
+template <int TM, int TN, int WM, int WN, int WB, int XB, int D, int BQ, bool NORM_ROPE>
+int launch_tiles(const GemmQParams& p, int B, hipStream_t stream) {
+  constexpr size_t stage_lds = sa_gemm::Pipe<TN, TM, WN, WM, WB, XB>::kLdsBytes;
+  constexpr size_t out_lds = TM * D * 4 > TM * TN * 2 ? (size_t)TM * D * 4 : (size_t)TM * TN * 2;
+  constexpr size_t epi_lds = out_lds + (TN + D + WN * TM) * 4;
   constexpr size_t lds = stage_lds > epi_lds ? stage_lds : epi_lds;
-  constexpr int threads = (BQ / 64) * (D / 64) * 64;
+  static_assert(lds <= 160 * 1024, "LDS of a CU");
+  constexpr int threads = WM * WN * 64;
   static std::once_flag once;
   static hipError_t attr_err = hipSuccess;
   std::call_once(once, [] {
-    attr_err = hipFuncSetAttribute((const void*)gemm_q_kernel<BQ, D, NORM_ROPE>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   (int)lds);
+    attr_err = hipFuncSetAttribute((const void*)gemm_q_kernel<TM, TN, WM, WN, WB, XB, D, BQ, NORM_ROPE>,
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   });
   if (attr_err != hipSuccess)
     return sa_fail(SPARSE_ATTN_ERR_HIP, "hipFuncSetAttribute failed: %s", hipGetErrorString(attr_err));
-  hipLaunchKernelGGL((gemm_q_kernel<BQ, D, NORM_ROPE>), dim3(tiles), dim3(threads), lds, stream, p);
+  const int n_tok = BQ > 0 ? (p.Tq + TM / (BQ > 0 ? BQ : 1) - 1) / (TM / (BQ > 0 ? BQ : 1)) : (p.tok_end - p.tok_begin + TM - 1) / TM;
+  const int tiles = B * n_tok * ((p.H * D + TN - 1) / TN);
+  hipLaunchKernelGGL((gemm_q_kernel<TM, TN, WM, WN, WB, XB, D, BQ, NORM_ROPE>), dim3(tiles), dim3(threads), lds, stream, p);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return sa_fail(SPARSE_ATTN_ERR_HIP, "gemm_q launch failed: %s", hipGetErrorString(e));
   return 0;
+}
+
+// Which tile.  One workgroup of the 256-token kernels fills a CU, two of the 128 x 128 one do; the figures are the
+// plain projection at C = 3072, us.
+//   no flags   up to 256 tiles of 128 x 128 (one per CU): those (24 heads x 1024 tokens: 28 against 32 and 55 for the
+//              two larger tiles); up to 512: 256 x 128 (2048 tokens: 41 against 44 and 57); beyond: 256 x 256, which
+//              asks L2 for half as many bytes per product (4608 tokens: 72 against 82 and 84; 33024: 528 against 587
+//              and 605).  A last round of 256 x 256 tiles that would be less than half full is done with the smaller
+//              tiles instead (33024 tokens are 6.05 rounds: 508).
+//   flags      two (block_q 64: four) computed blocks of one head share their weight rows: 33024 tokens, 80 % cached:
+//              161 against 187 with a tile per block, 4608 tokens, 56 %: 43 against 63.  Few tiles in all: one per block.
+template <int D, bool NR>
+int launch(GemmQParams p, int B, int block_q, hipStream_t stream) {
+  const int heads_per_128 = 128 / D;
+  if (!p.flags) {
+    const int tok = p.tok_end - p.tok_begin;
+    const long long units = (long long)B * ((tok + 127) / 128) * ((p.H + heads_per_128 - 1) / heads_per_128);
+    if (units <= 256) return launch_tiles<128, 128, 2, 2, 2, 3, D, 0, NR>(p, B, stream);
+    if (units <= 512) return launch_tiles<256, 128, 4, 2, 3, 3, D, 0, NR>(p, B, stream);
+    const int n_col = (p.H * D + 255) / 256, n_tok = (tok + 255) / 256;
+    const long long tiles = (long long)B * n_tok * n_col, full = tiles / 256 * 256;
+    const int keep = (int)(full / ((long long)B * n_col));         // token tiles per sequence that fill whole rounds
+    if (tiles > full && tiles - full <= 128 && keep > 0) {
+      GemmQParams rest = p;
+      p.tok_end = rest.tok_begin = p.tok_begin + keep * 256;
+      if (int rc = launch_tiles<256, 256, 4, 2, 2, 3, D, 0, NR>(p, B, stream)) return rc;
+      return launch<D, NR>(rest, B, block_q, stream);
+    }
+    return launch_tiles<256, 256, 4, 2, 2, 3, D, 0, NR>(p, B, stream);
+  }
+  const long long blocks = (long long)B * p.H * p.Tq;
+  if constexpr (D == 128) {
+    if (block_q == 128) {
+      if (blocks <= 256) return launch_tiles<128, 128, 2, 2, 2, 3, 128, 128, NR>(p, B, stream);
+      return launch_tiles<256, 128, 4, 2, 3, 3, 128, 128, NR>(p, B, stream);
+    }
+    if (blocks <= 512) return launch_tiles<128, 128, 2, 2, 2, 3, 128, 64, NR>(p, B, stream);
+    return launch_tiles<256, 128, 4, 2, 3, 3, 128, 64, NR>(p, B, stream);
+  } else {
+    if (block_q == 128) {
+      if (blocks <= 512) return launch_tiles<128, 64, 2, 1, 2, 3, 64, 128, NR>(p, B, stream);
+      return launch_tiles<256, 64, 4, 1, 2, 2, 64, 128, NR>(p, B, stream);
+    }
+    if (blocks <= 512) return launch_tiles<64, 64, 1, 1, 2, 3, 64, 64, NR>(p, B, stream);
+    if (blocks <= 1024) return launch_tiles<128, 64, 2, 1, 2, 3, 64, 64, NR>(p, B, stream);
+    return launch_tiles<256, 64, 4, 1, 2, 2, 64, 64, NR>(p, B, stream);
+  }
 }
 
 bool ranges_overlap(const void* a, size_t na, const void* b, size_t nb) {
@@ -315,20 +459,14 @@ int gemm_q_run(const void* X, const void* W, const void* bias, const uint8_t* ca
   p.L = L;
   p.C = C;
   p.Tq = tq;
+  p.tok_begin = 0;
+  p.tok_end = L;
   p.norm_w = (const uint16_t*)norm_weight;
   p.rope_cos = rope_cos;
   p.rope_sin = rope_sin;
   p.eps = eps;
-  if (norm_rope) {
-    if (block_q == 128 && D == 128) return launch<128, 128, true>(p, (int)tiles, stream);
-    if (block_q == 128 && D == 64) return launch<128, 64, true>(p, (int)tiles, stream);
-    if (block_q == 64 && D == 128) return launch<64, 128, true>(p, (int)tiles, stream);
-    return launch<64, 64, true>(p, (int)tiles, stream);
-  }
-  if (block_q == 128 && D == 128) return launch<128, 128, false>(p, (int)tiles, stream);
-  if (block_q == 128 && D == 64) return launch<128, 64, false>(p, (int)tiles, stream);
-  if (block_q == 64 && D == 128) return launch<64, 128, false>(p, (int)tiles, stream);
-  return launch<64, 64, false>(p, (int)tiles, stream);
+  if (norm_rope) return D == 128 ? launch<128, true>(p, B, block_q, stream) : launch<64, true>(p, B, block_q, stream);
+  return D == 128 ? launch<128, false>(p, B, block_q, stream) : launch<64, false>(p, B, block_q, stream);
 }
 
 }  // namespace

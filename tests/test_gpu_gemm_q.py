@@ -194,3 +194,48 @@ def test_short_last_token_block(D, bq, L):
         err = np.abs(vals - ref[~skipped])
         assert (err <= np.abs(ref[~skipped]) * 2.0 ** -8 + 1e-3).all()
         assert (got[~skipped] == ref_bits[~skipped]).mean() > 0.98
+
+
+# every tile of the dispatch at its edges: (B, L, C, H, D, block_q, cached share or None for no flags, norm + rope)
+TILE_CASES = [
+    (1, 1, 64, 1, 64, 64, None, False),         # one token, one stage, half a column tile
+    (2, 129, 128, 3, 128, 64, None, True),      # 128 x 128 tiles, two stages, one token in the last tile
+    (1, 4097, 192, 16, 128, 128, None, True),   # 256 x 128 tiles (528 blocks), three stages
+    (1, 3000, 256, 21, 64, 128, None, False),   # 256 x 128 tiles, an odd number of 64-channel heads, four stages
+    (1, 8191, 320, 9, 128, 128, None, True),    # 256 x 256 tiles, last column tile half full
+    (2, 4300, 64, 19, 64, 64, None, True),      # 256 x 256 tiles, two sequences, last column tile a quarter full
+    (1, 11300, 64, 24, 64, 128, None, False),   # 256 x 256 tiles and the last token tiles done with the small ones
+    (1, 1000, 128, 5, 128, 128, 0.5, True),     # one block per tile
+    (1, 4700, 192, 11, 128, 128, 0.4, True),    # two blocks per tile, block 31 among them, short last block
+    (1, 2500, 64, 13, 128, 64, 0.7, False),     # four blocks of 64 per tile, some missing
+    (1, 300, 256, 3, 128, 64, 0.3, True),       # two blocks of 64 per tile
+    (1, 5000, 64, 17, 64, 128, 0.6, True),
+    (1, 900, 320, 3, 64, 64, 0.4, False),       # one block of 64 per tile
+    (1, 2600, 128, 17, 64, 64, 0.4, True),      # two
+    (1, 38500, 64, 2, 64, 64, 0.9, True),       # more than 512 blocks in a head: several passes over its flags
+]
+
+
+@pytest.mark.parametrize("B,L,C,H,D,bq,cached,fused", TILE_CASES)
+def test_every_tile_at_its_edges(B, L, C, H, D, bq, cached, fused):
+    print(f"[case] gemm_q tiles B={B} L={L} C={C} H={H} D={D} bq={bq} cached={cached} fused={fused}", flush=True)
+    X, W, b, _ = _case(70 + L, B, L, C, H, D, bq, cached=0.0)
+    flags = None
+    if cached is not None:
+        flags = (np.random.default_rng(71 + L).random((B, H, -(-L // bq))) < cached).astype(np.uint8)
+        flags[0, 0] = 1                                   # a head without a computed block
+        flags[0, 1] = 0                                   # one without a cached block
+    kw = {}
+    if fused:
+        g = synth.f32_to_bf16_bits((1.0 + 0.2 * np.random.default_rng(72).standard_normal(D)).astype(np.float32))
+        cos, sin = _rope_tables(L, D)
+        got = _run_fused(X, W, b, g, 1e-6, cos, sin, flags, B, L, C, H, D, bq)
+        kw = dict(norm_weight=g, eps=float(np.float32(1e-6)), rope_cos=cos, rope_sin=sin)
+    else:
+        got = _run(X, W, b, flags, B, L, C, H, D, bq)
+    ref, ref_bits = oracle.gemm_q(X, W, b, flags, bq, H, D, **kw)
+    skipped = np.zeros((B, H, L), dtype=bool) if flags is None else np.repeat(flags != 0, bq, axis=2)[:, :, :L]
+    assert (got[skipped] == 0x4242).all(), "skipped blocks were written"
+    vals, want = synth.bf16_bits_to_f32(got).astype(np.float64)[~skipped], ref[~skipped]
+    assert (np.abs(vals - want) <= np.abs(want) * 2.0 ** -8 + 1e-3).all()      # the bar of the module text
+    assert (got[~skipped] == ref_bits[~skipped]).mean() > 0.98
