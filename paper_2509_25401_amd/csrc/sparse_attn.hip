@@ -1,10 +1,11 @@
 // FlashOmni attention (Algorithm 1 of the paper) for AMD MI355X / gfx950.
 //
-// Three kernels per call, all on the caller's stream:
-//   plan_rows   decodes the packed symbols of Section 3.3 once per (b,h,i) row into aligned
+// Two kernels per call, both on the caller's stream (the second alone where the order of the rows does not matter:
+// few rows, or no symbols and at most two rows per workgroup):
+//   plan_queues decodes the packed symbols of Section 3.3 once per (b,h,i) row into aligned
 //               32-bit words (bit j of the row = key block j, padding cleared), counts the
 //               kept key blocks of every non-cached row and notes the first of them;
-//   plan_order  sorts the rows into one work queue per XCD (a head's rows all go to one XCD, so
+//               sorts the rows into one work queue per XCD (a head's rows all go to one XCD, so
 //               its K/V stream through one L2): rows that are a large part of a workgroup's
 //               share first (longest first), the others head by head and heaviest first inside a
 //               head (55 kept-count buckets), cached rows (plain copies) last;
@@ -66,12 +67,12 @@ constexpr int kXcds = 8;               // accelerator dies (XCDs) of the MI355X,
 constexpr int kMaxHeadGroups = 24;    // head groups per (XCD, bucket) in the ordering histogram (48 KiB of LDS)
 constexpr int kMaxTq = 16384;
 constexpr unsigned kCopyFlag = 0x80000000u;
-// Queue counters: every queue head sits in a 128-byte line of its own (all workgroups of an XCD bump the same
-// head once per item; eight heads in one line would make every workgroup of the chip contend for that line),
-// the queue ends, which the attention kernel only reads, in a line that is never written while it runs.
+// Queue counters: every queue head (items handed out so far) sits in a 128-byte line of its own: all workgroups of an
+// XCD bump the same head once per item; eight heads in one line would make every workgroup of the chip contend for
+// that line.  Behind them the number of workgroups that are done (stored plans).
 constexpr int kHeadStride = 32;                   // words between two queue heads
-constexpr int kEndOffset = 8 * kHeadStride;       // first queue end
-constexpr int kQueueWords = kEndOffset + 64;      // 1280 bytes
+constexpr int kDoneOffset = 8 * kHeadStride;
+constexpr int kQueueWords = kDoneOffset + 64;     // 1280 bytes
 constexpr int kHwRegXccId = (3 << 11) | 20;   // s_getreg operand: 4 bits at offset 0 of hardware register 20 (XCC_ID)
 constexpr int kOrderThreads = 1024;
 constexpr int kMaxTerms = 4;            // stored feature + up to three derivatives
@@ -85,9 +86,14 @@ struct AttnParams {
   const char* O_cache;
   char* O;
   const uint32_t* words;   // [N][nw32] decoded symbol words
-  const uint32_t* order;   // [N][2] work list: {row | kCopyFlag, sort key of the row (see plan_rows)}
-  uint32_t* queues;        // kXcds queue heads at [q * kHeadStride], kXcds queue ends at [kEndOffset + q]
+  const uint32_t* order;   // [N][2] work list: {row | kCopyFlag, sort key of the row (see plan_queues)}
+  uint32_t* queues;        // kXcds queue heads at [q * kHeadStride]; nullptr: items are dealt out by workgroup number
+  int self_reset;          // the last workgroup to finish clears the queue heads for the next run
+  const uint8_t* raw_flags;   // symbols as the caller gave them, nullptr: none (read where items are dealt out)
+  const uint8_t* raw_mask;
+  int raw_row_bytes;
   int N;                   // B*H*Tq
+  int BH;
   int Tq;
   int Tkv;
   int L;
@@ -104,52 +110,14 @@ struct AttnParams {
 // ---------------------------------------------------------------------------------------
 // Symbol pre-pass
 // ---------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) plan_rows(const uint8_t* __restrict__ cache_flags,
-                                                 const uint8_t* __restrict__ kv_mask, int N, int Tq, int Tkv,
-                                                 int gran, int sym_Tq, int sym_row_bytes, int nw32,
-                                                 uint32_t* __restrict__ words, int32_t* __restrict__ keys) {
-  const int row = blockIdx.x * blockDim.x + threadIdx.x;
-  if (row >= N) return;
-  // one symbol covers gran x gran tiles: tile (i, j) reads flag i / gran and mask bit (i / gran, j / gran)
-  const int bh = row / Tq;
-  const size_t sym_row = (size_t)bh * sym_Tq + (row - bh * Tq) / gran;
-  const bool cached = cache_flags != nullptr && cache_flags[sym_row] != 0;
-  int count = 0, first_kept = -1;
-  const uint8_t* src = kv_mask ? kv_mask + sym_row * sym_row_bytes : nullptr;
-  for (int w = 0; w < nw32; ++w) {
-    uint32_t word = 0;
-    if (!cached) {
-      if (!src) {
-        word = 0xffffffffu;
-      } else if (gran == 1) {
-        for (int b = 0; b < 4; ++b) {
-          const int byte = 4 * w + b;
-          if (byte < sym_row_bytes) word |= (__brev((uint32_t)src[byte]) >> 24) << (8 * b);
-        }
-      } else {
-        for (int t = 0; t < 32 && 32 * w + t < Tkv; ++t) {
-          const int js = (32 * w + t) / gran;
-          word |= (uint32_t)((src[js >> 3] >> (7 - (js & 7))) & 1) << t;
-        }
-      }
-      const int valid = Tkv - 32 * w;   // >= 1 by construction of nw32
-      if (valid < 32) word &= (1u << valid) - 1u;
-    }
-    words[(size_t)row * nw32 + w] = word;
-    count += __popc(word);
-    if (first_kept < 0 && word != 0u) first_kept = 32 * w + __ffs(word) - 1;
-  }
-  // key of a computed row: kept blocks in the low 16 bits (0 .. 32768), first kept block above them
-  keys[row] = cached ? -1 : (count | (max(first_kept, 0) << 16));
-}
+// Rows and queues.  Head bh belongs to queue (XCD) bh % kXcds; the work list holds the queues one behind the other, so
+// where a queue begins follows from the shape.
+__host__ __device__ inline int queue_first_head(int q, int BH) { return q * (BH / kXcds) + (q < BH % kXcds ? q : BH % kXcds); }
 
-// Copies the initial queue heads and ends of a stored plan into the live ones its next run consumes.
-__global__ void reset_queues(const uint32_t* __restrict__ init, uint32_t* __restrict__ live) {
-  const int t = threadIdx.x;
-  if (t < kXcds) {
-    live[t * kHeadStride] = init[t * kHeadStride];
-    live[kEndOffset + t] = init[kEndOffset + t];
-  }
+// One decoded word of a symbol row given as bytes: bit j = key block 32 * w + j, padding cleared.
+__device__ inline uint32_t clear_padding(uint32_t word, int w, int Tkv) {
+  const int valid = Tkv - 32 * w;   // >= 1 by construction of nw32
+  return valid < 32 ? word & ((1u << valid) - 1u) : word;
 }
 
 // Work list order: one queue per XCD (head bh belongs to XCD bh % kXcds), in three parts.
@@ -175,107 +143,148 @@ __device__ inline int order_major(int key, int Tkv, int limit, int lightest) {
   return kLongBuckets + (kFineBuckets - 1) -
          (int)((unsigned)(count - lightest) * kFineBuckets / (unsigned)(limit - lightest + 1));
 }
-__device__ inline int order_bin(int key, int row, int Tq, int Tkv, int shift, int groups, const int* limit,
-                                const int* lightest) {
-  const int bh = row / Tq;
-  const int xcd = bh % kXcds;
-  const int group = (bh / kXcds) >> shift, major = order_major(key, Tkv, limit[xcd], lightest[xcd]);
-  int inner;
-  if (major < kLongBuckets)
-    inner = major * groups + group;
-  else if (major < kCachedBucket)
-    inner = kLongBuckets * groups + group * kFineBuckets + (major - kLongBuckets);
-  else
-    inner = kCachedBucket * groups + group;
-  return xcd * (kCachedBucket + 1) * groups + inner;
-}
-
-__global__ void __launch_bounds__(kOrderThreads) plan_order(const int32_t* __restrict__ keys, int N, int Tq,
-                                                            int Tkv, int shift, int groups,
-                                                            uint32_t* __restrict__ order,
-                                                            uint32_t* __restrict__ queues) {
-  __shared__ uint32_t bins[kXcds * (kCachedBucket + 1) * kMaxHeadGroups];
-  __shared__ uint32_t partial[kOrderThreads];
-  __shared__ unsigned long long queue_kept[kXcds];   // kept key blocks of all rows of a queue
-  __shared__ int limit[kXcds];                       // kept blocks from which a row of the queue counts as long
-  __shared__ uint32_t heaviest[kXcds], lightest_u[kXcds];   // largest / smallest kept count of its computed rows
-  __shared__ int lightest[kXcds];
+// Symbol pre-pass: workgroup q decodes the rows of queue q and writes its part of the work list.
+//   decode     one thread per row turns the packed symbols into aligned words, counts the kept key blocks and notes
+//              the first of them (key of the row; -1 for cached rows)
+//   order      counting sort into the buckets above
+// One kernel of eight workgroups, because the queues do not depend on each other; it is a chain of memory and LDS round
+// trips.  24 heads: 13 us at 33024 tokens, 7 us at 4608, where a decoding kernel and a single-workgroup sort over all
+// queues took 7 + 21 and 5 + 9 us and a launch more.
+constexpr int kLdsKeys = 8192;     // rows of a queue whose keys stay in LDS
+__global__ void __launch_bounds__(kOrderThreads) plan_queues(const uint8_t* __restrict__ cache_flags,
+                                                             const uint8_t* __restrict__ kv_mask, int BH, int Tq, int Tkv,
+                                                             int gran, int sym_Tq, int sym_row_bytes, int nw32, int shift,
+                                                             int groups, uint32_t* __restrict__ words, int32_t* keys,
+                                                             uint32_t* __restrict__ order, uint32_t* __restrict__ queues) {
+  __shared__ uint32_t bins[(kCachedBucket + 1) * kMaxHeadGroups];
+  __shared__ int32_t lds_keys[kLdsKeys];
+  __shared__ uint32_t wave_part[kOrderThreads / 64];
+  __shared__ unsigned long long kept_all;            // kept key blocks of all rows of the queue
+  __shared__ uint32_t heaviest, lightest_u;          // largest / smallest kept count of its computed rows
   __shared__ uint32_t seen_rows[kOrderThreads / 64][64];
-  const int tid = threadIdx.x;
-  const int per_xcd = (kCachedBucket + 1) * groups;
-  const int nbins = kXcds * per_xcd;
-  for (int b = tid; b < nbins; b += kOrderThreads) bins[b] = 0;
-  if (tid < kXcds) {
-    queue_kept[tid] = 0ull;
-    heaviest[tid] = 0u;
-    lightest_u[tid] = 0xffffu;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int q = blockIdx.x;
+  const int heads = (BH - q + kXcds - 1) / kXcds;    // bh = q, q + 8, ...
+  const int rows = heads * Tq;                       // local row r: head q + 8 * (r / Tq), query block r % Tq
+  const int nbins = (kCachedBucket + 1) * groups;
+  if (tid == 0) {
+    kept_all = 0ull;
+    heaviest = 0u;
+    lightest_u = 0xffffu;
+    queues[q * kHeadStride] = 0u;
+    if (q == 0) queues[kDoneOffset] = 0u;
   }
+  for (int b = tid; b < nbins; b += kOrderThreads) bins[b] = 0;
   __syncthreads();
+  const bool in_lds = rows <= kLdsKeys;
+  auto global_row = [&](int r) -> int { return (q + kXcds * (r / Tq)) * Tq + r % Tq; };
+  auto key_of = [&](int r) -> int { return in_lds ? lds_keys[r] : keys[global_row(r)]; };
+
   {
-    // one wave per head: sum, maximum and minimum of the kept counts of its rows (a head has at most 2^14 rows of at
-    // most 2^16 - 1 kept blocks: the sum fits in 32 bits), one atomic each per head
-    const int wave = tid >> 6, lane = tid & 63;
-    for (int bh = wave; bh < N / Tq; bh += kOrderThreads / 64) {
-      uint32_t sum = 0, hi = 0, lo = 0xffffu;
-      for (int i = lane; i < Tq; i += 64) {
-        const int key = keys[bh * Tq + i];
-        if (key >= 0) {
-          const uint32_t count = (uint32_t)(key & 0xffff);
-          sum += count;
-          hi = max(hi, count);
-          lo = min(lo, count);
+    unsigned long long sum = 0;
+    uint32_t hi = 0, lo = 0xffffu;
+    for (int r = tid; r < rows; r += kOrderThreads) {
+      const int row = global_row(r);
+      // one symbol covers gran x gran tiles: tile (i, j) reads flag i / gran and mask bit (i / gran, j / gran)
+      const size_t sym_row = (size_t)(q + kXcds * (r / Tq)) * sym_Tq + (r % Tq) / gran;
+      const bool cached = cache_flags != nullptr && cache_flags[sym_row] != 0;
+      int count = 0, first_kept = -1;
+      auto take = [&](int w, uint32_t word) {
+        word = clear_padding(word, w, Tkv);
+        words[(size_t)row * nw32 + w] = word;
+        count += __popc(word);
+        if (first_kept < 0 && word != 0u) first_kept = 32 * w + __ffs(word) - 1;
+      };
+      const uint8_t* src = kv_mask ? kv_mask + sym_row * sym_row_bytes : nullptr;
+      if (cached || !src) {
+        for (int w = 0; w < nw32; ++w) take(w, cached ? 0u : 0xffffffffu);
+      } else if (gran == 1) {
+        // rows start at any byte: aligned words, shifted together; only words that hold a byte of the row are read
+        const int skew = (int)((uintptr_t)src & 3);
+        const uint32_t* aligned = (const uint32_t*)(src - skew);
+        const int last = (skew + sym_row_bytes - 1) / 4;
+        for (int w0 = 0; w0 < nw32; w0 += 8) {
+          uint32_t d[9];
+#pragma unroll
+          for (int t = 0; t < 9; ++t) d[t] = w0 + t <= last ? aligned[w0 + t] : 0u;
+#pragma unroll
+          for (int t = 0; t < 8; ++t) {
+            if (w0 + t < nw32) {
+              const uint32_t v = (uint32_t)(((unsigned long long)d[t + 1] << 32 | d[t]) >> (8 * skew));
+              take(w0 + t, __builtin_bswap32(__brev(v)));      // most significant bit first inside each byte
+            }
+          }
+        }
+      } else {
+        for (int w = 0; w < nw32; ++w) {
+          uint32_t word = 0;
+          for (int t = 0; t < 32 && 32 * w + t < Tkv; ++t) {
+            const int js = (32 * w + t) / gran;
+            word |= (uint32_t)((src[js >> 3] >> (7 - (js & 7))) & 1) << t;
+          }
+          take(w, word);
         }
       }
-      for (int off = 32; off > 0; off >>= 1) {
-        sum += __shfl_xor(sum, off);
-        hi = max(hi, __shfl_xor(hi, off));
-        lo = min(lo, __shfl_xor(lo, off));
+      // key of a computed row: kept blocks in the low 16 bits (0 .. 32768), first kept block above them
+      const int key = cached ? -1 : (count | (max(first_kept, 0) << 16));
+      if (in_lds)
+        lds_keys[r] = key;
+      else
+        keys[row] = key;
+      if (!cached) {
+        sum += (uint32_t)count;
+        hi = max(hi, (uint32_t)count);
+        lo = min(lo, (uint32_t)count);
       }
-      if (lane == 0) {
-        atomicAdd(&queue_kept[bh % kXcds], (unsigned long long)sum);
-        atomicMax(&heaviest[bh % kXcds], hi);
-        atomicMin(&lightest_u[bh % kXcds], lo);
-      }
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+      sum += __shfl_xor(sum, off);
+      hi = max(hi, __shfl_xor(hi, off));
+      lo = min(lo, __shfl_xor(lo, off));
+    }
+    if (lane == 0) {
+      atomicAdd(&kept_all, sum);
+      atomicMax(&heaviest, hi);
+      atomicMin(&lightest_u, lo);
+    }
+  }
+  __syncthreads();                                   // keys and sums are in place
+  // long = more than a third of a workgroup's share; where no row is that long the fine buckets end at the heaviest
+  // row instead
+  const int share = (int)min(kept_all / (3ull * kWgsPerXcd), (unsigned long long)Tkv);
+  const int limit = (int)heaviest <= share ? (int)heaviest : share;
+  const int lightest = min((int)lightest_u, limit);
+  auto bin_of = [&](int major, int r) -> int {
+    const int group = (r / Tq) >> shift;
+    if (major < kLongBuckets) return major * groups + group;
+    if (major < kCachedBucket) return kLongBuckets * groups + group * kFineBuckets + (major - kLongBuckets);
+    return kCachedBucket * groups + group;
+  };
+  for (int r = tid; r < rows; r += kOrderThreads) atomicAdd(&bins[bin_of(order_major(key_of(r), Tkv, limit, lightest), r)], 1u);
+  __syncthreads();
+  // exclusive scan of the bins: a contiguous chunk per thread, then over the lanes of a wave, then over the waves
+  {
+    const int chunk = (nbins + kOrderThreads - 1) / kOrderThreads;
+    const int lo = min(nbins, tid * chunk), hi = min(nbins, lo + chunk);
+    uint32_t sum = 0;
+    for (int b = lo; b < hi; ++b) sum += bins[b];
+    uint32_t scan = sum;
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t add = __shfl_up(scan, off);
+      scan += lane >= off ? add : 0u;
+    }
+    if (lane == 63) wave_part[wave] = scan;
+    __syncthreads();
+    uint32_t run = scan - sum;
+    for (int w = 0; w < wave; ++w) run += wave_part[w];
+    for (int b = lo; b < hi; ++b) {
+      const uint32_t c = bins[b];
+      bins[b] = run;
+      run += c;
     }
   }
   __syncthreads();
-  if (tid < kXcds) {
-    // long = more than a third of a workgroup's share; where no row is that long the fine buckets end at the
-    // heaviest row instead
-    const int share = (int)min(queue_kept[tid] / (3ull * kWgsPerXcd), (unsigned long long)Tkv);
-    limit[tid] = (int)heaviest[tid] <= share ? (int)heaviest[tid] : share;
-    lightest[tid] = min((int)lightest_u[tid], limit[tid]);
-  }
-  __syncthreads();
-  for (int r = tid; r < N; r += kOrderThreads) atomicAdd(&bins[order_bin(keys[r], r, Tq, Tkv, shift, groups, limit, lightest)], 1u);
-  __syncthreads();
-  // exclusive scan of bins: contiguous chunk per thread, then a scan over the chunk sums
-  const int chunk = (nbins + kOrderThreads - 1) / kOrderThreads;
-  const int lo = min(nbins, tid * chunk), hi = min(nbins, lo + chunk);
-  uint32_t sum = 0;
-  for (int b = lo; b < hi; ++b) sum += bins[b];
-  partial[tid] = sum;
-  __syncthreads();
-  for (int off = 1; off < kOrderThreads; off <<= 1) {
-    uint32_t add = tid >= off ? partial[tid - off] : 0u;
-    __syncthreads();
-    partial[tid] += add;
-    __syncthreads();
-  }
-  uint32_t run = partial[tid] - sum;
-  for (int b = lo; b < hi; ++b) {
-    const uint32_t c = bins[b];
-    bins[b] = run;
-    run += c;
-  }
-  __syncthreads();
-  if (tid < kXcds) {
-    const uint32_t begin = bins[tid * per_xcd];
-    queues[tid * kHeadStride] = begin;                      // queue head
-    if (tid > 0) queues[kEndOffset + tid - 1] = begin;      // previous queue's end
-    if (tid == kXcds - 1) queues[kEndOffset + kXcds - 1] = (uint32_t)N;
-  }
-  __syncthreads();
+  uint32_t* const list = order + 2 * (size_t)Tq * queue_first_head(q, BH);
   // Inside a bin the rows keep their order in the sequence: neighbouring query blocks, which with windowed symbols
   // keep nearly the same key blocks, are then worked on at the same time and find each other's tiles in L2.  A bin
   // holds rows of one head as long as there are no more than kMaxHeadGroups heads per queue: a wave then walks a
@@ -283,17 +292,14 @@ __global__ void __launch_bounds__(kOrderThreads) plan_order(const int32_t* __res
   // start of its bin + that count + the rows of its bucket at lower lanes (ballots).  With more heads several of them
   // share a bin and the rows take their places in arrival order.
   if (shift == 0) {
-    const int wave = tid >> 6, lane = tid & 63;
-    const int heads = N / Tq;
     volatile uint32_t* seen = seen_rows[wave];   // rows of the current head met so far, per bucket
-    for (int bh = wave; bh < heads; bh += kOrderThreads / 64) {
+    for (int hl = wave; hl < heads; hl += kOrderThreads / 64) {
       seen[lane] = 0u;
       for (int i0 = 0; i0 < Tq; i0 += 64) {
-        const int i = i0 + lane;
-        const bool valid = i < Tq;
-        const int r = bh * Tq + min(i, Tq - 1);
-        const int key = keys[r];
-        const int major = valid ? order_major(key, Tkv, limit[bh % kXcds], lightest[bh % kXcds]) : 0;
+        const bool valid = i0 + lane < Tq;
+        const int r = hl * Tq + min(i0 + lane, Tq - 1);
+        const int key = key_of(r);
+        const int major = valid ? order_major(key, Tkv, limit, lightest) : 0;
         // the lanes whose row falls into the same bucket as this lane's: one ballot per bit of the bucket number
         unsigned long long same = __ballot(valid);
 #pragma unroll
@@ -307,19 +313,19 @@ __global__ void __launch_bounds__(kOrderThreads) plan_order(const int32_t* __res
           const uint32_t before = seen[major];
           const uint32_t rank = before + (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
           if ((same & ((1ull << lane) - 1ull)) == 0ull) seen[major] = before + (uint32_t)__popcll(same);
-          const uint32_t pos = bins[order_bin(key, r, Tq, Tkv, shift, groups, limit, lightest)] + rank;
-          order[2 * pos] = (uint32_t)r | (key < 0 ? kCopyFlag : 0u);
-          order[2 * pos + 1] = (uint32_t)key;
+          const uint32_t pos = bins[bin_of(major, r)] + rank;
+          list[2 * pos] = (uint32_t)global_row(r) | (key < 0 ? kCopyFlag : 0u);
+          list[2 * pos + 1] = (uint32_t)key;
         }
       }
     }
     return;
   }
-  for (int r = tid; r < N; r += kOrderThreads) {
-    const int key = keys[r];
-    const uint32_t pos = atomicAdd(&bins[order_bin(key, r, Tq, Tkv, shift, groups, limit, lightest)], 1u);
-    order[2 * pos] = (uint32_t)r | (key < 0 ? kCopyFlag : 0u);
-    order[2 * pos + 1] = (uint32_t)key;
+  for (int r = tid; r < rows; r += kOrderThreads) {
+    const int key = key_of(r);
+    const uint32_t pos = atomicAdd(&bins[bin_of(order_major(key, Tkv, limit, lightest), r)], 1u);
+    list[2 * pos] = (uint32_t)global_row(r) | (key < 0 ? kCopyFlag : 0u);
+    list[2 * pos + 1] = (uint32_t)key;
   }
 }
 
@@ -373,7 +379,8 @@ __device__ __forceinline__ int v_swizzle(int row) {
 // re-read the last row that exists, scores of missing keys are set to -inf before the softmax, stores of
 // missing query rows are dropped, and a 64-key sub-tile that lies entirely past the end is not visited.
 // The aligned instantiation contains none of this.
-template <int D, int BQ, int BK, bool RAGGED>
+// DEALT: items are dealt out by workgroup number and every workgroup decodes the symbols of its rows (see below).
+template <int D, int BQ, int BK, bool RAGGED, bool DEALT>
 __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
   constexpr int NWAVES = BQ / 32;
   constexpr int NT = NWAVES * 64;
@@ -433,48 +440,102 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
     }
   }
 
-  // This workgroup's home queue is the one of the XCD it runs on (hardware register XCC_ID).
+  // Work acquisition.
+  // DEALT: the eight XCDs (workgroup n runs on XCD n mod 8) own a contiguous part each of the rows, and a workgroup
+  // takes every nwg-th of its XCD's part.
+  // Queues: the queue of XCD q holds its rows at list positions queue_begin(q) .. queue_begin(q + 1) - 1.  The first
+  // nwg(q) of them are the first items of the workgroups n = q, q + 8, ...; the ticket of every further item is one
+  // atomic on the home queue -- the one of the XCD the workgroup runs on (hardware register XCC_ID) --, issued by wave
+  // 0 and left in flight; it is drawn a few kept blocks before the current item ends (earlier would let an idle
+  // workgroup find the queue empty while this one still sits on an item it has not started), so at the end of the
+  // item it has long arrived.  When the home queue is drained the workgroup looks at all queue heads at once and
+  // steals from the next one that has rows left (heads only grow: one that is seen drained stays so).
+  // The item number reaches the other waves through one of two LDS slots, used in turn: a wave reads slot s of item i
+  // before it arrives at the barrier of item i + 1, and the slot is not written again before that barrier has been
+  // passed, so one barrier per item is enough.  The barrier waits for LDS traffic only; __syncthreads() would also
+  // make every wave wait for the acknowledgement of its stores of the previous item.  The work-list entry then comes
+  // through the scalar cache and carries the row's kept-block count and first kept block, so the first K/V sub-tile
+  // is requested before the row's symbol words have been looked at.
   const int my_q = (int)(__builtin_amdgcn_s_getreg(kHwRegXccId) & 15u) % kXcds;
   uint32_t* const q_head = p.queues;
-  const uint32_t* const q_end = p.queues + kEndOffset;
-
-  // Work acquisition.  The ticket of the next item is one atomic on the home queue, issued by wave 0 and left in
-  // flight; it is drawn a few kept blocks before the current item ends (earlier would let an idle workgroup find
-  // the queue empty while this one still sits on an item it has not started), so at the end of the item it has
-  // long arrived.  The item number reaches the other waves through one of two LDS slots, used in turn: a wave
-  // reads slot s of item i before it arrives at the barrier of item i + 1, and the slot is not written again
-  // before that barrier has been passed, so one barrier per item is enough.  The barrier waits for LDS traffic
-  // only; __syncthreads() would also make every wave wait for the acknowledgement of its stores of the previous
-  // item.  The work-list entry then comes through the scalar cache and carries the row's kept-block count and
-  // first kept block, so the first K/V sub-tile is requested before the row's symbol words have been looked at.
+  auto nwg = [&](int q) -> int { return ((int)gridDim.x - q + kXcds - 1) / kXcds; };
+  auto queue_begin = [&](int q) -> int { return queue_first_head(q, p.BH) * p.Tq; };
+  int next_n;                          // DEALT: next row; queues: the first item
+  {
+    const int q0 = (int)blockIdx.x % kXcds, slot = (int)blockIdx.x / kXcds;
+    next_n = slot + (DEALT ? q0 * (p.N / kXcds) + min(q0, p.N % kXcds) : queue_begin(q0));
+    if (!DEALT && next_n >= queue_begin(q0 + 1)) next_n = -1;
+  }
   constexpr int kDrawTiles = 6;        // kept blocks an item still has to visit when the next ticket is drawn
-  bool drawn = false;
+  bool drawn = false, first_item = true;
   unsigned ticket = 0;                 // wave 0: lane 0 holds the ticket of the home queue, possibly still in flight
   auto draw_issue = [&]() {
-    if (wave == 0) ticket = sa_lane0_atomic_inc(q_head + my_q * kHeadStride);   // a drained queue just keeps counting
-    drawn = true;
+    if constexpr (!DEALT) {
+      if (wave == 0) ticket = sa_lane0_atomic_inc(q_head + my_q * kHeadStride);   // a drained queue just keeps counting
+      drawn = true;
+    }
   };
   for (int parity = 0;; parity ^= 1) {
-    if (!drawn) draw_issue();
-    drawn = false;
-    if (wave == 0) {
-      // resolve the ticket; when the home queue is drained, steal from the other XCDs' queues
-      const uint32_t t = sa_lane0_value(ticket);
-      int item = t < q_end[my_q] ? (int)t : -1;
-      for (int k = 1; k < kXcds && item < 0; ++k) {
-        const int q = (my_q + k) % kXcds;
-        const uint32_t end = q_end[q];
-        const uint32_t got = sa_lane0_value(sa_lane0_atomic_inc(q_head + q * kHeadStride));
-        if (got < end) item = (int)got;
+    int n = next_n;
+    if constexpr (DEALT) {
+      const int q0 = (int)blockIdx.x % kXcds;
+      if (n >= (q0 + 1) * (p.N / kXcds) + min(q0 + 1, p.N % kXcds)) break;
+      if (!first_item) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the LDS buffers are free
+      next_n = n + nwg(q0);
+    } else if (!first_item || n < 0) {
+      if (!drawn) draw_issue();
+      if (wave == 0) {
+        // resolve the ticket, or steal (a head counts at most the items and one overshoot per workgroup)
+        int item = queue_begin(my_q) + nwg(my_q) + (int)sa_lane0_value(ticket);
+        if (item >= queue_begin(my_q + 1)) item = -1;
+        unsigned drained = 0;          // queues an increment of this workgroup found empty: at most eight rounds fail
+        while (item < 0) {
+          const int q = (my_q + lane) % kXcds;       // lanes 0..7: the eight queues, the home queue first
+          const int room = queue_begin(q + 1) - queue_begin(q) - nwg(q);
+          const int taken = (int)__hip_atomic_load(q_head + q * kHeadStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          const unsigned long long open = __builtin_amdgcn_ballot_w64(lane < kXcds && taken < room && !((drained >> q) & 1u));
+          if (open == 0ull) break;
+          const int qs = (my_q + __builtin_ctzll(open)) % kXcds;
+          const int got = queue_begin(qs) + nwg(qs) + (int)sa_lane0_value(sa_lane0_atomic_inc(q_head + qs * kHeadStride));
+          if (got < queue_begin(qs + 1)) item = got;
+          drained |= 1u << qs;
+        }
+        s_item[parity] = item;         // every lane writes the same value
       }
-      s_item[parity] = item;           // every lane writes the same value
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      n = __builtin_amdgcn_readfirstlane(s_item[parity]);
+      if (n < 0) break;
     }
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    const int n = __builtin_amdgcn_readfirstlane(s_item[parity]);
-    if (n < 0) break;
-    const unsigned long long entry64 = sa_scalar_load_b64(p.order + 2 * (size_t)n);
-    const uint32_t entry = (uint32_t)entry64;
-    const uint32_t key = (uint32_t)(entry64 >> 32);
+    drawn = false;
+    first_item = false;
+    // row, and its key: kept blocks | first kept block << 16
+    uint32_t entry, key, raw_words = 0;
+    if constexpr (DEALT) {
+      // symbols as the caller gave them, at most 64 words a row: lane w decodes word w
+      entry = (uint32_t)n;
+      if (p.raw_flags && __builtin_amdgcn_readfirstlane((int)p.raw_flags[n]) != 0) entry |= kCopyFlag;
+      if (lane < p.nw32) {
+        raw_words = 0xffffffffu;
+        if (p.raw_mask) {
+          const uint8_t* src = p.raw_mask + (size_t)n * p.raw_row_bytes;
+          uint32_t v = 0;
+#pragma unroll
+          for (int b = 0; b < 4; ++b) v |= 4 * lane + b < p.raw_row_bytes ? (uint32_t)src[4 * lane + b] << (8 * b) : 0u;
+          raw_words = __builtin_bswap32(__brev(v));      // most significant bit first inside each byte
+        }
+        raw_words = clear_padding(raw_words, lane, p.Tkv);
+      }
+      int count = __popc(raw_words);
+      for (int off = 32; off > 0; off >>= 1) count += __shfl_xor(count, off);
+      const unsigned long long some = __builtin_amdgcn_ballot_w64(raw_words != 0u);
+      const int w = some ? __builtin_ctzll(some) : 0;
+      const uint32_t bits = (uint32_t)__builtin_amdgcn_readlane((int)raw_words, w);
+      key = (uint32_t)__builtin_amdgcn_readfirstlane(count) | (uint32_t)(some ? 32 * w + __builtin_ctz(bits) : 0) << 16;
+    } else {
+      const unsigned long long entry64 = sa_scalar_load_b64(p.order + 2 * (size_t)n);
+      entry = (uint32_t)entry64;
+      key = (uint32_t)(entry64 >> 32);
+    }
     const int row = (int)(entry & ~kCopyFlag);
     const int bh = row / p.Tq;
     const int iq = row - bh * p.Tq;
@@ -517,7 +578,7 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
     // ---- compute-on-demand ----
     const char* Kh = p.K + head_off;
     const char* Vh = p.V + head_off;
-    const uint32_t* wp = p.words + (size_t)row * p.nw32;
+    const uint32_t* wp = DEALT ? nullptr : p.words + (size_t)row * p.nw32;
 
     // Q fragment: B operand of S^T = K Q^T; lane holds query row l32, d = 16*ks + 8*half .. +7, exactly as stored:
     // the products accumulate in fp32 and the scale log2(e)/sqrt(D) is applied to the fp32 score on its way into
@@ -547,7 +608,10 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
     // not a memory access.
     int tiles_left = (int)(key & 0xffffu);          // kept blocks not yet visited, the current one included
     int w_idx = (int)(key >> 21);                    // word of the first kept block
-    auto load_words = [&](int w0) -> uint32_t { return w0 + lane < p.nw32 ? wp[w0 + lane] : 0u; };
+    auto load_words = [&](int w0) -> uint32_t {
+      if constexpr (DEALT) return raw_words;       // one word per lane, w0 == 0
+      return w0 + lane < p.nw32 ? wp[w0 + lane] : 0u;
+    };
     uint32_t w_lanes = load_words(w_idx & ~63);
     uint32_t w_bits = 0;
     auto next_block = [&]() -> int {
@@ -839,6 +903,17 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
       }
     }
   }
+  if constexpr (!DEALT) {
+    // Stored plans: the last workgroup to get here leaves the queue heads as the next run wants them.  Every
+    // workgroup has waited for its last ticket, so no increment is still on its way.
+    if (p.self_reset && wave == 0) {
+      const unsigned before = sa_lane0_value(sa_lane0_atomic_inc(q_head + kDoneOffset));
+      if (before == gridDim.x - 1) {
+        if (lane < kXcds) __hip_atomic_store(q_head + lane * kHeadStride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (lane == 0) __hip_atomic_store(q_head + kDoneOffset, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -890,7 +965,7 @@ int check_shape(int B, int H, int L, int D, int bq, int bk, bool need_d, Shape* 
   return 0;
 }
 
-// scratch layout: [queue heads and ends (kQueueBytes)] [order N x 2 u32] [keys N i32] [words N*nw32 u32]
+// scratch layout: [queue heads (kQueueBytes)] [order N x 2 u32] [keys N i32] [words N*nw32 u32]
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 constexpr size_t kQueueBytes = (size_t)kQueueWords * 4;
 size_t workspace_bytes(const Shape& s) {
@@ -974,30 +1049,34 @@ bool overlaps(const void* a, const void* b, size_t bytes) {
   return x < y + bytes && y < x + bytes;
 }
 
-template <int D, int BQ, int BK, bool RAGGED>
+template <int D, int BQ, int BK, bool RAGGED, bool DEALT>
 int launch_attn_variant(const AttnParams& p, int grid, hipStream_t stream) {
   constexpr size_t lds = 4 * (size_t)kKeys * D * 2 + 16;
   static std::once_flag once;
   static hipError_t attr_err = hipSuccess;
   std::call_once(once, [] {
-    attr_err = hipFuncSetAttribute((const void*)attn_kernel<D, BQ, BK, RAGGED>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   (int)lds);
+    attr_err = hipFuncSetAttribute((const void*)attn_kernel<D, BQ, BK, RAGGED, DEALT>,
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   });
   if (attr_err != hipSuccess)
     return fail(SPARSE_ATTN_ERR_HIP, "hipFuncSetAttribute failed: %s", hipGetErrorString(attr_err));
-  hipLaunchKernelGGL((attn_kernel<D, BQ, BK, RAGGED>), dim3(grid), dim3(BQ * 2), lds, stream, p);
+  hipLaunchKernelGGL((attn_kernel<D, BQ, BK, RAGGED, DEALT>), dim3(grid), dim3(BQ * 2), lds, stream, p);
   HIP_TRY(hipGetLastError());
   return 0;
 }
 
 template <int D, int BQ, int BK>
 int launch_attn(const AttnParams& p, int grid, hipStream_t stream) {
-  if (p.L % BQ || p.L % BK) return launch_attn_variant<D, BQ, BK, true>(p, grid, stream);
-  return launch_attn_variant<D, BQ, BK, false>(p, grid, stream);
+  const bool ragged = p.L % BQ || p.L % BK;
+  if (p.queues)
+    return ragged ? launch_attn_variant<D, BQ, BK, true, false>(p, grid, stream)
+                  : launch_attn_variant<D, BQ, BK, false, false>(p, grid, stream);
+  return ragged ? launch_attn_variant<D, BQ, BK, true, true>(p, grid, stream)
+                : launch_attn_variant<D, BQ, BK, false, true>(p, grid, stream);
 }
 
 struct PlanBuffers {
-  uint32_t* queues;   // live queue heads and ends (kQueueWords)
+  uint32_t* queues;   // queue heads (kQueueWords)
   uint32_t* order;    // [N][2]
   int32_t* keys;      // [N]
   uint32_t* words;    // [N][nw32]
@@ -1019,17 +1098,15 @@ struct sparse_attn_plan {
   Shape s;
   int gran;
   int dev;
-  void* mem;               // [initial queue heads and ends (kQueueBytes)] [workspace as carved above]
-  uint32_t* queues_init;
+  void* mem;               // workspace as carved above; the queue heads are zero between runs
   PlanBuffers bufs;
 };
 
 namespace {
 
-// Enqueues the symbol pre-pass: decode + count per row, then the ordered work list; the queue heads and
-// ends go to `queues_out`.
+// Enqueues the symbol pre-pass: decode + count per row, the ordered work list, queue heads at zero.
 int launch_plan(const uint8_t* cache_flags, const uint8_t* kv_mask, const Shape& s, int gran, const PlanBuffers& pb,
-                uint32_t* queues_out, hipStream_t stream) {
+                hipStream_t stream) {
   const int BH = s.B * s.H;
   const int heads_per_xcd = (BH + kXcds - 1) / kXcds;
   int shift = 0;
@@ -1037,11 +1114,8 @@ int launch_plan(const uint8_t* cache_flags, const uint8_t* kv_mask, const Shape&
   const int groups = ((heads_per_xcd - 1) >> shift) + 1;
   const int sym_Tq = (s.Tq + gran - 1) / gran;
   const int sym_row_bytes = ((s.Tkv + gran - 1) / gran + 7) / 8;
-  hipLaunchKernelGGL(plan_rows, dim3((s.N + 255) / 256), dim3(256), 0, stream, cache_flags, kv_mask, s.N, s.Tq, s.Tkv,
-                     gran, sym_Tq, sym_row_bytes, s.nw32, pb.words, pb.keys);
-  HIP_TRY(hipGetLastError());
-  hipLaunchKernelGGL(plan_order, dim3(1), dim3(kOrderThreads), 0, stream, pb.keys, s.N, s.Tq, s.Tkv, shift, groups,
-                     pb.order, queues_out);
+  hipLaunchKernelGGL(plan_queues, dim3(kXcds), dim3(kOrderThreads), 0, stream, cache_flags, kv_mask, BH, s.Tq, s.Tkv, gran,
+                     sym_Tq, sym_row_bytes, s.nw32, shift, groups, pb.words, pb.keys, pb.order, pb.queues);
   HIP_TRY(hipGetLastError());
   return 0;
 }
@@ -1127,27 +1201,39 @@ int run(const void* Q, const void* K, const void* V, const uint8_t* cache_flags,
   }
   if (record) HIP_TRY(hipEventRecord(ev[0], stream));
 
-  if (plan) {
-    hipLaunchKernelGGL(reset_queues, dim3(1), dim3(64), 0, stream, plan->queues_init, pb.queues);
-    HIP_TRY(hipGetLastError());
-  } else {
-    if (int rc = launch_plan(cache_flags, kv_mask, s, 1, pb, pb.queues, stream)) return rc;
+  // persistent grid: as many workgroups as the CUs hold (8 waves by registers, 160 KiB of LDS), fewer if there are fewer
+  // items.  With two per CU whatever their size, the 2-wave workgroups of 64-row blocks left half of the waves idle:
+  // 9001 tokens, 24 heads of 64, 64 x 128 blocks at 40 % keep: 330 -> 224 us.
+  const size_t wg_lds = 4 * (size_t)kKeys * D * 2 + 16;
+  const int by_lds = (int)(160 * 1024 / wg_lds), by_waves = 8 / (bq / 32);
+  const int room = cus * (by_waves < by_lds ? by_waves : by_lds);
+  const int grid = s.N < room ? s.N : room;
+  // No pre-pass where it cannot help: with no more rows than workgroups the order does not matter, and without symbols
+  // all rows are equally long, so with up to two per workgroup dealing them out by number does as well.  Every
+  // workgroup then decodes its own rows (at most 64 words each).  512 tokens, two heads of 64: 20.1 -> 12.3 us; 4608
+  // tokens, 24 heads, dense: 273 -> 261 us.
+  const bool symbols = cache_flags != nullptr || kv_mask != nullptr;
+  const bool dealt = !plan && s.nw32 <= 64 && s.N <= (symbols ? 1 : 2) * room;
+  if (!plan && !dealt) {
+    if (int rc = launch_plan(cache_flags, kv_mask, s, 1, pb, stream)) return rc;
   }
   if (record) HIP_TRY(hipEventRecord(ev[1], stream));
 
-  uint32_t* const queues = pb.queues;
-  uint32_t* const order = pb.order;
-  uint32_t* const words = pb.words;
   AttnParams p;
   p.Q = (const char*)Q;
   p.K = (const char*)K;
   p.V = (const char*)V;
   p.O_cache = (const char*)O_cache;
   p.O = (char*)O;
-  p.words = words;
-  p.order = order;
-  p.queues = queues;
+  p.words = pb.words;
+  p.order = pb.order;
+  p.queues = dealt ? nullptr : pb.queues;
+  p.self_reset = plan != nullptr ? 1 : 0;
+  p.raw_flags = cache_flags;
+  p.raw_mask = kv_mask;
+  p.raw_row_bytes = s.row_bytes;
   p.N = s.N;
+  p.BH = B * H;
   p.Tq = s.Tq;
   p.Tkv = s.Tkv;
   p.L = L;
@@ -1167,9 +1253,6 @@ int run(const void* Q, const void* K, const void* V, const uint8_t* cache_flags,
     }
   }
   p.scale_log2 = (float)(1.4426950408889634 / sqrt((double)D));
-  // persistent grid: two workgroups per CU (64 KiB of LDS each), fewer if there are fewer items
-  const int grid = s.N < 2 * cus ? s.N : 2 * cus;
-
   int rc = 0;
   if (D == 128 && bq == 128 && bk == 128) rc = launch_attn<128, 128, 128>(p, grid, stream);
   else if (D == 128 && bq == 128 && bk == 64) rc = launch_attn<128, 128, 64>(p, grid, stream);
@@ -1247,14 +1330,13 @@ int sparse_attn_plan_create(const uint8_t* cache_flags, const uint8_t* kv_mask, 
   pl->gran = granularity;
   pl->mem = nullptr;
   hipError_t e = hipGetDevice(&pl->dev);
-  if (e == hipSuccess) e = hipMalloc(&pl->mem, kQueueBytes + workspace_bytes(s));
+  if (e == hipSuccess) e = hipMalloc(&pl->mem, workspace_bytes(s));
   if (e != hipSuccess) {
     delete pl;
     return fail(SPARSE_ATTN_ERR_HIP, "plan allocation failed: %s", hipGetErrorString(e));
   }
-  pl->queues_init = (uint32_t*)pl->mem;
-  pl->bufs = carve((char*)pl->mem + kQueueBytes, s);
-  if (int rc = launch_plan(cache_flags, kv_mask, s, granularity, pl->bufs, pl->queues_init, (hipStream_t)hip_stream)) {
+  pl->bufs = carve((char*)pl->mem, s);
+  if (int rc = launch_plan(cache_flags, kv_mask, s, granularity, pl->bufs, (hipStream_t)hip_stream)) {
     (void)hipFree(pl->mem);
     delete pl;
     return rc;

@@ -139,3 +139,48 @@ def test_caller_supplied_workspace_and_scratch_release():
     pkg.sparse_attn_release_scratch()
     pkg.sparse_attn_release_scratch()          # nothing left to free: still fine
     assert (case.run() == want).all()
+
+
+# (B, H, L, D, block_q, block_k, keep or None for no mask, cached share): rows around what the chip runs at a time
+# (512 workgroups, 1024 for 64-row blocks of 64 channels), fewer rows than queues, heads that do not fill the queues
+ROUTES = [
+    (1, 1, 50, 64, 64, 64, None, 0.0),
+    (1, 5, 130, 128, 128, 64, 0.6, 0.3),
+    (1, 9, 2100, 64, 64, 64, 0.3, 0.3),
+    (2, 24, 1344, 64, 64, 64, 0.4, 0.4),       # 1008 rows: dealt out
+    (2, 24, 1400, 64, 64, 64, 0.4, 0.4),       # 1056 rows: work list
+    (1, 31, 2100, 128, 128, 128, 0.3, 0.0),    # 527 rows: work list, queues of three and four heads
+    (1, 31, 2100, 128, 128, 128, None, 0.0),   # 527 equal rows: dealt out, some workgroups take two
+    (1, 31, 4300, 64, 128, 128, None, 0.0),    # 1054 equal rows: work list
+    (1, 17, 4300, 64, 128, 128, None, 0.5),    # flags alone
+    (1, 2, 8300, 64, 64, 64, 0.1, 0.2),        # five words a row, 130 bits in rows of 17 bytes
+]
+
+
+@pytest.mark.parametrize("B,H,L,D,bq,bk,keep,cached", ROUTES)
+def test_dealt_rows_and_work_list_agree(B, H, L, D, bq, bk, keep, cached):
+    """The one-shot call deals few rows out by workgroup number and decodes them in place; a stored plan always walks
+    the work list.  Same rows, same bits; the symbols start at an odd byte."""
+    print(f"[case] routes B={B} H={H} L={L} D={D} {bq}x{bk} keep={keep} cached={cached}", flush=True)
+    w = synth.random_case(synth.BASE_SEED + 120 + L, B, H, L, D, bq, bk, keep=1.0 if keep is None else keep,
+                          cached_frac=cached, with_cache_tensor=True)
+    if keep is None:
+        w.M_s = None
+    elif w.cache_flags is None or not w.cache_flags[0, 0, 0]:
+        w.M_s[0, 0, 0] = 0                  # a computed row without a kept block
+    case = DeviceCase(w)
+    if case.mask is not None:
+        raw = torch.zeros(case.mask.numel() + 3, dtype=torch.uint8, device=dev())
+        odd = raw[3:].view(case.mask.shape)
+        odd.copy_(case.mask)
+        case.mask = odd
+    got = case.run()
+    plan = pkg.SparseAttnPlan(case.flags, case.mask, w.B, w.H, w.L, bq, bk)
+    for rep in range(3):
+        O = fresh_O(w)
+        plan.run(case.Q, case.K, case.V, case.Oc, O)
+        torch.cuda.synchronize()
+        assert (down_bits(O) == got).all(), f"run {rep} of the plan differs from the one-shot call"
+    plan.destroy()
+    ref, ref_bits = oracle_full(w)
+    check_against_oracle(w, got, ref, ref_bits, f"routes {B}x{H}x{L}")
