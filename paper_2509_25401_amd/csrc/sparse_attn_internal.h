@@ -48,16 +48,13 @@ __device__ __forceinline__ void sa_wait_vmem_but() {
 }
 
 // ---------------------------------------------------------------------------------------
-// Operand staging of the two projection kernels (query and output projection).
+// Reduction loop of the two projection kernels (query and output projection).
 //
-// Both compute a transposed product C^T[n][token] = sum_k W[n][k] X[token][k] with
-// v_mfma_f32_32x32x16_bf16 (A = weight rows, B = token rows, both k-contiguous) and stream the
-// operands through two LDS buffers, kStepK reduction channels per stage.  A stage holds W_ROWS
-// weight rows and X_ROWS token rows of kRowB bytes; LDS layout: W stage 0, W stage 1, X stage 0,
-// X stage 1.  The 16-byte chunks of a row are permuted by row_swizzle so that the operand reads of a
-// wave spread over all banks; a direct-to-LDS load writes consecutive LDS, so the permutation is
-// applied to the global address each lane fetches.  Every wave owns a 64 x 64 corner of the
-// tile: [2 blocks of 32 output channels][2 blocks of 32 tokens] accumulators.
+// Both compute a transposed product C^T[n][token] = sum_k W[n][k] X[token][k] with v_mfma_f32_32x32x16_bf16 (A = weight
+// rows, B = token rows, both k-contiguous) and stream the operands through LDS, kStepK reduction channels per stage,
+// rows of kRowB bytes.  The 16-byte chunks of a row are permuted by row_swizzle so that the operand reads of a wave
+// spread over all banks; a direct-to-LDS load writes consecutive LDS, so the permutation is applied to the global
+// address each lane fetches.
 // ---------------------------------------------------------------------------------------
 namespace sa_gemm {
 
@@ -69,82 +66,6 @@ constexpr int kRowB = kStepK * 2;   // bytes per tile row in LDS
 
 // 16-byte chunk permutation of a 128-byte tile row (two rows share a 256-byte bank line)
 __device__ __forceinline__ int row_swizzle(int row) { return (row >> 1) & 7; }
-
-template <int W_ROWS, int X_ROWS, int NWAVES>
-struct Stages {
-  static constexpr int W_TILEB = W_ROWS * kRowB;            // bytes of one weight stage
-  static constexpr int X_TILEB = X_ROWS * kRowB;            // bytes of one token stage
-  static constexpr int W_LOAD = W_TILEB / 1024 / NWAVES;    // direct-to-LDS wave instructions per stage and wave
-  static constexpr int X_LOAD = X_TILEB / 1024 / NWAVES;
-  static constexpr int kLdsBytes = 2 * (W_TILEB + X_TILEB);
-  static_assert((W_TILEB / 1024) % NWAVES == 0 && (X_TILEB / 1024) % NWAVES == 0, "stage loads must split evenly over the waves");
-
-  unsigned w_goff[W_LOAD], x_goff[X_LOAD];   // per-lane global offsets of this wave's stage loads (8 rows per instruction)
-  int w_off[kStepK / 16], x_off[kStepK / 16];   // per-lane LDS offsets of the operand reads, k-step ks
-  unsigned lds_base;
-  int wave;
-
-  // wn / wm: this wave's 64-channel / 64-token corner; w_pitch / x_pitch: bytes between rows of the operands in
-  // memory; token rows from x_rows_valid on do not exist (short last block): their loads re-read the last row that
-  // does, and the caller never stores their results.
-  __device__ __forceinline__ void init(unsigned lds_base_, int wave_, int lane, int wn, int wm, size_t w_pitch,
-                                       size_t x_pitch, int x_rows_valid) {
-    lds_base = lds_base_;
-    wave = wave_;
-    const int l32 = lane & 31, half = lane >> 5;
-#pragma unroll
-    for (int u = 0; u < W_LOAD; ++u) {
-      const int r = (wave + u * NWAVES) * 8 + lane / 8;
-      w_goff[u] = (unsigned)(r * w_pitch + (((lane % 8) ^ row_swizzle(r)) * 16));
-    }
-#pragma unroll
-    for (int u = 0; u < X_LOAD; ++u) {
-      const int r = (wave + u * NWAVES) * 8 + lane / 8;
-      x_goff[u] = (unsigned)(min(r, x_rows_valid - 1) * x_pitch + (((lane % 8) ^ row_swizzle(r)) * 16));
-    }
-#pragma unroll
-    for (int ks = 0; ks < kStepK / 16; ++ks) {
-      const int o = l32 * kRowB + (((2 * ks + half) ^ row_swizzle(l32)) * 16);
-      w_off[ks] = wn * 64 * kRowB + o;
-      x_off[ks] = 2 * W_TILEB + wm * 64 * kRowB + o;
-    }
-  }
-
-  // Requests one stage: w_src / x_src point at the first row's channels of this stage (wave-uniform).
-  template <int STAGE>
-  __device__ __forceinline__ void issue(const char* w_src, const char* x_src) const {
-#pragma unroll
-    for (int u = 0; u < W_LOAD; ++u)
-      sa_load_to_lds_16B(w_src, w_goff[u], lds_base + (unsigned)(STAGE * W_TILEB + (wave + u * NWAVES) * 1024));
-#pragma unroll
-    for (int u = 0; u < X_LOAD; ++u)
-      sa_load_to_lds_16B(x_src, x_goff[u], lds_base + (unsigned)(2 * W_TILEB + STAGE * X_TILEB + (wave + u * NWAVES) * 1024));
-  }
-
-  // The 16 MFMAs of one stage on this wave's corner.  The stage is a compile-time constant, so every LDS address
-  // is a lane register plus an immediate; all 16 operand reads are issued before the first MFMA, which then only
-  // waits for its own two operands.
-  template <int STAGE>
-  __device__ __forceinline__ void mfma(const char* smem, f32x16 (&acc)[2][2]) const {
-    bf16x8 wa[kStepK / 16][2], xb[kStepK / 16][2];
-#pragma unroll
-    for (int ks = 0; ks < kStepK / 16; ++ks) {
-#pragma unroll
-      for (int a = 0; a < 2; ++a) wa[ks][a] = *(const bf16x8*)(smem + STAGE * W_TILEB + a * 32 * kRowB + w_off[ks]);
-#pragma unroll
-      for (int c = 0; c < 2; ++c) xb[ks][c] = *(const bf16x8*)(smem + STAGE * X_TILEB + c * 32 * kRowB + x_off[ks]);
-    }
-    __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-    for (int ks = 0; ks < kStepK / 16; ++ks)
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-          acc[a][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa[ks][a], xb[ks][c], acc[a][c], 0, 0, 0);
-    __builtin_amdgcn_s_setprio(0);
-  }
-};
 
 // Barrier that waits for this wave's LDS traffic only; __syncthreads() would also wait for its outstanding loads.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
@@ -225,8 +146,12 @@ struct Pipe {
   // w_src / x_src: functors, called once per stage and in order: the (wave-uniform) address of the first weight row's
   // channels of the next stage, and the offset of its token channels from x_base.  On return every wave has read its
   // last operands; LDS may be written after a barrier.
-  template <class WSrc, class XSrc>
-  __device__ __forceinline__ void run(const char* smem, f32x16 (&acc)[kA][kC], int stages, WSrc&& w_src, XSrc&& x_src) const {
+  // extra: called once, when the last stage has been requested and one to two stages of MFMAs are still to come, for
+  // plain loads whose results are used behind the loop; it returns a number of load instructions that it has
+  // certainly issued (loads return in order: the wait for the last stage may leave that many out).
+  template <class WSrc, class XSrc, class Extra>
+  __device__ __forceinline__ void run(const char* smem, f32x16 (&acc)[kA][kC], int stages, WSrc&& w_src, XSrc&& x_src,
+                                      Extra&& extra) const {
     bf16x8 wa[2][kA], xb[2][kC];
     auto read = [&](auto ks_c, const char* wbase, const char* xbase) {
       constexpr int ks = decltype(ks_c)::value;
@@ -293,16 +218,29 @@ struct Pipe {
       const int w_free = wbuf == 0 ? WB - 1 : wbuf - 1, x_free = xbuf == 0 ? XB - 1 : xbuf - 1;
       read(K1{}, wb, xb0);
       mfma(K0{}, std::integral_constant<int, ask_w2 ? w2 : 0>{}, [&](int j) { issue_w(w_at, w_free, w1 + j, w1 + j + 1); });
+      int behind = 0;
+      constexpr bool x_now = ask_x && !more2;      // the last token rows go out now, before what is behind them
+      if constexpr (x_now) issue_x(x_src(), x_free, 0, kXLoad);
+      if constexpr (more1 && !more2) {
+        behind = extra();
+        asm volatile("" ::: "memory");             // none of its loads moves down past the wait that counts on them
+      }
       size_t x_at = 0;
-      if constexpr (ask_x) x_at = x_src();
+      if constexpr (ask_x && !x_now) x_at = x_src();
       read(K2{}, wb, xb0);
-      mfma(K1{}, std::integral_constant<int, ask_x ? x1 : 0>{}, [&](int j) { issue_x(x_at, x_free, j, j + 1); });
+      mfma(K1{}, std::integral_constant<int, ask_x && !x_now ? x1 : 0>{}, [&](int j) { issue_x(x_at, x_free, j, j + 1); });
       read(K3{}, wb, xb0);
-      mfma(K2{}, std::integral_constant<int, ask_x ? x2 : 0>{}, [&](int j) { issue_x(x_at, x_free, x1 + j, x1 + j + 1); });
+      mfma(K2{}, std::integral_constant<int, ask_x && !x_now ? x2 : 0>{}, [&](int j) { issue_x(x_at, x_free, x1 + j, x1 + j + 1); });
       const int w_done = wbuf;
       if constexpr (more1) {
         if constexpr (more2)
           sa_wait_vmem_but<kAhead>();
+        else if (behind >= 32)
+          sa_wait_vmem_but<32>();
+        else if (behind >= 16)
+          sa_wait_vmem_but<16>();
+        else if (behind >= 8)
+          sa_wait_vmem_but<8>();
         else
           sa_wait_vmem();
         lds_barrier();
@@ -323,7 +261,10 @@ struct Pipe {
       stage(T{}, T{}, std::integral_constant<bool, WB == 2>{});
       --left;
     }
-    if (left == 2) stage(T{}, F{}, F{});
+    if (left == 2)
+      stage(T{}, F{}, F{});
+    else
+      (void)extra();
     stage(F{}, F{}, F{});
   }
 };

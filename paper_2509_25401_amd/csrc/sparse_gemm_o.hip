@@ -14,9 +14,12 @@
 // as the stand-alone element-wise kernel rounds it), so a Dispatch step needs no separate pass that writes the
 // forecast bias and reads it back.  A token block none of whose heads is selected only streams: addend + bias.
 //
-// One workgroup per (token block, 128 output channels) tile; transposed MFMA product as in the
-// query projection (A = weight rows, B = token rows, both k-contiguous in LDS), direct-to-LDS
-// loads, 64 reduction channels per stage, double buffered.
+// One workgroup per (token tile, column tile); transposed MFMA product and staging as in the query projection (A =
+// weight rows, B = token rows, both k-contiguous in LDS).
+//
+// What bounds it (33024 tokens, 24 heads of 128, 3072 channels).  90 % cached heads, two terms: 650 MB, 126 us at the rate
+// of a large copy; 158 us: a tile is a chain of flags, first stage, five stages on average, epilogue, each a round
+// trip to memory, with two tiles per CU to hide them.  No flags: power, as the query projection.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -34,11 +37,10 @@ using sa_gemm::kStepK;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 #define LDS_PTR(T) T __attribute__((address_space(3)))*
 
-constexpr int kBN = 128;                   // output channels per workgroup
+constexpr int kBN = 128;                   // C_out is a multiple of this
 constexpr int kMaxTerms = 4;               // stored feature + up to three derivatives
 
 struct GemmOParams {
@@ -48,7 +50,8 @@ struct GemmOParams {
   const uint8_t* flags;  // [B, H, Tq] or nullptr
   const char* addend;    // bf16 [B, L, C_out] or nullptr; with n_terms > 0: the first term
   char* Out;             // bf16 [B, L, C_out]
-  int H, L, Tq, C_out, select;
+  int H, L, C_out, select;
+  int tok_begin, tok_end;  // tokens of every sequence that this launch works on (whole sequences where flags are given)
   // OP_reuse of the cached bias fused into the addend: addend = sum_d coef[d] * term[d], term[0] = `addend`
   const char* term[kMaxTerms - 1];
   float coef[kMaxTerms];
@@ -59,23 +62,40 @@ __device__ __forceinline__ float bf16_bits_to_float(unsigned bits16) {
   return __builtin_bit_cast(float, bits16 << 16);
 }
 
-template <int BQ, int D>
-__global__ void __launch_bounds__((BQ / 64) * 2 * 64, 2) gemm_o_kernel(const GemmOParams p) {
-  constexpr int WM = BQ / 64;              // waves along tokens
-  constexpr int WN = kBN / 64;             // waves along output channels
+// TM tokens x TN output channels per workgroup, WM x WN waves, WB / XB LDS buffers.  FLAGGED: the tokens are one token
+// block (TM = block_q) and the reduction visits the heads its flags select; otherwise TM consecutive tokens and all heads.
+template <int TM, int TN, int WM, int WN, int WB, int XB, int D, bool FLAGGED>
+__global__ void __launch_bounds__(WM * WN * 64, 2) gemm_o_kernel(const GemmOParams p) {
+  using Pipe = sa_gemm::Pipe<TN, TM, WN, WM, WB, XB>;
   constexpr int NWAVES = WM * WN;
-  constexpr int PARTS = D / kStepK;        // stages per head
-  using Stage = sa_gemm::Stages<kBN, BQ, NWAVES>;   // weight rows = the tile's output channels, token rows = the block
+  constexpr int A = Pipe::kA, C = Pipe::kC;
+  constexpr int CW = TN / WN, TW = TM / WM;       // channels / tokens of a wave's corner
+  constexpr int PARTS = D / kStepK;               // stages per head
 
-  // column tile fastest: the 8 XCDs (workgroup n runs on XCD n mod 8) each keep the weight rows of a
-  // fixed set of column tiles in their L2 while the token blocks stream past
-  const int ncol = p.C_out / kBN;
-  const int t = blockIdx.x;
-  const int col = t % ncol;
-  const int i = (t / ncol) % p.Tq;
-  const int b = t / (ncol * p.Tq);
+  // tile of this workgroup
+  const int n_col = (p.C_out + TN - 1) / TN, n_tok = (p.tok_end - p.tok_begin + TM - 1) / TM;
+  int col, i, b;
+  if constexpr (!FLAGGED && TN > 128) {
+    // as in the query projection: every XCD takes a contiguous part of the tiles in the order batch, group of 4 column
+    // tiles, token tile, column tile
+    const int tiles = (int)gridDim.x, x = blockIdx.x % 8, at = blockIdx.x / 8;
+    int n = x * (tiles / 8) + min(x, tiles % 8) + at;
+    b = n / (n_col * n_tok);
+    n -= b * (n_col * n_tok);
+    const int g = n / (4 * n_tok), width = min(4, n_col - 4 * g);
+    n -= g * 4 * n_tok;
+    i = n / width;
+    col = 4 * g + n % width;
+  } else {
+    // column tile fastest: the 8 XCDs (workgroup n runs on XCD n mod 8) each keep the weight rows of a fixed set of
+    // column tiles in their L2 while the token blocks stream past
+    col = blockIdx.x % n_col;
+    i = (blockIdx.x / n_col) % n_tok;
+    b = blockIdx.x / (n_col * n_tok);
+  }
+  const int tok0 = p.tok_begin + i * TM;
 
-  extern __shared__ __attribute__((aligned(1024))) char smem[];   // W stage 0, W stage 1, O stage 0, O stage 1
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
   const unsigned lds_base = (unsigned)(uintptr_t)(LDS_PTR(char))smem;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -85,216 +105,279 @@ __global__ void __launch_bounds__((BQ / 64) * 2 * 64, 2) gemm_o_kernel(const Gem
 
   // reduction-axis symbol of this token block: one bit per head, set = visit
   unsigned long long heads;
-  {
+  if constexpr (FLAGGED) {
     bool mine = false;
-    if (lane < p.H) {
-      const int flag = p.flags ? (p.flags[((size_t)b * p.H + lane) * p.Tq + i] != 0) : 0;
-      mine = flag == p.select;
-    }
+    if (lane < p.H) mine = (p.flags[((size_t)b * p.H + lane) * n_tok + i] != 0 ? 1 : 0) == p.select;
     heads = __builtin_amdgcn_ballot_w64(mine);
+  } else {
+    heads = p.select ? 0ull : (p.H == 64 ? ~0ull : (1ull << p.H) - 1ull);   // no flags: no head counts as cached
   }
 
   const size_t w_pitch = (size_t)p.H * D * 2;
-  const char* gW = p.W + (size_t)col * kBN * w_pitch;
-  const char* gO = p.O + ((size_t)b * p.H * p.L + (size_t)i * BQ) * (size_t)(D * 2);   // head 0; head h adds h*L*D*2
-
-  // the last token block may be short: loads of missing rows re-read the last row that exists, their results
-  // are never stored
-  const int rows_valid = min(BQ, p.L - i * BQ);
-  Stage st;
-  st.init(lds_base, wave, lane, wn, wm, w_pitch, (size_t)(D * 2), rows_valid);
-  auto issue = [&](int h, int part, auto stage_c) {
-    st.template issue<decltype(stage_c)::value>(gW + ((size_t)h * D + (size_t)part * kStepK) * 2,
-                                                gO + (size_t)h * p.L * (D * 2) + (size_t)part * kRowB);
-  };
-
-  f32x16 acc[2][2];   // [output-channel block][token block] of this wave's 64x64 corner
+  const int n0 = col * TN;                        // first output channel of the tile
+  // the last token tile and the last column tile may be short: loads of missing rows re-read the last row that
+  // exists, their results are never stored
+  const int rows_valid = min(TM, p.tok_end - tok0), cols_valid = min(TN, p.C_out - n0);
+  const char* gW = p.W + (size_t)n0 * w_pitch;
+  Pipe st;
+  st.init(lds_base, wave, lane, wn, wm, w_pitch, cols_valid);
+  {
+    const char* gO = sa_uniform_ptr(p.O + ((size_t)b * p.H * p.L + tok0) * (size_t)(D * 2));   // head 0; head h adds h*L*D*2
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+    for (int u = 0; u < Pipe::kXLoad; ++u)
+      st.set_x_rows(u, gO, min(Pipe::load_row(wave, lane, u), rows_valid - 1), (size_t)(D * 2), lane);
+  }
+
+  f32x16 acc[A][C];   // [output-channel block][token block] of this wave's corner
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
+  for (int a = 0; a < A; ++a)
+#pragma unroll
+    for (int c = 0; c < C; ++c)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[a][c][e] = 0.f;
 
-  auto compute = [&](auto stage_c) { st.template mfma<decltype(stage_c)::value>(smem, acc); };
+  // Output side: every wave handles its own corner, lane -> (row, group of 8 output channels), whole rows of the corner
+  // at a time, for the addend's loads as for the result's stores; both are streamed once: non-temporal, so that they do
+  // not push the weight rows out of the XCD's L2.
+  constexpr int CHO = CW / 8;                     // 16-byte pieces per row of the corner
+  constexpr int RPI = 64 / CHO;                   // rows per wave instruction
+  constexpr int OUT_ITERS = TW / RPI;
+  const int out_row = lane / CHO, out_ch = lane % CHO;
+  const size_t out0 = (((size_t)b * p.L + tok0 + wm * TW) * p.C_out + n0 + wn * CW) * 2;
+  auto out_offset = [&](int it) -> size_t { return out0 + ((size_t)(it * RPI + out_row) * p.C_out + out_ch * 8) * 2; };
+  auto there = [&](int it) -> bool { return wm * TW + it * RPI + out_row < rows_valid && wn * CW + out_ch * 8 < cols_valid; };
 
-  // Output side.  The result tile leaves through LDS so that a lane writes 16 contiguous bytes of a
-  // token's row (and reads the addend the same way): thread -> (token, group of 8 output channels).
-  constexpr int NT = NWAVES * 64;
-  constexpr int OUT_ITERS = BQ * 16 / NT;
-  const int out_g = tid % 16;              // 8-channel group inside the 128-channel tile
-  const size_t out_row0 = (size_t)b * p.L + (size_t)i * BQ;
-  auto out_offset = [&](int it) -> size_t {
-    const int token = it * (NT / 16) + tid / 16;
-    return ((out_row0 + token) * p.C_out + col * kBN + out_g * 8) * 2;
-  };
-  u32x4 add_bits[OUT_ITERS];
-  float bv[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  if (p.bias) {
+  // The first two terms of the addend are requested behind the last stage of the reduction and land under its MFMAs;
+  // their OP_reuse is formed in the epilogue.  Loads return in order, so requested earlier they would hold up the
+  // stages behind them (33024 tokens, 90 % cached heads, two terms: 158 us; 193 with the terms combined in front of the
+  // loop.  One term, 80 %: 183 us, 189 when requested with the first stages).  Returns the number of loads where it is
+  // certain: in a tile at the edge a wave may skip some.  (256 x 256 tiles have no registers for that: there the addend
+  // is requested behind the loop.)
+  constexpr bool kEarly = A * C < 8;
+  u32x4 term0[OUT_ITERS], term1[kEarly ? OUT_ITERS : 1];
+  const bool two = kEarly && p.n_terms > 1;
+  auto fetch_addend = [&]() -> int {
+    if (!p.addend) return 0;
+    if (rows_valid == TM && cols_valid == TN) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) bv[e] = bf16_bits_to_float(p.bias[col * kBN + out_g * 8 + e]);
-  }
-  // accumulated channels v[0..7] of one token + bias + addend -> 16 bytes of bf16
-  auto finish = [&](int it, float (&v)[8]) {
+      for (int it = 0; it < OUT_ITERS; ++it) term0[it] = __builtin_nontemporal_load((const u32x4*)(p.addend + out_offset(it)));
+      if (!two) return OUT_ITERS;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] += bv[e];
-    if (p.addend) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        v[2 * e] += bf16_bits_to_float(add_bits[it][e] & 0xffffu);
-        v[2 * e + 1] += bf16_bits_to_float(add_bits[it][e] >> 16);
-      }
+      for (int it = 0; it < OUT_ITERS; ++it) term1[kEarly ? it : 0] = __builtin_nontemporal_load((const u32x4*)(p.term[0] + out_offset(it)));
+      return 2 * OUT_ITERS;
     }
-    u32x4 pk;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      bf16x2 pr;
-      pr[0] = (__bf16)v[2 * e];
-      pr[1] = (__bf16)v[2 * e + 1];
-      pk[e] = __builtin_bit_cast(unsigned, pr);
-    }
-    // streamed once: non-temporal, so that it does not push the weight rows out of the XCD's L2
-    if (it * (NT / 16) + tid / 16 < rows_valid) __builtin_nontemporal_store(pk, (u32x4*)(p.Out + out_offset(it)));
-  };
-  // The addend (cached bias) is requested right after the first stage of the reduction loop: the stage's data comes
-  // from L2 and is needed first, the addend comes from HBM and is needed last, and loads return in order.
-  auto fetch_addend = [&]() {
-    if (p.addend) {
-#pragma unroll
-      for (int it = 0; it < OUT_ITERS; ++it)
-        if (it * (NT / 16) + tid / 16 < rows_valid)
-          add_bits[it] = __builtin_nontemporal_load((const u32x4*)(p.addend + out_offset(it)));
-      if (p.n_terms > 0) {
-        // OP_reuse(B_c): fp32 sum of the scaled terms in term order, one rounding to bf16 (what the element-wise
-        // kernel computes), kept packed like a plain addend
-#pragma unroll
-        for (int it = 0; it < OUT_ITERS; ++it) {
-          if (it * (NT / 16) + tid / 16 >= rows_valid) continue;
-          float v[8];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            v[2 * e] = p.coef[0] * bf16_bits_to_float(add_bits[it][e] & 0xffffu);
-            v[2 * e + 1] = p.coef[0] * bf16_bits_to_float(add_bits[it][e] >> 16);
-          }
-          for (int d = 1; d < p.n_terms; ++d) {
-            const u32x4 tb = __builtin_nontemporal_load((const u32x4*)(p.term[d - 1] + out_offset(it)));
-            const float cd = p.coef[d];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              v[2 * e] = fmaf(cd, bf16_bits_to_float(tb[e] & 0xffffu), v[2 * e]);
-              v[2 * e + 1] = fmaf(cd, bf16_bits_to_float(tb[e] >> 16), v[2 * e + 1]);
-            }
-          }
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            bf16x2 pr;
-            pr[0] = (__bf16)v[2 * e];
-            pr[1] = (__bf16)v[2 * e + 1];
-            add_bits[it][e] = __builtin_bit_cast(unsigned, pr);
-          }
-        }
-      }
-    }
-  };
-  if (heads == 0ull) {
-    // no head of this token block is selected: the tile is addend + bias, straight from registers
-    fetch_addend();
 #pragma unroll
     for (int it = 0; it < OUT_ITERS; ++it) {
-      float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      finish(it, v);
+      if (!there(it)) continue;
+      term0[it] = __builtin_nontemporal_load((const u32x4*)(p.addend + out_offset(it)));
+      if (two) term1[kEarly ? it : 0] = __builtin_nontemporal_load((const u32x4*)(p.term[0] + out_offset(it)));
+    }
+    return 0;
+  };
+  // the addend of one piece: as given, or OP_reuse(B_c): fp32 sum of the scaled terms in term order, one rounding to
+  // bf16 (what the element-wise kernel computes)
+  auto addend_of = [&](int it) -> u32x4 {
+    u32x4 r = term0[it];
+    if (p.n_terms > 0) {
+      float v[8];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        v[2 * e] = p.coef[0] * bf16_bits_to_float(term0[it][e] & 0xffffu);
+        v[2 * e + 1] = p.coef[0] * bf16_bits_to_float(term0[it][e] >> 16);
+      }
+      for (int d = 1; d < p.n_terms; ++d) {
+        const u32x4 tb = kEarly && d == 1 ? term1[kEarly ? it : 0] : __builtin_nontemporal_load((const u32x4*)(p.term[d - 1] + out_offset(it)));
+        const float cd = p.coef[d];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          v[2 * e] = fmaf(cd, bf16_bits_to_float(tb[e] & 0xffffu), v[2 * e]);
+          v[2 * e + 1] = fmaf(cd, bf16_bits_to_float(tb[e] >> 16), v[2 * e + 1]);
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        bf16x2 pr;
+        pr[0] = (__bf16)v[2 * e];
+        pr[1] = (__bf16)v[2 * e + 1];
+        r[e] = __builtin_bit_cast(unsigned, pr);
+      }
+    }
+    return r;
+  };
+
+  // bias of the corner's channels, one per lane, in flight during the reduction: loaded without a branch -- from the
+  // weights where there is none -- and converted behind the loop, so that nothing waits for it here
+  const uint16_t* const bias_p = p.bias ? p.bias : (const uint16_t*)p.W;
+  unsigned bias_raw[CW / 64];
+#pragma unroll
+  for (int u = 0; u < CW / 64; ++u) bias_raw[u] = bias_p[min(n0 + wn * CW + 64 * u + lane, p.C_out - 1)];
+
+  const int stages = __popcll(heads) * PARTS;
+  if (stages == 0) {
+    // no head of this token block is selected: the tile is addend + bias, straight from registers
+    (void)fetch_addend();
+    float bv[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      bv[e] = p.bias ? bf16_bits_to_float(p.bias[min(n0 + wn * CW + out_ch * 8 + e, p.C_out - 1)]) : 0.f;
+#pragma unroll
+    for (int it = 0; it < OUT_ITERS; ++it) {
+      if (!there(it)) continue;
+      u32x4 r = {0u, 0u, 0u, 0u};
+      const u32x4 ad = p.addend ? addend_of(it) : r;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        bf16x2 pr;
+        // (0 + bias) + addend, as the accumulators of the other branch
+        pr[0] = (__bf16)(bv[2 * e] + (p.addend ? bf16_bits_to_float(ad[e] & 0xffffu) : 0.f));
+        pr[1] = (__bf16)(bv[2 * e + 1] + (p.addend ? bf16_bits_to_float(ad[e] >> 16) : 0.f));
+        r[e] = __builtin_bit_cast(unsigned, pr);
+      }
+      __builtin_nontemporal_store(r, (u32x4*)(p.Out + out_offset(it)));
     }
     return;
   }
 
-  // scalar walk over the selected heads, PARTS stages per head
-  int h = heads ? __builtin_ctzll(heads) : -1;
-  int part = 0;
-  auto advance = [&](int& nh, int& npart) {
-    nh = h;
-    npart = part + 1;
-    if (npart == PARTS) {
-      npart = 0;
-      heads &= heads - 1ull;
-      nh = heads ? __builtin_ctzll(heads) : -1;
+  // scalar walks over the selected heads, PARTS stages per head, one for the weights and one for the tokens
+  struct Walk {
+    unsigned long long left;
+    int part;
+    __device__ __forceinline__ int next(int& part_out) {
+      const int h = __builtin_ctzll(left);
+      part_out = part;
+      if (++part == PARTS) {
+        part = 0;
+        left &= left - 1ull;
+      }
+      return h;
     }
   };
-  using S0 = std::integral_constant<int, 0>;
-  using S1 = std::integral_constant<int, 1>;
-  bool first = true;
-  auto step = [&](auto cur, auto other) {
-    int nh, npart;
-    advance(nh, npart);
-    // stage 0 has landed; the addend's OUT_ITERS requests, issued after it, may still be out.  Only where every
-    // wave has issued all of them: in a short last block a wave skips those of rows that do not exist.
-    if (first && p.addend && p.n_terms == 0 && rows_valid == BQ)
-      sa_wait_vmem_but<OUT_ITERS>();
-    else
-      sa_wait_vmem();
-    first = false;
-    __syncthreads();   // this stage has landed for every wave; the other buffer is free
-    if (nh >= 0) issue(nh, npart, other);
-    compute(cur);
-    h = nh;
-    part = npart;
+  Walk ww = {heads, 0}, wx = {heads, 0};
+  const size_t head_bytes = (size_t)p.L * (D * 2);
+  auto w_src = [&]() {
+    int part;
+    const int h = ww.next(part);
+    return sa_uniform_ptr(gW + ((size_t)h * D + (size_t)part * kStepK) * 2);
   };
-  issue(h, 0, S0{});
-  fetch_addend();
-  while (h >= 0) {
-    step(S0{}, S1{});
-    if (h < 0) break;
-    step(S1{}, S0{});
+  auto x_src = [&]() {
+    int part;
+    const int h = wx.next(part);
+    return (size_t)sa_uniform_ptr((const char*)((size_t)h * head_bytes + (size_t)part * kRowB));
+  };
+  if constexpr (kEarly) {
+    st.run(smem, acc, stages, w_src, x_src, fetch_addend);
+  } else {
+    st.run(smem, acc, stages, w_src, x_src, []() { return 0; });
+    (void)fetch_addend();
   }
-
-  // epilogue, part 1: the accumulators (lane = token l32 + 32*c, registers = output channels
-  // 32*a + 8*q4 + 4*half + 0..3 of this wave's corner) go to LDS as fp32 rows of 512 bytes, 16-byte
-  // chunks XOR-permuted by the token so that the 32 tokens of a store hit different banks
   __syncthreads();   // every wave is done reading the stage buffers
+
+  // Epilogue, all in the wave's own piece of LDS (rows of CW bf16, 16-byte chunks permuted by the row so that the 32
+  // tokens of an accumulator access hit different banks): the addend goes in as rows, comes out in the accumulators'
+  // layout (lane = token 32 * c + l32, registers = channels 32 * a + 8 * q4 + 4 * half + 0..3), the sum (accumulator +
+  // bias) + addend goes back rounded to the same place and leaves as rows.  LDS accesses of a wave execute in order.
+  auto swizzle = [](int row) { return CHO == 16 ? (row & 15) : ((row >> 1) & 7); };
+  char* const corner = smem + wave * TW * CW * 2;
+  if (p.addend) {
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+    for (int it = 0; it < OUT_ITERS; ++it) {
+      const int row = it * RPI + out_row;
+      if (there(it)) *(u32x4*)(corner + row * CW * 2 + ((out_ch ^ swizzle(row)) * 16)) = addend_of(it);
+    }
+  }
+  int bias_bits[CW / 64];
 #pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4)
+  for (int u = 0; u < CW / 64; ++u) bias_bits[u] = p.bias ? (int)(bias_raw[u] << 16) : 0;
 #pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        const int token = wm * 64 + 32 * c + l32;
-        const int chunk = wn * 16 + 8 * a + 2 * q4 + half;
-        f32x4 v;
+  for (int a = 0; a < A; ++a)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = acc[a][c][4 * q4 + e];
-        *(f32x4*)(smem + token * 512 + ((chunk ^ (token & 31)) * 16)) = v;
+    for (int q4 = 0; q4 < 4; ++q4) {
+      float bv[4];                                 // channel 32 * a + 8 * q4 + 4 * half + e of the corner
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int ch = 32 * a + 8 * q4 + e;
+        const int lo = __builtin_amdgcn_readlane(bias_bits[ch / 64], ch % 64), hi = __builtin_amdgcn_readlane(bias_bits[ch / 64], ch % 64 + 4);
+        bv[e] = __builtin_bit_cast(float, half ? hi : lo);
       }
-  __syncthreads();
-  // part 2: row-contiguous read back, + bias + addend, round to bf16, 16-byte stores
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        const int row = 32 * c + l32;
+        u32x2* const at = (u32x2*)(corner + row * CW * 2 + (((4 * a + q4) ^ swizzle(row)) * 16) + 8 * half);
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = acc[a][c][4 * q4 + e] + bv[e];
+        if (p.addend) {
+          const u32x2 ad = *at;
+          v[0] += bf16_bits_to_float(ad[0] & 0xffffu);
+          v[1] += bf16_bits_to_float(ad[0] >> 16);
+          v[2] += bf16_bits_to_float(ad[1] & 0xffffu);
+          v[3] += bf16_bits_to_float(ad[1] >> 16);
+        }
+        bf16x2 lo, hi;
+        lo[0] = (__bf16)v[0];
+        lo[1] = (__bf16)v[1];
+        hi[0] = (__bf16)v[2];
+        hi[1] = (__bf16)v[3];
+        u32x2 pk;
+        pk[0] = __builtin_bit_cast(unsigned, lo);
+        pk[1] = __builtin_bit_cast(unsigned, hi);
+        *at = pk;
+      }
+    }
 #pragma unroll
   for (int it = 0; it < OUT_ITERS; ++it) {
-    const int token = it * (NT / 16) + tid / 16;
-    const f32x4 v0 = *(const f32x4*)(smem + token * 512 + (((2 * out_g) ^ (token & 31)) * 16));
-    const f32x4 v1 = *(const f32x4*)(smem + token * 512 + (((2 * out_g + 1) ^ (token & 31)) * 16));
-    float v[8];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      v[e] = v0[e];
-      v[4 + e] = v1[e];
-    }
-    finish(it, v);
+    const int row = it * RPI + out_row;
+    const u32x4 v = *(const u32x4*)(corner + row * CW * 2 + ((out_ch ^ swizzle(row)) * 16));
+    if (there(it)) __builtin_nontemporal_store(v, (u32x4*)(p.Out + out_offset(it)));
   }
 }
 
-template <int BQ, int D>
-int launch(const GemmOParams& p, int tiles, hipStream_t stream) {
-  constexpr size_t lds = sa_gemm::Stages<kBN, BQ, (BQ / 64) * (kBN / 64)>::kLdsBytes;
-  constexpr int threads = (BQ / 64) * 2 * 64;
+template <int TM, int TN, int WM, int WN, int WB, int XB, int D, bool FLAGGED>
+int launch_tiles(const GemmOParams& p, int B, hipStream_t stream) {
+  constexpr size_t stage_lds = sa_gemm::Pipe<TN, TM, WN, WM, WB, XB>::kLdsBytes;
+  constexpr size_t out_lds = (size_t)TM * TN * 2;
+  constexpr size_t lds = stage_lds > out_lds ? stage_lds : out_lds;
+  static_assert(lds <= 160 * 1024, "LDS of a CU");
   static std::once_flag once;
   static hipError_t attr_err = hipSuccess;
   std::call_once(once, [] {
-    attr_err = hipFuncSetAttribute((const void*)gemm_o_kernel<BQ, D>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    attr_err = hipFuncSetAttribute((const void*)gemm_o_kernel<TM, TN, WM, WN, WB, XB, D, FLAGGED>,
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   });
   if (attr_err != hipSuccess)
     return sa_fail(SPARSE_ATTN_ERR_HIP, "hipFuncSetAttribute failed: %s", hipGetErrorString(attr_err));
-  hipLaunchKernelGGL((gemm_o_kernel<BQ, D>), dim3(tiles), dim3(threads), lds, stream, p);
+  const int tiles = B * ((p.tok_end - p.tok_begin + TM - 1) / TM) * ((p.C_out + TN - 1) / TN);
+  hipLaunchKernelGGL((gemm_o_kernel<TM, TN, WM, WN, WB, XB, D, FLAGGED>), dim3(tiles), dim3(WM * WN * 64), lds, stream, p);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return sa_fail(SPARSE_ATTN_ERR_HIP, "gemm_o launch failed: %s", hipGetErrorString(e));
   return 0;
+}
+
+// Which tile: without flags by the number of 128 x 128 tiles as in the query projection (33024 tokens, 24 heads of 128, 3072
+// channels: 625 -> 512 us plain, 697 -> 602 with two terms); with flags one token block per tile, because the heads it
+// visits are its own, and two workgroups per CU, because with few heads a tile is a chain of memory round trips (128 x
+// 256 tiles, one per CU: 5 % slower at 90 % cached heads); blocks of 64 tokens with 256 channels (9001 tokens, 50 %
+// cached: 113 against 119 us with 128 channels, 90 %: 38 against 36).
+template <int D>
+int launch(GemmOParams p, int B, int block_q, hipStream_t stream) {
+  if (!p.flags) {
+    const int tok = p.tok_end - p.tok_begin;
+    const long long units = (long long)B * ((tok + 127) / 128) * (p.C_out / 128);
+    if (units <= 256) return launch_tiles<128, 128, 2, 2, 2, 3, D, false>(p, B, stream);
+    if (units <= 512) return launch_tiles<256, 128, 4, 2, 3, 3, D, false>(p, B, stream);
+    const int n_col = (p.C_out + 255) / 256, n_tok = (tok + 255) / 256;
+    const long long tiles = (long long)B * n_tok * n_col, full = tiles / 256 * 256;
+    const int keep = (int)(full / ((long long)B * n_col));
+    if (tiles > full && tiles - full <= 128 && keep > 0) {
+      GemmOParams rest = p;
+      p.tok_end = rest.tok_begin = p.tok_begin + keep * 256;
+      if (int rc = launch_tiles<256, 256, 4, 2, 2, 3, D, false>(p, B, stream)) return rc;
+      return launch<D>(rest, B, block_q, stream);
+    }
+    return launch_tiles<256, 256, 4, 2, 2, 3, D, false>(p, B, stream);
+  }
+  if (block_q == 128) return launch_tiles<128, 128, 2, 2, 2, 3, D, true>(p, B, stream);
+  return launch_tiles<64, 256, 1, 4, 2, 2, D, true>(p, B, stream);
 }
 
 bool ranges_overlap(const void* a, size_t na, const void* b, size_t nb) {
@@ -341,7 +424,8 @@ int gemm_o_run(const void* O, const void* W, const void* bias, const uint8_t* ca
   p.Out = (char*)Out;
   p.H = H;
   p.L = L;
-  p.Tq = tq;
+  p.tok_begin = 0;
+  p.tok_end = L;
   p.C_out = C_out;
   p.select = select_cached;
   p.n_terms = 0;
@@ -366,10 +450,7 @@ int gemm_o_run(const void* O, const void* W, const void* bias, const uint8_t* ca
       for (int d = 1; d < n_terms; ++d) p.term[d - 1] = (const char*)terms[d];
     }
   }
-  if (block_q == 128 && D == 128) return launch<128, 128>(p, (int)tiles, stream);
-  if (block_q == 128 && D == 64) return launch<128, 64>(p, (int)tiles, stream);
-  if (block_q == 64 && D == 128) return launch<64, 128>(p, (int)tiles, stream);
-  return launch<64, 64>(p, (int)tiles, stream);
+  return D == 128 ? launch<128>(p, B, block_q, stream) : launch<64>(p, B, block_q, stream);
 }
 
 }  // namespace

@@ -31,6 +31,7 @@ using sa_gemm::kStepK;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 #define LDS_PTR(T) T __attribute__((address_space(3)))*
 
@@ -182,6 +183,44 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) gemm_q_kernel(const GemmQPara
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[a][c][e] = 0.f;
 
+  // The tile's cos / sin rows, 16-byte pieces.  They are requested behind the last stage and land under its MFMAs (256 x
+  // 256 tiles have no registers for that: there they are requested behind the loop).
+  constexpr int CHT = D / 8;                      // 16-byte chunks of a table row
+  constexpr int PER = TABB / 16 / NT;             // pieces of a table per thread
+  static_assert(TABB % (16 * NT) == 0, "table pieces must split evenly over the threads");
+  constexpr bool kEarly = A * C < 8;
+  f32x4 vc[kEarly ? PER : 1], vs[kEarly ? PER : 1];
+  auto table_at = [&](int u) -> unsigned {        // byte offset (at most 2^21 rows of 256 bytes)
+    const int e = u * NT + tid, row = e / CHT;
+    return ((unsigned)(run_tok0(row) + min(row % BR, max(run_rows(row), 1) - 1)) * CHT + e % CHT) * 16;
+  };
+  auto prefetch_tables = [&]() -> int {
+    if constexpr (NORM_ROPE && kEarly) {
+      if (p.rope_cos) {
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+          vc[u] = *(const f32x4*)((const char*)p.rope_cos + table_at(u));
+          vs[u] = *(const f32x4*)((const char*)p.rope_sin + table_at(u));
+        }
+        return 2 * PER;
+      }
+    }
+    return 0;
+  };
+
+  // Bias and gain of the tile, one value per thread, in flight during the reduction (256 x 256 tiles have no registers
+  // for that either).  Loaded without a branch -- from the weights where there is none -- and converted behind the
+  // loop, so that nothing waits for them here.
+  const uint16_t* const bias_p = p.bias ? p.bias : (const uint16_t*)p.W;
+  const uint16_t* const gain_p = p.norm_w ? p.norm_w : (const uint16_t*)p.W;
+  auto load_bias = [&]() -> unsigned { return bias_p[min(n0 + min(tid, TN - 1), p.H * D - 1)]; };
+  auto load_gain = [&]() -> unsigned { return gain_p[min(tid, D - 1)]; };
+  unsigned bias_bits = 0, gain_bits = 0;
+  if constexpr (kEarly) {
+    bias_bits = load_bias();
+    if constexpr (NORM_ROPE) gain_bits = load_gain();
+  }
+
   size_t k_off = 0;
   st.run(
       smem, acc, p.C / kStepK,
@@ -194,63 +233,62 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) gemm_q_kernel(const GemmQPara
         const size_t at = k_off;
         k_off += kRowB;
         return at;
-      });
+      },
+      prefetch_tables);
   __syncthreads();                                // every wave is done reading the operand stages
 
   // ---- epilogue: lane holds token 32 * c + l32 and, per accumulator quad q4, channels 32 * a + 8 * q4 + 4 * half
   // + 0..3 of this wave's corner
   float* const bias_f = (float*)(smem + kVec);
   float* const gain_f = (float*)(smem + kGain);
-  if (p.bias) {
-    for (int e = tid; e < TN; e += NT) bias_f[e] = __builtin_bit_cast(float, (unsigned)p.bias[min(n0 + e, p.H * D - 1)] << 16);
+  static_assert(TN <= NT && D <= NT, "one bias and one gain value per thread");
+  if constexpr (!kEarly) {
+    bias_bits = load_bias();
+    if constexpr (NORM_ROPE) gain_bits = load_gain();
   }
-  constexpr int CHT = D / 8;                      // 16-byte chunks of a table row
+  if (tid < TN) bias_f[tid] = p.bias ? __builtin_bit_cast(float, bias_bits << 16) : 0.f;
   auto tab_swizzle = [](int row) { return CHT == 16 ? (row & 15) : ((row >> 1) & 7); };
   if constexpr (NORM_ROPE) {
-    if (p.norm_w) {
-      for (int e = tid; e < D; e += NT) gain_f[e] = __builtin_bit_cast(float, (unsigned)p.norm_w[e] << 16);
-    }
+    if (tid < D) gain_f[tid] = p.norm_w ? __builtin_bit_cast(float, gain_bits << 16) : 1.f;
     // The tile's cos / sin rows come through LDS: read straight from memory in
-    // the accumulator layout, every lane would fetch 8 bytes from its own row.  All loads are requested before the
-    // first is stored; 16-byte chunks are permuted by the token so that the 32 tokens of a read spread over the banks.
+    // the accumulator layout, every lane would fetch 8 bytes from its own row.  16-byte chunks are permuted by the token so that the 32 tokens of a read spread over the banks.
     if (p.rope_cos) {
-      constexpr int PER = TABB / 16 / NT;
-      static_assert(TABB % (16 * NT) == 0, "table pieces must split evenly over the threads");
-      const float4* gc = (const float4*)p.rope_cos;
-      const float4* gs = (const float4*)p.rope_sin;
-      float4 vc[PER], vs[PER];
-#pragma unroll
-      for (int u = 0; u < PER; ++u) {
-        const int e = u * NT + tid, row = e / CHT;
-        const size_t at = (size_t)(run_tok0(row) + min(row % BR, max(run_rows(row), 1) - 1)) * CHT + e % CHT;
-        vc[u] = gc[at];
-        vs[u] = gs[at];
-      }
-#pragma unroll
-      for (int u = 0; u < PER; ++u) {
+      auto put = [&](int u, f32x4 c, f32x4 n) {
         const int e = u * NT + tid, row = e / CHT;
         const int o = row * CHT * 16 + ((e % CHT) ^ tab_swizzle(row)) * 16;
-        *(float4*)(smem + o) = vc[u];
-        *(float4*)(smem + TABB + o) = vs[u];
+        *(f32x4*)(smem + o) = c;
+        *(f32x4*)(smem + TABB + o) = n;
+      };
+      if constexpr (kEarly) {
+#pragma unroll
+        for (int u = 0; u < PER; ++u) put(u, vc[u], vs[u]);
+      } else {
+        f32x4 c[PER], n[PER];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+          c[u] = *(const f32x4*)((const char*)p.rope_cos + table_at(u));
+          n[u] = *(const f32x4*)((const char*)p.rope_sin + table_at(u));
+        }
+#pragma unroll
+        for (int u = 0; u < PER; ++u) put(u, c[u], n[u]);
       }
     }
   }
   __syncthreads();
-  if (p.bias) {
+  // (without a bias zeros are added: a branch here makes the compiler keep the accumulators twice)
 #pragma unroll
-    for (int a = 0; a < A; ++a)
+  for (int a = 0; a < A; ++a)
 #pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const float4 bv = *(const float4*)(bias_f + wn * CW + 32 * a + 8 * q4 + 4 * half);
+    for (int q4 = 0; q4 < 4; ++q4) {
+      const float4 bv = *(const float4*)(bias_f + wn * CW + 32 * a + 8 * q4 + 4 * half);
 #pragma unroll
-        for (int c = 0; c < C; ++c) {
-          acc[a][c][4 * q4 + 0] += bv.x;
-          acc[a][c][4 * q4 + 1] += bv.y;
-          acc[a][c][4 * q4 + 2] += bv.z;
-          acc[a][c][4 * q4 + 3] += bv.w;
-        }
+      for (int c = 0; c < C; ++c) {
+        acc[a][c][4 * q4 + 0] += bv.x;
+        acc[a][c][4 * q4 + 1] += bv.y;
+        acc[a][c][4 * q4 + 2] += bv.z;
+        acc[a][c][4 * q4 + 3] += bv.w;
       }
-  }
+    }
   if constexpr (NORM_ROPE) {
     // Equation 2: token-wise RMS normalisation over the head's D channels, then the rotation.  A token's sum of
     // squares is spread over this lane's values, the lane 32 further on, and the other wave of a head in two waves.
@@ -284,8 +322,7 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) gemm_q_kernel(const GemmQPara
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4) {
         const int d0 = (wn * CW + 32 * a + 8 * q4 + 4 * half) % D;     // channel inside the head
-        float4 gain = make_float4(1.f, 1.f, 1.f, 1.f);
-        if (p.norm_w) gain = *(const float4*)(gain_f + d0);
+        const float4 gain = *(const float4*)(gain_f + d0);
 #pragma unroll
         for (int c = 0; c < C; ++c) {
           const float inv = inv_rms[c][a / NB % HPW];

@@ -173,3 +173,50 @@ def test_output_initialised_by_op_reuse_in_one_call(D, bq, n_terms, L):
     print(f"[parity] gemm_o_reuse D={D} bq={bq} terms={n_terms}: max-abs {err.max():.3e}, beyond the usual bar "
           f"{(err > tol).mean() * 100:.3f}%, bit-identical to the rounded oracle {exact * 100:.2f}%", flush=True)
     assert (err <= loose).all() and (err > tol).mean() < 2e-3 and exact > 0.97
+
+
+# every tile of the dispatch at its edges: (B, H, L, D, C_out, block_q, cached share or None for no flags)
+TILE_CASES = [
+    (1, 1, 1, 64, 128, 64, None),            # one stage, one token
+    (2, 3, 129, 128, 384, 64, None),         # 128 x 128 tiles, one token in the last
+    (1, 2, 4097, 64, 2048, 128, None),       # 256 x 128 tiles (528 of 128 x 128), two stages
+    (1, 3, 8191, 64, 1152, 128, None),       # 256 x 256 tiles, last column tile half full, three stages
+    (1, 1, 11300, 128, 1536, 128, None),     # 256 x 256 tiles and the last token tiles done with the small ones
+    (1, 64, 300, 64, 256, 128, 0.9),         # as many heads as the bitmap holds, short last block
+    (2, 7, 700, 128, 384, 128, 0.7),
+    (2, 7, 700, 128, 384, 64, 0.7),          # 64 x 256 tiles, last column tile half full
+    (1, 5, 450, 64, 640, 64, 0.8),
+]
+
+
+@pytest.mark.parametrize("B,H,L,D,C_out,bq,cached", TILE_CASES)
+def test_every_tile_at_its_edges(B, H, L, D, C_out, bq, cached):
+    """Plain, with an addend, and with one to four terms of the cached bias (where the loads of the first two are in
+    flight during the reduction), for both values of the selector."""
+    print(f"[case] gemm_o tiles B={B} H={H} L={L} D={D} C={C_out} bq={bq} cached={cached}", flush=True)
+    O, W, bias, _ = _case(80 + L, B, H, L, D, C_out, bq, None)
+    flags = None
+    if cached is not None:
+        flags = (np.random.default_rng(81 + L).random((B, H, -(-L // bq))) < cached).astype(np.uint8)
+        flags[0, :, 0] = 1                   # a block without a computed head
+        flags[0, :, -1] = 0                  # one without a cached head
+    r = np.random.default_rng(82 + L)
+    terms = [synth.normal_bf16(r, (B, L, C_out)) for _ in range(4)]
+    for select in (0, 1):
+        ref, ref_bits = oracle.gemm_o(O, W, bias, flags, select, None, bq)
+        _check(_run(O, W, bias, flags, select, None, bq), ref, ref_bits, f"select {select}")
+    ref, ref_bits = oracle.gemm_o(O, W, bias, flags, 0, terms[0], bq)
+    _check(_run(O, W, bias, flags, 0, terms[0], bq), ref, ref_bits, "addend")
+    for n in (1, 2, 3, 4):
+        coef = pkg.sparse_taylor_coefficients(n - 1, 2.0)
+        ref, ref_bits = oracle.gemm_o_reuse(O, W, bias, flags, terms[:n], coef, bq)
+        Out = torch.zeros((B, L, C_out), dtype=torch.bfloat16, device="cuda:0")
+        pkg.sparse_gemm_o_reuse(up_bf16(O), up_bf16(W), up_bf16(bias), up_u8(flags), [up_bf16(t) for t in terms[:n]], coef,
+                                Out, bq)
+        torch.cuda.synchronize()
+        # the forecast bias is rounded to bf16 before it is added: where its fp32 sum and the oracle's fp64 sum lie on two
+        # sides of a rounding boundary it differs by one step, at most 2^-7 of its size
+        got = synth.bf16_bits_to_f32(down_bits(Out)).astype(np.float64)
+        forecast = sum(np.abs(c * synth.bf16_bits_to_f32(t).astype(np.float64)) for c, t in zip(coef, terms))
+        assert (np.abs(got - ref) <= np.abs(ref) * 2.0 ** -8 + forecast * 2.0 ** -7 + 2e-3).all(), f"{n} terms"
+        assert (down_bits(Out) == ref_bits).mean() > 0.97
