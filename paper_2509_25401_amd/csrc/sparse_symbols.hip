@@ -1,10 +1,10 @@
 // Sparse-symbol generation of an Update step (Section 3.3 "Logical Masks Generation", Equation 1, and
 // the tau_kv / S_q rules of the settings table in the appendix) for gfx950.
 //
-// Three kernels, all plain fp32 vector arithmetic:
+// Three kernels, all in fp32 (vector instructions, and matrix instructions for the map's scores):
 //   pool_blocks   mean of the n*b_q query rows / n*b_k key rows of every pooled block (granularity n): the only
 //                 pass over Q and K, HBM-bound (reads both tensors once, 16 bytes per lane, row-contiguous)
-//   map_rows      one workgroup per 8 rows of the compressed attention map of one head: scores of the
+//   map_rows      one workgroup per 16 rows of the compressed attention map of one head: scores of the
 //                 pooled queries against all pooled keys (scale 1/sqrt(d)), row softmax, then for
 //                 every row the block-skipping rule -- a key block is skipped iff the sum of all row
 //                 entries that come at or before it in ascending order (ties by index) stays <= tau_kv
@@ -17,9 +17,8 @@
 //                 ascending cumulative sums of C and of G both stay <= tau_c times the totals; text
 //                 blocks are never cached; if the share of blocks left to compute drops below S_q,
 //                 every block of the head is cached.
-// Neither rule needs a sort.  Equation 1 (once per head): entry v adds up every entry that is smaller, or equal with
-// a smaller-or-same index.  The skipping rule (once per map row): the skipped set is "everything up to a threshold
-// value", found by bisection on the bits of that value.
+// Neither rule needs a sort: both select everything up to a threshold value, found by bisection on the bits of that
+// value.  At 33024 tokens and 24 heads pool_blocks is at the memory's rate (61 us, 6.6 TB/s), the other two are latency.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -32,18 +31,9 @@
 
 namespace {
 
-constexpr int kMapRows = 8;          // map rows per workgroup (two per wave)
-constexpr int kChunk = 32;           // pooled key rows staged in LDS per step
+// map rows per workgroup: 16 for each tile of rows; long rows (beyond 512 entries) leave LDS for one tile only
+constexpr int map_rows_per_wg(bool long_rows) { return long_rows ? 16 : 32; }
 constexpr int kMaxBlocks = 2048;     // blocks per sequence the LDS arrays are sized for
-
-__device__ __forceinline__ float wave_max(float v) {
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-  return v;
-}
-__device__ __forceinline__ float wave_sum(float v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
-}
 
 // Sum over the 64 lanes, the same bits in every lane, without going through LDS: exchanges inside a row of 16
 // lanes are DPP operands of the add, the two exchanges between rows are the gfx950 lane-swap instructions.
@@ -67,22 +57,6 @@ __device__ __forceinline__ float wave_sum_dpp(float v) {
     v = __uint_as_float((unsigned)sw[0]) + __uint_as_float((unsigned)sw[1]);
   }
   return v;
-}
-
-// Block-wide reductions for 256 threads; `red` is 4 floats of LDS.  Every thread gets the result.
-__device__ __forceinline__ float block_max(float v, float* red) {
-  v = wave_max(v);
-  __syncthreads();
-  if (threadIdx.x % 64 == 0) red[threadIdx.x / 64] = v;
-  __syncthreads();
-  return fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-}
-__device__ __forceinline__ float block_sum(float v, float* red) {
-  v = wave_sum(v);
-  __syncthreads();
-  if (threadIdx.x % 64 == 0) red[threadIdx.x / 64] = v;
-  __syncthreads();
-  return (red[0] + red[1]) + (red[2] + red[3]);
 }
 
 // Pooled queries [BH][Tq][D], then pooled keys [BH][Tk][D]: mean over the pooled block's rows.  Grid
@@ -124,201 +98,345 @@ __global__ void __launch_bounds__(256) pool_blocks(const uint16_t* __restrict__ 
   }
 }
 
-// The skipping rule without a sort.  "Skip block j iff the ascending cumulative sum at j is <= tau" selects a prefix
-// of the ascending order, i.e. all entries up to some value theta (plus, among entries equal to the next value,
-// the first few in index order).  S(x) = sum of the entries <= x is a non-decreasing step function of x (also as
-// computed here in fp32: a fixed summation structure is monotone in every term), so the largest float theta with
-// S(theta) <= tau is found by fixing its bits from the top: 30 wave-wide conditional sums per row instead of one
-// per entry.  Entries lie in (0, 1], so bit 29 is the highest that can be set.  Two rows (pa, pb) are searched
-// together so that their reductions overlap.  s_* returns S(theta_*).
-__device__ __forceinline__ void find_thresholds2(const float* pa, const float* pb, int T, int lane, float tau,
-                                                 float& theta_a, float& theta_b, float& s_a, float& s_b) {
-  unsigned lo_a = 0u, lo_b = 0u;
-  float sa = 0.f, sb = 0.f;
-  for (int bit = 29; bit >= 0; --bit) {
-    const float ca = __uint_as_float(lo_a | (1u << bit)), cb = __uint_as_float(lo_b | (1u << bit));
-    float xa = 0.f, xb = 0.f;
-    for (int k = lane; k < T; k += 64) {
-      const float a = pa[k], b = pb[k];
-      xa += a <= ca ? a : 0.f;
-      xb += b <= cb ? b : 0.f;
-    }
-    xa = wave_sum_dpp(xa);   // the same sum in every lane
-    xb = wave_sum_dpp(xb);
-    if (xa <= tau) {
-      lo_a |= 1u << bit;
-      sa = xa;
-    }
-    if (xb <= tau) {
-      lo_b |= 1u << bit;
-      sb = xb;
+// Maximum over the 64 lanes, the same exchanges.
+__device__ __forceinline__ float wave_max_dpp(float v) {
+  auto dpp = [](float x, auto ctrl) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xf, 0xf, true));
+  };
+  v = fmaxf(v, dpp(v, std::integral_constant<int, 0xB1>{}));
+  v = fmaxf(v, dpp(v, std::integral_constant<int, 0x4E>{}));
+  v = fmaxf(v, dpp(v, std::integral_constant<int, 0x141>{}));
+  v = fmaxf(v, dpp(v, std::integral_constant<int, 0x140>{}));
+  {
+    const unsigned bits = __float_as_uint(v);
+    const auto sw = __builtin_amdgcn_permlane16_swap(bits, bits, false, false);
+    v = fmaxf(__uint_as_float((unsigned)sw[0]), __uint_as_float((unsigned)sw[1]));
+  }
+  {
+    const unsigned bits = __float_as_uint(v);
+    const auto sw = __builtin_amdgcn_permlane32_swap(bits, bits, false, false);
+    v = fmaxf(__uint_as_float((unsigned)sw[0]), __uint_as_float((unsigned)sw[1]));
+  }
+  return v;
+}
+
+// The first steps of the above: over the 16 lanes of a row of lanes.
+template <class Op>
+__device__ __forceinline__ float row16_reduce(float v, Op op) {
+  auto dpp = [](float x, auto ctrl) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xf, 0xf, true));
+  };
+  v = op(v, dpp(v, std::integral_constant<int, 0xB1>{}));
+  v = op(v, dpp(v, std::integral_constant<int, 0x4E>{}));
+  v = op(v, dpp(v, std::integral_constant<int, 0x141>{}));
+  return op(v, dpp(v, std::integral_constant<int, 0x140>{}));
+}
+template <int G>
+__device__ __forceinline__ float group_sum(float v) {
+  if constexpr (G == 64) return wave_sum_dpp(v);
+  else return row16_reduce(v, [](float a, float b) { return a + b; });
+}
+template <int G>
+__device__ __forceinline__ float group_max(float v) {
+  if constexpr (G == 64) return wave_max_dpp(v);
+  else return row16_reduce(v, [](float a, float b) { return fmaxf(a, b); });
+}
+
+// G lanes (a wave, or 16 lanes: four rows per wave) hold one row of values, entry l + G * n in the n-th place of lane l:
+// NP > 0: in registers (those past T hold +inf, which no finite threshold admits), NP = 0: in LDS.
+template <int G, int NP>
+struct Row {
+  float v[NP > 0 ? NP : 1];
+  const float* lds;
+  int T, l;
+  __device__ __forceinline__ void load(const float* p, int T_, int l_) {
+    lds = p;
+    T = T_;
+    l = l_;
+    if constexpr (NP > 0) {
+#pragma unroll
+      for (int n = 0; n < NP; ++n) v[n] = l + G * n < T ? p[l + G * n] : INFINITY;
     }
   }
-  theta_a = __uint_as_float(lo_a);
-  theta_b = __uint_as_float(lo_b);
-  s_a = sa;
-  s_b = sb;
+  template <class F>
+  __device__ __forceinline__ void each(F&& f) const {
+    if constexpr (NP > 0) {
+#pragma unroll
+      for (int n = 0; n < NP; ++n) f(n, v[n]);
+    } else {
+      for (int n = 0; G * n < T; ++n) f(n, l + G * n < T ? lds[l + G * n] : INFINITY);
+    }
+  }
+  // sum of the entries <= x, the same bits in every lane of the row
+  __device__ __forceinline__ float sum_upto(float x) const {
+    float s = 0.f;
+    each([&](int, float a) { s += a <= x ? a : 0.f; });
+    return group_sum<G>(s);
+  }
+};
+
+// Selection of a prefix of the ascending order without a sort.  "Select entry j iff the ascending cumulative sum at j is
+// <= limit" selects all entries up to some value theta (plus, among entries equal to the next value, the first few in
+// index order).  S(x) = sum of the entries <= x is a non-decreasing step function of x (also as computed here in
+// fp32: a fixed summation structure is monotone in every term), so the largest float theta with S(theta) <= limit is
+// found by fixing its bits from the top: at most 31 conditional sums per row instead of one per entry.  The lower bits
+// are not needed once no entry lies between the candidates left (looked at every third bit; mostly after some 14).
+// M rows per group of lanes are searched together so that their reductions overlap.  sum[r] returns S(theta[r]).
+template <int G, int NP, int M>
+__device__ __forceinline__ void find_thresholds(const Row<G, NP> (&row)[M], const float (&limit)[M], float (&theta)[M], float (&sum)[M]) {
+  unsigned lo[M];
+#pragma unroll
+  for (int r = 0; r < M; ++r) {
+    lo[r] = 0u;
+    sum[r] = 0.f;
+  }
+  for (int bit = 30; bit >= 0; --bit) {
+    float s[M];
+#pragma unroll
+    for (int r = 0; r < M; ++r) s[r] = row[r].sum_upto(__uint_as_float(lo[r] | (1u << bit)));
+#pragma unroll
+    for (int r = 0; r < M; ++r) {
+      // (the pattern of +inf and those above it are no candidates)
+      if (s[r] <= limit[r] && (lo[r] | (1u << bit)) < 0x7f800000u) {
+        lo[r] |= 1u << bit;
+        sum[r] = s[r];
+      }
+    }
+    if (bit % 3 == 0 && bit <= 18) {
+      bool open = false;
+#pragma unroll
+      for (int r = 0; r < M; ++r) {
+        const float from = __uint_as_float(lo[r]), to = __uint_as_float(lo[r] | ((1u << bit) - 1u));
+        row[r].each([&](int, float a) { open |= a > from && a <= to; });
+      }
+      if (__builtin_amdgcn_ballot_w64(open) == 0ull) break;
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < M; ++r) theta[r] = limit[r] >= 0.f ? __uint_as_float(lo[r]) : -1.f;   // (a limit that is no number admits nothing)
+}
+
+// This row's bits of a wave ballot.
+template <int G>
+__device__ __forceinline__ unsigned long long group_bits(unsigned long long ballot, int lane) {
+  return G == 64 ? ballot : (ballot >> (lane & 48)) & 0xffffull;
 }
 
 // Entries equal to the smallest value above theta come next in the ascending order, in index order: how many of
-// them still fit under tau when added one by one to S(theta).  (With distinct values: none, by the choice of theta.)
-__device__ __forceinline__ void next_value_ties(const float* pr, int T, int lane, float theta, float s_theta, float tau,
-                                                float& next, int& n_skip) {
+// them still fit under the limit when added one by one to S(theta).  (With distinct values: none, by the choice of theta.)
+template <int G, int NP>
+__device__ __forceinline__ void next_value_ties(const Row<G, NP>& row, int lane, float theta, float s_theta, float limit,
+                                                float& next, int& n_more) {
   float nx = INFINITY;
-  for (int k = lane; k < T; k += 64) {
-    const float a = pr[k];
-    nx = fminf(nx, a > theta ? a : INFINITY);
-  }
-  for (int o = 32; o > 0; o >>= 1) nx = fminf(nx, __shfl_xor(nx, o));
+  row.each([&](int, float a) { nx = fminf(nx, a > theta ? a : INFINITY); });
+  nx = -group_max<G>(-nx);
   int m = 0;
-  for (int k0 = 0; k0 < T; k0 += 64) m += __popcll(__ballot(k0 + lane < T && pr[min(k0 + lane, T - 1)] == nx));
-  int n = 0;
+  row.each([&](int, float a) { m += __popcll(group_bits<G>(__ballot(a == nx && a < INFINITY), lane)); });
+  int k = 0;
   float run = s_theta;
-  while (n < m) {
+  while (k < m) {
     run += nx;
-    if (!(run <= tau)) break;
-    ++n;
+    if (!(run <= limit)) break;
+    ++k;
   }
   next = nx;
-  n_skip = n;
+  n_more = k;
 }
 
-// Dynamic LDS: pooled query rows [kMapRows][D], one stage of pooled key rows [kChunk][D + 4] (padded so
-// that 16 lanes reading 16 bytes of 16 different rows hit 64 different banks), map rows [kMapRows][T_pad].
-template <int D>
-__global__ void __launch_bounds__(256) map_rows(const float* __restrict__ pooled, long long n_q_blocks, int Tq, int T, int T_pad,
-                                                int n_tq, int n_t, int row_bytes, float scale, float tau_kv,
-                                                uint8_t* __restrict__ kv_mask, float* __restrict__ text_rows,
-                                                float* __restrict__ text_cols) {
-  extern __shared__ float lds[];
-  constexpr int KS = D + 4;
-  float* q = lds;
-  float* kst = q + kMapRows * D;
-  float* p = kst + kChunk * KS;
-  const int tid = threadIdx.x;
+// 32 rows of one head's map per workgroup (16 if they are long), eight waves.
+//   scores    fp32 matrix instructions, 16 x 16 tiles with 4 products a step: lane (r = lane % 16, g = lane / 16) of an
+//             operand holds channels 16 * u + 4 * g + e of row r, so that both operands come straight from the pooled
+//             means with 16-byte loads of which four lanes share a line, and step (u, e) adds the four channels with
+//             that e.  Wave w takes the tiles of keys 16 * w, 16 * (w + 8), ... against all rows; the keys of the next
+//             two tiles are on their way.
+//   softmax, skipping rule: 16 lanes per row, four rows per wave, in registers (NP entries per lane); a row per wave and
+//             two rows one after the other from LDS where NP = 0.  (The search is issue bound: with a row per wave half
+//             of its instructions were the reduction over 64 lanes.)
+// Dot products with both operands from LDS and the search over 64 lanes took 50 us at 33024 tokens and 24 heads, this 29.
+// Dynamic LDS: map rows [kRows][T_pad].
+template <int D, int NP>
+__global__ void __launch_bounds__(512) map_rows(const float* __restrict__ pooled, long long n_q_blocks, int Tq, int T, int T_pad,
+                                                               int n_tq, int n_t, int row_bytes, float scale, float tau_kv,
+                                                               uint8_t* __restrict__ kv_mask, float* __restrict__ text_rows,
+                                                               float* __restrict__ text_cols) {
+  extern __shared__ float p[];
+  typedef __attribute__((ext_vector_type(4))) float f32x4;
+  constexpr int NWAVES = 8, kRows = map_rows_per_wg(NP == 0), RT = kRows / 16;
+  const int tid = threadIdx.x, w = tid / 64, lane = tid % 64;
   // T = pooled key blocks (columns of the map), n_t of them text; Tq = pooled query blocks (rows), n_tq of them text
-  const int groups = (Tq + kMapRows - 1) / kMapRows;
-  const int bh = blockIdx.x / groups, i0 = (blockIdx.x % groups) * kMapRows;
+  const int groups = (Tq + kRows - 1) / kRows;
+  const int bh = blockIdx.x / groups, i0 = (blockIdx.x % groups) * kRows;
   const float* qt = pooled + (size_t)bh * Tq * D;
   const float* kt = pooled + ((size_t)n_q_blocks + (size_t)bh * T) * D;
-  for (int e = tid; e < kMapRows * D; e += 256) {
-    const int r = e / D, i = min(i0 + r, Tq - 1);
-    q[e] = qt[(size_t)i * D + e % D];
-  }
-  for (int e = tid; e < kMapRows * (T_pad - T); e += 256) p[(e / (T_pad - T)) * T_pad + T + e % (T_pad - T)] = INFINITY;
+  const int r16 = lane & 15, g = lane >> 4;
 
-  // scores: keys come through LDS kChunk at a time (coalesced 16-byte reads of the pooled keys); thread
-  // (key tid % kChunk, row tid / kChunk) then takes one dot product
-  static_assert(256 / kChunk == kMapRows, "one thread per (staged key, row)");
-  const int jj = tid % kChunk, r = tid / kChunk;
-  constexpr int NPF = kChunk * (D / 4) / 256;          // 16-byte pieces of a key stage per thread
-  float4 pre[NPF];                                     // the next stage, in flight while this one is used
-  auto fetch = [&](int j0) {
-    const int nk = min(kChunk, T - j0);
+  constexpr int V = D / 16;                       // 16-byte pieces of a lane's channels
+  auto fetch = [&](const float* base, int row, f32x4 (&v)[V]) {
+    const f32x4* src = (const f32x4*)(base + (size_t)row * D) + g;
 #pragma unroll
-    for (int u = 0; u < NPF; ++u) {
-      const int e = tid + u * 256;
-      pre[u] = e < nk * (D / 4) ? *(const float4*)&kt[(size_t)j0 * D + 4 * e] : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
+    for (int u = 0; u < V; ++u) v[u] = src[4 * u];
   };
-  fetch(0);
-  for (int j0 = 0; j0 < T; j0 += kChunk) {
-    __syncthreads();                                   // the previous stage has been consumed
-    const int nk = min(kChunk, T - j0);
+  f32x4 q[RT][V], k[3][V];
+  const int tiles = (T + 15) / 16;
+  auto fetch_tile = [&](int t, f32x4 (&v)[V]) { fetch(kt, min(16 * min(t, tiles - 1) + r16, T - 1), v); };
+  fetch_tile(w, k[0]);
 #pragma unroll
-    for (int u = 0; u < NPF; ++u) {
-      const int e = tid + u * 256;
-      *(float4*)&kst[(e / (D / 4)) * KS + 4 * (e % (D / 4))] = pre[u];
+  for (int a = 0; a < RT; ++a) fetch(qt, min(i0 + 16 * a + r16, Tq - 1), q[a]);   // rows past the end repeat the last one
+  fetch_tile(w + NWAVES, k[1]);
+  for (int t = w; t < tiles; t += NWAVES) {
+    fetch_tile(t + 2 * NWAVES, k[2]);
+    f32x4 acc[RT];
+#pragma unroll
+    for (int a = 0; a < RT; ++a) acc[a] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < V; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int a = 0; a < RT; ++a)
+          acc[a] = __builtin_amdgcn_mfma_f32_16x16x4f32(q[a][u][e], k[0][u][e], acc[a], 0, 0, 0);
+    const int j = 16 * t + r16;                   // accumulator: column lane % 16, rows 4 * (lane / 16) + 0..3
+    if (j < T) {
+#pragma unroll
+      for (int a = 0; a < RT; ++a)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) p[(16 * a + 4 * g + e) * T_pad + j] = acc[a][e] * scale;
     }
-    __syncthreads();
-    if (j0 + kChunk < T) fetch(j0 + kChunk);
-    if (jj < nk) {
-      const float4* kr = (const float4*)(kst + jj * KS);
-      const float4* qr = (const float4*)(q + r * D);
-      float s0 = 0.f, s1 = 0.f;                         // two partial sums: even and odd 16-byte groups
-#pragma unroll 8
-      for (int c = 0; c < D / 4; c += 2) {
-        const float4 k0 = kr[c], a0 = qr[c], k1 = kr[c + 1], a1 = qr[c + 1];
-        s0 += k0.x * a0.x + k0.y * a0.y + k0.z * a0.z + k0.w * a0.w;
-        s1 += k1.x * a1.x + k1.y * a1.y + k1.z * a1.z + k1.w * a1.w;
+#pragma unroll
+    for (int u = 0; u < V; ++u) {
+      k[0][u] = k[1][u];
+      k[1][u] = k[2][u];
+    }
+  }
+  __syncthreads();
+
+  auto export_text = [&](int i, int j, float v) {
+    if (i < n_tq) text_rows[((size_t)bh * n_tq + i) * T + j] = v;         // i < n_tq < Tq
+    if (j < n_t && i < Tq) text_cols[((size_t)bh * Tq + i) * n_t + j] = v;
+  };
+  const float limit[1] = {tau_kv};
+  float theta[1], s_theta[1], next;
+  int n_more, seen = 0;                           // seen: entries equal to `next` at smaller indices
+  if constexpr (NP > 0) {
+    const int i = i0 + 4 * w + g;                 // this lane's row
+    Row<16, NP> row[1];
+    row[0].load(p + (4 * w + g) * T_pad, T, r16);
+    auto& v = row[0].v;
+    float m = -INFINITY, sum = 0.f;
+#pragma unroll
+    for (int n = 0; n < NP; ++n) m = fmaxf(m, r16 + 16 * n < T ? v[n] : -INFINITY);
+    m = group_max<16>(m);
+#pragma unroll
+    for (int n = 0; n < NP; ++n) {
+      v[n] = r16 + 16 * n < T ? expf(v[n] - m) : 0.f;
+      sum += v[n];
+    }
+    sum = group_sum<16>(sum);
+#pragma unroll
+    for (int n = 0; n < NP; ++n) {
+      const int j = r16 + 16 * n;
+      v[n] = j < T ? v[n] / sum : INFINITY;
+      if (j < T) export_text(i, j, v[n]);
+    }
+    find_thresholds<16, NP, 1>(row, limit, theta, s_theta);
+    next_value_ties(row[0], lane, theta[0], s_theta[0], tau_kv, next, n_more);
+    const unsigned long long below = (1ull << r16) - 1ull;
+#pragma unroll
+    for (int n = 0; n < NP; ++n) {
+      const unsigned long long tie = group_bits<16>(__ballot(v[n] == next), lane);
+      const bool skip = v[n] <= theta[0] || (v[n] == next && seen + __popcll(tie & below) < n_more);
+      seen += __popcll(tie);
+      const unsigned kept = (unsigned)group_bits<16>(__ballot(r16 + 16 * n < T && !skip), lane);   // bit b = block 16 * n + b
+      // the row's first two lanes write two bytes; first block of a byte = bit 7
+      const int byte = 2 * n + r16;
+      if (r16 < 2 && i < Tq && byte < row_bytes)
+        kv_mask[((size_t)bh * Tq + i) * row_bytes + byte] = (uint8_t)(__brev((kept >> (8 * r16)) & 0xffu) >> 24);
+    }
+  } else {
+    for (int rr = 0; rr < 2; ++rr) {
+      const int i = i0 + 2 * w + rr;
+      float* pr = p + (2 * w + rr) * T_pad;
+      float m = -INFINITY, sum = 0.f;
+      for (int j = lane; j < T; j += 64) m = fmaxf(m, pr[j]);
+      m = wave_max_dpp(m);
+      for (int j = lane; j < T; j += 64) {
+        const float e = expf(pr[j] - m);
+        pr[j] = e;
+        sum += e;
       }
-      p[r * T_pad + j0 + jj] = (s0 + s1) * scale;
-    }
-  }
-  __syncthreads();
-
-  // each wave owns two rows from here on; all waves run the same loops (bounds depend on T only)
-  const int w = tid / 64, lane = tid % 64;
-  for (int rr = 0; rr < 2; ++rr) {
-    const int i = i0 + 2 * w + rr;
-    float* pr = p + (2 * w + rr) * T_pad;
-    float m = -INFINITY;
-    for (int j = lane; j < T; j += 64) m = fmaxf(m, pr[j]);
-    m = wave_max(m);
-    float sum = 0.f;
-    for (int j = lane; j < T; j += 64) {
-      const float e = expf(pr[j] - m);
-      pr[j] = e;
-      sum += e;
-    }
-    sum = wave_sum(sum);
-    for (int j = lane; j < T; j += 64) {
-      const float v = pr[j] / sum;
-      pr[j] = v;
-      if (i < n_tq) text_rows[((size_t)bh * n_tq + i) * T + j] = v;       // i < n_tq < Tq
-      if (j < n_t && i < Tq) text_cols[((size_t)bh * Tq + i) * n_t + j] = v;
-    }
-  }
-  __syncthreads();
-
-  const float* pa = p + (2 * w) * T_pad;
-  const float* pb = pa + T_pad;
-  const int ia = i0 + 2 * w, ib = ia + 1;
-  float theta_a, theta_b, s_a, s_b, next_a, next_b;
-  int nskip_a, nskip_b;
-  find_thresholds2(pa, pb, T, lane, tau_kv, theta_a, theta_b, s_a, s_b);
-  next_value_ties(pa, T, lane, theta_a, s_a, tau_kv, next_a, nskip_a);
-  next_value_ties(pb, T, lane, theta_b, s_b, tau_kv, next_b, nskip_b);
-  const unsigned long long below = (1ull << lane) - 1ull;
-  int seen_a = 0, seen_b = 0;                                 // entries equal to next_* at smaller indices
-  for (int j0 = 0; j0 < T; j0 += 64) {
-    const int j = j0 + lane;
-    const bool in = j < T;
-    const float a = in ? pa[j] : INFINITY, b = in ? pb[j] : INFINITY;
-    const unsigned long long tie_a = __ballot(a == next_a), tie_b = __ballot(b == next_b);
-    const bool skip_a = a <= theta_a || (a == next_a && seen_a + __popcll(tie_a & below) < nskip_a);
-    const bool skip_b = b <= theta_b || (b == next_b && seen_b + __popcll(tie_b & below) < nskip_b);
-    seen_a += __popcll(tie_a);
-    seen_b += __popcll(tie_b);
-    const unsigned long long kept_a = __ballot(in && !skip_a), kept_b = __ballot(in && !skip_b);   // bit l = block j0 + l
-    // lanes 0-7 write the bytes of row a, lanes 8-15 those of row b; first block of a byte = bit 7
-    const int byte = j0 / 8 + (lane & 7);
-    const int i = lane < 8 ? ia : ib;
-    if (lane < 16 && i < Tq && byte < row_bytes) {
-      const unsigned long long kept = lane < 8 ? kept_a : kept_b;
-      const unsigned bits = (unsigned)(kept >> (8 * (lane & 7))) & 0xffu;
-      kv_mask[((size_t)bh * Tq + i) * row_bytes + byte] = (uint8_t)(__brev(bits) >> 24);
+      sum = wave_sum_dpp(sum);
+      for (int j = lane; j < T; j += 64) {
+        const float v = pr[j] / sum;
+        pr[j] = v;
+        export_text(i, j, v);
+      }
+      Row<64, 0> row[1];
+      row[0].load(pr, T, lane);                   // (a lane reads what it wrote itself)
+      find_thresholds<64, 0, 1>(row, limit, theta, s_theta);
+      next_value_ties(row[0], lane, theta[0], s_theta[0], tau_kv, next, n_more);
+      const unsigned long long below = (1ull << lane) - 1ull;
+      seen = 0;
+      row[0].each([&](int n, float a) {
+        const unsigned long long tie = __ballot(a == next);
+        const bool skip = a <= theta[0] || (a == next && seen + __popcll(tie & below) < n_more);
+        seen += __popcll(tie);
+        const unsigned long long kept = __ballot(lane + 64 * n < T && !skip);      // bit b = block 64 * n + b
+        const int byte = 8 * n + lane;
+        if (lane < 8 && i < Tq && byte < row_bytes)
+          kv_mask[((size_t)bh * Tq + i) * row_bytes + byte] = (uint8_t)(__brev((unsigned)(kept >> (8 * lane)) & 0xffu) >> 24);
+      });
     }
   }
 }
 
-// Tq / Tk pooled query / key blocks, n_tq / n_tk of them text; pool_q / pool_k tokens per pooled block.
+// One workgroup per head.  Tq / Tk pooled query / key blocks, n_tq / n_tk of them text; pool_q / pool_k tokens per pooled
+// block.  Waves take the text columns side by side for G, then wave 0 searches the threshold of C and wave 1 that of
+// G (19 us with a sum over all entries per entry, 33024 tokens; now 11).
+template <int NP>
 __global__ void __launch_bounds__(256) select_blocks(const float* __restrict__ text_rows,
                                                      const float* __restrict__ text_cols, int Tq, int Tk, int n_tq,
                                                      int n_tk, int pool_q, int pool_k, int L, float tau_c, float s_q,
                                                      uint8_t* __restrict__ cache_flags) {
-  __shared__ float C[kMaxBlocks], G[kMaxBlocks], Ck[kMaxBlocks];
-  __shared__ float red[4];
+  __shared__ float CG[2][kMaxBlocks], Ck[kMaxBlocks], E[4][kMaxBlocks];
+  __shared__ float theta_s[2], next_s[2];
+  __shared__ int more_s[2];
+  __shared__ int cached_s;
   const int bh = blockIdx.x, Tv = Tq - n_tq, Tu = Tk - n_tk, tid = threadIdx.x;
+  const int w = tid / 64, lane = tid % 64;
   const float* tr = text_rows + (size_t)bh * n_tq * Tk;
   const float* tc = text_cols + (size_t)bh * Tq * n_tk;
+  if (tid == 0) cached_s = 0;
   // contribution of every vision key block: what the text rows put on it
   for (int u = tid; u < Tu; u += 256) {
     float c = 0.f;
     for (int j = 0; j < n_tq; ++j) c += tr[(size_t)j * Tk + n_tk + u];
     Ck[u] = c;
   }
-  __syncthreads();
+  for (int v = tid; v < Tv; v += 256) CG[1][v] = 0.f;
+  for (int j0 = 0; j0 < n_tk; j0 += 4) {
+    const int j = j0 + w;
+    if (j < n_tk) {
+      float m = -INFINITY;
+      for (int v = lane; v < Tv; v += 64) {
+        const float x = tc[(size_t)(n_tq + v) * n_tk + j];
+        E[w][v] = x;
+        m = fmaxf(m, x);
+      }
+      m = wave_max_dpp(m);
+      float s = 0.f;
+      for (int v = lane; v < Tv; v += 64) {
+        const float e = expf(E[w][v] - m);
+        E[w][v] = e;
+        s += e;
+      }
+      s = wave_sum_dpp(s);
+      for (int v = lane; v < Tv; v += 64) E[w][v] /= s;
+    }
+    __syncthreads();
+    for (int v = tid; v < Tv; v += 256)
+      for (int jj = 0; jj < min(4, n_tk - j0); ++jj) CG[1][v] += E[jj][v];   // in column order; v belongs to one thread
+    __syncthreads();
+  }
   for (int v = tid; v < Tv; v += 256) {
     float c;
     if (pool_q == pool_k) {
@@ -334,44 +452,57 @@ __global__ void __launch_bounds__(256) select_blocks(const float* __restrict__ t
         if (common > 0) c += Ck[u] * (float)common / (float)(k1 - k0);
       }
     }
-    C[v] = c;
-    G[v] = 0.f;
-  }
-  for (int j = 0; j < n_tk; ++j) {
-    float m = -INFINITY;
-    for (int v = tid; v < Tv; v += 256) m = fmaxf(m, tc[(size_t)(n_tq + v) * n_tk + j]);
-    m = block_max(m, red);
-    float s = 0.f;
-    for (int v = tid; v < Tv; v += 256) s += expf(tc[(size_t)(n_tq + v) * n_tk + j] - m);
-    s = block_sum(s, red);
-    for (int v = tid; v < Tv; v += 256) G[v] += expf(tc[(size_t)(n_tq + v) * n_tk + j] - m) / s;   // v belongs to one thread
+    CG[0][v] = c;
   }
   __syncthreads();
-  // totals in index order: what the ascending sum of the largest entry adds up to as well
-  float tot_c = 0.f, tot_g = 0.f;
-  for (int u = 0; u < Tv; ++u) {
-    tot_c += C[u];
-    tot_g += G[u];
+  if (w < 2) {
+    // the total is the sum of everything in the same summation structure: tau_c = 1 then admits every block
+    Row<64, NP> row[1];
+    row[0].load(CG[w], Tv, lane);
+    float all = 0.f;
+    for (int v = lane; v < Tv; v += 64) all += CG[w][v];
+    all = wave_sum_dpp(all);
+    const float limit[1] = {tau_c * all};
+    float theta[1], s_theta[1], next;
+    int n_more;
+    find_thresholds<64, NP, 1>(row, limit, theta, s_theta);
+    next_value_ties(row[0], lane, theta[0], s_theta[0], limit[0], next, n_more);
+    if (lane == 0) {
+      theta_s[w] = theta[0];
+      next_s[w] = next;
+      more_s[w] = n_more;
+    }
   }
+  __syncthreads();
+  // decisions: 64 blocks per wave and round; equal entries are admitted in index order, so their ranks need the
+  // entries before them (ties are rare: counted only where some are admitted)
+  uint8_t* out = cache_flags + (size_t)bh * Tq;
+  auto admitted = [&](int which, int v) -> bool {
+    const float x = CG[which][v];
+    if (x <= theta_s[which]) return true;
+    if (more_s[which] == 0 || x != next_s[which]) return false;
+    int before = 0;
+    for (int u = 0; u < v; ++u) before += CG[which][u] == x ? 1 : 0;
+    return before < more_s[which];
+  };
   int n_cached = 0;
   unsigned mine = 0;                               // decisions of this thread's blocks, bit n = block tid + 256 n
   for (int v = tid, n = 0; v < Tv; v += 256, ++n) {
-    const float cv = C[v], gv = G[v];
-    float cs_c = 0.f, cs_g = 0.f;
-    for (int u = 0; u < Tv; ++u) {
-      const float cu = C[u], gu = G[u];
-      cs_c += ((cu < cv) | ((cu == cv) & (u <= v))) ? cu : 0.f;      // bitwise on purpose: no branches
-      cs_g += ((gu < gv) | ((gu == gv) & (u <= v))) ? gu : 0.f;
-    }
-    const bool cached = cs_c <= tau_c * tot_c && cs_g <= tau_c * tot_g;
+    const bool cached = admitted(0, v) && admitted(1, v);
     mine |= (cached ? 1u : 0u) << n;
     n_cached += cached ? 1 : 0;
   }
-  const float total_cached = block_sum((float)n_cached, red);    // exact: counts stay far below 2^24
-  const bool degrade = ((float)Tq - total_cached) / (float)Tq < s_q;
-  uint8_t* out = cache_flags + (size_t)bh * Tq;
+  for (int o = 32; o > 0; o >>= 1) n_cached += __shfl_xor(n_cached, o);
+  if (lane == 0) atomicAdd(&cached_s, n_cached);
+  __syncthreads();
+  const bool degrade = ((float)Tq - (float)cached_s) / (float)Tq < s_q;      // counts stay far below 2^24
   for (int b = tid; b < n_tq; b += 256) out[b] = degrade ? 1 : 0;
   for (int v = tid, n = 0; v < Tv; v += 256, ++n) out[n_tq + v] = (degrade || ((mine >> n) & 1u)) ? 1 : 0;
+}
+
+template <int D>
+auto map_for(int T) {
+  return T <= 64 ? map_rows<D, 4> : T <= 128 ? map_rows<D, 8> : T <= 272 ? map_rows<D, 17> : T <= 512 ? map_rows<D, 32> : map_rows<D, 0>;
 }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -432,36 +563,33 @@ int sparse_symbols_update_granular(const void* Q, const void* K, uint8_t* cache_
 
   const int row_bytes = (Tk + 7) / 8;
   const float scale = (float)(1.0 / sqrt((double)D));
-  const int groups = (Tq + kMapRows - 1) / kMapRows;
+  const int map_rows_wg = map_rows_per_wg(Tk > 512);
+  const int groups = (Tq + map_rows_wg - 1) / map_rows_wg;
   const int T_pad = (Tk + 3) & ~3;
-  const size_t map_lds = ((size_t)kMapRows * D + (size_t)kChunk * (D + 4) + (size_t)kMapRows * T_pad) * 4;
+  const size_t map_lds = (size_t)map_rows_wg * T_pad * 4;
   static std::once_flag attr_once;
   static hipError_t attr_err = hipSuccess;
   std::call_once(attr_once, [] {
-    constexpr int kMaxLds = (kMapRows * 128 + kChunk * 132 + kMapRows * kMaxBlocks) * 4;
-    attr_err = hipFuncSetAttribute((const void*)map_rows<128>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);
+    constexpr int kMaxLds = map_rows_per_wg(true) * kMaxBlocks * 4;
+    attr_err = hipFuncSetAttribute((const void*)map_rows<128, 0>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);
     if (attr_err == hipSuccess)
-      attr_err = hipFuncSetAttribute((const void*)map_rows<64>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);
+      attr_err = hipFuncSetAttribute((const void*)map_rows<64, 0>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);
   });
   if (attr_err != hipSuccess)
     return sa_fail(SPARSE_ATTN_ERR_HIP, "hipFuncSetAttribute(map_rows) failed: %s", hipGetErrorString(attr_err));
   const unsigned pool_grid = (unsigned)(BH * (Tq > Tk ? Tq : Tk));
-  if (D == 128) {
-    hipLaunchKernelGGL(pool_blocks<128>, dim3(pool_grid, 2), dim3(256), 0, stream, (const uint16_t*)Q,
-                       (const uint16_t*)K, pooled, pool_q, pool_k, Tq, Tk, L, n_q_blocks);
-    HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(map_rows<128>, dim3((unsigned)(BH * groups)), dim3(256), map_lds, stream, pooled, n_q_blocks, Tq, Tk,
-                       T_pad, n_tq, n_tk, row_bytes, scale, tau_kv, kv_mask, text_rows, text_cols);
-  } else {
-    hipLaunchKernelGGL(pool_blocks<64>, dim3(pool_grid, 2), dim3(256), 0, stream, (const uint16_t*)Q,
-                       (const uint16_t*)K, pooled, pool_q, pool_k, Tq, Tk, L, n_q_blocks);
-    HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(map_rows<64>, dim3((unsigned)(BH * groups)), dim3(256), map_lds, stream, pooled, n_q_blocks, Tq, Tk,
-                       T_pad, n_tq, n_tk, row_bytes, scale, tau_kv, kv_mask, text_rows, text_cols);
-  }
+  auto pool = D == 128 ? pool_blocks<128> : pool_blocks<64>;
+  hipLaunchKernelGGL(pool, dim3(pool_grid, 2), dim3(256), 0, stream, (const uint16_t*)Q, (const uint16_t*)K, pooled, pool_q,
+                     pool_k, Tq, Tk, L, n_q_blocks);
   HIP_TRY(hipGetLastError());
-  hipLaunchKernelGGL(select_blocks, dim3((unsigned)BH), dim3(256), 0, stream, text_rows, text_cols, Tq, Tk, n_tq, n_tk,
-                     pool_q, pool_k, L, tau_c, s_q, cache_flags);
+  // rows are searched in registers, 16 lanes to a row; beyond 512 entries in LDS
+  auto map = D == 128 ? map_for<128>(Tk) : map_for<64>(Tk);
+  hipLaunchKernelGGL(map, dim3((unsigned)(BH * groups)), dim3(512), map_lds, stream, pooled, n_q_blocks, Tq, Tk, T_pad,
+                     n_tq, n_tk, row_bytes, scale, tau_kv, kv_mask, text_rows, text_cols);
+  HIP_TRY(hipGetLastError());
+  auto select = Tq <= 128 ? select_blocks<2> : Tq <= 320 ? select_blocks<5> : select_blocks<0>;
+  hipLaunchKernelGGL(select, dim3((unsigned)BH), dim3(256), 0, stream, text_rows, text_cols, Tq, Tk, n_tq, n_tk, pool_q, pool_k,
+                     L, tau_c, s_q, cache_flags);
   HIP_TRY(hipGetLastError());
   return 0;
 }

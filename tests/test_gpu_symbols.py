@@ -215,3 +215,25 @@ def test_granular_symbols_drive_the_plan_they_were_made_for(L, D, bq, bk, n, tex
     print(f"[parity] update->dispatch at granularity {n}: max-abs {err.max():.3e} mean-abs {err.mean():.3e}", flush=True)
     assert (err <= bound).all() and err.mean() <= 1e-3
     plan.destroy()
+
+
+# blocks per sequence around the register tiers of the threshold search (64, 128, 272, 512; 128 and 320 for the flags) and
+# the 16- and 32-row tiles of the map; `repeat`: blocks that repeat, so that equal entries have to be ranked
+@pytest.mark.parametrize("T,short,D,repeat", [
+    (2, 0, 64, False), (16, 3, 128, False), (17, 0, 64, True), (33, 20, 64, False), (64, 0, 128, True), (65, 1, 64, False),
+    (128, 0, 64, False), (129, 0, 64, True), (272, 0, 64, False), (273, 63, 64, True), (320, 0, 64, False), (321, 0, 128, False),
+    (512, 0, 64, True), (513, 5, 64, False)])
+def test_search_tiers(T, short, D, repeat):
+    B, H, block = 1, 2, 64
+    L = T * block - short
+    Q, K = synth.structured_qk(synth.BASE_SEED + 300 + T, B, H, T * block, D, block)
+    if repeat:
+        for x in (Q, K):
+            v = x.reshape(B, H, T, block, D)
+            v[:, :, 2::5] = v[:, :, 1:2]
+    Q, K = np.ascontiguousarray(Q[:, :, :L]), np.ascontiguousarray(K[:, :, :L])
+    for tau_c, tau_kv in ((f32(0.5), f32(0.3)), (f32(0.35), f32(0.7))):
+        ref = oracle.update_symbols(Q, K, block, block, tau_c, tau_kv)
+        flags, mask = run_gpu(Q, K, block, block, tau_c, tau_kv)
+        # (blocks that repeat are near-ties for the fp64 oracle: it may order them by their last bits)
+        compare(ref, flags, mask, T, f"T{T} D{D} repeat={repeat}", max_ambiguous=1.0 if repeat else 0.05, require_identical=False)
