@@ -869,7 +869,9 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
       const auto sw = __builtin_amdgcn_permlane32_swap(bits, bits, false, false);
       const float l_tot = __builtin_bit_cast(float, (unsigned)sw[0]) + __builtin_bit_cast(float, (unsigned)sw[1]);
       const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-      char* const stage = (wave < 2 ? ldsK : ldsV) + (last ^ 1) * TILEB + (wave & 1) * 32 * ROWB;
+      // (256-row blocks: the buffer holds four waves' rows, the other four have a piece of LDS of their own)
+      char* const stage = wave < 4 ? (wave < 2 ? ldsK : ldsV) + (last ^ 1) * TILEB + (wave & 1) * 32 * ROWB
+                                   : smem + 4 * TILEB + 16 + (wave - 4) * 32 * ROWB;
       // (the lane number passes through an empty asm statement: otherwise the two dozen lane-dependent offsets
       // below are computed once, in front of the item loop, and occupy registers for the whole kernel)
       int ln = lane;
@@ -1049,9 +1051,12 @@ bool overlaps(const void* a, const void* b, size_t bytes) {
   return x < y + bytes && y < x + bytes;
 }
 
+// four K / V sub-tiles, two item slots, output rows of the waves beyond four
+constexpr size_t attn_lds(int D, int bq) { return 4 * (size_t)kKeys * D * 2 + 16 + (bq > 128 ? (size_t)(bq - 128) * D * 2 : 0); }
+
 template <int D, int BQ, int BK, bool RAGGED, bool DEALT>
 int launch_attn_variant(const AttnParams& p, int grid, hipStream_t stream) {
-  constexpr size_t lds = 4 * (size_t)kKeys * D * 2 + 16;
+  constexpr size_t lds = attn_lds(D, BQ);
   static std::once_flag once;
   static hipError_t attr_err = hipSuccess;
   std::call_once(once, [] {
@@ -1187,6 +1192,24 @@ int run(const void* Q, const void* K, const void* V, const uint8_t* cache_flags,
 
   HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
 
+  // Without symbols the blocks are the kernel's business.  Larger query blocks read K and V for more rows at a time; they
+  // pay as soon as there are more 128-row blocks than CUs.  24 heads, us, blocks of 64 / 128 / 256 rows: 33024 tokens of
+  // 128 channels - / 10850 / 10660, 4608 tokens - / 247 / 230, 9001 tokens 1573 / - / 926, 2000 tokens - / 60 / 55, 1000
+  // tokens (192 blocks of 128) - / 24 / 30; 9001 tokens of 64 channels 675 / 547 / 627.  The bits of the result do not
+  // depend on the choice: a wave's 32 rows and the order of the keys are the same.
+  if (!plan && !cache_flags && !kv_mask && (long long)B * H * ((L + 127) / 128) > cus) {
+    bq = D == 128 ? 256 : 128;
+    bk = 128;
+    s.bq = bq;
+    s.bk = bk;
+    s.Tq = (L + bq - 1) / bq;
+    s.Tkv = (L + bk - 1) / bk;
+    s.N = B * H * s.Tq;
+    s.row_bytes = (s.Tkv + 7) / 8;
+    s.nw32 = (s.Tkv + 31) / 32;
+    pb = carve((char*)pb.queues, s);     // (no larger than for the caller's blocks)
+  }
+
   hipEvent_t ev[3] = {nullptr, nullptr, nullptr};
   bool record = timed;
   if (timed) {
@@ -1204,7 +1227,7 @@ int run(const void* Q, const void* K, const void* V, const uint8_t* cache_flags,
   // persistent grid: as many workgroups as the CUs hold (8 waves by registers, 160 KiB of LDS), fewer if there are fewer
   // items.  With two per CU whatever their size, the 2-wave workgroups of 64-row blocks left half of the waves idle:
   // 9001 tokens, 24 heads of 64, 64 x 128 blocks at 40 % keep: 330 -> 224 us.
-  const size_t wg_lds = 4 * (size_t)kKeys * D * 2 + 16;
+  const size_t wg_lds = attn_lds(D, bq);
   const int by_lds = (int)(160 * 1024 / wg_lds), by_waves = 8 / (bq / 32);
   const int room = cus * (by_waves < by_lds ? by_waves : by_lds);
   const int grid = s.N < room ? s.N : room;
@@ -1254,7 +1277,8 @@ int run(const void* Q, const void* K, const void* V, const uint8_t* cache_flags,
   }
   p.scale_log2 = (float)(1.4426950408889634 / sqrt((double)D));
   int rc = 0;
-  if (D == 128 && bq == 128 && bk == 128) rc = launch_attn<128, 128, 128>(p, grid, stream);
+  if (D == 128 && bq == 256) rc = launch_attn<128, 256, 128>(p, grid, stream);
+  else if (D == 128 && bq == 128 && bk == 128) rc = launch_attn<128, 128, 128>(p, grid, stream);
   else if (D == 128 && bq == 128 && bk == 64) rc = launch_attn<128, 128, 64>(p, grid, stream);
   else if (D == 128 && bq == 64 && bk == 128) rc = launch_attn<128, 64, 128>(p, grid, stream);
   else if (D == 128 && bq == 64 && bk == 64) rc = launch_attn<128, 64, 64>(p, grid, stream);

@@ -153,6 +153,8 @@ ROUTES = [
     (1, 31, 2100, 128, 128, 128, None, 0.0),   # 527 equal rows: dealt out, some workgroups take two
     (1, 31, 4300, 64, 128, 128, None, 0.0),    # 1054 equal rows: work list
     (1, 17, 4300, 64, 128, 128, None, 0.5),    # flags alone
+    (1, 24, 1409, 128, 64, 64, None, 0.0),     # 288 blocks of 128 rows: done in 256-row blocks whatever the caller's
+    (2, 30, 2500, 128, 128, 128, None, 0.0),   # 600 blocks of 256 rows: some workgroups take three
     (1, 2, 8300, 64, 64, 64, 0.1, 0.2),        # five words a row, 130 bits in rows of 17 bytes
 ]
 
