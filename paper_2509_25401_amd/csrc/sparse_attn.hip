@@ -63,6 +63,7 @@ constexpr int kLongBuckets = 8;       // kept-count buckets of the long rows of 
 constexpr int kFineBuckets = 55;      // ... of its other rows (head by head); with the bucket of cached rows: 64,
 constexpr int kCachedBucket = kLongBuckets + kFineBuckets;   // one lane each in the ranking pass
 constexpr int kWgsPerXcd = 64;        // workgroups of the persistent grid per XCD (32 CUs x 2) the ordering plans for
+constexpr int kCusPerXcd = 32;
 constexpr int kXcds = 8;               // accelerator dies (XCDs) of the MI355X, each with its own L2
 constexpr int kMaxHeadGroups = 24;    // head groups per (XCD, bucket) in the ordering histogram (48 KiB of LDS)
 constexpr int kMaxTq = 16384;
@@ -135,14 +136,19 @@ __device__ inline uint32_t clear_padding(uint32_t word, int w, int Tkv) {
 // Bucket of a row: 0 .. kLongBuckets-1 long (heaviest = 0), then kFineBuckets buckets, then kCachedBucket.
 // `lightest` = the smallest kept count among the queue's computed rows: the fine buckets span lightest .. limit, so
 // that masks whose rows differ by a few blocks only are still sorted block by block.
-__device__ inline int order_major(int key, int Tkv, int limit, int lightest) {
+// The long buckets likewise span the counts that long rows really have (long_lo + 1 .. heaviest).
+struct OrderScale {
+  int limit, long_lo, heaviest, lightest;
+};
+__device__ inline int order_major(int key, const OrderScale& sc) {
   if (key < 0) return kCachedBucket;
   const int count = key & 0xffff;   // < 2^16, bucket counts < 2^6: the products fit in 32 bits
-  if (count > limit)
-    return (kLongBuckets - 1) - (int)((unsigned)(count - limit - 1) * kLongBuckets / (unsigned)(Tkv - limit));
+  if (count > sc.limit)
+    return (kLongBuckets - 1) - (int)((unsigned)(count - sc.long_lo - 1) * kLongBuckets / (unsigned)(sc.heaviest - sc.long_lo));
   return kLongBuckets + (kFineBuckets - 1) -
-         (int)((unsigned)(count - lightest) * kFineBuckets / (unsigned)(limit - lightest + 1));
+         (int)((unsigned)(count - sc.lightest) * kFineBuckets / (unsigned)(sc.limit - sc.lightest + 1));
 }
+
 // Symbol pre-pass: workgroup q decodes the rows of queue q and writes its part of the work list.
 //   decode     one thread per row turns the packed symbols into aligned words, counts the kept key blocks and notes
 //              the first of them (key of the row; -1 for cached rows)
@@ -253,14 +259,14 @@ __global__ void __launch_bounds__(kOrderThreads) plan_queues(const uint8_t* __re
   // row instead
   const int share = (int)min(kept_all / (3ull * kWgsPerXcd), (unsigned long long)Tkv);
   const int limit = (int)heaviest <= share ? (int)heaviest : share;
-  const int lightest = min((int)lightest_u, limit);
+  const OrderScale sc = {limit, max(limit, (int)min(lightest_u, heaviest) - 1), (int)heaviest, min((int)lightest_u, limit)};
   auto bin_of = [&](int major, int r) -> int {
     const int group = (r / Tq) >> shift;
     if (major < kLongBuckets) return major * groups + group;
     if (major < kCachedBucket) return kLongBuckets * groups + group * kFineBuckets + (major - kLongBuckets);
     return kCachedBucket * groups + group;
   };
-  for (int r = tid; r < rows; r += kOrderThreads) atomicAdd(&bins[bin_of(order_major(key_of(r), Tkv, limit, lightest), r)], 1u);
+  for (int r = tid; r < rows; r += kOrderThreads) atomicAdd(&bins[bin_of(order_major(key_of(r), sc), r)], 1u);
   __syncthreads();
   // exclusive scan of the bins: a contiguous chunk per thread, then over the lanes of a wave, then over the waves
   {
@@ -299,7 +305,7 @@ __global__ void __launch_bounds__(kOrderThreads) plan_queues(const uint8_t* __re
         const bool valid = i0 + lane < Tq;
         const int r = hl * Tq + min(i0 + lane, Tq - 1);
         const int key = key_of(r);
-        const int major = valid ? order_major(key, Tkv, limit, lightest) : 0;
+        const int major = valid ? order_major(key, sc) : 0;
         // the lanes whose row falls into the same bucket as this lane's: one ballot per bit of the bucket number
         unsigned long long same = __ballot(valid);
 #pragma unroll
@@ -323,7 +329,7 @@ __global__ void __launch_bounds__(kOrderThreads) plan_queues(const uint8_t* __re
   }
   for (int r = tid; r < rows; r += kOrderThreads) {
     const int key = key_of(r);
-    const uint32_t pos = atomicAdd(&bins[bin_of(order_major(key, Tkv, limit, lightest), r)], 1u);
+    const uint32_t pos = atomicAdd(&bins[bin_of(order_major(key, sc), r)], 1u);
     list[2 * pos] = (uint32_t)global_row(r) | (key < 0 ? kCopyFlag : 0u);
     list[2 * pos + 1] = (uint32_t)key;
   }
@@ -463,8 +469,17 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
   int next_n;                          // DEALT: next row; queues: the first item
   {
     const int q0 = (int)blockIdx.x % kXcds, slot = (int)blockIdx.x / kXcds;
-    next_n = slot + (DEALT ? q0 * (p.N / kXcds) + min(q0, p.N % kXcds) : queue_begin(q0));
-    if (!DEALT && next_n >= queue_begin(q0 + 1)) next_n = -1;
+    if constexpr (DEALT) {
+      next_n = slot + q0 * (p.N / kXcds) + min(q0, p.N % kXcds);
+    } else {
+      // Workgroups s and s + kCusPerXcd of an XCD share a CU.  A queue starts with its longest rows, longest first, so the
+      // first kCusPerXcd of them are handed out backwards: the CUs whose second workgroup comes away empty or with a
+      // short row then have the longest ones, and the sums are even where a queue has one or two rows per CU.
+      const int chunk = slot / kCusPerXcd * kCusPerXcd;
+      const bool back = (slot / kCusPerXcd) % 2 == 0 && chunk + kCusPerXcd <= nwg(q0);
+      next_n = queue_begin(q0) + (back ? 2 * chunk + kCusPerXcd - 1 - slot : slot);
+      if (next_n >= queue_begin(q0 + 1)) next_n = -1;
+    }
   }
   constexpr int kDrawTiles = 6;        // kept blocks an item still has to visit when the next ticket is drawn
   bool drawn = false, first_item = true;
