@@ -58,7 +58,10 @@ typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
 #define LDS_PTR(T) T __attribute__((address_space(3)))*
 #define GLOBAL_PTR(T) T __attribute__((address_space(1)))*
 
-constexpr int kKeys = 64;             // keys per LDS sub-tile
+// Keys per LDS sub-tile.  64-row blocks of 128 channels take 32: four K and V sub-tiles of 64 keys are 64 KiB, of which a
+// CU holds two, and two workgroups of two waves leave half of its waves idle (24 heads, 64-key sub-tiles
+// and now, us: 9001 tokens at 40 % keep 655 -> 478, 33024 tokens at 25 % keep and 50 % cached 2276 -> 1834).
+constexpr int attn_keys(int D, int bq) { return D == 128 && bq == 64 ? 32 : 64; }
 constexpr int kLongBuckets = 8;       // kept-count buckets of the long rows of a queue (longest first, across heads)
 constexpr int kFineBuckets = 55;      // ... of its other rows (head by head); with the bucket of cached rows: 64,
 constexpr int kCachedBucket = kLongBuckets + kFineBuckets;   // one lane each in the ranking pass
@@ -365,7 +368,7 @@ __device__ __forceinline__ unsigned long long sa_scalar_load_b64(const uint32_t*
 }
 
 // ---------------------------------------------------------------------------------------
-// LDS layouts.  A sub-tile is kKeys rows of D bf16, row major, with the 16-byte chunks of a
+// LDS layouts.  A sub-tile is KEYS rows of D bf16, row major, with the 16-byte chunks of a
 // row permuted by an XOR that depends on the row, so that (a) the 32 rows x 16 B that one
 // S^T operand read touches and (b) the 8 rows x 64 B that one transposed V read touches fall
 // into distinct banks.  A direct-to-LDS load writes 1 KiB of consecutive LDS per wave
@@ -390,17 +393,18 @@ template <int D, int BQ, int BK, bool RAGGED, bool DEALT>
 __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
   constexpr int NWAVES = BQ / 32;
   constexpr int NT = NWAVES * 64;
-  constexpr int SUB = BK / kKeys;          // LDS sub-tiles per symbol bit
+  constexpr int KEYS = attn_keys(D, BQ);   // keys per sub-tile
+  constexpr int SUB = BK / KEYS;           // LDS sub-tiles per symbol bit
   constexpr int CH = D / 8;                // 16-byte chunks per row
   constexpr int ROWB = D * 2;              // bytes per row
-  constexpr int TILEB = kKeys * ROWB;      // bytes per K or V sub-tile
+  constexpr int TILEB = KEYS * ROWB;      // bytes per K or V sub-tile
   constexpr int NINST = TILEB / 1024;      // direct-to-LDS wave instructions per sub-tile
   constexpr int NLOAD = NINST / NWAVES;    // of which this wave issues
   constexpr int ROWS_PER_INST = 1024 / ROWB;
   constexpr int KS = D / 16;               // k-steps of the S^T product
   constexpr int DB = D / 32;               // 32-row blocks of O^T
-  constexpr int NQK = 2 * KS;              // MFMAs of S^T per sub-tile
-  constexpr int NPV = 4 * DB;              // MFMAs of O^T per sub-tile
+  constexpr int NQK = KEYS / 32 * KS;      // MFMAs of S^T per sub-tile
+  constexpr int NPV = KEYS / 16 * DB;      // MFMAs of O^T per sub-tile
   constexpr int kPre = 4;                  // operand reads run this many MFMAs ahead
   static_assert(NINST % NWAVES == 0, "sub-tile loads must split evenly over the waves");
 
@@ -644,12 +648,12 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
     // loads lo .. hi-1 of this wave's NLOAD for sub-tile (j, sub)
     auto issue_loads = [&](int j, int sub, auto buf_c, int lo, int hi) {
       constexpr int buf = decltype(buf_c)::value;
-      const size_t tile_off = ((size_t)j * BK + (size_t)sub * kKeys) * ROWB;
+      const size_t tile_off = ((size_t)j * BK + (size_t)sub * KEYS) * ROWB;
       const char* gK = Kh + tile_off;
       const char* gV = Vh + tile_off;
       if constexpr (RAGGED) {
-        const int valid = p.L - (j * BK + sub * kKeys);     // >= 1: sub-tiles past the end are never requested
-        if (valid < kKeys) {
+        const int valid = p.L - (j * BK + sub * KEYS);     // >= 1: sub-tiles past the end are never requested
+        if (valid < KEYS) {
 #pragma unroll
           for (int t = lo; t < hi; ++t) {
             const int r = (wave + t * NWAVES) * ROWS_PER_INST + lane / CH;
@@ -770,10 +774,33 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
         if (nj >= 0) issue_loads(nj, nsub, other_c, t * NLOAD / KS, (t + 1) * NLOAD / KS);
       }
       if constexpr (RAGGED) {
-        if (valid < kKeys) mask_block(0);
+        if (valid < KEYS) mask_block(0);
       }
       if (first) move_reference(0, false);     // the first block of an item sets the reference; block 1 is not formed yet
       // first operands of the O^T product: on their way while the scores of block 1 are formed
+      if constexpr (KEYS == 32) {
+        // one block: its weights have no matrix instructions of this wave to hide under; four workgroups on the CU do
+        bf16x8 vv[NPV];
+#pragma unroll
+        for (int t = 0; t < kPre; ++t) vv[t] = v_read(t);
+        float dl = 0.f;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) chunk(0, c, dl);
+        if (__builtin_amdgcn_ballot_w64(!(dl <= kSumLimit)) != 0) {
+          move_reference(0, false);
+          dl = 0.f;
+#pragma unroll
+          for (int c = 0; c < 8; ++c) chunk(0, c, dl);
+        }
+        l_run += dl;
+#pragma unroll
+        for (int t = 0; t < NPV; ++t) {
+          if (t + kPre < NPV) vv[t + kPre] = v_read(t + kPre);
+          o[t % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vv[t], pb[t / DB], o[t % DB], 0, 0, 0);
+        }
+        __builtin_amdgcn_s_setprio(0);
+        return;
+      }
       bf16x8 va[NPV];
 #pragma unroll
       for (int t = 0; t < kPre; ++t) va[t] = v_read(t);
@@ -782,14 +809,14 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
 #pragma unroll
       for (int t = 0; t < KS; ++t) {
         if (KS + t + kPre < NQK) ka[KS + t + kPre] = k_read(KS + t + kPre);
-        s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[KS + t], qf[t], t == 0 ? neg_ref : s[1], 0, 0, 0);
+        s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[(KS + t) % NQK], qf[t], t == 0 ? neg_ref : s[1], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int cc = 0; cc < CPS; ++cc) chunk(0, t * CPS + cc, dl0);
         __builtin_amdgcn_sched_barrier(0);
       }
       if constexpr (RAGGED) {
-        if (valid < kKeys) mask_block(1);
+        if (valid < KEYS) mask_block(1);
       }
       // !(sum <= limit) also catches an overflowed (infinite or NaN) sum
       if (__builtin_amdgcn_ballot_w64(!(dl0 <= kSumLimit)) != 0) {
@@ -850,7 +877,7 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
     auto step = [&](auto cur, auto other) {
       int nj = j, nsub = sub + 1;
       if constexpr (RAGGED) {
-        if (nsub < SUB && j * BK + nsub * kKeys >= p.L) nsub = SUB;   // the rest of the last block does not exist
+        if (nsub < SUB && j * BK + nsub * KEYS >= p.L) nsub = SUB;   // the rest of the last block does not exist
       }
       if (nsub == SUB) {
         nsub = 0;
@@ -859,7 +886,7 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
       }
       sa_wait_vmem();
       __syncthreads();   // this sub-tile has landed for every wave; the other buffer is free
-      compute(cur, other, RAGGED ? p.L - (j * BK + sub * kKeys) : kKeys, nj, nsub);
+      compute(cur, other, RAGGED ? p.L - (j * BK + sub * KEYS) : KEYS, nj, nsub);
       j = nj;
       sub = nsub;
     };
@@ -884,8 +911,10 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
       const auto sw = __builtin_amdgcn_permlane32_swap(bits, bits, false, false);
       const float l_tot = __builtin_bit_cast(float, (unsigned)sw[0]) + __builtin_bit_cast(float, (unsigned)sw[1]);
       const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-      // (256-row blocks: the buffer holds four waves' rows, the other four have a piece of LDS of their own)
-      char* const stage = wave < 4 ? (wave < 2 ? ldsK : ldsV) + (last ^ 1) * TILEB + (wave & 1) * 32 * ROWB
+      // (a wave's rows take 32 keys' room: K and V hold KEYS / 32 waves' each; the waves 4 to 7 of 256-row blocks have a
+      // piece of LDS of their own)
+      constexpr int PER = KEYS / 32;
+      char* const stage = wave < 4 ? (wave < PER ? ldsK : ldsV) + (last ^ 1) * TILEB + wave % PER * 32 * ROWB
                                    : smem + 4 * TILEB + 16 + (wave - 4) * 32 * ROWB;
       // (the lane number passes through an empty asm statement: otherwise the two dozen lane-dependent offsets
       // below are computed once, in front of the item loop, and occupy registers for the whole kernel)
@@ -1067,7 +1096,7 @@ bool overlaps(const void* a, const void* b, size_t bytes) {
 }
 
 // four K / V sub-tiles, two item slots, output rows of the waves beyond four
-constexpr size_t attn_lds(int D, int bq) { return 4 * (size_t)kKeys * D * 2 + 16 + (bq > 128 ? (size_t)(bq - 128) * D * 2 : 0); }
+constexpr size_t attn_lds(int D, int bq) { return 4 * (size_t)attn_keys(D, bq) * D * 2 + 16 + (bq > 128 ? (size_t)(bq - 128) * D * 2 : 0); }
 
 template <int D, int BQ, int BK, bool RAGGED, bool DEALT>
 int launch_attn_variant(const AttnParams& p, int grid, hipStream_t stream) {
