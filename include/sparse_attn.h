@@ -92,7 +92,7 @@ int sparse_attn_fwd_stream(const void* Q, const void* K, const void* V,
  *   - Every GPU the library runs on holds its own copy of the array until the process ends.  All calls on a
  *     GPU share it, whatever their stream: two calls that overlap in time on one GPU race and give wrong
  *     results.  Calls on one stream, or otherwise ordered, are fine; the array keeps the previous call's
- *     contents and every word a call reads is written by that call's own pre-pass first.
+ *     contents and every word a call reads is written by that call itself first.
  */
 #define SPARSE_ATTN_NOALLOC_SCRATCH_BYTES ((size_t)2 << 20)
 int sparse_attn_fwd_noalloc(const void* Q, const void* K, const void* V,
@@ -104,8 +104,9 @@ int sparse_attn_fwd_noalloc(const void* Q, const void* K, const void* V,
 /*
  * Measurement variant: same work as sparse_attn_fwd_stream, bracketed by HIP events on the
  * given stream, synchronised before returning.  plan_ms (host, may be NULL) receives the
- * duration of the symbol pre-pass (decode, count and ordering of work items), attn_ms (host,
- * may be NULL) the duration of the attention kernel itself, both in milliseconds.
+ * duration of the symbol pre-pass (decode, count and ordering of work items; next to nothing for a call
+ * that needs none: few rows, or no symbols), attn_ms (host, may be NULL) the duration of the attention
+ * kernel itself, both in milliseconds.
  */
 int sparse_attn_fwd_timed(const void* Q, const void* K, const void* V,
                           const uint8_t* cache_flags, const uint8_t* kv_mask,
@@ -148,8 +149,8 @@ int sparse_gemm_q_stream(const void* X, const void* W, const void* bias, const u
  * create allocates the plan's device buffer (hipMalloc) and enqueues the pre-pass on hip_stream; the symbol
  * arrays may be changed or freed once that work has run.  The plan belongs to the device that was current at
  * create.  run allocates nothing; it must be ordered after create (same stream, or synchronise), and two
- * runs of one plan must not overlap in time (a run resets and consumes the plan's queue counters, which is why
- * the plan is not const).  destroy waits for the device
+ * runs of one plan must not overlap in time (a run consumes the plan's queue counters and its last workgroup
+ * sets them back, which is why the plan is not const).  destroy waits for the device
  * and frees.  Errors as for sparse_attn_fwd; on failure *plan is NULL.
  */
 typedef struct sparse_attn_plan sparse_attn_plan;

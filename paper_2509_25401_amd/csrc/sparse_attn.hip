@@ -9,8 +9,8 @@
 //               its K/V stream through one L2): rows that are a large part of a workgroup's
 //               share first (longest first), the others head by head and heaviest first inside a
 //               head (55 kept-count buckets), cached rows (plain copies) last;
-//   attn        a persistent grid of two workgroups per CU pulls items from its XCD's queue and
-//               steals from the others when that is drained.  A compute item is one query block:
+//   attn        a persistent grid that fills the CUs (two workgroups of 128 query rows each) pulls items
+//               from its XCD's queue and steals from the others when that is drained.  A compute item is one query block:
 //               Q lives in registers as stored (the 1/sqrt(D) scale is applied to the fp32 score),
 //               the reduction-axis symbol is walked with scalar find-first-set on the decoded words, and only kept
 //               K/V tiles are streamed to LDS with direct-to-LDS loads, double buffered in 64-key
@@ -1142,7 +1142,8 @@ PlanBuffers carve(char* base, const Shape& s) {
 
 }  // namespace
 
-// A stored pre-pass: decoded symbol words and the ordered work list of one set of symbols.
+// A stored pre-pass: decoded symbol words and the ordered work list of one set of symbols.  A run needs no other launch
+// than the attention kernel: its last workgroup leaves the queue heads at zero for the next one.
 struct sparse_attn_plan {
   Shape s;
   int gran;

@@ -4,7 +4,7 @@
 // Three kernels, all in fp32 (vector instructions, and matrix instructions for the map's scores):
 //   pool_blocks   mean of the n*b_q query rows / n*b_k key rows of every pooled block (granularity n): the only
 //                 pass over Q and K, HBM-bound (reads both tensors once, 16 bytes per lane, row-contiguous)
-//   map_rows      one workgroup per 16 rows of the compressed attention map of one head: scores of the
+//   map_rows      one workgroup per 32 (long rows: 16) rows of the compressed attention map of one head: scores of the
 //                 pooled queries against all pooled keys (scale 1/sqrt(d)), row softmax, then for
 //                 every row the block-skipping rule -- a key block is skipped iff the sum of all row
 //                 entries that come at or before it in ascending order (ties by index) stays <= tau_kv
