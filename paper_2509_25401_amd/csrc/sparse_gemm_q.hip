@@ -34,6 +34,7 @@ typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 #define LDS_PTR(T) T __attribute__((address_space(3)))*
+#define GLOBAL_PTR(T) T __attribute__((address_space(1)))*
 
 struct GemmQParams {
   const char* X;       // bf16 [B, L, C]
@@ -190,17 +191,22 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) gemm_q_kernel(const GemmQPara
   static_assert(TABB % (16 * NT) == 0, "table pieces must split evenly over the threads");
   constexpr bool kEarly = A * C < 8;
   f32x4 vc[kEarly ? PER : 1], vs[kEarly ? PER : 1];
-  auto table_at = [&](int u) -> unsigned {        // byte offset (at most 2^21 rows of 256 bytes)
-    const int e = u * NT + tid, row = e / CHT;
-    return ((unsigned)(run_tok0(row) + min(row % BR, max(run_rows(row), 1) - 1)) * CHT + e % CHT) * 16;
+  // piece u of this thread: a wave's 64 lie in one run, whose first token is a uniform 64-bit offset (a table may be
+  // larger than 4 GiB); the rest fits in 32 bits.  The tables need 8-byte alignment only.
+  typedef f32x4 __attribute__((aligned(8))) f32x4_a8;
+  auto table_piece = [&](const float* table, int u) -> f32x4 {
+    const int r0 = (u * NT + wave * 64) / CHT, row = (u * NT + tid) / CHT;
+    const char* base = sa_uniform_ptr((const char*)table + (size_t)run_tok0(r0) * (CHT * 16));
+    const unsigned off = (unsigned)(min(row % BR, max(run_rows(r0), 1) - 1) * CHT + tid % CHT) * 16;
+    return *(GLOBAL_PTR(const f32x4_a8))(base + off);   // (the address space got lost in sa_uniform_ptr)
   };
   auto prefetch_tables = [&]() -> int {
     if constexpr (NORM_ROPE && kEarly) {
       if (p.rope_cos) {
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
-          vc[u] = *(const f32x4*)((const char*)p.rope_cos + table_at(u));
-          vs[u] = *(const f32x4*)((const char*)p.rope_sin + table_at(u));
+          vc[u] = table_piece(p.rope_cos, u);
+          vs[u] = table_piece(p.rope_sin, u);
         }
         return 2 * PER;
       }
@@ -250,8 +256,9 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) gemm_q_kernel(const GemmQPara
   auto tab_swizzle = [](int row) { return CHT == 16 ? (row & 15) : ((row >> 1) & 7); };
   if constexpr (NORM_ROPE) {
     if (tid < D) gain_f[tid] = p.norm_w ? __builtin_bit_cast(float, gain_bits << 16) : 1.f;
-    // The tile's cos / sin rows come through LDS: read straight from memory in
-    // the accumulator layout, every lane would fetch 8 bytes from its own row.  16-byte chunks are permuted by the token so that the 32 tokens of a read spread over the banks.
+    // The tile's cos / sin rows come through LDS: read straight from memory in the accumulator layout, every lane would
+    // fetch 8 bytes from its own row.  16-byte chunks are permuted by the token so that the 32 tokens of a read spread
+    // over the banks.
     if (p.rope_cos) {
       auto put = [&](int u, f32x4 c, f32x4 n) {
         const int e = u * NT + tid, row = e / CHT;
@@ -266,8 +273,8 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) gemm_q_kernel(const GemmQPara
         f32x4 c[PER], n[PER];
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
-          c[u] = *(const f32x4*)((const char*)p.rope_cos + table_at(u));
-          n[u] = *(const f32x4*)((const char*)p.rope_sin + table_at(u));
+          c[u] = table_piece(p.rope_cos, u);
+          n[u] = table_piece(p.rope_sin, u);
         }
 #pragma unroll
         for (int u = 0; u < PER; ++u) put(u, c[u], n[u]);

@@ -239,3 +239,58 @@ def test_every_tile_at_its_edges(B, L, C, H, D, bq, cached, fused):
     vals, want = synth.bf16_bits_to_f32(got).astype(np.float64)[~skipped], ref[~skipped]
     assert (np.abs(vals - want) <= np.abs(want) * 2.0 ** -8 + 1e-3).all()      # the bar of the module text
     assert (got[~skipped] == ref_bits[~skipped]).mean() > 0.98
+
+
+@pytest.mark.parametrize("cached", [None, 0.5])
+def test_rope_rows_past_four_gibibytes_of_table(cached):
+    """2^24 tokens of a table with 64 angles are 4 GiB: the tokens behind them are rotated by their own rows.  The
+    head of the tables is zero, so a wrapped offset gives zeros.  Compared in fp64 with the tail computed alone."""
+    L, C, H, D, bq = (1 << 24) + 333, 64, 1, 128, 128
+    print(f"[case] gemm_q rope L={L} cached={cached}", flush=True)
+    tail = 700                                            # compared rows, from both sides of 2^24
+    Tq = -(-L // bq)
+    X = torch.zeros((1, L, C), dtype=torch.bfloat16, device="cuda:0")
+    cos, sin = (torch.zeros((L, D // 2), device="cuda:0") for _ in range(2))
+    r = np.random.default_rng(90)
+    x, w = (synth.normal_bf16(r, s) for s in ((tail, C), (H * D, C)))
+    c, s = _rope_tables(tail, D)
+    X[0, L - tail:], cos[L - tail:], sin[L - tail:] = up_bf16(x), torch.from_numpy(c).to("cuda:0"), torch.from_numpy(s).to("cuda:0")
+    flags = None
+    if cached is not None:
+        flags = torch.ones((1, H, Tq), dtype=torch.uint8, device="cuda:0")
+        flags[0, 0, [0, 5, Tq - 6, Tq - 5, Tq - 3, Tq - 2, Tq - 1]] = 0
+    Q = torch.zeros((1, H, L, D), dtype=torch.bfloat16, device="cuda:0")
+    pkg.sparse_gemm_q_norm_rope(X, up_bf16(w), None, None, 1e-6, cos, sin, flags, Q, bq)
+    torch.cuda.synchronize()
+    got = synth.bf16_bits_to_f32(down_bits(Q[0, 0, L - tail:])).astype(np.float64)
+    ref, _ = oracle.gemm_q(x[None], w, None, None, bq, H, D, eps=float(np.float32(1e-6)), rope_cos=c, rope_sin=s)
+    computed = np.ones(tail, dtype=bool)
+    if flags is not None:
+        f = flags[0, 0].cpu().numpy()
+        computed = f[(np.arange(L - tail, L)) // bq] == 0
+        assert (got[~computed] == 0).all() and 0 < (~computed).sum() < tail
+    err = np.abs(got - ref[0, 0])[computed]
+    assert (err <= np.abs(ref[0, 0])[computed] * 2.0 ** -8 + 1e-3).all(), err.max()
+
+
+def test_rope_tables_at_eight_byte_alignment():
+    """The tables need no more than 8-byte alignment: every tile reads them in 16-byte pieces all the same."""
+    for L, cached in ((300, 0.0), (300, 0.4), (2500, 0.0)):
+        B, C, H, D, bq = 1, 128, 24, 128, 128
+        X, W, b, _ = _case(95, B, L, C, H, D, bq, cached=0.0)
+        flags = None if not cached else (np.random.default_rng(96).random((B, H, -(-L // bq))) < cached).astype(np.uint8)
+        cos, sin = _rope_tables(L, D)
+        up = []
+        for t in (cos, sin):
+            buf = torch.zeros(t.size + 2, device="cuda:0")
+            up.append(buf[2:].view(t.shape))
+            up[-1].copy_(torch.from_numpy(t))
+            assert up[-1].data_ptr() % 16 == 8
+        Q = torch.from_numpy(np.full((B, H, L, D), 0x4242, dtype=np.uint16).view(np.int16)).view(torch.bfloat16).to("cuda:0")
+        pkg.sparse_gemm_q_norm_rope(up_bf16(X), up_bf16(W), up_bf16(b), None, 1e-6, *up, up_u8(flags), Q, bq)
+        torch.cuda.synchronize()
+        ref, ref_bits = oracle.gemm_q(X, W, b, flags, bq, H, D, eps=float(np.float32(1e-6)), rope_cos=cos, rope_sin=sin)
+        got, skipped = down_bits(Q), np.zeros((B, H, L), bool) if flags is None else np.repeat(flags != 0, bq, axis=2)[:, :, :L]
+        assert (got[skipped] == 0x4242).all()
+        err = np.abs(synth.bf16_bits_to_f32(got).astype(np.float64) - ref)[~skipped]
+        assert (err <= np.abs(ref)[~skipped] * 2.0 ** -8 + 1e-3).all()
