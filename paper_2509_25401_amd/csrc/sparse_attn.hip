@@ -386,7 +386,7 @@ __device__ __forceinline__ int v_swizzle(int row) {
 // RAGGED: the sequence length is not a multiple of the blocks (Definition 1 counts ceil(L / b) of them).
 // The last query block then has fewer rows and the last key block fewer keys: loads of missing rows
 // re-read the last row that exists, scores of missing keys are set to -inf before the softmax, stores of
-// missing query rows are dropped, and a 64-key sub-tile that lies entirely past the end is not visited.
+// missing query rows are dropped, and a sub-tile that lies entirely past the end is not visited.
 // The aligned instantiation contains none of this.
 // DEALT: items are dealt out by workgroup number and every workgroup decodes the symbols of its rows (see below).
 template <int D, int BQ, int BK, bool RAGGED, bool DEALT>
@@ -620,6 +620,8 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
 #pragma unroll
     for (int e = 0; e < 16; ++e) neg_ref[e] = 0.f;
     bool first = true;
+    bool late = false;   // 32-key sub-tiles: the even one raised the reference by late_by, the odd one has not followed yet
+    float late_by = 0.f;
     float l_run = 0.f;   // per-lane partial row sum (this lane's half of the keys)
 
     // Scalar walk over the set bits of the decoded symbol row.  The row's words sit one per lane in a vector
@@ -692,7 +694,7 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
         return __builtin_bit_cast(bf16x8, __builtin_shufflevector(t1, t2, 0, 1, 2, 3, 4, 5, 6, 7));
       };
 
-      // The sub-tile's 64 keys are two blocks of 32 (one 32x32 S^T accumulator each).  Within this wave the
+      // A sub-tile of 64 keys is two blocks of 32 (one 32x32 S^T accumulator each).  Within this wave the
       // instruction stream is ordered so that the vector work of the softmax sits BETWEEN matrix instructions
       // that do not depend on it -- a wave's VALU instructions issue while its own earlier MFMA is still in the
       // matrix pipe, but only if they come right behind it in program order:
@@ -728,8 +730,14 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
         for (int e = 0; e < 16; ++e) s[kb2][e] = (32 * kb2 + 8 * (e / 4) + e % 4 >= lim) ? -INFINITY : s[kb2][e];
       };
       // Moves the reference to the row maximum of block kb2 (upwards only, except on the very first block of an
-      // item, which sets it).  `other_too`: block 1's scores were formed against the old reference as well.
-      auto move_reference = [&](int kb2, bool other_too) {
+      // item, which sets it) in what has been computed against it and returns by how much; lower_reference() does the
+      // same to the negated reference itself.  `other_too`: block 1's scores were formed against the old reference as well.
+      auto lower_reference = [&](float d) {
+        const float nr = neg_ref[0] - d;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) neg_ref[e] = nr;
+      };
+      auto move_reference = [&](int kb2, bool other_too) -> float {
         float mx = s[kb2][0];
 #pragma unroll
         for (int e = 1; e < 16; ++e) mx = fmaxf(mx, s[kb2][e]);
@@ -754,10 +762,8 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
 #pragma unroll
             for (int e = 0; e < 16; ++e) o[db][e] *= alpha;
         }
-        const float nr = neg_ref[0] - d;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) neg_ref[e] = nr;
         first = false;
+        return d;
       };
 
       bf16x8 ka[NQK];
@@ -776,10 +782,20 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
       if constexpr (RAGGED) {
         if (valid < KEYS) mask_block(0);
       }
-      if (first) move_reference(0, false);     // the first block of an item sets the reference; block 1 is not formed yet
-      // first operands of the O^T product: on their way while the scores of block 1 are formed
+      if (first) lower_reference(move_reference(0, false));     // the first block of an item sets the reference; block 1 is not formed yet
       if constexpr (KEYS == 32) {
-        // one block: its weights have no matrix instructions of this wave to hide under; four workgroups on the CU do
+        // One block: its weights have no matrix instructions of this wave to hide under; four workgroups on the CU do.
+        // Two sub-tiles (the even one in buffer 0) are rounded like the two blocks of a 64-key sub-tile, where block 1's
+        // scores are formed before block 0's weights can raise the reference: a move of the even one takes effect on
+        // the scores of the odd one, not on the C operand that forms them.
+        if constexpr (buf == 1) {
+          if (late) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) s[0][e] -= late_by;
+            lower_reference(late_by);
+            late = false;
+          }
+        }
         bf16x8 vv[NPV];
 #pragma unroll
         for (int t = 0; t < kPre; ++t) vv[t] = v_read(t);
@@ -787,7 +803,11 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
 #pragma unroll
         for (int c = 0; c < 8; ++c) chunk(0, c, dl);
         if (__builtin_amdgcn_ballot_w64(!(dl <= kSumLimit)) != 0) {
-          move_reference(0, false);
+          late_by = move_reference(0, false);
+          if constexpr (buf == 0)
+            late = true;
+          else
+            lower_reference(late_by);
           dl = 0.f;
 #pragma unroll
           for (int c = 0; c < 8; ++c) chunk(0, c, dl);
@@ -798,57 +818,57 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
           if (t + kPre < NPV) vv[t + kPre] = v_read(t + kPre);
           o[t % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vv[t], pb[t / DB], o[t % DB], 0, 0, 0);
         }
-        __builtin_amdgcn_s_setprio(0);
-        return;
-      }
-      bf16x8 va[NPV];
+      } else {
+        // first operands of the O^T product: on their way while the scores of block 1 are formed
+        bf16x8 va[NPV];
 #pragma unroll
-      for (int t = 0; t < kPre; ++t) va[t] = v_read(t);
-      // ---- S1 || weights of block 0
-      float dl0 = 0.f;
+        for (int t = 0; t < kPre; ++t) va[t] = v_read(t);
+        // ---- S1 || weights of block 0
+        float dl0 = 0.f;
 #pragma unroll
-      for (int t = 0; t < KS; ++t) {
-        if (KS + t + kPre < NQK) ka[KS + t + kPre] = k_read(KS + t + kPre);
-        s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[(KS + t) % NQK], qf[t], t == 0 ? neg_ref : s[1], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
+        for (int t = 0; t < KS; ++t) {
+          if (KS + t + kPre < NQK) ka[KS + t + kPre] = k_read(KS + t + kPre);
+          s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[KS + t], qf[t], t == 0 ? neg_ref : s[1], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int cc = 0; cc < CPS; ++cc) chunk(0, t * CPS + cc, dl0);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      if constexpr (RAGGED) {
-        if (valid < KEYS) mask_block(1);
-      }
-      // !(sum <= limit) also catches an overflowed (infinite or NaN) sum
-      if (__builtin_amdgcn_ballot_w64(!(dl0 <= kSumLimit)) != 0) {
-        move_reference(0, true);
-        dl0 = 0.f;
+          for (int cc = 0; cc < CPS; ++cc) chunk(0, t * CPS + cc, dl0);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (RAGGED) {
+          if (valid < KEYS) mask_block(1);
+        }
+        // !(sum <= limit) also catches an overflowed (infinite or NaN) sum
+        if (__builtin_amdgcn_ballot_w64(!(dl0 <= kSumLimit)) != 0) {
+          lower_reference(move_reference(0, true));
+          dl0 = 0.f;
 #pragma unroll
-        for (int c = 0; c < 8; ++c) chunk(0, c, dl0);
-      }
-      l_run += dl0;
-      // ---- PV0 || weights of block 1
-      float dl1 = 0.f;
+          for (int c = 0; c < 8; ++c) chunk(0, c, dl0);
+        }
+        l_run += dl0;
+        // ---- PV0 || weights of block 1
+        float dl1 = 0.f;
 #pragma unroll
-      for (int t = 0; t < NPV / 2; ++t) {
-        if (t + kPre < NPV) va[t + kPre] = v_read(t + kPre);
-        o[t % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[t], pb[t / DB], o[t % DB], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
+        for (int t = 0; t < NPV / 2; ++t) {
+          if (t + kPre < NPV) va[t + kPre] = v_read(t + kPre);
+          o[t % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[t], pb[t / DB], o[t % DB], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int cc = 0; cc < CPS; ++cc) chunk(1, t * CPS + cc, dl1);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      if (__builtin_amdgcn_ballot_w64(!(dl1 <= kSumLimit)) != 0) {
-        move_reference(1, false);
-        dl1 = 0.f;
+          for (int cc = 0; cc < CPS; ++cc) chunk(1, t * CPS + cc, dl1);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if (__builtin_amdgcn_ballot_w64(!(dl1 <= kSumLimit)) != 0) {
+          lower_reference(move_reference(1, false));
+          dl1 = 0.f;
 #pragma unroll
-        for (int c = 0; c < 8; ++c) chunk(1, c, dl1);
-      }
-      l_run += dl1;
-      // ---- PV1
+          for (int c = 0; c < 8; ++c) chunk(1, c, dl1);
+        }
+        l_run += dl1;
+        // ---- PV1
 #pragma unroll
-      for (int t = NPV / 2; t < NPV; ++t) {
-        if (t + kPre < NPV) va[t + kPre] = v_read(t + kPre);
-        o[t % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[t], pb[t / DB], o[t % DB], 0, 0, 0);
+        for (int t = NPV / 2; t < NPV; ++t) {
+          if (t + kPre < NPV) va[t + kPre] = v_read(t + kPre);
+          o[t % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[t], pb[t / DB], o[t % DB], 0, 0, 0);
+        }
       }
       __builtin_amdgcn_s_setprio(0);
     };

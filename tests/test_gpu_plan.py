@@ -186,3 +186,33 @@ def test_dealt_rows_and_work_list_agree(B, H, L, D, bq, bk, keep, cached):
     plan.destroy()
     ref, ref_bits = oracle_full(w)
     check_against_oracle(w, got, ref, ref_bits, f"routes {B}x{H}x{L}")
+
+
+@pytest.mark.parametrize("profile", ["growing", "staircase", "spiky"])
+@pytest.mark.parametrize("D,bq,bk", [(128, 64, 64), (128, 64, 128), (128, 128, 64), (64, 64, 64)])
+def test_bits_do_not_depend_on_the_blocks_when_the_reference_moves(D, bq, bk, profile):
+    """Dense attention in the caller's blocks (a stored plan) and in the kernel's own (one-shot call, 272 blocks of 128
+    rows): same bits, also where the exponent's reference is raised in the middle of a row.  "staircase": every
+    64 keys are four times louder than the 64 before, so the first 32 of them raise it and the next 32 follow."""
+    B, H, L = 1, 17, 2000
+    print(f"[case] blocks D={D} {bq}x{bk} {profile}", flush=True)
+    w = synth.random_case(synth.BASE_SEED + 330 + D + bq, B, H, L, D, bq, bk, keep=1.0)
+    pos = np.arange(L, dtype=np.float32)[None, None, :, None]
+    scale = {"growing": 0.1 + 2.9 * pos / L, "staircase": 0.05 * 4.0 ** np.minimum(pos // 64, 3),
+             "spiky": np.where(pos % 97 == 0, 12.0, 0.5)}[profile].astype(np.float32)
+    w.K = synth.f32_to_bf16_bits(synth.bf16_bits_to_f32(w.K) * scale)
+    w.M_s = None
+    case = DeviceCase(w)
+    got = case.run()
+    plan = pkg.SparseAttnPlan(None, None, B, H, L, bq, bk)
+    O = fresh_O(w)
+    plan.run(case.Q, case.K, case.V, None, O)
+    torch.cuda.synchronize()
+    plan.destroy()
+    ref, _ = oracle_full(w)
+    err = np.abs(synth.bf16_bits_to_f32(got).astype(np.float64) - ref)
+    # weights are rounded to bf16 (relative 2^-9), the same ones in the product and in the sum it is divided by, and so
+    # is the result: at most 3 * 2^-9 of the largest value, however few keys a row's weight lies on
+    assert err.max() <= 3 * 2.0 ** -9 * np.abs(synth.bf16_bits_to_f32(w.V)).max()
+    differ = (down_bits(O) != got).sum()
+    assert differ == 0, f"{differ} of {got.size} values depend on the blocks"
