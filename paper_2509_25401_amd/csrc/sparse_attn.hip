@@ -352,6 +352,17 @@ __device__ __forceinline__ unsigned sa_lane0_atomic_inc(uint32_t* counter) {
       : "memory");
   return old;
 }
+// The same for a counter that goes from `last` back to 0.
+__device__ __forceinline__ unsigned sa_lane0_atomic_inc_wrap(uint32_t* counter, unsigned last) {
+  unsigned old;
+  unsigned long long saved;
+  asm volatile(
+      "s_mov_b64 %1, exec\n\ts_mov_b64 exec, 1\n\tglobal_atomic_inc %0, %2, %3, %4 sc0\n\ts_mov_b64 exec, %1"
+      : "=&v"(old), "=&s"(saved)
+      : "v"(0u), "v"(last), "s"(counter)
+      : "memory");
+  return old;
+}
 // Waits for this wave's outstanding memory operations and returns lane 0 of `v` as a wave-uniform value.
 __device__ __forceinline__ unsigned sa_lane0_value(unsigned v) {
   unsigned r;
@@ -971,13 +982,13 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
   }
   if constexpr (!DEALT) {
     // Stored plans: the last workgroup to get here leaves the queue heads as the next run wants them.  Every
-    // workgroup has waited for its last ticket, so no increment is still on its way.
+    // workgroup has waited for its last ticket, so no increment is still on its way.  The counter of workgroups that
+    // are done wraps by itself: it stays in step with the launches even where a program lets two runs of a plan overlap
+    // (their outputs are wrong then), and behind the last workgroup of both it and the heads are zero again.
     if (p.self_reset && wave == 0) {
-      const unsigned before = sa_lane0_value(sa_lane0_atomic_inc(q_head + kDoneOffset));
-      if (before == gridDim.x - 1) {
-        if (lane < kXcds) __hip_atomic_store(q_head + lane * kHeadStride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (lane == 0) __hip_atomic_store(q_head + kDoneOffset, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
+      const unsigned last = gridDim.x - 1;
+      if (sa_lane0_value(sa_lane0_atomic_inc_wrap(q_head + kDoneOffset, last)) == last && lane < kXcds)
+        __hip_atomic_store(q_head + lane * kHeadStride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
 }

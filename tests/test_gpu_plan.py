@@ -216,3 +216,24 @@ def test_bits_do_not_depend_on_the_blocks_when_the_reference_moves(D, bq, bk, pr
     assert err.max() <= 3 * 2.0 ** -9 * np.abs(synth.bf16_bits_to_f32(w.V)).max()
     differ = (down_bits(O) != got).sum()
     assert differ == 0, f"{differ} of {got.size} values depend on the blocks"
+
+
+def test_plan_is_intact_behind_runs_that_overlapped():
+    """Two runs of one plan that overlap in time share its queue counters and leave out blocks of their outputs.  What
+    follows them, ordered behind both, is right: the counters are back at zero when the last workgroup of both ends."""
+    w = synth.random_case(synth.BASE_SEED + 340, 1, 24, 4608, 128, 128, 128, keep=0.4, cached_frac=0.3)
+    case = DeviceCase(w)
+    plan = pkg.SparseAttnPlan(case.flags, case.mask, w.B, w.H, w.L, 128, 128)
+    want, O = fresh_O(w), fresh_O(w)
+    plan.run(case.Q, case.K, case.V, case.Oc, want)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    for rep in range(20):
+        for st in streams:
+            plan.run(case.Q, case.K, case.V, case.Oc, O, stream=st)
+        torch.cuda.synchronize()
+        got = fresh_O(w)
+        plan.run(case.Q, case.K, case.V, case.Oc, got)
+        torch.cuda.synchronize()
+        assert (down_bits(got) == down_bits(want)).all(), f"run behind the {rep}-th overlapping pair"
+    plan.destroy()
