@@ -79,10 +79,13 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 //     ks 2 | operands of ks 3                    | ... 2nd half
 //     stage s + 1 has landed (everything but what belongs to later stages), all waves' reads have returned: barrier
 //     ks 3 | operands of ks 0 of stage s + 1     | ... weights of stage s + WB, 1st half
+// (XB = 2: the token rows of stage s + 2 go out in ks 3 too, in front of the weights; in ks 1 and 2, behind the barrier
+// that frees their buffer by half a stage, they would arrive late: 33024 tokens, 24 heads, 64 x 256 tiles: 669 -> 660 us)
 // so a step's operands are on their way while the previous step's MFMAs run, across the stage boundary too; the
 // requests go out one at a time behind an MFMA (in a burst they keep the wave from issuing the next one).
 // Buffer safety: the weights requested in ks 3 of stage s (and ks 0 of the next) overwrite those of stage s, the token
-// rows requested in ks 1 and 2 those of stage s - 1; all waves' reads of a stage have returned at the barrier inside it.
+// rows requested in ks 1 and 2 those of stage s - 1 (XB = 2, ks 3: of stage s); all waves' reads of a stage have returned
+// at the barrier inside it.
 template <int TN, int TM, int WN, int WM, int WB, int XB>
 struct Pipe {
   static constexpr int kWaves = WN * WM;
@@ -153,7 +156,7 @@ struct Pipe {
   __device__ __forceinline__ void run(const char* smem, f32x16 (&acc)[kA][kC], int stages, WSrc&& w_src, XSrc&& x_src,
                                       Extra&& extra) const {
     bf16x8 wa[2][kA], xb[2][kC];
-    auto read = [&](auto ks_c, const char* wbase, const char* xbase) {
+    auto read = [&](auto ks_c, const char* wbase, const char* xbase) __attribute__((always_inline)) {
       constexpr int ks = decltype(ks_c)::value;
 #pragma unroll
       for (int c = 0; c < kC; ++c) xb[ks & 1][c] = *(const bf16x8*)(xbase + c * 32 * kRowB + x_off[ks]);
@@ -161,7 +164,7 @@ struct Pipe {
       for (int a = 0; a < kA; ++a) wa[ks & 1][a] = *(const bf16x8*)(wbase + a * 32 * kRowB + w_off[ks]);
     };
     // the MFMAs of a step with n requests spread between them: ask(j) makes the j-th
-    auto mfma = [&](auto ks_c, auto n_c, auto&& ask) {
+    auto mfma = [&](auto ks_c, auto n_c, auto&& ask) __attribute__((always_inline)) {
       constexpr int ks = decltype(ks_c)::value, n = decltype(n_c)::value;
       int j = 0;
       __builtin_amdgcn_sched_barrier(0);
@@ -192,13 +195,13 @@ struct Pipe {
     issue_w(w_at, 0, 0, kWLoad);
     issue_x(x_src(), 0, 0, kXLoad);
     if (WB == 3 && stages > 1) issue_w(w_src(), 1, 0, kWLoad);
-    if (XB == 3 && stages > 1) issue_x(x_src(), 1, 0, kXLoad);
+    if (stages > 1) issue_x(x_src(), 1, 0, kXLoad);
     if (stages >= WB) {
       w_at = w_src();
       issue_w(w_at, WB - 1, 0, w1);
     }
     if (stages >= 3)
-      sa_wait_vmem_but<(WB - 2) * kWLoad + (XB - 2) * kXLoad + w1>();
+      sa_wait_vmem_but<(WB - 2) * kWLoad + kXLoad + w1>();
     else
       sa_wait_vmem();
     lds_barrier();
@@ -212,31 +215,27 @@ struct Pipe {
     // one stage; whether there is a next stage, one after it, and weights to ask for in ks 3 are compile-time matters,
     // so that the steady state has no branch in it (a branch between the operand reads and the MFMAs makes the
     // compiler wait for all reads at once)
-    auto stage = [&](auto more1_c, auto more2_c, auto ask_w_c) {
+    auto stage = [&](auto more1_c, auto more2_c, auto ask_w_c) __attribute__((always_inline)) {
       constexpr bool more1 = decltype(more1_c)::value, more2 = decltype(more2_c)::value, ask_w = decltype(ask_w_c)::value;
-      constexpr bool ask_w2 = WB == 3 ? more2 : more1, ask_x = XB == 3 ? more2 : more1;
+      constexpr bool ask_w2 = WB == 3 ? more2 : more1, ask_x = XB == 3 && more2, ask_x2 = XB == 2 && more2;
       const int w_free = wbuf == 0 ? WB - 1 : wbuf - 1, x_free = xbuf == 0 ? XB - 1 : xbuf - 1;
       read(K1{}, wb, xb0);
       mfma(K0{}, std::integral_constant<int, ask_w2 ? w2 : 0>{}, [&](int j) { issue_w(w_at, w_free, w1 + j, w1 + j + 1); });
       int behind = 0;
-      constexpr bool x_now = ask_x && !more2;      // the last token rows go out now, before what is behind them
-      if constexpr (x_now) issue_x(x_src(), x_free, 0, kXLoad);
       if constexpr (more1 && !more2) {
         behind = extra();
         asm volatile("" ::: "memory");             // none of its loads moves down past the wait that counts on them
       }
       size_t x_at = 0;
-      if constexpr (ask_x && !x_now) x_at = x_src();
+      if constexpr (ask_x) x_at = x_src();
       read(K2{}, wb, xb0);
-      mfma(K1{}, std::integral_constant<int, ask_x && !x_now ? x1 : 0>{}, [&](int j) { issue_x(x_at, x_free, j, j + 1); });
+      mfma(K1{}, std::integral_constant<int, ask_x ? x1 : 0>{}, [&](int j) { issue_x(x_at, x_free, j, j + 1); });
       read(K3{}, wb, xb0);
-      mfma(K2{}, std::integral_constant<int, ask_x && !x_now ? x2 : 0>{}, [&](int j) { issue_x(x_at, x_free, x1 + j, x1 + j + 1); });
-      const int w_done = wbuf;
+      mfma(K2{}, std::integral_constant<int, ask_x ? x2 : 0>{}, [&](int j) { issue_x(x_at, x_free, x1 + j, x1 + j + 1); });
+      const int w_done = wbuf, x_done = xbuf;
       if constexpr (more1) {
         if constexpr (more2)
           sa_wait_vmem_but<kAhead>();
-        else if (behind >= 32)
-          sa_wait_vmem_but<32>();
         else if (behind >= 16)
           sa_wait_vmem_but<16>();
         else if (behind >= 8)
@@ -249,9 +248,15 @@ struct Pipe {
         wb = smem + wbuf * kWStage;
         xb0 = smem + xbuf * kXStage;
         read(K0{}, wb, xb0);
+        if constexpr (ask_x2) x_at = x_src();
         if constexpr (ask_w) w_at = w_src();
       }
-      mfma(K3{}, std::integral_constant<int, ask_w ? w1 : 0>{}, [&](int j) { issue_w(w_at, w_done, j, j + 1); });
+      mfma(K3{}, std::integral_constant<int, (ask_x2 ? kXLoad : 0) + (ask_w ? w1 : 0)>{}, [&](int j) {
+        if (ask_x2 && j < kXLoad)
+          issue_x(x_at, x_done, j, j + 1);
+        else
+          issue_w(w_at, w_done, j - (ask_x2 ? kXLoad : 0), j - (ask_x2 ? kXLoad : 0) + 1);
+      });
     };
     using T = std::true_type;
     using F = std::false_type;
@@ -266,6 +271,62 @@ struct Pipe {
     else
       (void)extra();
     stage(F{}, F{}, F{});
+  }
+
+  // The loop for few stages (the heads that the flags of a token block select).  There a tile is a chain of round trips
+  // to memory, and what counts is that a stage is requested early: all of it in one go, as soon as the barrier has freed
+  // its buffers (output projection, 64 x 128 tiles, 33024 tokens, two heads per block: 99 us, 102 with run(); 1024
+  // tokens, 24 heads: 32 against 35).
+  // early: called behind the first stage's requests for plain loads whose results are used behind the loop; it returns
+  // 8 if it has certainly issued that many load instructions, else 0 (loads return in order: the wait for the first stage
+  // may leave them out).
+  template <class WSrc, class XSrc, class Early>
+  __device__ __forceinline__ void run_short(const char* smem, f32x16 (&acc)[kA][kC], int stages, WSrc&& w_src, XSrc&& x_src,
+                                            Early&& early) const {
+    static_assert(WB == 2 && XB == 2, "two buffers");
+    auto issue = [&](auto buf_c) __attribute__((always_inline)) {
+      issue_w(w_src(), decltype(buf_c)::value, 0, kWLoad);
+      issue_x(x_src(), decltype(buf_c)::value, 0, kXLoad);
+    };
+    using B0 = std::integral_constant<int, 0>;
+    using B1 = std::integral_constant<int, 1>;
+    int left = stages;
+    bool first = true;
+    int early_loads = 0;
+    auto step = [&](auto buf_c, auto other_c) __attribute__((always_inline)) {
+      constexpr int buf = decltype(buf_c)::value;
+      if (first && early_loads == 8)
+        sa_wait_vmem_but<8>();
+      else
+        sa_wait_vmem();
+      first = false;
+      lds_barrier();                               // this stage has landed for every wave; the other buffers are free
+      if (--left > 0) issue(other_c);
+      bf16x8 wa[kSteps][kA], xb[kSteps][kC];
+#pragma unroll
+      for (int ks = 0; ks < kSteps; ++ks) {
+#pragma unroll
+        for (int a = 0; a < kA; ++a) wa[ks][a] = *(const bf16x8*)(smem + buf * kWStage + a * 32 * kRowB + w_off[ks]);
+#pragma unroll
+        for (int c = 0; c < kC; ++c) xb[ks][c] = *(const bf16x8*)(smem + buf * kXStage + c * 32 * kRowB + x_off[ks]);
+      }
+      __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+      for (int ks = 0; ks < kSteps; ++ks)
+#pragma unroll
+        for (int a = 0; a < kA; ++a)
+#pragma unroll
+          for (int c = 0; c < kC; ++c) acc[a][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa[ks][a], xb[ks][c], acc[a][c], 0, 0, 0);
+      __builtin_amdgcn_s_setprio(0);
+    };
+    issue(B0{});
+    early_loads = early();
+    asm volatile("" ::: "memory");                 // none of its loads moves down past the wait that counts on them
+    while (left > 0) {
+      step(B0{}, B1{});
+      if (left == 0) break;
+      step(B1{}, B0{});
+    }
   }
 };
 

@@ -18,8 +18,8 @@
 // weight rows, B = token rows, both k-contiguous in LDS).
 //
 // What bounds it (33024 tokens, 24 heads of 128, 3072 channels).  90 % cached heads, two terms: 650 MB, 126 us at the rate
-// of a large copy; 158 us: a tile is a chain of flags, first stage, five stages on average, epilogue, each a round
-// trip to memory, with two tiles per CU to hide them.  No flags: power, as the query projection.
+// of a large copy; 151 us: a tile is a chain of flags, first stage, five stages on average, addend and store, each a
+// round trip to memory, with two tiles per CU to hide them.  No flags: power, as the query projection.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -37,6 +37,7 @@ using sa_gemm::kStepK;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 #define LDS_PTR(T) T __attribute__((address_space(3)))*
 
@@ -64,7 +65,8 @@ __device__ __forceinline__ float bf16_bits_to_float(unsigned bits16) {
 
 // TM tokens x TN output channels per workgroup, WM x WN waves, WB / XB LDS buffers.  FLAGGED: the tokens are one token
 // block (TM = block_q) and the reduction visits the heads its flags select; otherwise TM consecutive tokens and all heads.
-template <int TM, int TN, int WM, int WN, int WB, int XB, int D, bool FLAGGED>
+// TWO: there may be a second term of the addend to request early; without it (FLAGGED) the loop for few stages is used.
+template <int TM, int TN, int WM, int WN, int WB, int XB, int D, bool FLAGGED, bool TWO>
 __global__ void __launch_bounds__(WM * WN * 64, 2) gemm_o_kernel(const GemmOParams p) {
   using Pipe = sa_gemm::Pipe<TN, TM, WN, WM, WB, XB>;
   constexpr int NWAVES = WM * WN;
@@ -136,47 +138,50 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) gemm_o_kernel(const GemmOPara
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[a][c][e] = 0.f;
 
-  // Output side: every wave handles its own corner, lane -> (row, group of 8 output channels), whole rows of the corner
-  // at a time, for the addend's loads as for the result's stores; both are streamed once: non-temporal, so that they do
-  // not push the weight rows out of the XCD's L2.
-  constexpr int CHO = CW / 8;                     // 16-byte pieces per row of the corner
-  constexpr int RPI = 64 / CHO;                   // rows per wave instruction
-  constexpr int OUT_ITERS = TW / RPI;
-  const int out_row = lane / CHO, out_ch = lane % CHO;
-  const size_t out0 = (((size_t)b * p.L + tok0 + wm * TW) * p.C_out + n0 + wn * CW) * 2;
+  // Output side: thread -> (row, group of 8 output channels), whole rows of the tile at a time (256 x 256 tiles: of the
+  // wave's corner), for the addend's loads as for the result's stores; both are streamed once: non-temporal, so that they
+  // do not push the weight rows out of the XCD's L2.
+  constexpr bool kWhole = TM * TN * 4 <= 160 * 1024;   // the tile fits into LDS in fp32
+  constexpr int kLanes = kWhole ? NWAVES * 64 : 64;
+  constexpr int CHO = (kWhole ? TN : CW) / 8;     // 16-byte pieces per row
+  constexpr int RPI = kLanes / CHO;               // rows per pass
+  constexpr int OUT_ITERS = (kWhole ? TM : TW) / RPI;
+  const int out_row = tid % kLanes / CHO, out_ch = tid % CHO;
+  const int row0 = kWhole ? 0 : wm * TW, col0 = kWhole ? 0 : wn * CW;
+  const size_t out0 = (((size_t)b * p.L + tok0 + row0) * p.C_out + n0 + col0) * 2;
   auto out_offset = [&](int it) -> size_t { return out0 + ((size_t)(it * RPI + out_row) * p.C_out + out_ch * 8) * 2; };
-  auto there = [&](int it) -> bool { return wm * TW + it * RPI + out_row < rows_valid && wn * CW + out_ch * 8 < cols_valid; };
+  auto there = [&](int it) -> bool { return row0 + it * RPI + out_row < rows_valid && col0 + out_ch * 8 < cols_valid; };
 
   // The first two terms of the addend are requested behind the last stage of the reduction and land under its MFMAs;
   // their OP_reuse is formed in the epilogue.  Loads return in order, so requested earlier they would hold up the
-  // stages behind them (33024 tokens, 90 % cached heads, two terms: 158 us; 193 with the terms combined in front of the
-  // loop.  One term, 80 %: 183 us, 189 when requested with the first stages).  Returns the number of loads where it is
-  // certain: in a tile at the edge a wave may skip some.  (256 x 256 tiles have no registers for that: there the addend
-  // is requested behind the loop.)
-  constexpr bool kEarly = A * C < 8;
-  u32x4 term0[OUT_ITERS], term1[kEarly ? OUT_ITERS : 1];
-  const bool two = kEarly && p.n_terms > 1;
-  auto fetch_addend = [&]() -> int {
+  // stages behind them (128 x 128 tiles, 33024 tokens, one term, 4 heads per block: 153 us; 165 when requested behind the
+  // first stages).  The loop for few stages asks for its one term behind the first stage.  Returns the number of loads
+  // where it is certain: in a tile at the edge a wave may skip some.  (256 x 256 tiles have no registers for that: there
+  // the addend is requested behind the loop.)
+  static_assert(!kWhole || OUT_ITERS == 8, "the loops count on 8 or 16 loads");
+  u32x4 term0[OUT_ITERS], term1[kWhole && TWO ? OUT_ITERS : 1];
+  const bool two = kWhole && TWO && p.n_terms > 1;
+  auto fetch_addend = [&]() __attribute__((always_inline)) -> int {
     if (!p.addend) return 0;
     if (rows_valid == TM && cols_valid == TN) {
 #pragma unroll
       for (int it = 0; it < OUT_ITERS; ++it) term0[it] = __builtin_nontemporal_load((const u32x4*)(p.addend + out_offset(it)));
       if (!two) return OUT_ITERS;
 #pragma unroll
-      for (int it = 0; it < OUT_ITERS; ++it) term1[kEarly ? it : 0] = __builtin_nontemporal_load((const u32x4*)(p.term[0] + out_offset(it)));
+      for (int it = 0; it < OUT_ITERS; ++it) term1[kWhole && TWO ? it : 0] = __builtin_nontemporal_load((const u32x4*)(p.term[0] + out_offset(it)));
       return 2 * OUT_ITERS;
     }
 #pragma unroll
     for (int it = 0; it < OUT_ITERS; ++it) {
       if (!there(it)) continue;
       term0[it] = __builtin_nontemporal_load((const u32x4*)(p.addend + out_offset(it)));
-      if (two) term1[kEarly ? it : 0] = __builtin_nontemporal_load((const u32x4*)(p.term[0] + out_offset(it)));
+      if (two) term1[kWhole && TWO ? it : 0] = __builtin_nontemporal_load((const u32x4*)(p.term[0] + out_offset(it)));
     }
     return 0;
   };
   // the addend of one piece: as given, or OP_reuse(B_c): fp32 sum of the scaled terms in term order, one rounding to
   // bf16 (what the element-wise kernel computes)
-  auto addend_of = [&](int it) -> u32x4 {
+  auto addend_of = [&](int it) __attribute__((always_inline)) -> u32x4 {
     u32x4 r = term0[it];
     if (p.n_terms > 0) {
       float v[8];
@@ -186,7 +191,7 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) gemm_o_kernel(const GemmOPara
         v[2 * e + 1] = p.coef[0] * bf16_bits_to_float(term0[it][e] >> 16);
       }
       for (int d = 1; d < p.n_terms; ++d) {
-        const u32x4 tb = kEarly && d == 1 ? term1[kEarly ? it : 0] : __builtin_nontemporal_load((const u32x4*)(p.term[d - 1] + out_offset(it)));
+        const u32x4 tb = kWhole && TWO && d == 1 ? term1[kWhole && TWO ? it : 0] : __builtin_nontemporal_load((const u32x4*)(p.term[d - 1] + out_offset(it)));
         const float cd = p.coef[d];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -205,35 +210,44 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) gemm_o_kernel(const GemmOPara
     return r;
   };
 
-  // bias of the corner's channels, one per lane, in flight during the reduction: loaded without a branch -- from the
-  // weights where there is none -- and converted behind the loop, so that nothing waits for it here
+  // Bias, in flight during the reduction: loaded without a branch -- from the weights where there is none -- and converted
+  // behind the loop, so that nothing waits for it here.  A thread's 8 channels in one load (at the 2-byte alignment of the
+  // bias: eight loads of 2 bytes would be as many requests as a tile without a head has stores), or the channels of
+  // the corner, one per lane.
+  typedef u32x4 __attribute__((aligned(2))) u32x4_a2;
   const uint16_t* const bias_p = p.bias ? p.bias : (const uint16_t*)p.W;
+  const u32x4 bias8 = *(const u32x4_a2*)(bias_p + min(n0 + col0 + out_ch * 8, p.C_out - 8));
   unsigned bias_raw[CW / 64];
 #pragma unroll
   for (int u = 0; u < CW / 64; ++u) bias_raw[u] = bias_p[min(n0 + wn * CW + 64 * u + lane, p.C_out - 1)];
+  // (sum + bias) + addend, rounded
+  auto finish = [&](int it, float (&v)[8]) __attribute__((always_inline)) {
+    const u32x4 ad = p.addend ? addend_of(it) : u32x4{0u, 0u, 0u, 0u};
+    u32x4 r;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float lo = v[2 * e] + (p.bias ? bf16_bits_to_float(bias8[e] & 0xffffu) : 0.f);
+      float hi = v[2 * e + 1] + (p.bias ? bf16_bits_to_float(bias8[e] >> 16) : 0.f);
+      if (p.addend) {
+        lo += bf16_bits_to_float(ad[e] & 0xffffu);
+        hi += bf16_bits_to_float(ad[e] >> 16);
+      }
+      bf16x2 pr;
+      pr[0] = (__bf16)lo;
+      pr[1] = (__bf16)hi;
+      r[e] = __builtin_bit_cast(unsigned, pr);
+    }
+    __builtin_nontemporal_store(r, (u32x4*)(p.Out + out_offset(it)));
+  };
 
   const int stages = __popcll(heads) * PARTS;
   if (stages == 0) {
     // no head of this token block is selected: the tile is addend + bias, straight from registers
     (void)fetch_addend();
-    float bv[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-      bv[e] = p.bias ? bf16_bits_to_float(p.bias[min(n0 + wn * CW + out_ch * 8 + e, p.C_out - 1)]) : 0.f;
 #pragma unroll
     for (int it = 0; it < OUT_ITERS; ++it) {
-      if (!there(it)) continue;
-      u32x4 r = {0u, 0u, 0u, 0u};
-      const u32x4 ad = p.addend ? addend_of(it) : r;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        bf16x2 pr;
-        // (0 + bias) + addend, as the accumulators of the other branch
-        pr[0] = (__bf16)(bv[2 * e] + (p.addend ? bf16_bits_to_float(ad[e] & 0xffffu) : 0.f));
-        pr[1] = (__bf16)(bv[2 * e + 1] + (p.addend ? bf16_bits_to_float(ad[e] >> 16) : 0.f));
-        r[e] = __builtin_bit_cast(unsigned, pr);
-      }
-      __builtin_nontemporal_store(r, (u32x4*)(p.Out + out_offset(it)));
+      float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      if (there(it)) finish(it, v);
     }
     return;
   }
@@ -264,7 +278,9 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) gemm_o_kernel(const GemmOPara
     const int h = wx.next(part);
     return (size_t)sa_uniform_ptr((const char*)((size_t)h * head_bytes + (size_t)part * kRowB));
   };
-  if constexpr (kEarly) {
+  if constexpr (FLAGGED && !TWO) {
+    st.run_short(smem, acc, stages, w_src, x_src, fetch_addend);
+  } else if constexpr (kWhole) {
     st.run(smem, acc, stages, w_src, x_src, fetch_addend);
   } else {
     st.run(smem, acc, stages, w_src, x_src, []() { return 0; });
@@ -272,17 +288,54 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) gemm_o_kernel(const GemmOPara
   }
   __syncthreads();   // every wave is done reading the stage buffers
 
-  // Epilogue, all in the wave's own piece of LDS (rows of CW bf16, 16-byte chunks permuted by the row so that the 32
-  // tokens of an accumulator access hit different banks): the addend goes in as rows, comes out in the accumulators'
-  // layout (lane = token 32 * c + l32, registers = channels 32 * a + 8 * q4 + 4 * half + 0..3), the sum (accumulator +
-  // bias) + addend goes back rounded to the same place and leaves as rows.  LDS accesses of a wave execute in order.
-  auto swizzle = [](int row) { return CHO == 16 ? (row & 15) : ((row >> 1) & 7); };
-  char* const corner = smem + wave * TW * CW * 2;
-  if (p.addend) {
+  if (kWhole && p.addend) {
+    // Epilogue with an addend: the accumulators (lane = token 32 * c + l32, registers = channels 32 * a + 8 * q4 + 4 * half
+    // + 0..3 of the wave's corner) go to LDS as fp32 rows, 16-byte chunks permuted by the row so that the 32 tokens of an
+    // access hit different banks, and come back as whole rows, to which a thread adds bias and addend.  Behind the arrival
+    // of the addend there is nothing left but the store (33024 tokens, four heads per block, one term: 155 us; 164 with
+    // the addend sent through LDS to the accumulators).
+    auto chunk_at = [&](int row, int ch) -> char* { return smem + row * TN * 4 + ((ch ^ (row & 31)) * 16); };
+#pragma unroll
+    for (int a = 0; a < A; ++a)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4)
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+          f32x4 v;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = acc[a][c][4 * q4 + e];
+          *(f32x4*)chunk_at(wm * TW + 32 * c + l32, (wn * CW + 32 * a + 8 * q4) / 4 + half) = v;
+        }
+    sa_gemm::lds_barrier();
 #pragma unroll
     for (int it = 0; it < OUT_ITERS; ++it) {
       const int row = it * RPI + out_row;
-      if (there(it)) *(u32x4*)(corner + row * CW * 2 + ((out_ch ^ swizzle(row)) * 16)) = addend_of(it);
+      const f32x4 v0 = *(const f32x4*)chunk_at(row, 2 * out_ch), v1 = *(const f32x4*)chunk_at(row, 2 * out_ch + 1);
+      float v[8];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        v[e] = v0[e];
+        v[4 + e] = v1[e];
+      }
+      if (there(it)) finish(it, v);
+    }
+    return;
+  }
+  // Epilogue without an addend, and of 256 x 256 tiles, all in the wave's own piece of LDS (rows of CW bf16, 16-byte
+  // chunks permuted by the row): the addend goes in as rows, comes out in the accumulators' layout, the sum (accumulator +
+  // bias) + addend goes back rounded to the same place and leaves as rows.  LDS accesses of a wave execute in order, so
+  // there is no barrier.
+  constexpr int CHC = CW / 8, RPC = 64 / CHC;     // 16-byte pieces per row of the corner, rows per wave instruction
+  const int c_row = lane / CHC, c_ch = lane % CHC;
+  auto swizzle = [](int row) { return CHC == 16 ? (row & 15) : ((row >> 1) & 7); };
+  char* const corner = smem + wave * TW * CW * 2;
+  if constexpr (!kWhole) {
+    if (p.addend) {
+#pragma unroll
+      for (int it = 0; it < OUT_ITERS; ++it) {
+        const int row = it * RPC + c_row;
+        if (there(it)) *(u32x4*)(corner + row * CW * 2 + ((c_ch ^ swizzle(row)) * 16)) = addend_of(it);
+      }
     }
   }
   int bias_bits[CW / 64];
@@ -306,7 +359,7 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) gemm_o_kernel(const GemmOPara
         float v[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] = acc[a][c][4 * q4 + e] + bv[e];
-        if (p.addend) {
+        if (!kWhole && p.addend) {
           const u32x2 ad = *at;
           v[0] += bf16_bits_to_float(ad[0] & 0xffffu);
           v[1] += bf16_bits_to_float(ad[0] >> 16);
@@ -325,29 +378,30 @@ __global__ void __launch_bounds__(WM * WN * 64, 2) gemm_o_kernel(const GemmOPara
       }
     }
 #pragma unroll
-  for (int it = 0; it < OUT_ITERS; ++it) {
-    const int row = it * RPI + out_row;
-    const u32x4 v = *(const u32x4*)(corner + row * CW * 2 + ((out_ch ^ swizzle(row)) * 16));
-    if (there(it)) __builtin_nontemporal_store(v, (u32x4*)(p.Out + out_offset(it)));
+  for (int it = 0; it < TW / RPC; ++it) {
+    const int row = it * RPC + c_row;
+    const u32x4 v = *(const u32x4*)(corner + row * CW * 2 + ((c_ch ^ swizzle(row)) * 16));
+    char* const out = p.Out + (((size_t)b * p.L + tok0 + wm * TW + row) * p.C_out + n0 + wn * CW + c_ch * 8) * 2;
+    if (wm * TW + row < rows_valid && wn * CW + c_ch * 8 < cols_valid) __builtin_nontemporal_store(v, (u32x4*)out);
   }
 }
 
-template <int TM, int TN, int WM, int WN, int WB, int XB, int D, bool FLAGGED>
+template <int TM, int TN, int WM, int WN, int WB, int XB, int D, bool FLAGGED, bool TWO>
 int launch_tiles(const GemmOParams& p, int B, hipStream_t stream) {
   constexpr size_t stage_lds = sa_gemm::Pipe<TN, TM, WN, WM, WB, XB>::kLdsBytes;
-  constexpr size_t out_lds = (size_t)TM * TN * 2;
+  constexpr size_t out_lds = (size_t)TM * TN * (TM * TN * 4 <= 160 * 1024 ? 4 : 2);   // the epilogue's rows
   constexpr size_t lds = stage_lds > out_lds ? stage_lds : out_lds;
   static_assert(lds <= 160 * 1024, "LDS of a CU");
   static std::once_flag once;
   static hipError_t attr_err = hipSuccess;
   std::call_once(once, [] {
-    attr_err = hipFuncSetAttribute((const void*)gemm_o_kernel<TM, TN, WM, WN, WB, XB, D, FLAGGED>,
+    attr_err = hipFuncSetAttribute((const void*)gemm_o_kernel<TM, TN, WM, WN, WB, XB, D, FLAGGED, TWO>,
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   });
   if (attr_err != hipSuccess)
     return sa_fail(SPARSE_ATTN_ERR_HIP, "hipFuncSetAttribute failed: %s", hipGetErrorString(attr_err));
   const int tiles = B * ((p.tok_end - p.tok_begin + TM - 1) / TM) * ((p.C_out + TN - 1) / TN);
-  hipLaunchKernelGGL((gemm_o_kernel<TM, TN, WM, WN, WB, XB, D, FLAGGED>), dim3(tiles), dim3(WM * WN * 64), lds, stream, p);
+  hipLaunchKernelGGL((gemm_o_kernel<TM, TN, WM, WN, WB, XB, D, FLAGGED, TWO>), dim3(tiles), dim3(WM * WN * 64), lds, stream, p);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return sa_fail(SPARSE_ATTN_ERR_HIP, "gemm_o launch failed: %s", hipGetErrorString(e));
   return 0;
@@ -355,29 +409,42 @@ int launch_tiles(const GemmOParams& p, int B, hipStream_t stream) {
 
 // Which tile: without flags by the number of 128 x 128 tiles as in the query projection (33024 tokens, 24 heads of 128, 3072
 // channels: 625 -> 512 us plain, 697 -> 602 with two terms); with flags one token block per tile, because the heads it
-// visits are its own, and two workgroups per CU, because with few heads a tile is a chain of memory round trips (128 x
-// 256 tiles, one per CU: 5 % slower at 90 % cached heads); blocks of 64 tokens with 256 channels (9001 tokens, 50 %
-// cached: 113 against 119 us with 128 channels, 90 %: 38 against 36).
+// visits are its own, and at least two workgroups per CU, because with few heads a tile is a chain of memory round trips
+// (128 x 256 tiles, one per CU: 5 % slower at 90 % cached heads).
+// Blocks of 64 tokens: tiles of 256 channels read the token rows half as often, tiles of 128 leave room for three
+// workgroups per CU and fill the chip where tiles are few.  24 heads of 128, 3072 channels, us, 256 / 128 channels:
+//   33024 tokens (6192 tiles of 256), one term:  2 heads per block 136 / 125, 4: 199 / 182, 8: 294 / 292, 24: 704 / 733
+//   4608 tokens (864), no term:                  4 heads 27.3 / 28.0, 8: 42 / 45, 24: 101 / 112
+//   1024 tokens (192), one term:                 4 heads 12.4 / 9.6, 24: 41 / 33
+// So 128 channels up to 256 tiles (one per CU) and beyond 1280 (two and a half rounds of two per CU) where computed heads
+// are selected, which are few; 256 channels in between and where cached heads are selected, which are many.  With two
+// terms it is the addend that counts, not the heads: 256 channels beyond one per CU.
 template <int D>
 int launch(GemmOParams p, int B, int block_q, hipStream_t stream) {
   if (!p.flags) {
     const int tok = p.tok_end - p.tok_begin;
     const long long units = (long long)B * ((tok + 127) / 128) * (p.C_out / 128);
-    if (units <= 256) return launch_tiles<128, 128, 2, 2, 2, 3, D, false>(p, B, stream);
-    if (units <= 512) return launch_tiles<256, 128, 4, 2, 3, 3, D, false>(p, B, stream);
+    if (units <= 256) return launch_tiles<128, 128, 2, 2, 2, 3, D, false, true>(p, B, stream);
+    if (units <= 512) return launch_tiles<256, 128, 4, 2, 3, 3, D, false, true>(p, B, stream);
     const int n_col = (p.C_out + 255) / 256, n_tok = (tok + 255) / 256;
     const long long tiles = (long long)B * n_tok * n_col, full = tiles / 256 * 256;
     const int keep = (int)(full / ((long long)B * n_col));
     if (tiles > full && tiles - full <= 128 && keep > 0) {
       GemmOParams rest = p;
       p.tok_end = rest.tok_begin = p.tok_begin + keep * 256;
-      if (int rc = launch_tiles<256, 256, 4, 2, 2, 3, D, false>(p, B, stream)) return rc;
+      if (int rc = launch_tiles<256, 256, 4, 2, 2, 3, D, false, true>(p, B, stream)) return rc;
       return launch<D>(rest, B, block_q, stream);
     }
-    return launch_tiles<256, 256, 4, 2, 2, 3, D, false>(p, B, stream);
+    return launch_tiles<256, 256, 4, 2, 2, 3, D, false, true>(p, B, stream);
   }
-  if (block_q == 128) return launch_tiles<128, 128, 2, 2, 2, 3, D, true>(p, B, stream);
-  return launch_tiles<64, 256, 1, 4, 2, 2, D, true>(p, B, stream);
+  if (block_q == 128) return launch_tiles<128, 128, 2, 2, 2, 3, D, true, true>(p, B, stream);
+  const long long tiles = (long long)B * ((p.L + 63) / 64) * ((p.C_out + 255) / 256);
+  if (p.n_terms > 1) {
+    if (tiles <= 256) return launch_tiles<64, 128, 1, 2, 2, 3, D, true, true>(p, B, stream);
+    return launch_tiles<64, 256, 1, 4, 2, 2, D, true, true>(p, B, stream);
+  }
+  if (tiles <= 256 || (tiles > 1280 && !p.select)) return launch_tiles<64, 128, 1, 2, 2, 2, D, true, false>(p, B, stream);
+  return launch_tiles<64, 256, 1, 4, 2, 2, D, true, true>(p, B, stream);
 }
 
 bool ranges_overlap(const void* a, size_t na, const void* b, size_t nb) {

@@ -186,6 +186,8 @@ TILE_CASES = [
     (2, 7, 700, 128, 384, 128, 0.7),
     (2, 7, 700, 128, 384, 64, 0.7),          # 64 x 256 tiles, last column tile half full
     (1, 5, 450, 64, 640, 64, 0.8),
+    (1, 3, 6100, 64, 640, 64, 0.6),          # 64-token blocks, 288 tiles of 256 channels, the last one half full
+    (1, 3, 6100, 64, 3584, 64, 0.6),         # 1344 of them: 128 channels where computed heads are selected
 ]
 
 
@@ -220,3 +222,24 @@ def test_every_tile_at_its_edges(B, H, L, D, C_out, bq, cached):
         forecast = sum(np.abs(c * synth.bf16_bits_to_f32(t).astype(np.float64)) for c, t in zip(coef, terms))
         assert (np.abs(got - ref) <= np.abs(ref) * 2.0 ** -8 + forecast * 2.0 ** -7 + 2e-3).all(), f"{n} terms"
         assert (down_bits(Out) == ref_bits).mean() > 0.97
+
+
+@pytest.mark.parametrize("bq,cached", [(128, 0.6), (64, 0.6), (128, None)])
+def test_bias_at_any_two_byte_address(bq, cached):
+    """The bias is read in pieces of 16 bytes and needs no more than its own alignment."""
+    B, H, L, D, C_out = 1, 3, 300, 64, 384
+    O, W, bias, _ = _case(95, B, H, L, D, C_out, bq, None)
+    flags = None if cached is None else (np.random.default_rng(96).random((B, H, -(-L // bq))) < cached).astype(np.uint8)
+    if flags is not None:
+        flags[0, :, 0] = 1                   # a block without a computed head
+    buf = torch.zeros(C_out + 1, dtype=torch.bfloat16, device="cuda:0")
+    odd = buf[1:]
+    odd.copy_(up_bf16(bias))
+    assert odd.data_ptr() % 4 == 2
+    add = synth.normal_bf16(np.random.default_rng(97), (B, L, C_out))
+    for a in (None, add):
+        ref, ref_bits = oracle.gemm_o(O, W, bias, flags, 0, a, bq)
+        Out = torch.zeros((B, L, C_out), dtype=torch.bfloat16, device="cuda:0")
+        pkg.sparse_gemm_o(up_bf16(O), up_bf16(W), odd, up_u8(flags), 0, None if a is None else up_bf16(a), Out, bq)
+        torch.cuda.synchronize()
+        _check(down_bits(Out), ref, ref_bits, f"odd bias bq={bq}")
