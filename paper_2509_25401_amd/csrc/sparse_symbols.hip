@@ -31,8 +31,11 @@
 
 namespace {
 
-// map rows per workgroup: 16 for each tile of rows; long rows (beyond 512 entries) leave LDS for one tile only
-constexpr int map_rows_per_wg(bool long_rows) { return long_rows ? 16 : 32; }
+// Map rows per workgroup and its threads by the entries of a row that a lane holds (NP of map_rows, 0: rows in LDS).  Up
+// to 64 entries 16 rows and four waves: there the time is the chain of one workgroup, and it gets shorter (24 heads of 63
+// blocks: the call 32.7 -> 29.0 us).  Beyond 512 entries LDS has room for 16 rows only.
+constexpr int map_rows_per_wg(int np) { return np <= 4 ? 16 : 32; }
+constexpr int map_threads(int np) { return np == 2 || np == 4 ? 256 : 512; }
 constexpr int kMaxBlocks = 2048;     // blocks per sequence the LDS arrays are sized for
 
 // Sum over the 64 lanes, the same bits in every lane, without going through LDS: exchanges inside a row of 16
@@ -243,7 +246,7 @@ __device__ __forceinline__ void next_value_ties(const Row<G, NP>& row, int lane,
   n_more = k;
 }
 
-// 32 rows of one head's map per workgroup (16 if they are long), eight waves.
+// 32 rows of one head's map per workgroup, eight waves (16 and four or eight if the rows are short or long, see above).
 //   scores    fp32 matrix instructions, 16 x 16 tiles with 4 products a step: lane (r = lane % 16, g = lane / 16) of an
 //             operand holds channels 16 * u + 4 * g + e of row r, so that both operands come straight from the pooled
 //             means with 16-byte loads of which four lanes share a line, and step (u, e) adds the four channels with
@@ -255,13 +258,13 @@ __device__ __forceinline__ void next_value_ties(const Row<G, NP>& row, int lane,
 // Dot products with both operands from LDS and the search over 64 lanes took 50 us at 33024 tokens and 24 heads, this 29.
 // Dynamic LDS: map rows [kRows][T_pad].
 template <int D, int NP>
-__global__ void __launch_bounds__(512) map_rows(const float* __restrict__ pooled, long long n_q_blocks, int Tq, int T, int T_pad,
+__global__ void __launch_bounds__(map_threads(NP)) map_rows(const float* __restrict__ pooled, long long n_q_blocks, int Tq, int T, int T_pad,
                                                                int n_tq, int n_t, int row_bytes, float scale, float tau_kv,
                                                                uint8_t* __restrict__ kv_mask, float* __restrict__ text_rows,
                                                                float* __restrict__ text_cols) {
   extern __shared__ float p[];
   typedef __attribute__((ext_vector_type(4))) float f32x4;
-  constexpr int NWAVES = 8, kRows = map_rows_per_wg(NP == 0), RT = kRows / 16;
+  constexpr int NWAVES = map_threads(NP) / 64, kRows = map_rows_per_wg(NP), RT = kRows / 16;
   const int tid = threadIdx.x, w = tid / 64, lane = tid % 64;
   // T = pooled key blocks (columns of the map), n_t of them text; Tq = pooled query blocks (rows), n_tq of them text
   const int groups = (Tq + kRows - 1) / kRows;
@@ -282,9 +285,10 @@ __global__ void __launch_bounds__(512) map_rows(const float* __restrict__ pooled
   fetch_tile(w, k[0]);
 #pragma unroll
   for (int a = 0; a < RT; ++a) fetch(qt, min(i0 + 16 * a + r16, Tq - 1), q[a]);   // rows past the end repeat the last one
-  fetch_tile(w + NWAVES, k[1]);
+  constexpr bool kFew = NP == 2 || NP == 4;       // at most four tiles of keys: one per wave, nothing to fetch ahead
+  if constexpr (!kFew) fetch_tile(w + NWAVES, k[1]);
   for (int t = w; t < tiles; t += NWAVES) {
-    fetch_tile(t + 2 * NWAVES, k[2]);
+    if constexpr (!kFew) fetch_tile(t + 2 * NWAVES, k[2]);
     f32x4 acc[RT];
 #pragma unroll
     for (int a = 0; a < RT; ++a) acc[a] = {0.f, 0.f, 0.f, 0.f};
@@ -302,10 +306,12 @@ __global__ void __launch_bounds__(512) map_rows(const float* __restrict__ pooled
 #pragma unroll
         for (int e = 0; e < 4; ++e) p[(16 * a + 4 * g + e) * T_pad + j] = acc[a][e] * scale;
     }
+    if constexpr (!kFew) {
 #pragma unroll
-    for (int u = 0; u < V; ++u) {
-      k[0][u] = k[1][u];
-      k[1][u] = k[2][u];
+      for (int u = 0; u < V; ++u) {
+        k[0][u] = k[1][u];
+        k[1][u] = k[2][u];
+      }
     }
   }
   __syncthreads();
@@ -500,9 +506,20 @@ __global__ void __launch_bounds__(256) select_blocks(const float* __restrict__ t
   for (int v = tid, n = 0; v < Tv; v += 256, ++n) out[n_tq + v] = (degrade || ((mine >> n) & 1u)) ? 1 : 0;
 }
 
+// Entries per lane, 16 lanes to a row: powers of two, and 17 because 33024 tokens in blocks of 128 are 258 blocks, which
+// would fall into the tier of 512.  A tier costs what its last size costs (24 heads, blocks of 64 tokens, us: 258 entries
+// 74, with 32 registers 84; 273 entries, the first in that tier, 87: 32 registers a lane, 48 scalar registers spilled).
+int map_np(int T) { return T <= 32 ? 2 : T <= 64 ? 4 : T <= 128 ? 8 : T <= 272 ? 17 : T <= 512 ? 32 : 0; }
 template <int D>
 auto map_for(int T) {
-  return T <= 64 ? map_rows<D, 4> : T <= 128 ? map_rows<D, 8> : T <= 272 ? map_rows<D, 17> : T <= 512 ? map_rows<D, 32> : map_rows<D, 0>;
+  switch (map_np(T)) {
+    case 2: return map_rows<D, 2>;
+    case 4: return map_rows<D, 4>;
+    case 8: return map_rows<D, 8>;
+    case 17: return map_rows<D, 17>;
+    case 32: return map_rows<D, 32>;
+    default: return map_rows<D, 0>;
+  }
 }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -563,14 +580,14 @@ int sparse_symbols_update_granular(const void* Q, const void* K, uint8_t* cache_
 
   const int row_bytes = (Tk + 7) / 8;
   const float scale = (float)(1.0 / sqrt((double)D));
-  const int map_rows_wg = map_rows_per_wg(Tk > 512);
+  const int np = map_np(Tk), map_rows_wg = map_rows_per_wg(np);
   const int groups = (Tq + map_rows_wg - 1) / map_rows_wg;
   const int T_pad = (Tk + 3) & ~3;
   const size_t map_lds = (size_t)map_rows_wg * T_pad * 4;
   static std::once_flag attr_once;
   static hipError_t attr_err = hipSuccess;
   std::call_once(attr_once, [] {
-    constexpr int kMaxLds = map_rows_per_wg(true) * kMaxBlocks * 4;
+    constexpr int kMaxLds = map_rows_per_wg(0) * kMaxBlocks * 4;
     attr_err = hipFuncSetAttribute((const void*)map_rows<128, 0>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);
     if (attr_err == hipSuccess)
       attr_err = hipFuncSetAttribute((const void*)map_rows<64, 0>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);
@@ -584,10 +601,11 @@ int sparse_symbols_update_granular(const void* Q, const void* K, uint8_t* cache_
   HIP_TRY(hipGetLastError());
   // rows are searched in registers, 16 lanes to a row; beyond 512 entries in LDS
   auto map = D == 128 ? map_for<128>(Tk) : map_for<64>(Tk);
-  hipLaunchKernelGGL(map, dim3((unsigned)(BH * groups)), dim3(512), map_lds, stream, pooled, n_q_blocks, Tq, Tk, T_pad,
+  hipLaunchKernelGGL(map, dim3((unsigned)(BH * groups)), dim3(map_threads(np)), map_lds, stream, pooled, n_q_blocks, Tq, Tk, T_pad,
                      n_tq, n_tk, row_bytes, scale, tau_kv, kv_mask, text_rows, text_cols);
   HIP_TRY(hipGetLastError());
-  auto select = Tq <= 128 ? select_blocks<2> : Tq <= 320 ? select_blocks<5> : select_blocks<0>;
+  // (entries per lane, 64 lanes to a row: 5 for the 258 blocks of 33024 tokens; more are searched in LDS)
+  auto select = Tq <= 64 ? select_blocks<1> : Tq <= 128 ? select_blocks<2> : Tq <= 320 ? select_blocks<5> : select_blocks<0>;
   hipLaunchKernelGGL(select, dim3((unsigned)BH), dim3(256), 0, stream, text_rows, text_cols, Tq, Tk, n_tq, n_tk, pool_q, pool_k,
                      L, tau_c, s_q, cache_flags);
   HIP_TRY(hipGetLastError());

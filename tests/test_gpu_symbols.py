@@ -217,10 +217,10 @@ def test_granular_symbols_drive_the_plan_they_were_made_for(L, D, bq, bk, n, tex
     plan.destroy()
 
 
-# blocks per sequence around the register tiers of the threshold search (64, 128, 272, 512; 128 and 320 for the flags) and
-# the 16- and 32-row tiles of the map; `repeat`: blocks that repeat, so that equal entries have to be ranked
+# blocks per sequence around the register tiers of the threshold search (32, 64, 128, 272, 512; 64, 128 and 320 for the
+# flags) and the 16- and 32-row tiles of the map; `repeat`: blocks that repeat, so that equal entries have to be ranked
 @pytest.mark.parametrize("T,short,D,repeat", [
-    (2, 0, 64, False), (16, 3, 128, False), (17, 0, 64, True), (33, 20, 64, False), (64, 0, 128, True), (65, 1, 64, False),
+    (2, 0, 64, False), (16, 3, 128, False), (17, 0, 64, True), (32, 0, 128, False), (33, 20, 64, False), (64, 0, 128, True), (65, 1, 64, False),
     (128, 0, 64, False), (129, 0, 64, True), (272, 0, 64, False), (273, 63, 64, True), (320, 0, 64, False), (321, 0, 128, False),
     (512, 0, 64, True), (513, 5, 64, False)])
 def test_search_tiers(T, short, D, repeat):
