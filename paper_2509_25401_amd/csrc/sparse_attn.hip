@@ -1,7 +1,7 @@
 // FlashOmni attention (Algorithm 1 of the paper) for AMD MI355X / gfx950.
 //
 // Two kernels per call, both on the caller's stream (the second alone where the order of the rows does not matter:
-// few rows, or no symbols and at most two rows per workgroup):
+// few rows, or no symbols and at most two rows per workgroup; one more, decode_rows, where a queue has many symbols):
 //   plan_queues decodes the packed symbols of Section 3.3 once per (b,h,i) row into aligned
 //               32-bit words (bit j of the row = key block j, padding cleared), counts the
 //               kept key blocks of every non-cached row and notes the first of them;
@@ -68,7 +68,7 @@ constexpr int kCachedBucket = kLongBuckets + kFineBuckets;   // one lane each in
 constexpr int kWgsPerXcd = 64;        // workgroups of the persistent grid per XCD (32 CUs x 2) the ordering plans for
 constexpr int kCusPerXcd = 32;
 constexpr int kXcds = 8;               // accelerator dies (XCDs) of the MI355X, each with its own L2
-constexpr int kMaxHeadGroups = 24;    // head groups per (XCD, bucket) in the ordering histogram (48 KiB of LDS)
+constexpr int kMaxHeadGroups = 24;    // head groups per bucket in the ordering histogram of a queue (6 KiB of LDS)
 constexpr int kMaxTq = 16384;
 constexpr unsigned kCopyFlag = 0x80000000u;
 // Queue counters: every queue head (items handed out so far) sits in a 128-byte line of its own: all workgroups of an
@@ -152,7 +152,58 @@ __device__ inline int order_major(int key, const OrderScale& sc) {
          (int)((unsigned)(count - sc.lightest) * kFineBuckets / (unsigned)(sc.limit - sc.lightest + 1));
 }
 
-// Symbol pre-pass: workgroup q decodes the rows of queue q and writes its part of the work list.
+// Word w of a row at granularity gran > 1: tile j reads bit j / gran.
+__device__ inline uint32_t granular_word(const uint8_t* src, int w, int Tkv, int gran) {
+  uint32_t word = 0;
+  for (int t = 0; t < 32 && 32 * w + t < Tkv; ++t) {
+    const int js = (32 * w + t) / gran;
+    word |= (uint32_t)((src[js >> 3] >> (7 - (js & 7))) & 1) << t;
+  }
+  return word;
+}
+// Key of a row: kept blocks in the low 16 bits (0 .. 32768), first kept block above them; -1 for cached rows.
+__device__ inline int row_key(bool cached, int count, int first_kept) { return cached ? -1 : (count | (max(first_kept, 0) << 16)); }
+
+// Decodes the rows of all queues, 16 lanes to a row: words and keys for plan_queues, which does it by itself where there
+// are few words (see launch_plan).
+__global__ void __launch_bounds__(256) decode_rows(const uint8_t* __restrict__ cache_flags, const uint8_t* __restrict__ kv_mask,
+                                                   int N, int Tq, int Tkv, int gran, int sym_Tq, int sym_row_bytes, int nw32,
+                                                   uint32_t* __restrict__ words, int32_t* __restrict__ keys) {
+  const int row = (int)blockIdx.x * 16 + (int)threadIdx.x / 16, l16 = threadIdx.x % 16;
+  if (row >= N) return;                            // (16 lanes at a time)
+  const int bh = row / Tq;
+  const size_t sym_row = (size_t)bh * sym_Tq + (row - bh * Tq) / gran;
+  const bool cached = cache_flags != nullptr && cache_flags[sym_row] != 0;
+  const uint8_t* src = kv_mask ? kv_mask + sym_row * sym_row_bytes : nullptr;
+  int count = 0, first_kept = 0x7fffffff;
+  for (int w = l16; w < nw32; w += 16) {
+    uint32_t word = cached ? 0u : 0xffffffffu;
+    if (!cached && src) {
+      if (gran == 1) {
+        word = 0;
+        for (int b = 0; b < 4; ++b) {
+          const int byte = 4 * w + b;
+          if (byte < sym_row_bytes) word |= (uint32_t)src[byte] << (8 * b);
+        }
+        word = __builtin_bswap32(__brev(word));    // most significant bit first inside each byte
+      } else {
+        word = granular_word(src, w, Tkv, gran);
+      }
+    }
+    word = clear_padding(word, w, Tkv);
+    words[(size_t)row * nw32 + w] = word;
+    count += __popc(word);
+    if (word != 0u) first_kept = min(first_kept, 32 * w + __ffs(word) - 1);
+  }
+  for (int off = 8; off > 0; off >>= 1) {
+    count += __shfl_xor(count, off);
+    first_kept = min(first_kept, __shfl_xor(first_kept, off));
+  }
+  if (l16 == 0) keys[row] = row_key(cached, count, count > 0 ? first_kept : 0);
+}
+
+// Symbol pre-pass: workgroup q decodes the rows of queue q (unless decode_rows has done so) and writes its part of the
+// work list.
 //   decode     one thread per row turns the packed symbols into aligned words, counts the kept key blocks and notes
 //              the first of them (key of the row; -1 for cached rows)
 //   order      counting sort into the buckets above
@@ -163,7 +214,7 @@ constexpr int kLdsKeys = 8192;     // rows of a queue whose keys stay in LDS
 __global__ void __launch_bounds__(kOrderThreads) plan_queues(const uint8_t* __restrict__ cache_flags,
                                                              const uint8_t* __restrict__ kv_mask, int BH, int Tq, int Tkv,
                                                              int gran, int sym_Tq, int sym_row_bytes, int nw32, int shift,
-                                                             int groups, uint32_t* __restrict__ words, int32_t* keys,
+                                                             int groups, bool decoded, uint32_t* __restrict__ words, int32_t* keys,
                                                              uint32_t* __restrict__ order, uint32_t* __restrict__ queues) {
   __shared__ uint32_t bins[(kCachedBucket + 1) * kMaxHeadGroups];
   __shared__ int32_t lds_keys[kLdsKeys];
@@ -194,56 +245,54 @@ __global__ void __launch_bounds__(kOrderThreads) plan_queues(const uint8_t* __re
     uint32_t hi = 0, lo = 0xffffu;
     for (int r = tid; r < rows; r += kOrderThreads) {
       const int row = global_row(r);
-      // one symbol covers gran x gran tiles: tile (i, j) reads flag i / gran and mask bit (i / gran, j / gran)
-      const size_t sym_row = (size_t)(q + kXcds * (r / Tq)) * sym_Tq + (r % Tq) / gran;
-      const bool cached = cache_flags != nullptr && cache_flags[sym_row] != 0;
-      int count = 0, first_kept = -1;
-      auto take = [&](int w, uint32_t word) {
-        word = clear_padding(word, w, Tkv);
-        words[(size_t)row * nw32 + w] = word;
-        count += __popc(word);
-        if (first_kept < 0 && word != 0u) first_kept = 32 * w + __ffs(word) - 1;
-      };
-      const uint8_t* src = kv_mask ? kv_mask + sym_row * sym_row_bytes : nullptr;
-      if (cached || !src) {
-        for (int w = 0; w < nw32; ++w) take(w, cached ? 0u : 0xffffffffu);
-      } else if (gran == 1) {
-        // rows start at any byte: aligned words, shifted together; only words that hold a byte of the row are read
-        const int skew = (int)((uintptr_t)src & 3);
-        const uint32_t* aligned = (const uint32_t*)(src - skew);
-        const int last = (skew + sym_row_bytes - 1) / 4;
-        for (int w0 = 0; w0 < nw32; w0 += 8) {
-          uint32_t d[9];
+      int key;
+      if (decoded) {
+        key = keys[row];
+      } else {
+        // one symbol covers gran x gran tiles: tile (i, j) reads flag i / gran and mask bit (i / gran, j / gran)
+        const size_t sym_row = (size_t)(q + kXcds * (r / Tq)) * sym_Tq + (r % Tq) / gran;
+        const bool cached = cache_flags != nullptr && cache_flags[sym_row] != 0;
+        int count = 0, first_kept = -1;
+        auto take = [&](int w, uint32_t word) {
+          word = clear_padding(word, w, Tkv);
+          words[(size_t)row * nw32 + w] = word;
+          count += __popc(word);
+          if (first_kept < 0 && word != 0u) first_kept = 32 * w + __ffs(word) - 1;
+        };
+        const uint8_t* src = kv_mask ? kv_mask + sym_row * sym_row_bytes : nullptr;
+        if (cached || !src) {
+          for (int w = 0; w < nw32; ++w) take(w, cached ? 0u : 0xffffffffu);
+        } else if (gran == 1) {
+          // rows start at any byte: aligned words, shifted together; only words that hold a byte of the row are read
+          const int skew = (int)((uintptr_t)src & 3);
+          const uint32_t* aligned = (const uint32_t*)(src - skew);
+          const int last = (skew + sym_row_bytes - 1) / 4;
+          for (int w0 = 0; w0 < nw32; w0 += 8) {
+            uint32_t d[9];
 #pragma unroll
-          for (int t = 0; t < 9; ++t) d[t] = w0 + t <= last ? aligned[w0 + t] : 0u;
+            for (int t = 0; t < 9; ++t) d[t] = w0 + t <= last ? aligned[w0 + t] : 0u;
 #pragma unroll
-          for (int t = 0; t < 8; ++t) {
-            if (w0 + t < nw32) {
-              const uint32_t v = (uint32_t)(((unsigned long long)d[t + 1] << 32 | d[t]) >> (8 * skew));
-              take(w0 + t, __builtin_bswap32(__brev(v)));      // most significant bit first inside each byte
+            for (int t = 0; t < 8; ++t) {
+              if (w0 + t < nw32) {
+                const uint32_t v = (uint32_t)(((unsigned long long)d[t + 1] << 32 | d[t]) >> (8 * skew));
+                take(w0 + t, __builtin_bswap32(__brev(v)));      // most significant bit first inside each byte
+              }
             }
           }
+        } else {
+          for (int w = 0; w < nw32; ++w) take(w, granular_word(src, w, Tkv, gran));
         }
-      } else {
-        for (int w = 0; w < nw32; ++w) {
-          uint32_t word = 0;
-          for (int t = 0; t < 32 && 32 * w + t < Tkv; ++t) {
-            const int js = (32 * w + t) / gran;
-            word |= (uint32_t)((src[js >> 3] >> (7 - (js & 7))) & 1) << t;
-          }
-          take(w, word);
-        }
+        key = row_key(cached, count, first_kept);
       }
-      // key of a computed row: kept blocks in the low 16 bits (0 .. 32768), first kept block above them
-      const int key = cached ? -1 : (count | (max(first_kept, 0) << 16));
       if (in_lds)
         lds_keys[r] = key;
-      else
+      else if (!decoded)
         keys[row] = key;
-      if (!cached) {
-        sum += (uint32_t)count;
-        hi = max(hi, (uint32_t)count);
-        lo = min(lo, (uint32_t)count);
+      if (key >= 0) {
+        const uint32_t count = (uint32_t)(key & 0xffff);
+        sum += count;
+        hi = max(hi, count);
+        lo = min(lo, count);
       }
     }
     for (int off = 32; off > 0; off >>= 1) {
@@ -263,13 +312,13 @@ __global__ void __launch_bounds__(kOrderThreads) plan_queues(const uint8_t* __re
   const int share = (int)min(kept_all / (3ull * kWgsPerXcd), (unsigned long long)Tkv);
   const int limit = (int)heaviest <= share ? (int)heaviest : share;
   const OrderScale sc = {limit, max(limit, (int)min(lightest_u, heaviest) - 1), (int)heaviest, min((int)lightest_u, limit)};
-  auto bin_of = [&](int major, int r) -> int {
-    const int group = (r / Tq) >> shift;
+  auto bin_of = [&](int major, int head) -> int {     // head: of this queue, 0 ..
+    const int group = head >> shift;
     if (major < kLongBuckets) return major * groups + group;
     if (major < kCachedBucket) return kLongBuckets * groups + group * kFineBuckets + (major - kLongBuckets);
     return kCachedBucket * groups + group;
   };
-  for (int r = tid; r < rows; r += kOrderThreads) atomicAdd(&bins[bin_of(order_major(key_of(r), sc), r)], 1u);
+  for (int r = tid; r < rows; r += kOrderThreads) atomicAdd(&bins[bin_of(order_major(key_of(r), sc), r / Tq)], 1u);
   __syncthreads();
   // exclusive scan of the bins: a contiguous chunk per thread, then over the lanes of a wave, then over the waves
   {
@@ -306,8 +355,8 @@ __global__ void __launch_bounds__(kOrderThreads) plan_queues(const uint8_t* __re
       seen[lane] = 0u;
       for (int i0 = 0; i0 < Tq; i0 += 64) {
         const bool valid = i0 + lane < Tq;
-        const int r = hl * Tq + min(i0 + lane, Tq - 1);
-        const int key = key_of(r);
+        const int i = min(i0 + lane, Tq - 1);
+        const int key = in_lds ? lds_keys[hl * Tq + i] : keys[(q + kXcds * hl) * Tq + i];
         const int major = valid ? order_major(key, sc) : 0;
         // the lanes whose row falls into the same bucket as this lane's: one ballot per bit of the bucket number
         unsigned long long same = __ballot(valid);
@@ -322,8 +371,8 @@ __global__ void __launch_bounds__(kOrderThreads) plan_queues(const uint8_t* __re
           const uint32_t before = seen[major];
           const uint32_t rank = before + (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
           if ((same & ((1ull << lane) - 1ull)) == 0ull) seen[major] = before + (uint32_t)__popcll(same);
-          const uint32_t pos = bins[bin_of(major, r)] + rank;
-          list[2 * pos] = (uint32_t)global_row(r) | (key < 0 ? kCopyFlag : 0u);
+          const uint32_t pos = bins[bin_of(major, hl)] + rank;
+          list[2 * pos] = (uint32_t)((q + kXcds * hl) * Tq + i0 + lane) | (key < 0 ? kCopyFlag : 0u);
           list[2 * pos + 1] = (uint32_t)key;
         }
       }
@@ -332,7 +381,7 @@ __global__ void __launch_bounds__(kOrderThreads) plan_queues(const uint8_t* __re
   }
   for (int r = tid; r < rows; r += kOrderThreads) {
     const int key = key_of(r);
-    const uint32_t pos = atomicAdd(&bins[bin_of(order_major(key, sc), r)], 1u);
+    const uint32_t pos = atomicAdd(&bins[bin_of(order_major(key, sc), r / Tq)], 1u);
     list[2 * pos] = (uint32_t)global_row(r) | (key < 0 ? kCopyFlag : 0u);
     list[2 * pos + 1] = (uint32_t)key;
   }
@@ -1195,8 +1244,18 @@ int launch_plan(const uint8_t* cache_flags, const uint8_t* kv_mask, const Shape&
   const int groups = ((heads_per_xcd - 1) >> shift) + 1;
   const int sym_Tq = (s.Tq + gran - 1) / gran;
   const int sym_row_bytes = ((s.Tkv + gran - 1) / gran + 7) / 8;
+  // A queue's workgroup decodes its rows with one thread per row, which is quickest while a queue has few words: many words
+  // through one CU, each lane at a row of its own, are slow, and then a kernel over all rows decodes first.  Creating a
+  // plan, us, without / with it: 2115 words in a queue 10 / 14, 6966: 15 / 15, 8772: 19 / 16, 26316: 35 / 18, 131072 (one head
+  // of 131072 tokens in blocks of 64): 194 / 31; bit by bit at granularity 2: 639 words 16 / 17, 6966: 59 / 18.
+  const bool decoded = (long long)heads_per_xcd * s.Tq * s.nw32 > (gran == 1 ? 8192 : 1024);
+  if (decoded) {
+    hipLaunchKernelGGL(decode_rows, dim3((s.N + 15) / 16), dim3(256), 0, stream, cache_flags, kv_mask, s.N, s.Tq, s.Tkv, gran,
+                       sym_Tq, sym_row_bytes, s.nw32, pb.words, pb.keys);
+    HIP_TRY(hipGetLastError());
+  }
   hipLaunchKernelGGL(plan_queues, dim3(kXcds), dim3(kOrderThreads), 0, stream, cache_flags, kv_mask, BH, s.Tq, s.Tkv, gran,
-                     sym_Tq, sym_row_bytes, s.nw32, shift, groups, pb.words, pb.keys, pb.order, pb.queues);
+                     sym_Tq, sym_row_bytes, s.nw32, shift, groups, decoded, pb.words, pb.keys, pb.order, pb.queues);
   HIP_TRY(hipGetLastError());
   return 0;
 }

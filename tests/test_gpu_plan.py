@@ -156,6 +156,7 @@ ROUTES = [
     (1, 24, 1409, 128, 64, 64, None, 0.0),     # 288 blocks of 128 rows: done in 256-row blocks whatever the caller's
     (2, 30, 2500, 128, 128, 128, None, 0.0),   # 600 blocks of 256 rows: some workgroups take three
     (1, 2, 8300, 64, 64, 64, 0.1, 0.2),        # five words a row, 130 bits in rows of 17 bytes
+    (1, 1, 33100, 64, 64, 64, 0.04, 0.2),      # 518 rows of 17 words in one queue: decoded by a kernel of its own
 ]
 
 
@@ -237,3 +238,34 @@ def test_plan_is_intact_behind_runs_that_overlapped():
         torch.cuda.synchronize()
         assert (down_bits(got) == down_bits(want)).all(), f"run behind the {rep}-th overlapping pair"
     plan.destroy()
+
+
+@pytest.mark.parametrize("n", [1, 2, 3])
+def test_symbols_decoded_in_front_of_the_queues(n):
+    """202 rows of 7 words per queue: at granularity 1 the queue's workgroup decodes them, else a kernel of its own; both
+    give the bits of the one-shot call with the symbols expanded to tiles."""
+    B, H, L, D, blk = 1, 3, 12900, 64, 64
+    T = -(-L // blk)
+    sT = -(-T // n)
+    rng = np.random.default_rng(synth.BASE_SEED + 350 + n)
+    w = synth.random_case(synth.BASE_SEED + 351 + n, B, H, L, D, blk, blk, keep=1.0, cached_frac=0.0, with_cache_tensor=True)
+    coarse_flags = (rng.random((B, H, sT)) < 0.3).astype(np.uint8)
+    coarse_M = (rng.random((B, H, sT, sT)) < 0.1).astype(np.uint8)
+    coarse_flags[0, 0, 1], coarse_M[0, 0, 1] = 0, 0                # computed rows without a kept block
+    f, m = oracle.expand_granularity(coarse_flags, coarse_M, n, T, T)
+    Q, K, V, Oc = up_bf16(w.Q), up_bf16(w.K), up_bf16(w.V), up_bf16(w.O_cache)
+    packed = up_u8(pkg.sparse_attn_pack_mask(coarse_M))
+    raw = torch.zeros(packed.numel() + 1, dtype=torch.uint8, device=dev())
+    odd = raw[1:].view(packed.shape)
+    odd.copy_(packed)
+    plan = pkg.SparseAttnPlan(up_u8(coarse_flags), odd, B, H, L, blk, blk, granularity=n)
+    O, O1 = fresh_O(w), fresh_O(w)
+    plan.run(Q, K, V, Oc, O)
+    pkg.sparse_attn_fwd(Q, K, V, up_u8(f), up_u8(pkg.sparse_attn_pack_mask(m)), Oc, O1, blk, blk)
+    torch.cuda.synchronize()
+    plan.destroy()
+    assert (down_bits(O) == down_bits(O1)).all()
+    c = np.repeat(f != 0, blk, axis=2)[:, :, :L]
+    assert (down_bits(O)[c] == w.O_cache[c]).all()
+    empty = np.repeat((f == 0) & ~m.any(axis=-1), blk, axis=2)[:, :, :L]
+    assert empty.any() and (down_bits(O)[empty] == 0).all()
