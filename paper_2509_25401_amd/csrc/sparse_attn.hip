@@ -65,7 +65,12 @@ constexpr int attn_keys(int D, int bq) { return D == 128 && bq == 64 ? 32 : 64; 
 constexpr int kLongBuckets = 8;       // kept-count buckets of the long rows of a queue (longest first, across heads)
 constexpr int kFineBuckets = 55;      // ... of its other rows (head by head); with the bucket of cached rows: 64,
 constexpr int kCachedBucket = kLongBuckets + kFineBuckets;   // one lane each in the ranking pass
-constexpr int kWgsPerXcd = 64;        // workgroups of the persistent grid per XCD (32 CUs x 2) the ordering plans for
+// Workgroups per XCD that the ordering plans for: those of 128-row blocks (32 CUs x 2).  64-row blocks have twice as many;
+// for them a long row is one of two thirds of a share instead of one third, which is the better line for nearly equal
+// rows and the worse one for some skewed masks (24 heads, 9001 tokens, 64 x 128 blocks, us, line at two thirds / one
+// third: the ragged mask at 40 % keep 225 / 235, a tenth of the rows at 90 % and the others at 10 % 164 / 169, a fifth at 50 % and
+// the others at 10 % 166 / 143).
+constexpr int kWgsPerXcd = 64;
 constexpr int kCusPerXcd = 32;
 constexpr int kXcds = 8;               // accelerator dies (XCDs) of the MI355X, each with its own L2
 constexpr int kMaxHeadGroups = 24;    // head groups per bucket in the ordering histogram of a queue (6 KiB of LDS)
@@ -126,7 +131,7 @@ __device__ inline uint32_t clear_padding(uint32_t word, int w, int Tkv) {
 
 // Work list order: one queue per XCD (head bh belongs to XCD bh % kXcds), in three parts.
 //   long rows    rows with more kept blocks than `limit` = a third of what one workgroup gets to do in total
-//                (kept blocks of the queue / (3 * kWgsPerXcd)): longest first across heads (kLongBuckets buckets,
+//                (kept blocks of the queue / (3 * kWgsPerXcd); see there for 64-row blocks): longest first across heads (kLongBuckets buckets,
 //                heads adjacent inside a bucket), so that none of them starts late.  Uniform masks have none; with
 //                few rows per workgroup (short sequences) every row is long.
 //   other rows   head by head, inside a head the heaviest first (kFineBuckets buckets), inside a bucket in sequence

@@ -269,3 +269,29 @@ def test_symbols_decoded_in_front_of_the_queues(n):
     assert (down_bits(O)[c] == w.O_cache[c]).all()
     empty = np.repeat((f == 0) & ~m.any(axis=-1), blk, axis=2)[:, :, :L]
     assert empty.any() and (down_bits(O)[empty] == 0).all()
+
+
+@pytest.mark.parametrize("D,bk", [(64, 64), (128, 128)])
+def test_skewed_rows_of_64_row_blocks(D, bk):
+    """A tenth of the rows keeps nine tenths of the key blocks, the others 5 %: long rows, fine buckets and a queue whose
+    grid has four workgroups per CU.  Every block once, same bits as the plan's."""
+    B, H, L, bq = 1, 24, 2900, 64                                  # 1104 rows: work list
+    w = synth.random_case(synth.BASE_SEED + 360 + D, B, H, L, D, bq, bk, keep=1.0, cached_frac=0.1)
+    rng = np.random.default_rng(synth.BASE_SEED + 361 + D)
+    p = np.where(rng.random((B, H, w.M_s.shape[2], 1)) < 0.1, 0.9, 0.05)
+    w.M_s = (rng.random(w.M_s.shape) < p).astype(w.M_s.dtype)
+    case = DeviceCase(w)
+    got = case.run()
+    plan = pkg.SparseAttnPlan(case.flags, case.mask, B, H, L, bq, bk)
+    O = fresh_O(w)
+    plan.run(case.Q, case.K, case.V, case.Oc, O)
+    torch.cuda.synchronize()
+    plan.destroy()
+    assert (down_bits(O) == got).all()
+    # a row with a single kept block of K keys is a mean of that many values: the usual bar, and per value the bound of
+    # rounded weights and a rounded result
+    ref, ref_bits = oracle_full(w)
+    c = np.repeat(w.cache_flags != 0, bq, axis=2)[:, :, :L]
+    assert (got[c] == ref_bits[c]).all()
+    err = np.abs(synth.bf16_bits_to_f32(got).astype(np.float64) - ref)[~c]
+    assert err.max() <= 3 * 2.0 ** -9 * np.abs(synth.bf16_bits_to_f32(w.V)).max() and err.mean() <= 1e-3
