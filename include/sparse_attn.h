@@ -151,7 +151,7 @@ int sparse_gemm_q_stream(const void* X, const void* W, const void* bias, const u
  * create.  run allocates nothing; it must be ordered after create (same stream, or synchronise), and two
  * runs of one plan must not overlap in time (a run consumes the plan's queue counters and its last workgroup
  * sets them back, which is why the plan is not const): blocks of their outputs are left out if they do.  A run
- * ordered behind both is right again.  destroy waits for the device and frees.  Errors as for sparse_attn_fwd; on failure *plan is NULL.
+ * ordered behind both is right again (if both had the same D).  destroy waits for the device and frees.  Errors as for sparse_attn_fwd; on failure *plan is NULL.
  */
 typedef struct sparse_attn_plan sparse_attn_plan;
 int sparse_attn_plan_create(const uint8_t* cache_flags, const uint8_t* kv_mask, int B, int H, int L, int block_q,

@@ -58,10 +58,18 @@ typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
 #define LDS_PTR(T) T __attribute__((address_space(3)))*
 #define GLOBAL_PTR(T) T __attribute__((address_space(1)))*
 
-// Keys per LDS sub-tile.  64-row blocks of 128 channels take 32: four K and V sub-tiles of 64 keys are 64 KiB, of which a
-// CU holds two, and two workgroups of two waves leave half of its waves idle (24 heads, 64-key sub-tiles
-// and now, us: 9001 tokens at 40 % keep 655 -> 478, 33024 tokens at 25 % keep and 50 % cached 2276 -> 1834).
-constexpr int attn_keys(int D, int bq) { return D == 128 && bq == 64 ? 32 : 64; }
+// Keys per LDS sub-tile: 64, except for 64-row blocks of 128 channels when there are many of them.  Four K and V sub-tiles
+// of 64 keys are 64 KiB, of which a CU holds two, and two workgroups of two waves leave half of its waves idle; with 32
+// keys it holds four (24 heads, us, 64 / 32 keys: 9001 tokens at 40 % keep 655 / 478, 33024 tokens at 25 % keep and 50 % cached
+// 2276 / 1834).  A workgroup by itself is quicker with 64, where the softmax of one half lies under the matrix
+// instructions of the other, so 64 as long as a CU has no more than about two rows to compute: up to two rows per CU, or
+// three where some are cached (24 heads, 30 % keep: 1344 tokens, 504 rows, 20.4 / 20.8 and half of them cached 19.6 / 21.3;
+// 2048 tokens, 768 rows, none cached 37 / 30, half of them cached 27.6 / 32.7).  A mask whose time is that of a few heavy
+// rows among many light ones loses with 32 as well (9001 tokens, 2 % of the rows at 95 %, the others at 3 %: 213 / 240); that
+// is not known when the kernel is chosen.
+constexpr int attn_keys(int D, int bq, long long rows, bool some_cached, int cus) {
+  return D == 128 && bq == 64 && rows > (some_cached ? 3LL : 2LL) * cus ? 32 : 64;
+}
 constexpr int kLongBuckets = 8;       // kept-count buckets of the long rows of a queue (longest first, across heads)
 constexpr int kFineBuckets = 55;      // ... of its other rows (head by head); with the bucket of cached rows: 64,
 constexpr int kCachedBucket = kLongBuckets + kFineBuckets;   // one lane each in the ranking pass
@@ -453,12 +461,11 @@ __device__ __forceinline__ int v_swizzle(int row) {
 // re-read the last row that exists, scores of missing keys are set to -inf before the softmax, stores of
 // missing query rows are dropped, and a sub-tile that lies entirely past the end is not visited.
 // The aligned instantiation contains none of this.
-// DEALT: items are dealt out by workgroup number and every workgroup decodes the symbols of its rows (see below).
-template <int D, int BQ, int BK, bool RAGGED, bool DEALT>
+// KEYS: keys per sub-tile.  DEALT: items are dealt out by workgroup number and every workgroup decodes the symbols of its rows (see below).
+template <int D, int BQ, int BK, int KEYS, bool RAGGED, bool DEALT>
 __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
   constexpr int NWAVES = BQ / 32;
   constexpr int NT = NWAVES * 64;
-  constexpr int KEYS = attn_keys(D, BQ);   // keys per sub-tile
   constexpr int SUB = BK / KEYS;           // LDS sub-tiles per symbol bit
   constexpr int CH = D / 8;                // 16-byte chunks per row
   constexpr int ROWB = D * 2;              // bytes per row
@@ -1181,32 +1188,32 @@ bool overlaps(const void* a, const void* b, size_t bytes) {
 }
 
 // four K / V sub-tiles, two item slots, output rows of the waves beyond four
-constexpr size_t attn_lds(int D, int bq) { return 4 * (size_t)attn_keys(D, bq) * D * 2 + 16 + (bq > 128 ? (size_t)(bq - 128) * D * 2 : 0); }
+constexpr size_t attn_lds(int D, int bq, int keys) { return 4 * (size_t)keys * D * 2 + 16 + (bq > 128 ? (size_t)(bq - 128) * D * 2 : 0); }
 
-template <int D, int BQ, int BK, bool RAGGED, bool DEALT>
+template <int D, int BQ, int BK, int KEYS, bool RAGGED, bool DEALT>
 int launch_attn_variant(const AttnParams& p, int grid, hipStream_t stream) {
-  constexpr size_t lds = attn_lds(D, BQ);
+  constexpr size_t lds = attn_lds(D, BQ, KEYS);
   static std::once_flag once;
   static hipError_t attr_err = hipSuccess;
   std::call_once(once, [] {
-    attr_err = hipFuncSetAttribute((const void*)attn_kernel<D, BQ, BK, RAGGED, DEALT>,
+    attr_err = hipFuncSetAttribute((const void*)attn_kernel<D, BQ, BK, KEYS, RAGGED, DEALT>,
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   });
   if (attr_err != hipSuccess)
     return fail(SPARSE_ATTN_ERR_HIP, "hipFuncSetAttribute failed: %s", hipGetErrorString(attr_err));
-  hipLaunchKernelGGL((attn_kernel<D, BQ, BK, RAGGED, DEALT>), dim3(grid), dim3(BQ * 2), lds, stream, p);
+  hipLaunchKernelGGL((attn_kernel<D, BQ, BK, KEYS, RAGGED, DEALT>), dim3(grid), dim3(BQ * 2), lds, stream, p);
   HIP_TRY(hipGetLastError());
   return 0;
 }
 
-template <int D, int BQ, int BK>
+template <int D, int BQ, int BK, int KEYS = 64>
 int launch_attn(const AttnParams& p, int grid, hipStream_t stream) {
   const bool ragged = p.L % BQ || p.L % BK;
   if (p.queues)
-    return ragged ? launch_attn_variant<D, BQ, BK, true, false>(p, grid, stream)
-                  : launch_attn_variant<D, BQ, BK, false, false>(p, grid, stream);
-  return ragged ? launch_attn_variant<D, BQ, BK, true, true>(p, grid, stream)
-                : launch_attn_variant<D, BQ, BK, false, true>(p, grid, stream);
+    return ragged ? launch_attn_variant<D, BQ, BK, KEYS, true, false>(p, grid, stream)
+                  : launch_attn_variant<D, BQ, BK, KEYS, false, false>(p, grid, stream);
+  return ragged ? launch_attn_variant<D, BQ, BK, KEYS, true, true>(p, grid, stream)
+                : launch_attn_variant<D, BQ, BK, KEYS, false, true>(p, grid, stream);
 }
 
 struct PlanBuffers {
@@ -1232,6 +1239,7 @@ PlanBuffers carve(char* base, const Shape& s) {
 struct sparse_attn_plan {
   Shape s;
   int gran;
+  bool some_cached;        // the plan has cache flags
   int dev;
   void* mem;               // workspace as carved above; the queue heads are zero between runs
   PlanBuffers bufs;
@@ -1367,7 +1375,8 @@ int run(const void* Q, const void* K, const void* V, const uint8_t* cache_flags,
   // persistent grid: as many workgroups as the CUs hold (8 waves by registers, 160 KiB of LDS), fewer if there are fewer
   // items.  With two per CU whatever their size, the 2-wave workgroups of 64-row blocks left half of the waves idle:
   // 9001 tokens, 24 heads of 64, 64 x 128 blocks at 40 % keep: 330 -> 224 us.
-  const size_t wg_lds = attn_lds(D, bq);
+  const int keys = attn_keys(D, bq, s.N, plan ? plan->some_cached : cache_flags != nullptr, cus);
+  const size_t wg_lds = attn_lds(D, bq, keys);
   const int by_lds = (int)(160 * 1024 / wg_lds), by_waves = 8 / (bq / 32);
   const int room = cus * (by_waves < by_lds ? by_waves : by_lds);
   const int grid = s.N < room ? s.N : room;
@@ -1420,8 +1429,10 @@ int run(const void* Q, const void* K, const void* V, const uint8_t* cache_flags,
   if (D == 128 && bq == 256) rc = launch_attn<128, 256, 128>(p, grid, stream);
   else if (D == 128 && bq == 128 && bk == 128) rc = launch_attn<128, 128, 128>(p, grid, stream);
   else if (D == 128 && bq == 128 && bk == 64) rc = launch_attn<128, 128, 64>(p, grid, stream);
-  else if (D == 128 && bq == 64 && bk == 128) rc = launch_attn<128, 64, 128>(p, grid, stream);
-  else if (D == 128 && bq == 64 && bk == 64) rc = launch_attn<128, 64, 64>(p, grid, stream);
+  else if (D == 128 && bq == 64 && bk == 128)
+    rc = keys == 32 ? launch_attn<128, 64, 128, 32>(p, grid, stream) : launch_attn<128, 64, 128>(p, grid, stream);
+  else if (D == 128 && bq == 64 && bk == 64)
+    rc = keys == 32 ? launch_attn<128, 64, 64, 32>(p, grid, stream) : launch_attn<128, 64, 64>(p, grid, stream);
   else if (D == 64 && bq == 128 && bk == 128) rc = launch_attn<64, 128, 128>(p, grid, stream);
   else if (D == 64 && bq == 128 && bk == 64) rc = launch_attn<64, 128, 64>(p, grid, stream);
   else if (D == 64 && bq == 64 && bk == 128) rc = launch_attn<64, 64, 128>(p, grid, stream);
@@ -1492,6 +1503,7 @@ int sparse_attn_plan_create(const uint8_t* cache_flags, const uint8_t* kv_mask, 
   if (!pl) return fail(SPARSE_ATTN_ERR_HIP, "out of host memory");
   pl->s = s;
   pl->gran = granularity;
+  pl->some_cached = cache_flags != nullptr;
   pl->mem = nullptr;
   hipError_t e = hipGetDevice(&pl->dev);
   if (e == hipSuccess) e = hipMalloc(&pl->mem, workspace_bytes(s));

@@ -156,6 +156,9 @@ ROUTES = [
     (1, 24, 1409, 128, 64, 64, None, 0.0),     # 288 blocks of 128 rows: done in 256-row blocks whatever the caller's
     (2, 30, 2500, 128, 128, 128, None, 0.0),   # 600 blocks of 256 rows: some workgroups take three
     (1, 2, 8300, 64, 64, 64, 0.1, 0.2),        # five words a row, 130 bits in rows of 17 bytes
+    (1, 24, 1330, 128, 64, 128, 0.4, 0.0),     # 504 rows of 64 x 128 channels: 64-key sub-tiles
+    (1, 24, 2040, 128, 64, 64, 0.4, 0.3),      # 768, some cached: the same, one round and a half
+    (1, 24, 2050, 128, 64, 64, 0.4, 0.3),      # 792: 32-key sub-tiles
     (1, 1, 33100, 64, 64, 64, 0.04, 0.2),      # 518 rows of 17 words in one queue: decoded by a kernel of its own
 ]
 
