@@ -235,5 +235,20 @@ def test_search_tiers(T, short, D, repeat):
     for tau_c, tau_kv in ((f32(0.5), f32(0.3)), (f32(0.35), f32(0.7))):
         ref = oracle.update_symbols(Q, K, block, block, tau_c, tau_kv)
         flags, mask = run_gpu(Q, K, block, block, tau_c, tau_kv)
-        # (blocks that repeat are near-ties for the fp64 oracle: it may order them by their last bits)
-        compare(ref, flags, mask, T, f"T{T} D{D} repeat={repeat}", max_ambiguous=1.0 if repeat else 0.05, require_identical=False)
+        # (blocks that repeat are near-ties for the fp64 oracle: it may order them by their last bits; it calls at most 6.6 % of
+        # the entries of these shapes undecidable)
+        compare(ref, flags, mask, T, f"T{T} D{D} repeat={repeat}", max_ambiguous=0.1 if repeat else 0.05, require_identical=False)
+
+
+@pytest.mark.parametrize("T,D", [(20, 128), (32, 64), (33, 128), (65, 64), (129, 64), (273, 64), (321, 128), (513, 64)])
+def test_equal_entries_are_taken_in_index_order_in_every_tier(T, D):
+    """Q = 0: all entries of a row tie, and so do C and G: exactly the first floor(tau * count) blocks are skipped and
+    cached.  The thresholds lie half an entry away from a whole number of entries."""
+    B, H, block = 1, 2, 64
+    _, K = synth.structured_qk(synth.BASE_SEED + 700 + T, B, H, T * block, D, block)
+    for share in (0.12, 0.47):
+        n_kv, n_c = int(share * T), int(share * (T - 1))
+        flags, mask = run_gpu(np.zeros_like(K), K, block, block, f32((n_c + 0.5) / (T - 1)), f32((n_kv + 0.5) / T))
+        bits = oracle.unpack_symbols(mask, T)
+        assert (bits[..., :n_kv] == 0).all() and (bits[..., n_kv:] == 1).all()
+        assert (flags[..., 0] == 0).all() and (flags[..., 1:1 + n_c] == 1).all() and (flags[..., 1 + n_c:] == 0).all()
