@@ -61,6 +61,7 @@ namespace sa_gemm {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
+constexpr int kCus = 256;           // compute units of the MI355X: what the choice of a tile counts rounds with
 constexpr int kStepK = 64;          // reduction channels per LDS stage
 constexpr int kRowB = kStepK * 2;   // bytes per tile row in LDS
 

@@ -32,6 +32,7 @@
 namespace {
 
 using sa_gemm::f32x16;
+using sa_gemm::kCus;
 using sa_gemm::kRowB;
 using sa_gemm::kStepK;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
@@ -424,12 +425,12 @@ int launch(GemmOParams p, int B, int block_q, hipStream_t stream) {
   if (!p.flags) {
     const int tok = p.tok_end - p.tok_begin;
     const long long units = (long long)B * ((tok + 127) / 128) * (p.C_out / 128);
-    if (units <= 256) return launch_tiles<128, 128, 2, 2, 2, 3, D, false, true>(p, B, stream);
-    if (units <= 512) return launch_tiles<256, 128, 4, 2, 3, 3, D, false, true>(p, B, stream);
+    if (units <= kCus) return launch_tiles<128, 128, 2, 2, 2, 3, D, false, true>(p, B, stream);
+    if (units <= 2 * kCus) return launch_tiles<256, 128, 4, 2, 3, 3, D, false, true>(p, B, stream);
     const int n_col = (p.C_out + 255) / 256, n_tok = (tok + 255) / 256;
-    const long long tiles = (long long)B * n_tok * n_col, full = tiles / 256 * 256;
+    const long long tiles = (long long)B * n_tok * n_col, full = tiles / kCus * kCus;
     const int keep = (int)(full / ((long long)B * n_col));
-    if (tiles > full && tiles - full <= 128 && keep > 0) {
+    if (tiles > full && tiles - full <= kCus / 2 && keep > 0) {
       GemmOParams rest = p;
       p.tok_end = rest.tok_begin = p.tok_begin + keep * 256;
       if (int rc = launch_tiles<256, 256, 4, 2, 2, 3, D, false, true>(p, B, stream)) return rc;
@@ -440,10 +441,10 @@ int launch(GemmOParams p, int B, int block_q, hipStream_t stream) {
   if (block_q == 128) return launch_tiles<128, 128, 2, 2, 2, 3, D, true, true>(p, B, stream);
   const long long tiles = (long long)B * ((p.L + 63) / 64) * ((p.C_out + 255) / 256);
   if (p.n_terms > 1) {
-    if (tiles <= 256) return launch_tiles<64, 128, 1, 2, 2, 3, D, true, true>(p, B, stream);
+    if (tiles <= kCus) return launch_tiles<64, 128, 1, 2, 2, 3, D, true, true>(p, B, stream);
     return launch_tiles<64, 256, 1, 4, 2, 2, D, true, true>(p, B, stream);
   }
-  if (tiles <= 256 || (tiles > 1280 && !p.select)) return launch_tiles<64, 128, 1, 2, 2, 2, D, true, false>(p, B, stream);
+  if (tiles <= kCus || (tiles > 5 * kCus && !p.select)) return launch_tiles<64, 128, 1, 2, 2, 2, D, true, false>(p, B, stream);
   return launch_tiles<64, 256, 1, 4, 2, 2, D, true, true>(p, B, stream);
 }
 

@@ -26,6 +26,7 @@
 namespace {
 
 using sa_gemm::f32x16;
+using sa_gemm::kCus;
 using sa_gemm::kRowB;
 using sa_gemm::kStepK;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
@@ -428,12 +429,12 @@ int launch(GemmQParams p, int B, int block_q, hipStream_t stream) {
   if (!p.flags) {
     const int tok = p.tok_end - p.tok_begin;
     const long long units = (long long)B * ((tok + 127) / 128) * ((p.H + heads_per_128 - 1) / heads_per_128);
-    if (units <= 256) return launch_tiles<128, 128, 2, 2, 2, 3, D, 0, NR>(p, B, stream);
-    if (units <= 512) return launch_tiles<256, 128, 4, 2, 3, 3, D, 0, NR>(p, B, stream);
+    if (units <= kCus) return launch_tiles<128, 128, 2, 2, 2, 3, D, 0, NR>(p, B, stream);
+    if (units <= 2 * kCus) return launch_tiles<256, 128, 4, 2, 3, 3, D, 0, NR>(p, B, stream);
     const int n_col = (p.H * D + 255) / 256, n_tok = (tok + 255) / 256;
-    const long long tiles = (long long)B * n_tok * n_col, full = tiles / 256 * 256;
+    const long long tiles = (long long)B * n_tok * n_col, full = tiles / kCus * kCus;
     const int keep = (int)(full / ((long long)B * n_col));         // token tiles per sequence that fill whole rounds
-    if (tiles > full && tiles - full <= 128 && keep > 0) {
+    if (tiles > full && tiles - full <= kCus / 2 && keep > 0) {
       GemmQParams rest = p;
       p.tok_end = rest.tok_begin = p.tok_begin + keep * 256;
       if (int rc = launch_tiles<256, 256, 4, 2, 2, 3, D, 0, NR>(p, B, stream)) return rc;
@@ -444,18 +445,18 @@ int launch(GemmQParams p, int B, int block_q, hipStream_t stream) {
   const long long blocks = (long long)B * p.H * p.Tq;
   if constexpr (D == 128) {
     if (block_q == 128) {
-      if (blocks <= 256) return launch_tiles<128, 128, 2, 2, 2, 3, 128, 128, NR>(p, B, stream);
+      if (blocks <= kCus) return launch_tiles<128, 128, 2, 2, 2, 3, 128, 128, NR>(p, B, stream);
       return launch_tiles<256, 128, 4, 2, 3, 3, 128, 128, NR>(p, B, stream);
     }
-    if (blocks <= 512) return launch_tiles<128, 128, 2, 2, 2, 3, 128, 64, NR>(p, B, stream);
+    if (blocks <= 2 * kCus) return launch_tiles<128, 128, 2, 2, 2, 3, 128, 64, NR>(p, B, stream);
     return launch_tiles<256, 128, 4, 2, 3, 3, 128, 64, NR>(p, B, stream);
   } else {
     if (block_q == 128) {
-      if (blocks <= 512) return launch_tiles<128, 64, 2, 1, 2, 3, 64, 128, NR>(p, B, stream);
+      if (blocks <= 2 * kCus) return launch_tiles<128, 64, 2, 1, 2, 3, 64, 128, NR>(p, B, stream);
       return launch_tiles<256, 64, 4, 1, 2, 2, 64, 128, NR>(p, B, stream);
     }
-    if (blocks <= 512) return launch_tiles<64, 64, 1, 1, 2, 3, 64, 64, NR>(p, B, stream);
-    if (blocks <= 1024) return launch_tiles<128, 64, 2, 1, 2, 3, 64, 64, NR>(p, B, stream);
+    if (blocks <= 2 * kCus) return launch_tiles<64, 64, 1, 1, 2, 3, 64, 64, NR>(p, B, stream);
+    if (blocks <= 4 * kCus) return launch_tiles<128, 64, 2, 1, 2, 3, 64, 64, NR>(p, B, stream);
     return launch_tiles<256, 64, 4, 1, 2, 2, 64, 64, NR>(p, B, stream);
   }
 }
