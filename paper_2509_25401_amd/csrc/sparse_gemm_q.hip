@@ -10,10 +10,10 @@
 // kernel reads.
 //
 // What bounds it (33024 tokens, C = 3072, 24 heads of 128, inputs that are not in the caches).  Dense: power; the
-// matrix pipe is busy 71 % of a round at 1.73 GHz, where one tile alone on the chip runs at 2.4 GHz and 87 %: 632 -> 508
-// us (1227 TFLOP/s), with RMSNorm and RoPE 737 -> 540 us; the 128 x 128 tiles it replaces streamed 64 KB from L2 per
-// 1024 MFMA cycles of a CU, these 32.  Few computed blocks: what leaves L2 (0.9 GB at 80 % cached, 5.6 TB/s: a token
-// block's rows are wanted by heads whose weights live on different XCDs).
+// matrix pipe is busy 67 % of the time at 1.66 GHz: 632 -> 508 us (1227 TFLOP/s), with RMSNorm and RoPE 737 -> 540 us; the
+// 128 x 128 tiles it replaces streamed 64 KB from L2 per 1024 MFMA cycles of a CU, these 32.  80 % of the blocks cached:
+// 166 us, matrix pipe busy 40 %, 0.95 GB fetched past L2 (a token block's rows are wanted by heads whose weights live on
+// different XCDs) and 624 tiles on 256 CUs, 2.4 rounds; which of the two holds it back has not been separated.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
