@@ -80,12 +80,14 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 //     ks 2 | operands of ks 3                    | ... 2nd half
 //     stage s + 1 has landed (everything but what belongs to later stages), all waves' reads have returned: barrier
 //     ks 3 | operands of ks 0 of stage s + 1     | ... weights of stage s + WB, 1st half
-// (XB = 2: the token rows of stage s + 2 go out in ks 3 too, in front of the weights; in ks 1 and 2, behind the barrier
-// that frees their buffer by half a stage, they would arrive late: 33024 tokens, 24 heads, 64 x 256 tiles: 669 -> 660 us)
+// (XB = 2: the token rows of stage s + 2 go out like the weights, the first half in ks 3, in front of theirs, the second in ks
+// 0 of the next stage.  In ks 1 and 2, half a stage behind the barrier that frees their buffer, they arrive late: query
+// projection, 9001 tokens, 24 heads of 64, 90 % cached 25.0 -> 22.6 us; all of them in ks 3 crowds that step: 4608 tokens, 64
+// heads of 64, half cached, blocks of 128 tokens 90.3 -> 94.6.)
 // so a step's operands are on their way while the previous step's MFMAs run, across the stage boundary too; the
 // requests go out one at a time behind an MFMA (in a burst they keep the wave from issuing the next one).
 // Buffer safety: the weights requested in ks 3 of stage s (and ks 0 of the next) overwrite those of stage s, the token
-// rows requested in ks 1 and 2 those of stage s - 1 (XB = 2, ks 3: of stage s); all waves' reads of a stage have returned
+// rows requested in ks 1 and 2 those of stage s - 1 (XB = 2: ks 3 and the next ks 0, of stage s); all waves' reads of a stage have returned
 // at the barrier inside it.
 template <int TN, int TM, int WN, int WM, int WB, int XB>
 struct Pipe {
@@ -196,13 +198,17 @@ struct Pipe {
     issue_w(w_at, 0, 0, kWLoad);
     issue_x(x_src(), 0, 0, kXLoad);
     if (WB == 3 && stages > 1) issue_w(w_src(), 1, 0, kWLoad);
-    if (stages > 1) issue_x(x_src(), 1, 0, kXLoad);
+    size_t x_next = 0;                           // XB = 2: the token channels that the next ks 0 asks for the rest of
+    if (stages > 1) {
+      x_next = x_src();
+      issue_x(x_next, 1, 0, XB == 3 ? kXLoad : x1);
+    }
     if (stages >= WB) {
       w_at = w_src();
       issue_w(w_at, WB - 1, 0, w1);
     }
     if (stages >= 3)
-      sa_wait_vmem_but<(WB - 2) * kWLoad + kXLoad + w1>();
+      sa_wait_vmem_but<(WB - 2) * kWLoad + (XB == 3 ? kXLoad : x1) + w1>();
     else
       sa_wait_vmem();
     lds_barrier();
@@ -218,10 +224,15 @@ struct Pipe {
     // compiler wait for all reads at once)
     auto stage = [&](auto more1_c, auto more2_c, auto ask_w_c) __attribute__((always_inline)) {
       constexpr bool more1 = decltype(more1_c)::value, more2 = decltype(more2_c)::value, ask_w = decltype(ask_w_c)::value;
-      constexpr bool ask_w2 = WB == 3 ? more2 : more1, ask_x = XB == 3 && more2, ask_x2 = XB == 2 && more2;
+      constexpr bool ask_w2 = WB == 3 ? more2 : more1, ask_x = XB == 3 && more2, ask_x2 = XB == 2 && more2, ask_x1 = XB == 2 && more1;
       const int w_free = wbuf == 0 ? WB - 1 : wbuf - 1, x_free = xbuf == 0 ? XB - 1 : xbuf - 1;
       read(K1{}, wb, xb0);
-      mfma(K0{}, std::integral_constant<int, ask_w2 ? w2 : 0>{}, [&](int j) { issue_w(w_at, w_free, w1 + j, w1 + j + 1); });
+      mfma(K0{}, std::integral_constant<int, (ask_x1 ? x2 : 0) + (ask_w2 ? w2 : 0)>{}, [&](int j) {
+        if (ask_x1 && j < x2)
+          issue_x(x_next, x_free, x1 + j, x1 + j + 1);
+        else
+          issue_w(w_at, w_free, w1 + j - (ask_x1 ? x2 : 0), w1 + j - (ask_x1 ? x2 : 0) + 1);
+      });
       int behind = 0;
       if constexpr (more1 && !more2) {
         behind = extra();
@@ -249,14 +260,14 @@ struct Pipe {
         wb = smem + wbuf * kWStage;
         xb0 = smem + xbuf * kXStage;
         read(K0{}, wb, xb0);
-        if constexpr (ask_x2) x_at = x_src();
+        if constexpr (ask_x2) x_next = x_src();
         if constexpr (ask_w) w_at = w_src();
       }
-      mfma(K3{}, std::integral_constant<int, (ask_x2 ? kXLoad : 0) + (ask_w ? w1 : 0)>{}, [&](int j) {
-        if (ask_x2 && j < kXLoad)
-          issue_x(x_at, x_done, j, j + 1);
+      mfma(K3{}, std::integral_constant<int, (ask_x2 ? x1 : 0) + (ask_w ? w1 : 0)>{}, [&](int j) {
+        if (ask_x2 && j < x1)
+          issue_x(x_next, x_done, j, j + 1);
         else
-          issue_w(w_at, w_done, j - (ask_x2 ? kXLoad : 0), j - (ask_x2 ? kXLoad : 0) + 1);
+          issue_w(w_at, w_done, j - (ask_x2 ? x1 : 0), j - (ask_x2 ? x1 : 0) + 1);
       });
     };
     using T = std::true_type;
