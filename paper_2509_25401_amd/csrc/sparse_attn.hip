@@ -55,6 +55,16 @@ typedef __attribute__((ext_vector_type(8))) short s16x8;
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
 
+// f(integral_constant 0), ..., f(integral_constant N - 1)
+template <int... I, typename F>
+__device__ __forceinline__ void static_for_impl(std::integer_sequence<int, I...>, const F& f) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(const F& f) {
+  static_for_impl(std::make_integer_sequence<int, N>{}, f);
+}
+
 #define LDS_PTR(T) T __attribute__((address_space(3)))*
 #define GLOBAL_PTR(T) T __attribute__((address_space(1)))*
 
@@ -70,6 +80,10 @@ typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
 constexpr int attn_keys(int D, int bq, long long rows, bool some_cached, int cus) {
   return D == 128 && bq == 64 && rows > (some_cached ? 3LL : 2LL) * cus ? 32 : 64;
 }
+// Wavefronts per SIMD that the registers are laid out for.  64 channels leave room for three (168 registers, no spill), which
+// 128-row blocks use (three workgroups of 32 KiB LDS per CU; 24 heads, us, two / three: 9001 tokens dense 577 / 552, 33024
+// tokens at 25 % keep 1745 / 1681); of the 64-row workgroups LDS holds four, two wavefronts per SIMD, either way.
+constexpr int attn_waves_per_simd(int D, bool dealt) { return D == 64 && !dealt ? 3 : 2; }
 constexpr int kLongBuckets = 8;       // kept-count buckets of the long rows of a queue (longest first, across heads)
 constexpr int kFineBuckets = 55;      // ... of its other rows (head by head); with the bucket of cached rows: 64,
 constexpr int kCachedBucket = kLongBuckets + kFineBuckets;   // one lane each in the ranking pass
@@ -425,6 +439,13 @@ __device__ __forceinline__ unsigned sa_lane0_atomic_inc_wrap(uint32_t* counter, 
       : "memory");
   return old;
 }
+// The lane number, formed where it is needed: offsets that follow from it are then not computed once, in front of the item
+// loop, to occupy registers for the whole kernel (the headline instance: 240 vector registers -> 224).
+__device__ __forceinline__ int sa_fresh_lane() {
+  int ln;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
+  return ln;
+}
 // Waits for this wave's outstanding memory operations and returns lane 0 of `v` as a wave-uniform value.
 __device__ __forceinline__ unsigned sa_lane0_value(unsigned v) {
   unsigned r;
@@ -439,6 +460,33 @@ __device__ __forceinline__ unsigned long long sa_scalar_load_b64(const uint32_t*
   asm volatile("s_load_dwordx2 %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=s"(v) : "s"(ptr) : "memory");
   return v;
 }
+
+// Buffer descriptor of `bytes` bytes at `base` (both wave-uniform): reads past the end give zeros.
+__device__ __forceinline__ u32x4 sa_buffer(const char* base, unsigned bytes) {
+  const unsigned long long a = (unsigned long long)base;
+  u32x4 r;
+  r[0] = __builtin_amdgcn_readfirstlane((unsigned)a);
+  r[1] = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32)) & 0xffffu;   // stride 0
+  r[2] = bytes;
+  r[3] = 0x00020000u;                                                     // raw buffer of 32-bit words
+  return r;
+}
+// Direct-to-LDS load through a buffer descriptor: every lane fetches 16 bytes at lane_off + tile_off + DT of the buffer, the
+// wave's 1 KiB lands at lds_addr + LDS0 + DT; lanes past the end of the buffer write zeros.  The distance of the
+// loads of a tile is the same in memory and in LDS, so what fits the instruction's offset field (it moves both addresses)
+// goes there, and M0 is formed from one register: no address sits in a register of its own.  In assembly for the reason
+// given at sa_load_to_lds_16B.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+template <int LDS0, int DT>
+__device__ __forceinline__ void sa_tile_to_lds(const u32x4& buffer, unsigned lane_off, unsigned tile_off, unsigned lds_addr) {
+  constexpr int HI = DT / 4096 * 4096, LO = DT % 4096;
+  asm volatile("s_add_u32 m0, %0, %4\n\tbuffer_load_dwordx4 %1, %2, %3 offen offset:%5 lds"
+               :
+               : "s"(lds_addr), "v"(lane_off), "s"(buffer), "s"(tile_off + HI), "i"(LDS0 + HI), "i"(LO)
+               : "memory", "m0", "scc");
+}
+#pragma clang diagnostic pop
 
 // ---------------------------------------------------------------------------------------
 // LDS layouts.  A sub-tile is KEYS rows of D bf16, row major, with the 16-byte chunks of a
@@ -457,13 +505,13 @@ __device__ __forceinline__ int v_swizzle(int row) {
 }
 
 // RAGGED: the sequence length is not a multiple of the blocks (Definition 1 counts ceil(L / b) of them).
-// The last query block then has fewer rows and the last key block fewer keys: loads of missing rows
-// re-read the last row that exists, scores of missing keys are set to -inf before the softmax, stores of
+// The last query block then has fewer rows and the last key block fewer keys: missing K and V rows are zeros
+// (range check of the buffer loads), scores of missing keys are set to -inf before the softmax, stores of
 // missing query rows are dropped, and a sub-tile that lies entirely past the end is not visited.
 // The aligned instantiation contains none of this.
 // KEYS: keys per sub-tile.  DEALT: items are dealt out by workgroup number and every workgroup decodes the symbols of its rows (see below).
 template <int D, int BQ, int BK, int KEYS, bool RAGGED, bool DEALT>
-__global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
+__global__ void __launch_bounds__(BQ * 2, attn_waves_per_simd(D, DEALT)) attn_kernel(const AttnParams p) {
   constexpr int NWAVES = BQ / 32;
   constexpr int NT = NWAVES * 64;
   constexpr int SUB = BK / KEYS;           // LDS sub-tiles per symbol bit
@@ -484,11 +532,10 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
   char* const ldsK = smem;                 // two K sub-tiles, then two V sub-tiles
   char* const ldsV = smem + 2 * TILEB;
   LDS_PTR(volatile int) const s_item = (LDS_PTR(volatile int))(smem + 4 * TILEB);
-  const unsigned lds_base = (unsigned)(uintptr_t)(LDS_PTR(char))smem;
 
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const unsigned lds_wave = (unsigned)(uintptr_t)(LDS_PTR(char))smem + (unsigned)wave * 1024u;   // where its loads go
   const int l32 = lane & 31;    // query row inside the wave's 32-row slab / key row of an operand read
   const int half = lane >> 5;   // which 8 of the 16 k-slots of an MFMA this lane feeds
   const int i16 = lane & 15;
@@ -496,18 +543,17 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
   const float score_scale = p.scale_log2;
 
   // Per-lane offsets, the same for every item.
-  // Global byte offsets inside a sub-tile (swizzle applied to the source).  The swizzles repeat every 16 rows, so
-  // the offsets of load t and load t + TP differ by a constant that goes into the (scalar) base address.
+  // Global byte offsets inside a sub-tile (swizzle applied to the source).  Load t of a wave lies t * NWAVES KiB behind its
+  // first, in memory and in LDS; the swizzles repeat every 16 rows, so up to that the lane offsets of load t and t + TP agree.
   constexpr int TP = NWAVES * ROWS_PER_INST >= 16 ? 1 : 16 / (NWAVES * ROWS_PER_INST);
-  constexpr int TSTEP = TP * NWAVES * ROWS_PER_INST * ROWB;
   static_assert(NLOAD % TP == 0, "loads of a wave must be whole swizzle periods");
   unsigned k_goff[TP], v_goff[TP];
 #pragma unroll
   for (int t = 0; t < TP; ++t) {
     const int r = (wave + t * NWAVES) * ROWS_PER_INST + lane / CH;
     const int pch = lane % CH;
-    k_goff[t] = (unsigned)(r * ROWB + ((pch ^ k_swizzle<D>(r)) * 16));
-    v_goff[t] = (unsigned)(r * ROWB + ((pch ^ v_swizzle<D>(r)) * 16));
+    k_goff[t] = (unsigned)(r * ROWB + ((pch ^ k_swizzle<D>(r)) * 16) - t * NWAVES * 1024);
+    v_goff[t] = (unsigned)(r * ROWB + ((pch ^ v_swizzle<D>(r)) * 16) - t * NWAVES * 1024);
   }
   int k_off[KS];     // S^T operand (K rows): LDS byte offset of k-step ks inside this lane's key row
 #pragma unroll
@@ -579,12 +625,13 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
         // resolve the ticket, or steal (a head counts at most the items and one overshoot per workgroup)
         int item = queue_begin(my_q) + nwg(my_q) + (int)sa_lane0_value(ticket);
         if (item >= queue_begin(my_q + 1)) item = -1;
+        const int ln = sa_fresh_lane();
         unsigned drained = 0;          // queues an increment of this workgroup found empty: at most eight rounds fail
         while (item < 0) {
-          const int q = (my_q + lane) % kXcds;       // lanes 0..7: the eight queues, the home queue first
+          const int q = (my_q + ln) % kXcds;       // lanes 0..7: the eight queues, the home queue first
           const int room = queue_begin(q + 1) - queue_begin(q) - nwg(q);
           const int taken = (int)__hip_atomic_load(q_head + q * kHeadStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          const unsigned long long open = __builtin_amdgcn_ballot_w64(lane < kXcds && taken < room && !((drained >> q) & 1u));
+          const unsigned long long open = __builtin_amdgcn_ballot_w64(ln < kXcds && taken < room && !((drained >> q) & 1u));
           if (open == 0ull) break;
           const int qs = (my_q + __builtin_ctzll(open)) % kXcds;
           const int got = queue_begin(qs) + nwg(qs) + (int)sa_lane0_value(sa_lane0_atomic_inc(q_head + qs * kHeadStride));
@@ -637,11 +684,12 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
       // cache-then-reuse: O_i <- cached O_i, bit exact
       int NV = BQ * ROWB / 16;
       if constexpr (RAGGED) NV = min(BQ, p.L - iq * BQ) * (ROWB / 16);
+      const int first_vec = wave * 64 + sa_fresh_lane();
       if (p.n_terms > 0) {
         // forecast: fp32 sum of the scaled terms in order, rounded once to bf16
         const bf16x8* t0 = (const bf16x8*)(p.O_cache + blk_off);
         bf16x8* dst = (bf16x8*)(p.O + blk_off);
-        for (int t = tid; t < NV; t += NT) {
+        for (int t = first_vec; t < NV; t += NT) {
           const bf16x8 a = t0[t];
           float acc[8];
 #pragma unroll
@@ -661,14 +709,14 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
         const u32x4* src = (const u32x4*)(p.O_cache + blk_off);
         u32x4* dst = (u32x4*)(p.O + blk_off);
 #pragma unroll 4
-        for (int t = tid; t < NV; t += NT) dst[t] = src[t];
+        for (int t = first_vec; t < NV; t += NT) dst[t] = src[t];
       }
       continue;
     }
 
     // ---- compute-on-demand ----
-    const char* Kh = p.K + head_off;
-    const char* Vh = p.V + head_off;
+    const u32x4 Kh = sa_buffer(p.K + head_off, (unsigned)(p.L * ROWB));      // (at most 2^21 rows of 256 bytes)
+    const u32x4 Vh = sa_buffer(p.V + head_off, (unsigned)(p.L * ROWB));
     const uint32_t* wp = DEALT ? nullptr : p.words + (size_t)row * p.nw32;
 
     // Q fragment: B operand of S^T = K Q^T; lane holds query row l32, d = 16*ks + 8*half .. +7, exactly as stored:
@@ -719,34 +767,13 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
       return 32 * w_idx + b;
     };
 
-    // loads lo .. hi-1 of this wave's NLOAD for sub-tile (j, sub)
-    auto issue_loads = [&](int j, int sub, auto buf_c, int lo, int hi) {
-      constexpr int buf = decltype(buf_c)::value;
-      const size_t tile_off = ((size_t)j * BK + (size_t)sub * KEYS) * ROWB;
-      const char* gK = Kh + tile_off;
-      const char* gV = Vh + tile_off;
-      if constexpr (RAGGED) {
-        const int valid = p.L - (j * BK + sub * KEYS);     // >= 1: sub-tiles past the end are never requested
-        if (valid < KEYS) {
-#pragma unroll
-          for (int t = lo; t < hi; ++t) {
-            const int r = (wave + t * NWAVES) * ROWS_PER_INST + lane / CH;
-            const int pch = lane % CH;
-            const int src_row = min(r, valid - 1);            // LDS row r receives the last row that exists
-            const unsigned dst = (unsigned)(buf * TILEB + (wave + t * NWAVES) * 1024);
-            sa_load_to_lds_16B(gK, (unsigned)(src_row * ROWB + ((pch ^ k_swizzle<D>(r)) * 16)), lds_base + dst);
-            sa_load_to_lds_16B(gV, (unsigned)(src_row * ROWB + ((pch ^ v_swizzle<D>(r)) * 16)), lds_base + 2 * TILEB + dst);
-          }
-          return;
-        }
-      }
-#pragma unroll
-      for (int t = lo; t < hi; ++t) {
-        const unsigned dst = (unsigned)(buf * TILEB + (wave + t * NWAVES) * 1024);
-        sa_load_to_lds_16B(gK + (t / TP) * TSTEP, k_goff[t % TP], lds_base + dst);
-        sa_load_to_lds_16B(gV + (t / TP) * TSTEP, v_goff[t % TP], lds_base + 2 * TILEB + dst);
-      }
+    // load t of this wave's NLOAD for the sub-tile at byte tile_off of the head
+    auto issue_load = [&](unsigned tile_off, auto buf_c, auto t_c) {
+      constexpr int buf = decltype(buf_c)::value, t = decltype(t_c)::value;
+      sa_tile_to_lds<buf * TILEB, t * NWAVES * 1024>(Kh, k_goff[t % TP], tile_off, lds_wave);
+      sa_tile_to_lds<(2 + buf) * TILEB, t * NWAVES * 1024>(Vh, v_goff[t % TP], tile_off, lds_wave);
     };
+    auto tile_offset = [&](int j, int sub) -> unsigned { return (unsigned)(j * BK + sub * KEYS) * ROWB; };
 
     // valid: keys of this sub-tile that exist (RAGGED only); (nj, nsub): the sub-tile to fetch into the other
     // buffer meanwhile, nj < 0 if there is none
@@ -842,15 +869,26 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
 #pragma unroll
       for (int t = 0; t < kPre; ++t) ka[t] = k_read(t);
       __builtin_amdgcn_s_setprio(kMfmaPrio);
-      // ---- S0
-#pragma unroll
-      for (int t = 0; t < KS; ++t) {
-        if (t + kPre < NQK) ka[t + kPre] = k_read(t + kPre);
-        s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[t], qf[t], t == 0 ? neg_ref : s[0], 0, 0, 0);
-        // the next sub-tile's loads go out here, a few behind each matrix instruction, instead of in one
-        // burst in front of the first one
-        if (nj >= 0) issue_loads(nj, nsub, other_c, t * NLOAD / KS, (t + 1) * NLOAD / KS);
-      }
+      // ---- S0; the next sub-tile's loads go out here, a few behind each matrix instruction, instead of in one burst in
+      // front of the first one.  One branch around all of it: with one per load, 64-bit addresses and an M0 value for each, the
+      // scalar instructions between the matrix instructions took longer than these (24 heads, 9001 tokens at 40 % keep
+      // and 25 % cached, before / after: 64 channels 225 / 211 us, 128 channels 331 / 318).
+      auto s0 = [&](auto loads) {
+        const unsigned next_off = tile_offset(nj, nsub);
+        static_for<KS>([&](auto t_c) {
+          constexpr int t = decltype(t_c)::value;
+          if constexpr (t + kPre < NQK) ka[t + kPre] = k_read(t + kPre);
+          s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[t], qf[t], t == 0 ? neg_ref : s[0], 0, 0, 0);
+          if constexpr (decltype(loads)::value) {
+            constexpr int lo = t * NLOAD / KS, hi = (t + 1) * NLOAD / KS;
+            static_for<hi - lo>([&](auto i) { issue_load(next_off, other_c, std::integral_constant<int, lo + decltype(i)::value>{}); });
+          }
+        });
+      };
+      if (nj >= 0)
+        s0(std::true_type{});
+      else
+        s0(std::false_type{});
       if constexpr (RAGGED) {
         if (valid < KEYS) mask_block(0);
       }
@@ -907,6 +945,9 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
           __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (RAGGED) {
+          // (the sum passes through an empty asm statement in front of the branch: otherwise the compiler moves the weights
+          // behind it, where no matrix instruction of this wave hides them)
+          asm volatile("" : "+v"(dl0));
           if (valid < KEYS) mask_block(1);
         }
         // !(sum <= limit) also catches an overflowed (infinite or NaN) sum
@@ -951,11 +992,12 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
     using Buf1 = std::integral_constant<int, 1>;
     int j = tiles_left > 0 ? (int)(key >> 16) : -1;
     int sub = 0;
-    if (j >= 0) issue_loads(j, 0, Buf0{}, 0, NLOAD);
+    if (j >= 0) static_for<NLOAD>([&](auto t) { issue_load(tile_offset(j, 0), Buf0{}, t); });
     {
-      int qr = wave * 32 + l32;
+      const int ln = sa_fresh_lane();
+      int qr = wave * 32 + (ln & 31);
       if constexpr (RAGGED) qr = min(qr, p.L - 1 - iq * BQ);
-      const char* qrow = p.Q + blk_off + (size_t)qr * ROWB + half * 16;
+      const char* qrow = p.Q + blk_off + (size_t)qr * ROWB + (ln >> 5) * 16;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
         const bf16x8 q = *(const bf16x8*)(qrow + ks * 32);
@@ -1008,10 +1050,7 @@ __global__ void __launch_bounds__(BQ * 2, 2) attn_kernel(const AttnParams p) {
       constexpr int PER = KEYS / 32;
       char* const stage = wave < 4 ? (wave < PER ? ldsK : ldsV) + (last ^ 1) * TILEB + wave % PER * 32 * ROWB
                                    : smem + 4 * TILEB + 16 + (wave - 4) * 32 * ROWB;
-      // (the lane number passes through an empty asm statement: otherwise the two dozen lane-dependent offsets
-      // below are computed once, in front of the item loop, and occupy registers for the whole kernel)
-      int ln = lane;
-      asm volatile("" : "+v"(ln));
+      const int ln = sa_fresh_lane();
       const int srow = ln & 31;
       char* const wr = stage + srow * ROWB + (ln >> 5) * 8;
 #pragma unroll
@@ -1372,20 +1411,22 @@ int run(const void* Q, const void* K, const void* V, const uint8_t* cache_flags,
   }
   if (record) HIP_TRY(hipEventRecord(ev[0], stream));
 
-  // persistent grid: as many workgroups as the CUs hold (8 waves by registers, 160 KiB of LDS), fewer if there are fewer
-  // items.  With two per CU whatever their size, the 2-wave workgroups of 64-row blocks left half of the waves idle:
-  // 9001 tokens, 24 heads of 64, 64 x 128 blocks at 40 % keep: 330 -> 224 us.
+  // persistent grid: as many workgroups as the CUs hold (8 waves by registers, 12 with 64 channels; 160 KiB of LDS), fewer if
+  // there are fewer items.  With two per CU whatever their size, the 2-wave workgroups of 64-row blocks left half of the
+  // waves idle: 9001 tokens, 24 heads of 64, 64 x 128 blocks at 40 % keep: 330 -> 224 us.
   const int keys = attn_keys(D, bq, s.N, plan ? plan->some_cached : cache_flags != nullptr, cus);
-  const size_t wg_lds = attn_lds(D, bq, keys);
-  const int by_lds = (int)(160 * 1024 / wg_lds), by_waves = 8 / (bq / 32);
-  const int room = cus * (by_waves < by_lds ? by_waves : by_lds);
-  const int grid = s.N < room ? s.N : room;
+  const int by_lds = (int)(160 * 1024 / attn_lds(D, bq, keys));
+  auto room = [&](bool dealt) -> int {
+    const int by_waves = 4 * attn_waves_per_simd(D, dealt) / (bq / 32);
+    return cus * (by_waves < by_lds ? by_waves : by_lds);
+  };
   // No pre-pass where it cannot help: with no more rows than workgroups the order does not matter, and without symbols
   // all rows are equally long, so with up to two per workgroup dealing them out by number does as well.  Every
   // workgroup then decodes its own rows (at most 64 words each).  512 tokens, two heads of 64: 20.1 -> 12.3 us; 4608
   // tokens, 24 heads, dense: 273 -> 261 us.
   const bool symbols = cache_flags != nullptr || kv_mask != nullptr;
-  const bool dealt = !plan && s.nw32 <= 64 && s.N <= (symbols ? 1 : 2) * room;
+  const bool dealt = !plan && s.nw32 <= 64 && s.N <= (symbols ? 1 : 2) * room(true);
+  const int grid = s.N < room(dealt) ? s.N : room(dealt);
   if (!plan && !dealt) {
     if (int rc = launch_plan(cache_flags, kv_mask, s, 1, pb, stream)) return rc;
   }
