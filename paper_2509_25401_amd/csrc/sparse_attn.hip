@@ -1,7 +1,8 @@
 // FlashOmni attention (Algorithm 1 of the paper) for AMD MI355X / gfx950.
 //
-// Two kernels per call, both on the caller's stream (the second alone where the order of the rows does not matter:
-// few rows, or no symbols and at most two rows per workgroup; one more, decode_rows, where a queue has many symbols):
+// Two kernels per call, both on the caller's stream (the second alone where the order of the rows does not matter, few
+// rows, or no symbols and at most two rows per workgroup, and where its workgroups sort the rows themselves, a few rows per CU;
+// one more, decode_rows, where a queue has many symbols):
 //   plan_queues decodes the packed symbols of Section 3.3 once per (b,h,i) row into aligned
 //               32-bit words (bit j of the row = key block j, padding cleared), counts the
 //               kept key blocks of every non-cached row and notes the first of them;
@@ -80,10 +81,20 @@ __device__ __forceinline__ void static_for(const F& f) {
 constexpr int attn_keys(int D, int bq, long long rows, bool some_cached, int cus) {
   return D == 128 && bq == 64 && rows > (some_cached ? 3LL : 2LL) * cus ? 32 : 64;
 }
+// How the rows (query blocks) get to the workgroups.
+//   kQueues  plan_queues has ordered them; tickets, stealing
+//   kDealt   by workgroup number, every workgroup decodes the symbols of its rows: where the order does not matter
+//   kSorted  every workgroup decodes and sorts the rows of its XCD (an eighth of all, at most kSortRows of kSortWords words) and
+//            takes those that fall to its number, the longest first; cached rows go to workgroups without a computed one.  For
+//            calls of a few rows per CU, where the pre-pass is a large part of the time (see run())
+enum : int { kQueues = 0, kDealt = 1, kSorted = 2 };
+constexpr int kSortRows = 256, kSortWords = 4;
+constexpr int kSortLds = kSortRows * 4 * 2 + kSortRows * kSortWords * 4 + 16;   // keys, list, words, number of computed rows
+
 // Wavefronts per SIMD that the registers are laid out for.  64 channels leave room for three (168 registers, no spill), which
 // 128-row blocks use (three workgroups of 32 KiB LDS per CU; 24 heads, us, two / three: 9001 tokens dense 577 / 552, 33024
 // tokens at 25 % keep 1745 / 1681); of the 64-row workgroups LDS holds four, two wavefronts per SIMD, either way.
-constexpr int attn_waves_per_simd(int D, bool dealt) { return D == 64 && !dealt ? 3 : 2; }
+constexpr int attn_waves_per_simd(int D, int mode) { return D == 64 && mode == kQueues ? 3 : 2; }
 constexpr int kLongBuckets = 8;       // kept-count buckets of the long rows of a queue (longest first, across heads)
 constexpr int kFineBuckets = 55;      // ... of its other rows (head by head); with the bucket of cached rows: 64,
 constexpr int kCachedBucket = kLongBuckets + kFineBuckets;   // one lane each in the ranking pass
@@ -118,7 +129,8 @@ struct AttnParams {
   char* O;
   const uint32_t* words;   // [N][nw32] decoded symbol words
   const uint32_t* order;   // [N][2] work list: {row | kCopyFlag, sort key of the row (see plan_queues)}
-  uint32_t* queues;        // kXcds queue heads at [q * kHeadStride]; nullptr: items are dealt out by workgroup number
+  uint32_t* queues;        // kXcds queue heads at [q * kHeadStride]; (kQueues)
+  int mode;                // kQueues ..
   int self_reset;          // the last workgroup to finish clears the queue heads for the next run
   const uint8_t* raw_flags;   // symbols as the caller gave them, nullptr: none (read where items are dealt out)
   const uint8_t* raw_mask;
@@ -509,9 +521,10 @@ __device__ __forceinline__ int v_swizzle(int row) {
 // (range check of the buffer loads), scores of missing keys are set to -inf before the softmax, stores of
 // missing query rows are dropped, and a sub-tile that lies entirely past the end is not visited.
 // The aligned instantiation contains none of this.
-// KEYS: keys per sub-tile.  DEALT: items are dealt out by workgroup number and every workgroup decodes the symbols of its rows (see below).
-template <int D, int BQ, int BK, int KEYS, bool RAGGED, bool DEALT>
-__global__ void __launch_bounds__(BQ * 2, attn_waves_per_simd(D, DEALT)) attn_kernel(const AttnParams p) {
+// KEYS: keys per sub-tile.  MODE: how the rows get to the workgroups.
+template <int D, int BQ, int BK, int KEYS, bool RAGGED, int MODE>
+__global__ void __launch_bounds__(BQ * 2, attn_waves_per_simd(D, MODE)) attn_kernel(const AttnParams p) {
+  constexpr bool DEALT = MODE == kDealt, SORTED = MODE == kSorted;
   constexpr int NWAVES = BQ / 32;
   constexpr int NT = NWAVES * 64;
   constexpr int SUB = BK / KEYS;           // LDS sub-tiles per symbol bit
@@ -588,18 +601,93 @@ __global__ void __launch_bounds__(BQ * 2, attn_waves_per_simd(D, DEALT)) attn_ke
   uint32_t* const q_head = p.queues;
   auto nwg = [&](int q) -> int { return ((int)gridDim.x - q + kXcds - 1) / kXcds; };
   auto queue_begin = [&](int q) -> int { return queue_first_head(q, p.BH) * p.Tq; };
+  // Workgroups s and s + kCusPerXcd of an XCD share a CU.  A list starts with its longest rows, longest first, so the
+  // first kCusPerXcd of them are handed out backwards: the CUs whose second workgroup comes away empty or with a
+  // short row then have the longest ones, and the sums are even where a list has one or two rows per CU.
+  auto first_of = [&](int q0, int slot) -> int {
+    const int chunk = slot / kCusPerXcd * kCusPerXcd;
+    const bool back = (slot / kCusPerXcd) % 2 == 0 && chunk + kCusPerXcd <= nwg(q0);
+    return back ? 2 * chunk + kCusPerXcd - 1 - slot : slot;
+  };
+  // SORTED
+  uint32_t* const sort_keys = (uint32_t*)(smem + 4 * TILEB + 16);
+  uint32_t* const sort_list = sort_keys + kSortRows;
+  uint32_t* const sort_words = sort_list + kSortRows;
+  uint32_t* const sort_computed = sort_words + kSortRows * kSortWords;
+  int list_at = -1, list_round = 0, copy_at = 0, copy_step = 1, copy_end = 0, rest_at = 0, n_computed = 0, n_list = 0;
+  if constexpr (SORTED) {
+    const int q0 = (int)blockIdx.x % kXcds, slot = (int)blockIdx.x / kXcds, W = nwg(q0);
+    const int row0 = q0 * (p.N / kXcds) + min(q0, p.N % kXcds), rows = p.N / kXcds + (q0 < p.N % kXcds ? 1 : 0);
+    const int tid = (int)threadIdx.x;
+    if (tid == 0) *sort_computed = 0u;
+    for (int r = tid; r < (rows + 3) / 4 * 4; r += NT) {
+      uint32_t k = 0u;
+      if (r < rows) {
+        const unsigned flag = p.raw_flags ? p.raw_flags[row0 + r] : 0u;
+        // rows start at any byte: aligned words, shifted together; only words that hold a byte of the row are read
+        const uint8_t* src = p.raw_mask ? p.raw_mask + (size_t)(row0 + r) * p.raw_row_bytes : (const uint8_t*)p.Q;
+        const int skew = p.raw_mask ? (int)((uintptr_t)src & 3) : 0;
+        const uint32_t* aligned = (const uint32_t*)(src - skew);
+        const int last = (skew + p.raw_row_bytes - 1) / 4;
+        uint32_t low = aligned[0];
+        int count = 0;
+#pragma unroll
+        for (int w = 0; w < kSortWords; ++w) {
+          const uint32_t high = aligned[min(w + 1, last)];
+          uint32_t word = (uint32_t)(((unsigned long long)high << 32 | low) >> (8 * skew));
+          word = p.raw_mask ? __builtin_bswap32(__brev(word)) : ~0u;       // most significant bit first inside each byte
+          word = w < p.nw32 ? clear_padding(word, w, p.Tkv) : 0u;
+          sort_words[r * kSortWords + w] = word;
+          count += __popc(word);
+          low = high;
+        }
+        // computed rows above cached ones, more kept blocks above fewer, earlier rows above later ones
+        k = (flag ? 0u : (uint32_t)(count + 1) << 16) | (uint32_t)(rows - 1 - r);
+      }
+      sort_keys[r] = k;
+    }
+    __syncthreads();
+    for (int r = tid; r < rows; r += NT) {
+      const uint32_t k = sort_keys[r];
+      int rank = 0;
+      for (int i = 0; i < rows; i += 4) {
+        const u32x4 o = *(const u32x4*)(sort_keys + i);
+        rank += (o[0] > k) + (o[1] > k) + (o[2] > k) + (o[3] > k);
+      }
+      sort_list[rank] = k;
+      if (k >> 16) atomicAdd(sort_computed, 1u);
+    }
+    __syncthreads();
+    n_list = rows;
+    n_computed = __builtin_amdgcn_readfirstlane((int)*sort_computed);
+    list_at = first_of(q0, slot);
+    if (p.n_terms > 0 || p.do_copy) {
+      // Cached rows: workgroups without a computed one take some each, as many as fit beside the longest computed row
+      // (moving a row takes about as long as three blocks of it); the others are dealt to all.
+      const int cached = rows - n_computed, idle = max(0, W - n_computed);
+      const int each = max(1, (int)(__builtin_amdgcn_readfirstlane((int)sort_list[0]) >> 16) / 3);
+      const int by_idle = min(cached, idle * each);
+      if (list_at >= n_computed) {
+        copy_at = list_at - n_computed;
+        copy_step = idle;
+        copy_end = by_idle;
+      }
+      rest_at = by_idle + (idle ? slot : W - 1 - slot);
+      n_list = rows;
+    } else {
+      n_list = n_computed;
+      rest_at = rows;
+    }
+  }
   int next_n;                          // DEALT: next row; queues: the first item
   {
     const int q0 = (int)blockIdx.x % kXcds, slot = (int)blockIdx.x / kXcds;
-    if constexpr (DEALT) {
+    if constexpr (SORTED) {
+      next_n = 0;
+    } else if constexpr (DEALT) {
       next_n = slot + q0 * (p.N / kXcds) + min(q0, p.N % kXcds);
     } else {
-      // Workgroups s and s + kCusPerXcd of an XCD share a CU.  A queue starts with its longest rows, longest first, so the
-      // first kCusPerXcd of them are handed out backwards: the CUs whose second workgroup comes away empty or with a
-      // short row then have the longest ones, and the sums are even where a queue has one or two rows per CU.
-      const int chunk = slot / kCusPerXcd * kCusPerXcd;
-      const bool back = (slot / kCusPerXcd) % 2 == 0 && chunk + kCusPerXcd <= nwg(q0);
-      next_n = queue_begin(q0) + (back ? 2 * chunk + kCusPerXcd - 1 - slot : slot);
+      next_n = queue_begin(q0) + first_of(q0, slot);
       if (next_n >= queue_begin(q0 + 1)) next_n = -1;
     }
   }
@@ -607,14 +695,30 @@ __global__ void __launch_bounds__(BQ * 2, attn_waves_per_simd(D, DEALT)) attn_ke
   bool drawn = false, first_item = true;
   unsigned ticket = 0;                 // wave 0: lane 0 holds the ticket of the home queue, possibly still in flight
   auto draw_issue = [&]() {
-    if constexpr (!DEALT) {
+    if constexpr (MODE == kQueues) {
       if (wave == 0) ticket = sa_lane0_atomic_inc(q_head + my_q * kHeadStride);   // a drained queue just keeps counting
       drawn = true;
     }
   };
   for (int parity = 0;; parity ^= 1) {
     int n = next_n;
-    if constexpr (DEALT) {
+    if constexpr (SORTED) {
+      // computed rows in turn from both ends of the workgroups, then cached ones
+      const int q0 = (int)blockIdx.x % kXcds, slot = (int)blockIdx.x / kXcds, W = nwg(q0);
+      if (list_at < n_computed) {
+        n = list_at;
+        ++list_round;
+        list_at = list_round * W + (list_round % 2 ? W - 1 - slot : slot);
+      } else if (copy_at < copy_end) {
+        n = n_computed + copy_at;
+        copy_at += copy_step;
+      } else {
+        n = n_computed + rest_at;
+        rest_at += W;
+        if (n >= n_list) break;
+      }
+      if (!first_item) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the LDS buffers are free
+    } else if constexpr (DEALT) {
       const int q0 = (int)blockIdx.x % kXcds;
       if (n >= (q0 + 1) * (p.N / kXcds) + min(q0 + 1, p.N % kXcds)) break;
       if (!first_item) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the LDS buffers are free
@@ -646,29 +750,60 @@ __global__ void __launch_bounds__(BQ * 2, attn_waves_per_simd(D, DEALT)) attn_ke
     }
     drawn = false;
     first_item = false;
+    // Q fragment: B operand of S^T = K Q^T; lane holds query row l32, d = 16*ks + 8*half .. +7, exactly as stored:
+    // the products accumulate in fp32 and the scale log2(e)/sqrt(D) is applied to the fp32 score on its way into
+    // the exponential (scaling the fragment instead would save that multiply but round the queries a second time).
+    bf16x8 qf[KS];
+    auto load_q = [&](size_t off, int block) {
+      const int ln = sa_fresh_lane();
+      int qr = wave * 32 + (ln & 31);
+      if constexpr (RAGGED) qr = min(qr, p.L - 1 - block * BQ);
+      const char* qrow = p.Q + off + (size_t)qr * ROWB + (ln >> 5) * 16;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const bf16x8 q = *(const bf16x8*)(qrow + ks * 32);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) qf[ks][e] = q[e];
+      }
+    };
     // row, and its key: kept blocks | first kept block << 16
     uint32_t entry, key, raw_words = 0;
-    if constexpr (DEALT) {
-      // symbols as the caller gave them, at most 64 words a row: lane w decodes word w
-      entry = (uint32_t)n;
-      if (p.raw_flags && __builtin_amdgcn_readfirstlane((int)p.raw_flags[n]) != 0) entry |= kCopyFlag;
-      if (lane < p.nw32) {
-        raw_words = 0xffffffffu;
-        if (p.raw_mask) {
-          const uint8_t* src = p.raw_mask + (size_t)n * p.raw_row_bytes;
-          uint32_t v = 0;
-#pragma unroll
-          for (int b = 0; b < 4; ++b) v |= 4 * lane + b < p.raw_row_bytes ? (uint32_t)src[4 * lane + b] << (8 * b) : 0u;
-          raw_words = __builtin_bswap32(__brev(v));      // most significant bit first inside each byte
-        }
-        raw_words = clear_padding(raw_words, lane, p.Tkv);
-      }
-      int count = __popc(raw_words);
-      for (int off = 32; off > 0; off >>= 1) count += __shfl_xor(count, off);
+    if constexpr (SORTED) {
+      const int q0 = (int)blockIdx.x % kXcds;
+      const uint32_t k = (uint32_t)__builtin_amdgcn_readfirstlane((int)sort_list[n]);
+      const int rows = p.N / kXcds + (q0 < p.N % kXcds ? 1 : 0), r = rows - 1 - (int)(k & 0xffffu);
+      entry = (uint32_t)(q0 * (p.N / kXcds) + min(q0, p.N % kXcds) + r) | (k >> 16 ? 0u : kCopyFlag);
+      raw_words = lane < kSortWords ? sort_words[r * kSortWords + lane] : 0u;
       const unsigned long long some = __builtin_amdgcn_ballot_w64(raw_words != 0u);
       const int w = some ? __builtin_ctzll(some) : 0;
       const uint32_t bits = (uint32_t)__builtin_amdgcn_readlane((int)raw_words, w);
-      key = (uint32_t)__builtin_amdgcn_readfirstlane(count) | (uint32_t)(some ? 32 * w + __builtin_ctz(bits) : 0) << 16;
+      key = some ? 1u | (uint32_t)(32 * w + __builtin_ctz(bits)) << 16 : 0u;      // (the count is for queues: any, or none)
+    } else if constexpr (DEALT) {
+      // Symbols as the caller gave them, at most 64 words a row: lane w decodes word w.  A short call is a chain of round
+      // trips to memory, so flag, symbols and queries are requested together (40 heads of 64, 1024 tokens: 12.5 -> 12.1 us).
+      entry = (uint32_t)n;
+      const unsigned flag = p.raw_flags ? p.raw_flags[n] : 0u;
+      const bool has_word = lane < p.nw32;
+      uint32_t byte[4];
+#pragma unroll
+      for (int b = 0; b < 4; ++b) byte[b] = 0xffu;
+      if (p.raw_mask) {
+        const uint8_t* src = p.raw_mask + (size_t)n * p.raw_row_bytes;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) byte[b] = src[min(4 * lane + b, p.raw_row_bytes - 1)];
+      }
+      {
+        const int head = n / p.Tq, block = n - head * p.Tq;
+        load_q(((size_t)head * p.L + (size_t)block * BQ) * ROWB, block);
+      }
+      raw_words = byte[0] | byte[1] << 8 | byte[2] << 16 | byte[3] << 24;
+      // most significant bit first inside each byte; bytes past the row's last are padding
+      raw_words = has_word ? clear_padding(__builtin_bswap32(__brev(raw_words)), lane, p.Tkv) : 0u;
+      if (__builtin_amdgcn_readfirstlane((int)flag) != 0) entry |= kCopyFlag;
+      const unsigned long long some = __builtin_amdgcn_ballot_w64(raw_words != 0u);
+      const int w = some ? __builtin_ctzll(some) : 0;
+      const uint32_t bits = (uint32_t)__builtin_amdgcn_readlane((int)raw_words, w);
+      key = some ? 1u | (uint32_t)(32 * w + __builtin_ctz(bits)) << 16 : 0u;      // (the count is for queues: any, or none)
     } else {
       const unsigned long long entry64 = sa_scalar_load_b64(p.order + 2 * (size_t)n);
       entry = (uint32_t)entry64;
@@ -717,13 +852,7 @@ __global__ void __launch_bounds__(BQ * 2, attn_waves_per_simd(D, DEALT)) attn_ke
     // ---- compute-on-demand ----
     const u32x4 Kh = sa_buffer(p.K + head_off, (unsigned)(p.L * ROWB));      // (at most 2^21 rows of 256 bytes)
     const u32x4 Vh = sa_buffer(p.V + head_off, (unsigned)(p.L * ROWB));
-    const uint32_t* wp = DEALT ? nullptr : p.words + (size_t)row * p.nw32;
-
-    // Q fragment: B operand of S^T = K Q^T; lane holds query row l32, d = 16*ks + 8*half .. +7, exactly as stored:
-    // the products accumulate in fp32 and the scale log2(e)/sqrt(D) is applied to the fp32 score on its way into
-    // the exponential (scaling the fragment instead would save that multiply but round the queries a second time).
-    // (It is loaded further down, behind the first K/V sub-tile's loads, so that the two latencies overlap.)
-    bf16x8 qf[KS];
+    const uint32_t* wp = MODE != kQueues ? nullptr : p.words + (size_t)row * p.nw32;
 
     f32x16 o[DB];
 #pragma unroll
@@ -750,7 +879,7 @@ __global__ void __launch_bounds__(BQ * 2, attn_waves_per_simd(D, DEALT)) attn_ke
     int tiles_left = (int)(key & 0xffffu);          // kept blocks not yet visited, the current one included
     int w_idx = (int)(key >> 21);                    // word of the first kept block
     auto load_words = [&](int w0) -> uint32_t {
-      if constexpr (DEALT) return raw_words;       // one word per lane, w0 == 0
+      if constexpr (MODE != kQueues) return raw_words;       // one word per lane, w0 == 0
       return w0 + lane < p.nw32 ? wp[w0 + lane] : 0u;
     };
     uint32_t w_lanes = load_words(w_idx & ~63);
@@ -993,18 +1122,7 @@ __global__ void __launch_bounds__(BQ * 2, attn_waves_per_simd(D, DEALT)) attn_ke
     int j = tiles_left > 0 ? (int)(key >> 16) : -1;
     int sub = 0;
     if (j >= 0) static_for<NLOAD>([&](auto t) { issue_load(tile_offset(j, 0), Buf0{}, t); });
-    {
-      const int ln = sa_fresh_lane();
-      int qr = wave * 32 + (ln & 31);
-      if constexpr (RAGGED) qr = min(qr, p.L - 1 - iq * BQ);
-      const char* qrow = p.Q + blk_off + (size_t)qr * ROWB + (ln >> 5) * 16;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const bf16x8 q = *(const bf16x8*)(qrow + ks * 32);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) qf[ks][e] = q[e];
-      }
-    }
+    if constexpr (!DEALT) load_q(blk_off, iq);    // behind the first sub-tile's requests: the two latencies overlap
     // the walk continues behind the first kept block
     if (j >= 0) w_bits = (uint32_t)__builtin_amdgcn_readlane((int)w_lanes, w_idx & 63) & ~((2u << (j & 31)) - 1u);
     if (tiles_left <= kDrawTiles) draw_issue();
@@ -1080,7 +1198,7 @@ __global__ void __launch_bounds__(BQ * 2, attn_waves_per_simd(D, DEALT)) attn_ke
       }
     }
   }
-  if constexpr (!DEALT) {
+  if constexpr (MODE == kQueues) {
     // Stored plans: the last workgroup to get here leaves the queue heads as the next run wants them.  Every
     // workgroup has waited for its last ticket, so no increment is still on its way.  The counter of workgroups that
     // are done wraps by itself: it stays in step with the launches even where a program lets two runs of a plan overlap
@@ -1227,20 +1345,22 @@ bool overlaps(const void* a, const void* b, size_t bytes) {
 }
 
 // four K / V sub-tiles, two item slots, output rows of the waves beyond four
-constexpr size_t attn_lds(int D, int bq, int keys) { return 4 * (size_t)keys * D * 2 + 16 + (bq > 128 ? (size_t)(bq - 128) * D * 2 : 0); }
+constexpr size_t attn_lds(int D, int bq, int keys, int mode) {
+  return 4 * (size_t)keys * D * 2 + 16 + (bq > 128 ? (size_t)(bq - 128) * D * 2 : 0) + (mode == kSorted ? kSortLds : 0);
+}
 
-template <int D, int BQ, int BK, int KEYS, bool RAGGED, bool DEALT>
+template <int D, int BQ, int BK, int KEYS, bool RAGGED, int MODE>
 int launch_attn_variant(const AttnParams& p, int grid, hipStream_t stream) {
-  constexpr size_t lds = attn_lds(D, BQ, KEYS);
+  constexpr size_t lds = attn_lds(D, BQ, KEYS, MODE);
   static std::once_flag once;
   static hipError_t attr_err = hipSuccess;
   std::call_once(once, [] {
-    attr_err = hipFuncSetAttribute((const void*)attn_kernel<D, BQ, BK, KEYS, RAGGED, DEALT>,
+    attr_err = hipFuncSetAttribute((const void*)attn_kernel<D, BQ, BK, KEYS, RAGGED, MODE>,
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   });
   if (attr_err != hipSuccess)
     return fail(SPARSE_ATTN_ERR_HIP, "hipFuncSetAttribute failed: %s", hipGetErrorString(attr_err));
-  hipLaunchKernelGGL((attn_kernel<D, BQ, BK, KEYS, RAGGED, DEALT>), dim3(grid), dim3(BQ * 2), lds, stream, p);
+  hipLaunchKernelGGL((attn_kernel<D, BQ, BK, KEYS, RAGGED, MODE>), dim3(grid), dim3(BQ * 2), lds, stream, p);
   HIP_TRY(hipGetLastError());
   return 0;
 }
@@ -1248,11 +1368,16 @@ int launch_attn_variant(const AttnParams& p, int grid, hipStream_t stream) {
 template <int D, int BQ, int BK, int KEYS = 64>
 int launch_attn(const AttnParams& p, int grid, hipStream_t stream) {
   const bool ragged = p.L % BQ || p.L % BK;
-  if (p.queues)
-    return ragged ? launch_attn_variant<D, BQ, BK, KEYS, true, false>(p, grid, stream)
-                  : launch_attn_variant<D, BQ, BK, KEYS, false, false>(p, grid, stream);
-  return ragged ? launch_attn_variant<D, BQ, BK, KEYS, true, true>(p, grid, stream)
-                : launch_attn_variant<D, BQ, BK, KEYS, false, true>(p, grid, stream);
+  auto go = [&](auto mode) -> int {
+    constexpr int MODE = decltype(mode)::value;
+    return ragged ? launch_attn_variant<D, BQ, BK, KEYS, true, MODE>(p, grid, stream)
+                  : launch_attn_variant<D, BQ, BK, KEYS, false, MODE>(p, grid, stream);
+  };
+  if (p.mode == kQueues) return go(std::integral_constant<int, kQueues>{});
+  if constexpr (BQ <= 128) {
+    if (p.mode == kSorted) return go(std::integral_constant<int, kSorted>{});
+  }
+  return go(std::integral_constant<int, kDealt>{});
 }
 
 struct PlanBuffers {
@@ -1415,19 +1540,29 @@ int run(const void* Q, const void* K, const void* V, const uint8_t* cache_flags,
   // there are fewer items.  With two per CU whatever their size, the 2-wave workgroups of 64-row blocks left half of the
   // waves idle: 9001 tokens, 24 heads of 64, 64 x 128 blocks at 40 % keep: 330 -> 224 us.
   const int keys = attn_keys(D, bq, s.N, plan ? plan->some_cached : cache_flags != nullptr, cus);
-  const int by_lds = (int)(160 * 1024 / attn_lds(D, bq, keys));
-  auto room = [&](bool dealt) -> int {
-    const int by_waves = 4 * attn_waves_per_simd(D, dealt) / (bq / 32);
+  auto room = [&](int mode) -> int {
+    const int by_waves = 4 * attn_waves_per_simd(D, mode) / (bq / 32), by_lds = (int)(160 * 1024 / attn_lds(D, bq, keys, mode));
     return cus * (by_waves < by_lds ? by_waves : by_lds);
   };
-  // No pre-pass where it cannot help: with no more rows than workgroups the order does not matter, and without symbols
+  // No pre-pass where it cannot help: with no more rows than workgroups the order matters little, and without symbols
   // all rows are equally long, so with up to two per workgroup dealing them out by number does as well.  Every
   // workgroup then decodes its own rows (at most 64 words each).  512 tokens, two heads of 64: 20.1 -> 12.3 us; 4608
   // tokens, 24 heads, dense: 273 -> 261 us.
+  // None either where the rows differ and there are between one per CU and two and a quarter per workgroup: the workgroups
+  // sort them.  24 heads, us, queues or dealt / sorted: 4608 tokens, 30 % keep, 56 % cached 56.1 / 50.5; 64 channels, 64-row
+  // blocks, 40 % cached 48.4 / 37.2; 6000 tokens (1128 rows on 512 workgroups), 20 % keep 106 / 99, 70 % 312 / 300; 1200
+  // tokens in 64-row blocks (456 rows) 18.0 / 16.3; 16 heads of 777 tokens (208 rows) 12.4 / 13.6.  Beyond, tickets and stealing
+  // balance better (7500 tokens, 1416 rows, 40 % keep, 30 % cached 199 / 203; 10500 tokens, 60 % cached 190 / 200), and so they
+  // do without a mask, where a row too many for the workgroups of one XCD is a whole row (64 channels, 4608 tokens, 40 % cached
+  // 127 / 140; with a mask at 90 % keep 114 / 122, at 50 % 79 / 70).
   const bool symbols = cache_flags != nullptr || kv_mask != nullptr;
-  const bool dealt = !plan && s.nw32 <= 64 && s.N <= (symbols ? 1 : 2) * room(true);
-  const int grid = s.N < room(dealt) ? s.N : room(dealt);
-  if (!plan && !dealt) {
+  int mode = kQueues;
+  if (!plan && kv_mask && s.nw32 <= kSortWords && s.N > cus && s.N <= kXcds * kSortRows && 4LL * s.N <= 9LL * room(kSorted))
+    mode = kSorted;
+  else if (!plan && s.nw32 <= 64 && s.N <= (symbols ? 1 : 2) * room(kDealt))
+    mode = kDealt;
+  const int grid = s.N < room(mode) ? s.N : room(mode);
+  if (!plan && mode == kQueues) {
     if (int rc = launch_plan(cache_flags, kv_mask, s, 1, pb, stream)) return rc;
   }
   if (record) HIP_TRY(hipEventRecord(ev[1], stream));
@@ -1440,7 +1575,8 @@ int run(const void* Q, const void* K, const void* V, const uint8_t* cache_flags,
   p.O = (char*)O;
   p.words = pb.words;
   p.order = pb.order;
-  p.queues = dealt ? nullptr : pb.queues;
+  p.queues = pb.queues;
+  p.mode = mode;
   p.self_reset = plan != nullptr ? 1 : 0;
   p.raw_flags = cache_flags;
   p.raw_mask = kv_mask;
