@@ -4,7 +4,7 @@
 // Three kernels, all in fp32 (vector instructions, and matrix instructions for the map's scores):
 //   pool_blocks   mean of the n*b_q query rows / n*b_k key rows of every pooled block (granularity n): the only
 //                 pass over Q and K, HBM-bound (reads both tensors once, 16 bytes per lane, row-contiguous)
-//   map_rows      one workgroup per 32 (long rows: 16) rows of the compressed attention map of one head: scores of the
+//   map_rows      one workgroup per 16 rows of the compressed attention map of one head: scores of the
 //                 pooled queries against all pooled keys (scale 1/sqrt(d)), row softmax, then for
 //                 every row the block-skipping rule -- a key block is skipped iff the sum of all row
 //                 entries that come at or before it in ascending order (ties by index) stays <= tau_kv
@@ -18,7 +18,8 @@
 //                 blocks are never cached; if the share of blocks left to compute drops below S_q,
 //                 every block of the head is cached.
 // Neither rule needs a sort: both select everything up to a threshold value, found by bisection on the bits of that
-// value.  At 33024 tokens and 24 heads pool_blocks is at the memory's rate (61 us, 6.6 TB/s), the other two are latency.
+// value.  At 33024 tokens and 24 heads pool_blocks is at the memory's rate (61 us, 6.6 TB/s), the other two (24 and 8) are
+// latency.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -31,11 +32,12 @@
 
 namespace {
 
-// Map rows per workgroup and its threads by the entries of a row that a lane holds (NP of map_rows, 0: rows in LDS).  Up
-// to 64 entries 16 rows and four waves: there the time is the chain of one workgroup, and it gets shorter (24 heads of 63
-// blocks: the call 32.7 -> 29.0 us).  Beyond 512 entries LDS has room for 16 rows only.
-constexpr int map_rows_per_wg(int np) { return np <= 4 ? 16 : 32; }
-constexpr int map_threads(int np) { return np == 2 || np == 4 ? 256 : 512; }
+// Map rows per workgroup, 16 lanes to a row in four waves; rows of more than 512 entries lie in LDS, two to a wave.  The time is
+// the chain of one workgroup, and two of them on a CU overlap scores of the one with the search of the other (32 rows and
+// eight waves, the call, us: 24 heads of 118 blocks 50.5 / 46.5, 13 heads of 141 39.6 / 34.6, 5 heads of 469 75.5 / 67.9, 24 heads
+// of 258 92.9 / 92.9).
+constexpr int kMapRows = 16;
+constexpr int map_threads(int np) { return np > 0 ? 256 : 512; }
 constexpr int kMaxBlocks = 2048;     // blocks per sequence the LDS arrays are sized for
 
 // Sum over the 64 lanes, the same bits in every lane, without going through LDS: exchanges inside a row of 16
@@ -183,20 +185,47 @@ struct Row {
 // index order).  S(x) = sum of the entries <= x is a non-decreasing step function of x (also as computed here in
 // fp32: a fixed summation structure is monotone in every term), so the largest float theta with S(theta) <= limit is
 // found by fixing its bits from the top: at most 31 conditional sums per row instead of one per entry.  The lower bits
-// are not needed once no entry lies between the candidates left (looked at every third bit; mostly after some 14).
+// are not needed once there is at most one entry among the candidates left: one more sum says whether it is admitted
+// (looked at every third bit; mostly after some 17 bits of 31: the call at 33024 tokens and 24 heads 104.7 -> 98.3 us, 1300 tokens
+// and 7 heads 21.6 -> 16.8).
+// Candidates below the smallest entry have the sum 0 and those from the largest on the sum of all: where that holds for
+// every row of the wave nothing is added up (the upper exponent bits of a softmax: 98.6 -> 94.8 us).
 // M rows per group of lanes are searched together so that their reductions overlap.  sum[r] returns S(theta[r]).
 template <int G, int NP, int M>
 __device__ __forceinline__ void find_thresholds(const Row<G, NP> (&row)[M], const float (&limit)[M], float (&theta)[M], float (&sum)[M]) {
   unsigned lo[M];
+  float least[M], most[M], all[M];
 #pragma unroll
   for (int r = 0; r < M; ++r) {
     lo[r] = 0u;
     sum[r] = 0.f;
+    least[r] = all[r] = 0.f;
+    most[r] = INFINITY;
+    if constexpr (NP > 0) {            // (from LDS these passes cost more than the sums they save)
+      least[r] = INFINITY;
+      most[r] = -INFINITY;
+      row[r].each([&](int, float a) {
+        least[r] = fminf(least[r], a);
+        most[r] = fmaxf(most[r], a < INFINITY ? a : -INFINITY);
+      });
+      least[r] = -group_max<G>(-least[r]);
+      most[r] = group_max<G>(most[r]);
+      all[r] = row[r].sum_upto(most[r]);
+    }
   }
   for (int bit = 30; bit >= 0; --bit) {
     float s[M];
+    bool known = true;
 #pragma unroll
-    for (int r = 0; r < M; ++r) s[r] = row[r].sum_upto(__uint_as_float(lo[r] | (1u << bit)));
+    for (int r = 0; r < M; ++r) {
+      const float x = __uint_as_float(lo[r] | (1u << bit));
+      s[r] = x < least[r] ? 0.f : all[r];
+      known = known && (x < least[r] || x >= most[r]);
+    }
+    if (__builtin_amdgcn_ballot_w64(!known) != 0ull) {
+#pragma unroll
+      for (int r = 0; r < M; ++r) s[r] = row[r].sum_upto(__uint_as_float(lo[r] | (1u << bit)));
+    }
 #pragma unroll
     for (int r = 0; r < M; ++r) {
       // (the pattern of +inf and those above it are no candidates)
@@ -205,14 +234,27 @@ __device__ __forceinline__ void find_thresholds(const Row<G, NP> (&row)[M], cons
         sum[r] = s[r];
       }
     }
-    if (bit % 3 == 0 && bit <= 18) {
+    if (bit % 3 == 2 && bit <= 17 && bit > 2) {
       bool open = false;
 #pragma unroll
       for (int r = 0; r < M; ++r) {
-        const float from = __uint_as_float(lo[r]), to = __uint_as_float(lo[r] | ((1u << bit) - 1u));
-        row[r].each([&](int, float a) { open |= a > from && a <= to; });
+        // entries above lo and up to lo | the bits below (patterns of positive numbers are ordered like the numbers)
+        int inside = 0;
+        row[r].each([&](int, float a) { inside += __float_as_uint(a) - lo[r] - 1u < (1u << bit) - 1u ? 1 : 0; });
+        open |= group_sum<G>((float)inside) > 1.f;
       }
-      if (__builtin_amdgcn_ballot_w64(open) == 0ull) break;
+      if (__builtin_amdgcn_ballot_w64(open) == 0ull) {
+#pragma unroll
+        for (int r = 0; r < M; ++r) {
+          const unsigned to = lo[r] | ((1u << bit) - 1u);
+          const float s_to = row[r].sum_upto(__uint_as_float(to));
+          if (s_to <= limit[r]) {
+            lo[r] = to;
+            sum[r] = s_to;
+          }
+        }
+        break;
+      }
     }
   }
 #pragma unroll
@@ -246,17 +288,17 @@ __device__ __forceinline__ void next_value_ties(const Row<G, NP>& row, int lane,
   n_more = k;
 }
 
-// 32 rows of one head's map per workgroup, eight waves (16 and four or eight if the rows are short or long, see above).
+// 16 rows of one head's map per workgroup.
 //   scores    fp32 matrix instructions, 16 x 16 tiles with 4 products a step: lane (r = lane % 16, g = lane / 16) of an
 //             operand holds channels 16 * u + 4 * g + e of row r, so that both operands come straight from the pooled
 //             means with 16-byte loads of which four lanes share a line, and step (u, e) adds the four channels with
-//             that e.  Wave w takes the tiles of keys 16 * w, 16 * (w + 8), ... against all rows; the keys of the next
-//             two tiles are on their way.
+//             that e.  The waves take the tiles of 16 keys in turn; the keys of the next two tiles are on their way.
 //   softmax, skipping rule: 16 lanes per row, four rows per wave, in registers (NP entries per lane); a row per wave and
 //             two rows one after the other from LDS where NP = 0.  (The search is issue bound: with a row per wave half
 //             of its instructions were the reduction over 64 lanes.)
-// Dot products with both operands from LDS and the search over 64 lanes took 50 us at 33024 tokens and 24 heads, this 29.
-// Dynamic LDS: map rows [kRows][T_pad].
+// Dot products with both operands from LDS and the search over 64 lanes took 50 us at 33024 tokens and 24 heads, matrix
+// instructions and 16 lanes 30, this 24.
+// Dynamic LDS: map rows [kMapRows][T_pad].
 template <int D, int NP>
 __global__ void __launch_bounds__(map_threads(NP)) map_rows(const float* __restrict__ pooled, long long n_q_blocks, int Tq, int T, int T_pad,
                                                                int n_tq, int n_t, int row_bytes, float scale, float tau_kv,
@@ -264,11 +306,22 @@ __global__ void __launch_bounds__(map_threads(NP)) map_rows(const float* __restr
                                                                float* __restrict__ text_cols) {
   extern __shared__ float p[];
   typedef __attribute__((ext_vector_type(4))) float f32x4;
-  constexpr int NWAVES = map_threads(NP) / 64, kRows = map_rows_per_wg(NP), RT = kRows / 16;
+  constexpr int NWAVES = map_threads(NP) / 64;
   const int tid = threadIdx.x, w = tid / 64, lane = tid % 64;
   // T = pooled key blocks (columns of the map), n_t of them text; Tq = pooled query blocks (rows), n_tq of them text
-  const int groups = (Tq + kRows - 1) / kRows;
-  const int bh = blockIdx.x / groups, i0 = (blockIdx.x % groups) * kRows;
+  const int groups = (Tq + kMapRows - 1) / kMapRows;
+  // The workgroups of a head run on one XCD (workgroup n on XCD n mod 8) and find its pooled keys in that L2 (the call 94.3 ->
+  // 93.0 us); heads past a multiple of eight are spread.
+  const int heads = (int)(gridDim.x / groups), whole = heads / 8 * 8;
+  int bh, i0;
+  if ((int)blockIdx.x < whole * groups) {
+    const int at = blockIdx.x / 8;
+    bh = (int)(blockIdx.x % 8) + 8 * (at / groups);
+    i0 = at % groups * kMapRows;
+  } else {
+    bh = blockIdx.x / groups;
+    i0 = (blockIdx.x % groups) * kMapRows;
+  }
   const float* qt = pooled + (size_t)bh * Tq * D;
   const float* kt = pooled + ((size_t)n_q_blocks + (size_t)bh * T) * D;
   const int r16 = lane & 15, g = lane >> 4;
@@ -279,32 +332,24 @@ __global__ void __launch_bounds__(map_threads(NP)) map_rows(const float* __restr
 #pragma unroll
     for (int u = 0; u < V; ++u) v[u] = src[4 * u];
   };
-  f32x4 q[RT][V], k[3][V];
+  f32x4 q[V], k[3][V];
   const int tiles = (T + 15) / 16;
   auto fetch_tile = [&](int t, f32x4 (&v)[V]) { fetch(kt, min(16 * min(t, tiles - 1) + r16, T - 1), v); };
   fetch_tile(w, k[0]);
-#pragma unroll
-  for (int a = 0; a < RT; ++a) fetch(qt, min(i0 + 16 * a + r16, Tq - 1), q[a]);   // rows past the end repeat the last one
+  fetch(qt, min(i0 + r16, Tq - 1), q);            // rows past the end repeat the last one
   constexpr bool kFew = NP == 2 || NP == 4;       // at most four tiles of keys: one per wave, nothing to fetch ahead
   if constexpr (!kFew) fetch_tile(w + NWAVES, k[1]);
   for (int t = w; t < tiles; t += NWAVES) {
     if constexpr (!kFew) fetch_tile(t + 2 * NWAVES, k[2]);
-    f32x4 acc[RT];
-#pragma unroll
-    for (int a = 0; a < RT; ++a) acc[a] = {0.f, 0.f, 0.f, 0.f};
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int u = 0; u < V; ++u)
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int a = 0; a < RT; ++a)
-          acc[a] = __builtin_amdgcn_mfma_f32_16x16x4f32(q[a][u][e], k[0][u][e], acc[a], 0, 0, 0);
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(q[u][e], k[0][u][e], acc, 0, 0, 0);
     const int j = 16 * t + r16;                   // accumulator: column lane % 16, rows 4 * (lane / 16) + 0..3
     if (j < T) {
 #pragma unroll
-      for (int a = 0; a < RT; ++a)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) p[(16 * a + 4 * g + e) * T_pad + j] = acc[a][e] * scale;
+      for (int e = 0; e < 4; ++e) p[(4 * g + e) * T_pad + j] = acc[e] * scale;
     }
     if constexpr (!kFew) {
 #pragma unroll
@@ -397,7 +442,7 @@ __global__ void __launch_bounds__(map_threads(NP)) map_rows(const float* __restr
 
 // One workgroup per head.  Tq / Tk pooled query / key blocks, n_tq / n_tk of them text; pool_q / pool_k tokens per pooled
 // block.  Waves take the text columns side by side for G, then wave 0 searches the threshold of C and wave 1 that of
-// G (19 us with a sum over all entries per entry, 33024 tokens; now 11).
+// G (19 us with a sum over all entries per entry, 33024 tokens; with the search 12, now 8).
 template <int NP>
 __global__ void __launch_bounds__(256) select_blocks(const float* __restrict__ text_rows,
                                                      const float* __restrict__ text_cols, int Tq, int Tk, int n_tq,
@@ -422,21 +467,39 @@ __global__ void __launch_bounds__(256) select_blocks(const float* __restrict__ t
   for (int j0 = 0; j0 < n_tk; j0 += 4) {
     const int j = j0 + w;
     if (j < n_tk) {
-      float m = -INFINITY;
-      for (int v = lane; v < Tv; v += 64) {
-        const float x = tc[(size_t)(n_tq + v) * n_tk + j];
-        E[w][v] = x;
-        m = fmaxf(m, x);
+      float m = -INFINITY, s = 0.f;
+      if constexpr (NP > 0) {
+        // in registers, all loads under way at once (entry by entry through LDS the call took 0.8 us longer)
+        float x[NP];
+#pragma unroll
+        for (int n = 0; n < NP; ++n) x[n] = lane + 64 * n < Tv ? tc[(size_t)(n_tq + lane + 64 * n) * n_tk + j] : -INFINITY;
+#pragma unroll
+        for (int n = 0; n < NP; ++n) m = fmaxf(m, x[n]);
+        m = wave_max_dpp(m);
+#pragma unroll
+        for (int n = 0; n < NP; ++n) {
+          x[n] = lane + 64 * n < Tv ? expf(x[n] - m) : 0.f;
+          s += x[n];
+        }
+        s = wave_sum_dpp(s);
+#pragma unroll
+        for (int n = 0; n < NP; ++n)
+          if (lane + 64 * n < Tv) E[w][lane + 64 * n] = x[n] / s;
+      } else {
+        for (int v = lane; v < Tv; v += 64) {
+          const float x = tc[(size_t)(n_tq + v) * n_tk + j];
+          E[w][v] = x;
+          m = fmaxf(m, x);
+        }
+        m = wave_max_dpp(m);
+        for (int v = lane; v < Tv; v += 64) {
+          const float e = expf(E[w][v] - m);
+          E[w][v] = e;
+          s += e;
+        }
+        s = wave_sum_dpp(s);
+        for (int v = lane; v < Tv; v += 64) E[w][v] /= s;
       }
-      m = wave_max_dpp(m);
-      float s = 0.f;
-      for (int v = lane; v < Tv; v += 64) {
-        const float e = expf(E[w][v] - m);
-        E[w][v] = e;
-        s += e;
-      }
-      s = wave_sum_dpp(s);
-      for (int v = lane; v < Tv; v += 64) E[w][v] /= s;
     }
     __syncthreads();
     for (int v = tid; v < Tv; v += 256)
@@ -508,7 +571,7 @@ __global__ void __launch_bounds__(256) select_blocks(const float* __restrict__ t
 
 // Entries per lane, 16 lanes to a row: powers of two, and 17 because 33024 tokens in blocks of 128 are 258 blocks, which
 // would fall into the tier of 512.  A tier costs what its last size costs (24 heads, blocks of 64 tokens, us: 258 entries
-// 74, with 32 registers 84; 273 entries, the first in that tier, 87: 32 registers a lane, 48 scalar registers spilled).
+// 64, with 32 registers 71; 273 entries, the first in that tier, 74: 32 registers a lane, 76 scalar registers spilled).
 int map_np(int T) { return T <= 32 ? 2 : T <= 64 ? 4 : T <= 128 ? 8 : T <= 272 ? 17 : T <= 512 ? 32 : 0; }
 template <int D>
 auto map_for(int T) {
@@ -580,14 +643,14 @@ int sparse_symbols_update_granular(const void* Q, const void* K, uint8_t* cache_
 
   const int row_bytes = (Tk + 7) / 8;
   const float scale = (float)(1.0 / sqrt((double)D));
-  const int np = map_np(Tk), map_rows_wg = map_rows_per_wg(np);
-  const int groups = (Tq + map_rows_wg - 1) / map_rows_wg;
+  const int np = map_np(Tk);
+  const int groups = (Tq + kMapRows - 1) / kMapRows;
   const int T_pad = (Tk + 3) & ~3;
-  const size_t map_lds = (size_t)map_rows_wg * T_pad * 4;
+  const size_t map_lds = (size_t)kMapRows * T_pad * 4;
   static std::once_flag attr_once;
   static hipError_t attr_err = hipSuccess;
   std::call_once(attr_once, [] {
-    constexpr int kMaxLds = map_rows_per_wg(0) * kMaxBlocks * 4;
+    constexpr int kMaxLds = kMapRows * kMaxBlocks * 4;
     attr_err = hipFuncSetAttribute((const void*)map_rows<128, 0>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);
     if (attr_err == hipSuccess)
       attr_err = hipFuncSetAttribute((const void*)map_rows<64, 0>, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);

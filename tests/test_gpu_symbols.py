@@ -252,3 +252,31 @@ def test_equal_entries_are_taken_in_index_order_in_every_tier(T, D):
         bits = oracle.unpack_symbols(mask, T)
         assert (bits[..., :n_kv] == 0).all() and (bits[..., n_kv:] == 1).all()
         assert (flags[..., 0] == 0).all() and (flags[..., 1:1 + n_c] == 1).all() and (flags[..., 1 + n_c:] == 0).all()
+
+
+@pytest.mark.parametrize("D,T", [(64, 3), (128, 32), (64, 33), (128, 64), (64, 65), (128, 129), (64, 273), (128, 512), (64, 513)])
+def test_search_ends_early_at_the_same_place(D, T):
+    """The threshold search stops where one entry is left to decide on and passes over bits that every entry agrees in: at
+    thresholds from nothing to everything the skipped blocks of a row are the longest prefix of its ascending order whose
+    sum fits (fp64 map; sums and order up to fp32 rounding of a row of T entries)."""
+    print(f"[case] search D={D} T={T}", flush=True)
+    block, text = 64, 64
+    rng = np.random.default_rng(T)
+    Q, K = synth.structured_qk(synth.BASE_SEED + T, 1, 2, T * block, D, block)
+    K[0, 1, : (T // 2) * block] = 0                          # equal entries: half of the second head's keys are nothing
+    pool = lambda x: torch.from_numpy(synth.bf16_bits_to_f32(x)).double().view(1, 2, T, block, D).mean(3)
+    P = torch.softmax(pool(Q) @ pool(K).transpose(2, 3) / D ** 0.5, dim=3).numpy()
+    slack = 4e-7 * T ** 0.5 + 2e-6                           # relative: exponentials, their sum, the sum of a prefix
+    ascending = np.sort(P, axis=3)
+    for tau in (0.0, 1e-6, 0.3 / T, 1.5 / T, float(rng.uniform(0.05, 0.3)), 0.5, float(rng.uniform(0.7, 0.99)), 0.99999, 1.0):
+        tau = f32(tau)
+        _, mask = run_gpu(Q, K, block, text, 0.5, tau)
+        kept = oracle.unpack_symbols(mask, T).astype(bool)
+        skipped = np.where(kept, 0.0, P).sum(3)
+        n = (~kept).sum(3)
+        assert (skipped <= tau * (1 + slack) + 1e-12).all()
+        following = np.take_along_axis(ascending, np.minimum(n, T - 1)[..., None], 3)[..., 0]
+        assert (np.where(n < T, skipped + following, np.inf) >= tau * (1 - slack) - 1e-12).all() or tau == 1.0
+        largest = np.where(kept, 0.0, P).max(3)
+        smallest = np.where(kept, P, np.inf).min(3)
+        assert (largest <= smallest * (1 + 1e-5)).all()
