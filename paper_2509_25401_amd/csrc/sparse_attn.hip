@@ -487,16 +487,24 @@ __device__ __forceinline__ u32x4 sa_buffer(const char* base, unsigned bytes) {
 // wave's 1 KiB lands at lds_addr + LDS0 + DT; lanes past the end of the buffer write zeros.  The distance of the
 // loads of a tile is the same in memory and in LDS, so what fits the instruction's offset field (it moves both addresses)
 // goes there, and M0 is formed from one register: no address sits in a register of its own.  In assembly for the reason
-// given at sa_load_to_lds_16B.
+// given at sa_load_to_lds_16B; the wait state behind the write of M0 is the addition that forms the scalar offset, where there is one.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 template <int LDS0, int DT>
 __device__ __forceinline__ void sa_tile_to_lds(const u32x4& buffer, unsigned lane_off, unsigned tile_off, unsigned lds_addr) {
   constexpr int HI = DT / 4096 * 4096, LO = DT % 4096;
-  asm volatile("s_add_u32 m0, %0, %4\n\tbuffer_load_dwordx4 %1, %2, %3 offen offset:%5 lds"
-               :
-               : "s"(lds_addr), "v"(lane_off), "s"(buffer), "s"(tile_off + HI), "i"(LDS0 + HI), "i"(LO)
-               : "memory", "m0", "scc");
+  if constexpr (HI == 0) {
+    asm volatile("s_add_u32 m0, %0, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen offset:%5 lds"
+                 :
+                 : "s"(lds_addr), "v"(lane_off), "s"(buffer), "s"(tile_off), "i"(LDS0), "i"(LO)
+                 : "memory", "m0", "scc");
+  } else {
+    unsigned off;
+    asm volatile("s_add_u32 m0, %1, %5\n\ts_add_u32 %0, %4, %7\n\tbuffer_load_dwordx4 %2, %3, %0 offen offset:%6 lds"
+                 : "=&s"(off)
+                 : "s"(lds_addr), "v"(lane_off), "s"(buffer), "s"(tile_off), "i"(LDS0 + HI), "i"(LO), "i"(HI)
+                 : "memory", "m0", "scc");
+  }
 }
 #pragma clang diagnostic pop
 

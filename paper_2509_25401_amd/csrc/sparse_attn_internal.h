@@ -18,11 +18,12 @@ int sa_get_scratch(size_t need, hipStream_t stream, void** out);
 // 1 KiB lands at consecutive LDS addresses starting at the wave-uniform `lds_addr`.  Written as
 // inline assembly so that the compiler does not serialise later LDS reads of the OTHER buffer
 // behind these loads (it cannot tell the two buffers apart); the kernels wait for them themselves
-// (s_waitcnt vmcnt(0) + barrier) before the buffer is read.
+// (s_waitcnt vmcnt(0) + barrier) before the buffer is read.  A scalar write of M0 and the load that takes its LDS address from
+// it need one wait state between them, which the compiler keeps for its own instructions but not inside a statement.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void sa_load_to_lds_16B(const char* gbase, unsigned lane_off, unsigned lds_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                :
                : "s"(lds_addr), "v"(lane_off), "s"(gbase)
                : "memory", "m0");
