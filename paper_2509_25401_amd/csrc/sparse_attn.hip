@@ -426,30 +426,34 @@ __global__ void __launch_bounds__(kOrderThreads) plan_queues(const uint8_t* __re
   }
 }
 
-// One atomic increment per wave, issued by lane 0 only and left in flight: returns a register whose lane 0
-// will hold the counter's previous value.  Written as assembly around an exec-mask switch, not as
-// `if (lane == 0) atomicAdd(...)`: a value that stays live across loop iterations inside a lane-dependent
-// branch makes the compiler treat the whole scheduling state of the kernel as lane-dependent.
+// One atomic increment per wave, by lane 0 only; returns the counter's previous value, wave-uniform.  Written as assembly
+// around an exec-mask switch, not as `if (lane == 0) atomicAdd(...)`: a value that stays live across loop iterations
+// inside a lane-dependent branch makes the compiler treat the whole scheduling state of the kernel as lane-dependent.
+// The wait is part of the statement: the compiler takes an output for written when the statement ends and may copy or
+// spill its register, which an increment still in flight would make a copy of something else.  It costs nothing, since every
+// place that draws a ticket waits for all of the wave's requests right behind it.
 __device__ __forceinline__ unsigned sa_lane0_atomic_inc(uint32_t* counter) {
-  unsigned old;
+  unsigned old, value;
   unsigned long long saved;
   asm volatile(
-      "s_mov_b64 %1, exec\n\ts_mov_b64 exec, 1\n\tglobal_atomic_add %0, %2, %3, %4 sc0\n\ts_mov_b64 exec, %1"
-      : "=&v"(old), "=&s"(saved)
+      "s_mov_b64 %1, exec\n\ts_mov_b64 exec, 1\n\tglobal_atomic_add %0, %3, %4, %5 sc0\n\ts_mov_b64 exec, %1\n\t"
+      "s_waitcnt vmcnt(0)\n\tv_readfirstlane_b32 %2, %0"
+      : "=&v"(old), "=&s"(saved), "=&s"(value)
       : "v"(0u), "v"(1u), "s"(counter)
       : "memory");
-  return old;
+  return value;
 }
 // The same for a counter that goes from `last` back to 0.
 __device__ __forceinline__ unsigned sa_lane0_atomic_inc_wrap(uint32_t* counter, unsigned last) {
-  unsigned old;
+  unsigned old, value;
   unsigned long long saved;
   asm volatile(
-      "s_mov_b64 %1, exec\n\ts_mov_b64 exec, 1\n\tglobal_atomic_inc %0, %2, %3, %4 sc0\n\ts_mov_b64 exec, %1"
-      : "=&v"(old), "=&s"(saved)
+      "s_mov_b64 %1, exec\n\ts_mov_b64 exec, 1\n\tglobal_atomic_inc %0, %3, %4, %5 sc0\n\ts_mov_b64 exec, %1\n\t"
+      "s_waitcnt vmcnt(0)\n\tv_readfirstlane_b32 %2, %0"
+      : "=&v"(old), "=&s"(saved), "=&s"(value)
       : "v"(0u), "v"(last), "s"(counter)
       : "memory");
-  return old;
+  return value;
 }
 // The lane number, formed where it is needed: offsets that follow from it are then not computed once, in front of the item
 // loop, to occupy registers for the whole kernel (the headline instance: 240 vector registers -> 224).
@@ -457,12 +461,6 @@ __device__ __forceinline__ int sa_fresh_lane() {
   int ln;
   asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
   return ln;
-}
-// Waits for this wave's outstanding memory operations and returns lane 0 of `v` as a wave-uniform value.
-__device__ __forceinline__ unsigned sa_lane0_value(unsigned v) {
-  unsigned r;
-  asm volatile("s_waitcnt vmcnt(0)\n\tv_readfirstlane_b32 %0, %1" : "=s"(r) : "v"(v) : "memory");
-  return r;
 }
 // A work-list entry (two words) read with one scalar load instead of a vector load and a lane broadcast.  Load and
 // wait are one statement on purpose: the compiler does not know that the result arrives late and may copy the
@@ -595,9 +593,9 @@ __global__ void __launch_bounds__(BQ * 2, attn_waves_per_simd(D, MODE)) attn_ker
   // Queues: the queue of XCD q holds its rows at list positions queue_begin(q) .. queue_begin(q + 1) - 1.  The first
   // nwg(q) of them are the first items of the workgroups n = q, q + 8, ...; the ticket of every further item is one
   // atomic on the home queue -- the one of the XCD the workgroup runs on (hardware register XCC_ID) --, issued by wave
-  // 0 and left in flight; it is drawn a few kept blocks before the current item ends (earlier would let an idle
-  // workgroup find the queue empty while this one still sits on an item it has not started), so at the end of the
-  // item it has long arrived.  When the home queue is drained the workgroup looks at all queue heads at once and
+  // 0 a few kept blocks before the current item ends (earlier would let an idle workgroup find the queue empty while
+  // this one still sits on an item it has not started), where it waits for its requests anyway, so that at the end of
+  // the item the ticket is there.  When the home queue is drained the workgroup looks at all queue heads at once and
   // steals from the next one that has rows left (heads only grow: one that is seen drained stays so).
   // The item number reaches the other waves through one of two LDS slots, used in turn: a wave reads slot s of item i
   // before it arrives at the barrier of item i + 1, and the slot is not written again before that barrier has been
@@ -701,7 +699,7 @@ __global__ void __launch_bounds__(BQ * 2, attn_waves_per_simd(D, MODE)) attn_ker
   }
   constexpr int kDrawTiles = 6;        // kept blocks an item still has to visit when the next ticket is drawn
   bool drawn = false, first_item = true;
-  unsigned ticket = 0;                 // wave 0: lane 0 holds the ticket of the home queue, possibly still in flight
+  unsigned ticket = 0;                 // wave 0: the ticket of the home queue, where `drawn`
   auto draw_issue = [&]() {
     if constexpr (MODE == kQueues) {
       if (wave == 0) ticket = sa_lane0_atomic_inc(q_head + my_q * kHeadStride);   // a drained queue just keeps counting
@@ -735,7 +733,7 @@ __global__ void __launch_bounds__(BQ * 2, attn_waves_per_simd(D, MODE)) attn_ker
       if (!drawn) draw_issue();
       if (wave == 0) {
         // resolve the ticket, or steal (a head counts at most the items and one overshoot per workgroup)
-        int item = queue_begin(my_q) + nwg(my_q) + (int)sa_lane0_value(ticket);
+        int item = queue_begin(my_q) + nwg(my_q) + (int)ticket;
         if (item >= queue_begin(my_q + 1)) item = -1;
         const int ln = sa_fresh_lane();
         unsigned drained = 0;          // queues an increment of this workgroup found empty: at most eight rounds fail
@@ -746,7 +744,7 @@ __global__ void __launch_bounds__(BQ * 2, attn_waves_per_simd(D, MODE)) attn_ker
           const unsigned long long open = __builtin_amdgcn_ballot_w64(ln < kXcds && taken < room && !((drained >> q) & 1u));
           if (open == 0ull) break;
           const int qs = (my_q + __builtin_ctzll(open)) % kXcds;
-          const int got = queue_begin(qs) + nwg(qs) + (int)sa_lane0_value(sa_lane0_atomic_inc(q_head + qs * kHeadStride));
+          const int got = queue_begin(qs) + nwg(qs) + (int)sa_lane0_atomic_inc(q_head + qs * kHeadStride);
           if (got < queue_begin(qs + 1)) item = got;
           drained |= 1u << qs;
         }
@@ -1213,7 +1211,7 @@ __global__ void __launch_bounds__(BQ * 2, attn_waves_per_simd(D, MODE)) attn_ker
     // (their outputs are wrong then), and behind the last workgroup of both it and the heads are zero again.
     if (p.self_reset && wave == 0) {
       const unsigned last = gridDim.x - 1;
-      if (sa_lane0_value(sa_lane0_atomic_inc_wrap(q_head + kDoneOffset, last)) == last && lane < kXcds)
+      if (sa_lane0_atomic_inc_wrap(q_head + kDoneOffset, last) == last && lane < kXcds)
         __hip_atomic_store(q_head + lane * kHeadStride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }

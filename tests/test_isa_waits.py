@@ -95,6 +95,18 @@ def violations(code):
     return bad
 
 
+def unawaited(code):
+    """Atomics with a result that are not waited for before anything else than the exec mask is touched: all of them are
+    issued in assembly statements, whose outputs the compiler takes for written at the end of the statement."""
+    bad = []
+    for i, (address, op, operands, _) in enumerate(code):
+        if op.startswith("global_atomic") and operands.endswith(" sc0"):
+            rest = [ins for ins in code[i + 1:i + 4] if not (ins[1] == "s_mov_b64" and ins[2].startswith("exec"))]
+            if not rest or rest[0][1] != "s_waitcnt" or "vmcnt(0)" not in rest[0][2]:
+                bad.append((address, op, operands))
+    return bad
+
+
 @pytest.fixture(scope="module")
 def kernels(tmp_path_factory):
     where = tmp_path_factory.mktemp("isa")
@@ -138,3 +150,10 @@ def test_wait_states_in_front_of_memory_instructions(kernels):
     count = sum(len(v) for v in bad.values())
     first = next((f"{name}: {v[0][1]} {v[0][2]}" for name, v in bad.items() if v), "")
     assert count == 0, f"{count} of them come too early, for instance {first}"
+
+
+def test_tickets_are_waited_for_where_they_are_drawn(kernels):
+    attention = {name: code for name, code in kernels.items() if "attn_kernel" in name}
+    assert sum(op.startswith("global_atomic") for code in attention.values() for _, op, _, _ in code) > 0
+    bad = {name: unawaited(code) for name, code in attention.items()}
+    assert not any(bad.values()), f"{sum(map(len, bad.values()))} of them, for instance {next(v[0] for v in bad.values() if v)}"
