@@ -471,7 +471,9 @@ __device__ __forceinline__ unsigned long long sa_scalar_load_b64(const uint32_t*
   return v;
 }
 
-// Buffer descriptor of `bytes` bytes at `base` (both wave-uniform): reads past the end give zeros.
+// Buffer descriptor of `bytes` bytes at `base` (both wave-uniform): reads past the end give zeros.  A lane reads past it if its
+// offset, lane register and instruction field, is not below `bytes` less the scalar offset; a scalar offset past the end would
+// leave that difference to how it wraps.
 __device__ __forceinline__ u32x4 sa_buffer(const char* base, unsigned bytes) {
   const unsigned long long a = (unsigned long long)base;
   u32x4 r;
@@ -485,16 +487,24 @@ __device__ __forceinline__ u32x4 sa_buffer(const char* base, unsigned bytes) {
 // wave's 1 KiB lands at lds_addr + LDS0 + DT; lanes past the end of the buffer write zeros.  The distance of the
 // loads of a tile is the same in memory and in LDS, so what fits the instruction's offset field (it moves both addresses)
 // goes there, and M0 is formed from one register: no address sits in a register of its own.  In assembly for the reason
-// given at sa_load_to_lds_16B; the wait state behind the write of M0 is the addition that forms the scalar offset, where there is one.
+// given at sa_load_to_lds_16B; the wait state behind the write of M0 is the addition that forms an offset, where there is one.
+// CHECKED: the tile may reach past the end of the buffer.  It starts inside, so with all of the distance in the lane's offset the
+// scalar offset stays inside too.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
-template <int LDS0, int DT>
+template <int LDS0, int DT, bool CHECKED>
 __device__ __forceinline__ void sa_tile_to_lds(const u32x4& buffer, unsigned lane_off, unsigned tile_off, unsigned lds_addr) {
   constexpr int HI = DT / 4096 * 4096, LO = DT % 4096;
   if constexpr (HI == 0) {
     asm volatile("s_add_u32 m0, %0, %4\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen offset:%5 lds"
                  :
                  : "s"(lds_addr), "v"(lane_off), "s"(buffer), "s"(tile_off), "i"(LDS0), "i"(LO)
+                 : "memory", "m0", "scc");
+  } else if constexpr (CHECKED) {
+    unsigned off;
+    asm volatile("s_add_u32 m0, %1, %5\n\tv_add_u32 %0, %7, %2\n\tbuffer_load_dwordx4 %0, %3, %4 offen offset:%6 lds"
+                 : "=&v"(off)
+                 : "s"(lds_addr), "v"(lane_off), "s"(buffer), "s"(tile_off), "i"(LDS0 + HI), "i"(LO), "i"(HI)
                  : "memory", "m0", "scc");
   } else {
     unsigned off;
@@ -905,8 +915,8 @@ __global__ void __launch_bounds__(BQ * 2, attn_waves_per_simd(D, MODE)) attn_ker
     // load t of this wave's NLOAD for the sub-tile at byte tile_off of the head
     auto issue_load = [&](unsigned tile_off, auto buf_c, auto t_c) {
       constexpr int buf = decltype(buf_c)::value, t = decltype(t_c)::value;
-      sa_tile_to_lds<buf * TILEB, t * NWAVES * 1024>(Kh, k_goff[t % TP], tile_off, lds_wave);
-      sa_tile_to_lds<(2 + buf) * TILEB, t * NWAVES * 1024>(Vh, v_goff[t % TP], tile_off, lds_wave);
+      sa_tile_to_lds<buf * TILEB, t * NWAVES * 1024, RAGGED>(Kh, k_goff[t % TP], tile_off, lds_wave);
+      sa_tile_to_lds<(2 + buf) * TILEB, t * NWAVES * 1024, RAGGED>(Vh, v_goff[t % TP], tile_off, lds_wave);
     };
     auto tile_offset = [&](int j, int sub) -> unsigned { return (unsigned)(j * BK + sub * KEYS) * ROWB; };
 

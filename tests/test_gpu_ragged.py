@@ -105,30 +105,44 @@ def test_plan_and_forecast_on_a_short_sequence():
     assert err.max() <= 1e-2 and err.mean() <= 1e-3
 
 
-@pytest.mark.parametrize("D,bq,bk,L", [
-    (128, 128, 128, 1025),     # the last key block holds one key; its second sub-tile does not exist
-    (128, 64, 64, 1087),       # the last key block lacks one key
-    (128, 64, 128, 8203),      # 32-key sub-tiles, more rows than the chip holds: work queues
-    (64, 128, 128, 1151),
-    (64, 64, 128, 1090),
+@pytest.mark.parametrize("D,bq,bk,H,L,keep", [
+    (128, 128, 128, 2, 1025, 0.3),     # the last key block holds one key; its second sub-tile does not exist
+    (128, 64, 64, 2, 1087, 0.3),       # the last key block lacks one key
+    (128, 64, 128, 8, 8203, 0.3),      # 1032 rows: the workgroups sort them; the plan has 32-key sub-tiles
+    (128, 128, 128, 4, 8203, 0.3),     # 260 rows of 128, 11 keys in the last block
+    (128, 128, 64, 2, 1089, 0.3),
+    (64, 128, 128, 2, 1151, 0.3),
+    (64, 128, 64, 2, 1093, 0.3),
+    (64, 64, 128, 2, 1090, 0.3),
+    (64, 64, 64, 2, 1153, 0.3),
+    (128, 128, 128, 8, 8203, None),    # no symbols: 264 blocks of 256 rows, dealt out
+    (128, 128, 128, 16, 8203, None),   # 528 of them: work queues
+    (64, 128, 128, 2, 1025, None),
 ])
-def test_short_key_block_does_not_reach_into_the_next_head(D, bq, bk, L):
-    """K and V of one head end where those of the next begin: NaN in the odd heads may not show in the even ones."""
-    print(f"[case] next head D={D} {bq}x{bk} L={L}", flush=True)
-    H = 8 if L > 4096 else 2
+def test_short_key_block_does_not_reach_into_the_next_head(D, bq, bk, H, L, keep):
+    """K and V of one head end where those of the next begin: NaN in the odd heads may not show in the even ones.  The
+    one-shot call and a stored plan (always work queues) are kernels of their own."""
+    print(f"[case] next head D={D} {bq}x{bk} H={H} L={L} keep={keep}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(synth.BASE_SEED + L)
     Q, K, V = (torch.randn(1, H, L, D, device="cuda", generator=g).bfloat16() for _ in range(3))
-    mask = torch.rand(1, H, -(-L // bq), -(-L // bk), device="cuda", generator=g) < 0.3
-    mask[..., -1] = True
-    packed = up_u8(pkg.sparse_attn_pack_mask(mask.cpu().numpy().astype(np.uint8)))
+    mask, packed = torch.ones(1, H, -(-L // bq), -(-L // bk), dtype=torch.bool, device="cuda"), None
+    if keep is not None:
+        mask = torch.rand(mask.shape, device="cuda", generator=g) < keep
+        mask[..., -1] = True
+        packed = up_u8(pkg.sparse_attn_pack_mask(mask.cpu().numpy().astype(np.uint8)))
     K[:, 1::2], V[:, 1::2] = float("nan"), float("nan")
-    O = torch.empty_like(Q)
-    pkg.sparse_attn_fwd(Q, K, V, None, packed, None, O, bq, bk)
-    keep = mask.repeat_interleave(bq, 2).repeat_interleave(bk, 3)[:, ::2, :L, :L]
+    plan = pkg.SparseAttnPlan(None, packed, 1, H, L, bq, bk)
+    results = torch.empty_like(Q), torch.empty_like(Q)
+    pkg.sparse_attn_fwd(Q, K, V, None, packed, None, results[0], bq, bk)
+    plan.run(Q, K, V, None, results[1])
     for h in range(0, H, 2):
+        kept = mask[0, h].repeat_interleave(bq, 0).repeat_interleave(bk, 1)[:L, :L]
         s = (Q[0, h].float() @ K[0, h].float().t()) / D ** 0.5
-        ref = torch.softmax(s.masked_fill(~keep[0, h // 2], -float("inf")), dim=1) @ V[0, h].float()
-        err = (O[0, h].float() - ref).abs()
-        assert torch.isfinite(O[0, h]).all()
-        assert err.max() <= 1e-2 and err.mean() <= 1e-3      # the bound of the oracle comparisons (rounded weights and result)
-    assert torch.isnan(O[0, 1::2].float()).all()
+        ref = torch.softmax(s.masked_fill(~kept, -float("inf")), dim=1) @ V[0, h].float()
+        for O in results:
+            err = (O[0, h].float() - ref).abs()
+            assert torch.isfinite(O[0, h]).all()
+            assert err.max() <= 1e-2 and err.mean() <= 1e-3      # the bound of the oracle comparisons (rounded weights and result)
+    for O in results:
+        assert torch.isnan(O[0, 1::2].float()).all()
+    plan.destroy()
