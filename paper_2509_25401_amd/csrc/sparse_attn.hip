@@ -93,8 +93,9 @@ constexpr int kSortLds = kSortRows * 4 * 2 + kSortRows * kSortWords * 4 + 16;   
 
 // Wavefronts per SIMD that the registers are laid out for.  64 channels leave room for three (168 registers, no spill), which
 // 128-row blocks use (three workgroups of 32 KiB LDS per CU; 24 heads, us, two / three: 9001 tokens dense 577 / 552, 33024
-// tokens at 25 % keep 1745 / 1681); of the 64-row workgroups LDS holds four, two wavefronts per SIMD, either way.
-constexpr int attn_waves_per_simd(int D, int mode) { return D == 64 && mode == kQueues ? 3 : 2; }
+// tokens at 25 % keep 1745 / 1681; in sorted calls see `W`); of the 64-row workgroups LDS holds four, two wavefronts per SIMD,
+// either way.  Dealt instances take up to 170 registers and would spill.
+constexpr int attn_waves_per_simd(int D, int mode) { return D == 64 && mode != kDealt ? 3 : 2; }
 constexpr int kLongBuckets = 8;       // kept-count buckets of the long rows of a queue (longest first, across heads)
 constexpr int kFineBuckets = 55;      // ... of its other rows (head by head); with the bucket of cached rows: 64,
 constexpr int kCachedBucket = kLongBuckets + kFineBuckets;   // one lane each in the ranking pass
@@ -541,6 +542,7 @@ __device__ __forceinline__ int v_swizzle(int row) {
 template <int D, int BQ, int BK, int KEYS, bool RAGGED, int MODE>
 __global__ void __launch_bounds__(BQ * 2, attn_waves_per_simd(D, MODE)) attn_kernel(const AttnParams p) {
   constexpr bool DEALT = MODE == kDealt, SORTED = MODE == kSorted;
+  constexpr bool kThreePerCu = SORTED && BQ == 128 && attn_waves_per_simd(D, kSorted) == 3;
   constexpr int NWAVES = BQ / 32;
   constexpr int NT = NWAVES * 64;
   constexpr int SUB = BK / KEYS;           // LDS sub-tiles per symbol bit
@@ -625,14 +627,26 @@ __global__ void __launch_bounds__(BQ * 2, attn_waves_per_simd(D, MODE)) attn_ker
     const bool back = (slot / kCusPerXcd) % 2 == 0 && chunk + kCusPerXcd <= nwg(q0);
     return back ? 2 * chunk + kCusPerXcd - 1 - slot : slot;
   };
-  // SORTED
+  int W = 0;                           // SORTED: workgroups of this XCD that take rows
+  // SORTED.  After the first round the rows go to the workgroups from the end, the shortest row's first, except in a last round
+  // that does not reach all of them: there to those launched first, whose waves issue first and which are done first, while the
+  // others still run.  Of four two-wave workgroups on a CU each shares a SIMD with the one launched before it and one with the one
+  // launched after it (read from HW_ID), so the first and the third are taken before the second; where more than these have a
+  // second row the shortest ones' are better.  24 heads, keep and cached share, us, work list / from the end / this: 64 channels in
+  // 64 x 128 blocks, 3584 tokens, 90 % 109 / 116 / 102; 4096, 90 % 128 / 136 / 123, 50 % 87 / 82 / 75; 4608, 90 % and 30 % 131 / 140 / 119;
+  // 128 channels in 128-row blocks, 3500 tokens, 90 % 156 / 152 / 145; 4608, 30 % and 30 % 82 / 81 / 73.
+  auto early_of = [&](int slot) -> int {
+    if (W != 4 * kCusPerXcd) return slot;
+    const int c = slot / kCusPerXcd;
+    return (c == 1 ? 2 : c == 2 ? 1 : c) * kCusPerXcd + slot % kCusPerXcd;
+  };
   uint32_t* const sort_keys = (uint32_t*)(smem + 4 * TILEB + 16);
   uint32_t* const sort_list = sort_keys + kSortRows;
   uint32_t* const sort_words = sort_list + kSortRows;
   uint32_t* const sort_computed = sort_words + kSortRows * kSortWords;
   int list_at = -1, list_round = 0, copy_at = 0, copy_step = 1, copy_end = 0, rest_at = 0, n_computed = 0, n_list = 0;
   if constexpr (SORTED) {
-    const int q0 = (int)blockIdx.x % kXcds, slot = (int)blockIdx.x / kXcds, W = nwg(q0);
+    const int q0 = (int)blockIdx.x % kXcds, slot = (int)blockIdx.x / kXcds;
     const int row0 = q0 * (p.N / kXcds) + min(q0, p.N % kXcds), rows = p.N / kXcds + (q0 < p.N % kXcds ? 1 : 0);
     const int tid = (int)threadIdx.x;
     if (tid == 0) *sort_computed = 0u;
@@ -676,8 +690,17 @@ __global__ void __launch_bounds__(BQ * 2, attn_waves_per_simd(D, MODE)) attn_ker
     __syncthreads();
     n_list = rows;
     n_computed = __builtin_amdgcn_readfirstlane((int)*sort_computed);
+    // Three workgroups on a CU as long as none has a second row, else two, where the second round is fuller (64 channels,
+    // 128-row blocks, 24 heads, us, two / three: 4000 tokens, 90 % keep 115 / 102; 4608, 90 % and 40 % cached 116 / 98; 90 % and none
+    // cached 146 / 152; 6000, 70 % 183 / 192).
+    W = nwg(q0);
+    if constexpr (kThreePerCu) {
+      if (n_computed > W) W = min(W, 2 * kCusPerXcd);
+    }
     list_at = first_of(q0, slot);
-    if (p.n_terms > 0 || p.do_copy) {
+    if (slot >= W) {
+      list_at = rest_at = rows;
+    } else if (p.n_terms > 0 || p.do_copy) {
       // Cached rows: workgroups without a computed one take some each, as many as fit beside the longest computed row
       // (moving a row takes about as long as three blocks of it); the others are dealt to all.
       const int cached = rows - n_computed, idle = max(0, W - n_computed);
@@ -720,11 +743,13 @@ __global__ void __launch_bounds__(BQ * 2, attn_waves_per_simd(D, MODE)) attn_ker
     int n = next_n;
     if constexpr (SORTED) {
       // computed rows in turn from both ends of the workgroups, then cached ones
-      const int q0 = (int)blockIdx.x % kXcds, slot = (int)blockIdx.x / kXcds, W = nwg(q0);
+      const int slot = (int)blockIdx.x / kXcds;
       if (list_at < n_computed) {
         n = list_at;
         ++list_round;
-        list_at = list_round * W + (list_round % 2 ? W - 1 - slot : slot);
+        const int left = n_computed - list_round * W;
+        const bool from_end = left >= W ? list_round % 2 == 1 : W == 4 * kCusPerXcd && left > W / 2;
+        list_at = list_round * W + (from_end ? W - 1 - slot : early_of(slot));
       } else if (copy_at < copy_end) {
         n = n_computed + copy_at;
         copy_at += copy_step;
@@ -1564,7 +1589,7 @@ int run(const void* Q, const void* K, const void* V, const uint8_t* cache_flags,
   // all rows are equally long, so with up to two per workgroup dealing them out by number does as well.  Every
   // workgroup then decodes its own rows (at most 64 words each).  512 tokens, two heads of 64: 20.1 -> 12.3 us; 4608
   // tokens, 24 heads, dense: 273 -> 261 us.
-  // None either where the rows differ and there are between one per CU and two and a quarter per workgroup: the workgroups
+  // None either where the rows differ and there are between one per CU and two and a quarter per workgroup (two waves on a SIMD): the workgroups
   // sort them.  24 heads, us, queues or dealt / sorted: 4608 tokens, 30 % keep, 56 % cached 56.1 / 50.5; 64 channels, 64-row
   // blocks, 40 % cached 48.4 / 37.2; 6000 tokens (1128 rows on 512 workgroups), 20 % keep 106 / 99, 70 % 312 / 300; 1200
   // tokens in 64-row blocks (456 rows) 18.0 / 16.3; 16 heads of 777 tokens (208 rows) 12.4 / 13.6.  Beyond, tickets and stealing
@@ -1573,7 +1598,7 @@ int run(const void* Q, const void* K, const void* V, const uint8_t* cache_flags,
   // 127 / 140; with a mask at 90 % keep 114 / 122, at 50 % 79 / 70).
   const bool symbols = cache_flags != nullptr || kv_mask != nullptr;
   int mode = kQueues;
-  if (!plan && kv_mask && s.nw32 <= kSortWords && s.N > cus && s.N <= kXcds * kSortRows && 4LL * s.N <= 9LL * room(kSorted))
+  if (!plan && kv_mask && s.nw32 <= kSortWords && s.N > cus && s.N <= kXcds * kSortRows && 4LL * s.N <= 9LL * std::min(room(kSorted), 8 * cus / (bq / 32)))
     mode = kSorted;
   else if (!plan && s.nw32 <= 64 && s.N <= (symbols ? 1 : 2) * room(kDealt))
     mode = kDealt;
