@@ -655,8 +655,8 @@ __global__ void __launch_bounds__(BQ * 2, attn_waves_per_simd(D, MODE)) attn_ker
       if (r < rows) {
         const unsigned flag = p.raw_flags ? p.raw_flags[row0 + r] : 0u;
         // rows start at any byte: aligned words, shifted together; only words that hold a byte of the row are read
-        const uint8_t* src = p.raw_mask ? p.raw_mask + (size_t)(row0 + r) * p.raw_row_bytes : (const uint8_t*)p.Q;
-        const int skew = p.raw_mask ? (int)((uintptr_t)src & 3) : 0;
+        const uint8_t* src = p.raw_mask + (size_t)(row0 + r) * p.raw_row_bytes;      // (these calls have a mask)
+        const int skew = (int)((uintptr_t)src & 3);
         const uint32_t* aligned = (const uint32_t*)(src - skew);
         const int last = (skew + p.raw_row_bytes - 1) / 4;
         uint32_t low = aligned[0];
@@ -665,7 +665,7 @@ __global__ void __launch_bounds__(BQ * 2, attn_waves_per_simd(D, MODE)) attn_ker
         for (int w = 0; w < kSortWords; ++w) {
           const uint32_t high = aligned[min(w + 1, last)];
           uint32_t word = (uint32_t)(((unsigned long long)high << 32 | low) >> (8 * skew));
-          word = p.raw_mask ? __builtin_bswap32(__brev(word)) : ~0u;       // most significant bit first inside each byte
+          word = __builtin_bswap32(__brev(word));       // most significant bit first inside each byte
           word = w < p.nw32 ? clear_padding(word, w, p.Tkv) : 0u;
           sort_words[r * kSortWords + w] = word;
           count += __popc(word);
@@ -712,7 +712,6 @@ __global__ void __launch_bounds__(BQ * 2, attn_waves_per_simd(D, MODE)) attn_ker
         copy_end = by_idle;
       }
       rest_at = by_idle + (idle ? slot : W - 1 - slot);
-      n_list = rows;
     } else {
       n_list = n_computed;
       rest_at = rows;
