@@ -103,7 +103,8 @@ constexpr int kCachedBucket = kLongBuckets + kFineBuckets;   // one lane each in
 // for them a long row is one of two thirds of a share instead of one third, which is the better line for nearly equal
 // rows and the worse one for some skewed masks (24 heads, 9001 tokens, 64 x 128 blocks, us, line at two thirds / one
 // third: the ragged mask at 40 % keep 225 / 235, a tenth of the rows at 90 % and the others at 10 % 164 / 169, a fifth at 50 % and
-// the others at 10 % 166 / 143).
+// the others at 10 % 166 / 143).  128-row blocks of 64 channels run 96, and are not better off with a line for these (64 / 96: 9001
+// tokens, 40 % keep, 25 % cached 198 / 196, 7500 tokens, 90 % keep 359 / 369, 16000 tokens 367 / 371, 33024 tokens 1649 / 1648).
 constexpr int kWgsPerXcd = 64;
 constexpr int kCusPerXcd = 32;
 constexpr int kXcds = 8;               // accelerator dies (XCDs) of the MI355X, each with its own L2
@@ -701,8 +702,10 @@ __global__ void __launch_bounds__(BQ * 2, attn_waves_per_simd(D, MODE)) attn_ker
     if (slot >= W) {
       list_at = rest_at = rows;
     } else if (p.n_terms > 0 || p.do_copy) {
-      // Cached rows: workgroups without a computed one take some each, as many as fit beside the longest computed row
-      // (moving a row takes about as long as three blocks of it); the others are dealt to all.
+      // Cached rows: workgroups without a computed one take some each, as many as fit beside the longest computed row; the others
+      // are dealt to all.  Moving a row is taken to last as long as three blocks of one; a call's time is the same for one to
+      // three and grows beyond (24 heads, us, 1 / 3 / 6 / 12 blocks: 4608 tokens, 30 % keep, 56 % cached 50.8 / 50.9 / 50.7 / 54.7; 6000,
+      // 20 % and 90 % 48.5 / 48.5 / 49.7 / 52.5; 64 channels, 64-row blocks, 4608, 10 % and 90 % 26.0 / 26.0 / 27.2 / 28.0).
       const int cached = rows - n_computed, idle = max(0, W - n_computed);
       const int each = max(1, (int)(__builtin_amdgcn_readfirstlane((int)sort_list[0]) >> 16) / 3);
       const int by_idle = min(cached, idle * each);
