@@ -52,6 +52,19 @@ class DeviceCase:
         return (down_bits(O), res) if timed else down_bits(O)
 
 
+def prepass_ran(case):
+    """Whether the one-shot call of this case orders its rows in a kernel in front (which writes the work list and the decoded
+    symbols to the workspace) or leaves that to the attention kernel (dealt or sorted rows: the workspace stays as it is)."""
+    w = case.w
+    need = pkg.sparse_attn_workspace_bytes(w.B, w.H, w.L, w.block_q, w.block_k)
+    ws = torch.full((need + 256,), 0xAB, dtype=torch.uint8, device=dev())
+    base = (-ws.data_ptr()) % 256
+    pkg.sparse_attn_fwd_workspace(case.Q, case.K, case.V, case.flags, case.mask, case.Oc, torch.empty_like(case.Q), w.block_q,
+                                  w.block_k, ws[base:base + need])
+    torch.cuda.synchronize()
+    return bool((ws != 0xAB).any())
+
+
 def oracle_full(w):
     mask = None if w.M_s is None else oracle.pack_symbols(w.M_s)
     return oracle.sparse_attention(w.Q, w.K, w.V, w.cache_flags, mask, w.O_cache, w.block_q, w.block_k)

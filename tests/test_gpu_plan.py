@@ -7,7 +7,7 @@ import torch
 import oracle
 import paper_2509_25401_amd as pkg
 from paper_2509_25401_amd import synth
-from gpu_utils import DeviceCase, dev, up_bf16, up_u8, down_bits, oracle_full, check_against_oracle
+from gpu_utils import DeviceCase, dev, up_bf16, up_u8, down_bits, oracle_full, check_against_oracle, prepass_ran
 
 pytestmark = pytest.mark.gpu
 
@@ -121,7 +121,8 @@ def test_plan_without_symbols_is_dense_attention_and_skips_the_prepass_time():
 def test_caller_supplied_workspace_and_scratch_release():
     """sparse_attn_fwd_workspace writes the bits of the one-shot call using only the caller's buffer (a buffer one
     byte short is refused); releasing the library's scratch of the stream leaves the next one-shot call working."""
-    w = synth.random_case(synth.BASE_SEED + 97, 2, 3, 1100, 128, 128, 64, keep=0.5, cached_frac=0.3)
+    # 1112 rows of five words: more than the attention kernel sees to itself, so the pre-pass fills the buffer
+    w = synth.random_case(synth.BASE_SEED + 97, 2, 4, 8833, 64, 64, 64, keep=0.1, cached_frac=0.3)
     case = DeviceCase(w)
     want = case.run()
     need = pkg.sparse_attn_workspace_bytes(w.B, w.H, w.L, w.block_q, w.block_k)
@@ -132,6 +133,7 @@ def test_caller_supplied_workspace_and_scratch_release():
                                   ws[base:base + need])
     torch.cuda.synchronize()
     assert (down_bits(O) == want).all()
+    assert (ws[base:base + need] != 0xAB).any(), "the call did without the workspace"
     assert (ws[base + need:] == 0xAB).all() and (ws[:base] == 0xAB).all(), "wrote outside the workspace"
     with pytest.raises(pkg.SparseAttnError):
         pkg.sparse_attn_fwd_workspace(case.Q, case.K, case.V, case.flags, case.mask, case.Oc, O, w.block_q, w.block_k,
@@ -141,32 +143,38 @@ def test_caller_supplied_workspace_and_scratch_release():
     assert (case.run() == want).all()
 
 
-# (B, H, L, D, block_q, block_k, keep or None for no mask, cached share): rows around what the chip runs at a time
-# (512 workgroups, 1024 for 64-row blocks of 64 channels), fewer rows than queues, heads that do not fill the queues
+# (B, H, L, D, block_q, block_k, keep or None for no mask, cached share, one-shot route): rows around what the chip runs at a
+# time (512 workgroups, 1024 for 64-row blocks of 64 channels) and around where the one-shot call changes its way to hand them
+# out, fewer rows than queues, heads that do not fill the queues
 ROUTES = [
-    (1, 1, 50, 64, 64, 64, None, 0.0),
-    (1, 5, 130, 128, 128, 64, 0.6, 0.3),
-    (1, 9, 2100, 64, 64, 64, 0.3, 0.3),
-    (2, 24, 1344, 64, 64, 64, 0.4, 0.4),       # 1008 rows: dealt out
-    (2, 24, 1400, 64, 64, 64, 0.4, 0.4),       # 1056 rows: work list
-    (1, 31, 2100, 128, 128, 128, 0.3, 0.0),    # 527 rows: work list, queues of three and four heads
-    (1, 31, 2100, 128, 128, 128, None, 0.0),   # 527 equal rows: dealt out, some workgroups take two
-    (1, 31, 4300, 64, 128, 128, None, 0.0),    # 1054 equal rows: work list
-    (1, 17, 4300, 64, 128, 128, None, 0.5),    # flags alone
-    (1, 24, 1409, 128, 64, 64, None, 0.0),     # 288 blocks of 128 rows: done in 256-row blocks whatever the caller's
-    (2, 30, 2500, 128, 128, 128, None, 0.0),   # 600 blocks of 256 rows: some workgroups take three
-    (1, 2, 8300, 64, 64, 64, 0.1, 0.2),        # five words a row, 130 bits in rows of 17 bytes
-    (1, 24, 1330, 128, 64, 128, 0.4, 0.0),     # 504 rows of 64 x 128 channels: 64-key sub-tiles
-    (1, 24, 2040, 128, 64, 64, 0.4, 0.3),      # 768, some cached: the same, one round and a half
-    (1, 24, 2050, 128, 64, 64, 0.4, 0.3),      # 792: 32-key sub-tiles
-    (1, 1, 33100, 64, 64, 64, 0.04, 0.2),      # 518 rows of 17 words in one queue: decoded by a kernel of its own
+    (1, 1, 50, 64, 64, 64, None, 0.0, "dealt"),
+    (1, 5, 130, 128, 128, 64, 0.6, 0.3, "dealt"),
+    (1, 9, 2100, 64, 64, 64, 0.3, 0.3, "sorted"),
+    (2, 24, 1344, 64, 64, 64, 0.4, 0.4, "sorted"),       # 1008 rows
+    (2, 24, 1400, 64, 64, 64, 0.4, 0.4, "sorted"),       # 1056 rows
+    (1, 31, 2100, 128, 128, 128, 0.3, 0.0, "sorted"),    # 527 rows
+    (1, 31, 2100, 128, 128, 128, None, 0.0, "dealt"),    # 527 equal rows: some workgroups take two
+    (1, 31, 4300, 64, 128, 128, None, 0.0, "list"),      # 1054 equal rows
+    (1, 17, 4300, 64, 128, 128, None, 0.5, "list"),      # flags alone
+    (1, 24, 1409, 128, 64, 64, None, 0.0, "dealt"),      # 288 blocks of 128 rows: done in 256-row blocks whatever the caller's
+    (2, 30, 2500, 128, 128, 128, None, 0.0, "list"),     # 600 blocks of 256 rows: some workgroups take three
+    (1, 2, 8300, 64, 64, 64, 0.1, 0.2, "dealt"),         # five words a row, 130 bits in rows of 17 bytes
+    (1, 16, 8300, 64, 64, 64, 0.05, 0.2, "list"),        # 2080 such rows: five words are too many to sort
+    (2, 24, 3100, 64, 64, 64, 0.3, 0.3, "list"),         # 2352 rows: too many to sort
+    (1, 24, 6300, 64, 128, 64, 0.2, 0.3, "list"),        # 1200 rows of 128: more than two and a quarter per workgroup
+    (1, 25, 6017, 128, 128, 128, 0.2, 0.2, "list"),      # 1200, queues of three and four heads, one row in the last block
+    (1, 24, 1330, 128, 64, 128, 0.4, 0.0, "sorted"),     # 504 rows of 64 x 128 channels: 64-key sub-tiles
+    (1, 24, 2040, 128, 64, 64, 0.4, 0.3, "sorted"),      # 768, some cached: the same, one round and a half
+    (1, 24, 2050, 128, 64, 64, 0.4, 0.3, "sorted"),      # 792: 32-key sub-tiles
+    (2, 22, 3100, 128, 64, 64, 0.1, 0.3, "list"),        # 2156
+    (1, 1, 33100, 64, 64, 64, 0.04, 0.2, "dealt"),       # 518 rows of 17 words; the plan decodes them in a kernel of its own
 ]
 
 
-@pytest.mark.parametrize("B,H,L,D,bq,bk,keep,cached", ROUTES)
-def test_dealt_rows_and_work_list_agree(B, H, L, D, bq, bk, keep, cached):
-    """The one-shot call deals few rows out by workgroup number and decodes them in place; a stored plan always walks
-    the work list.  Same rows, same bits; the symbols start at an odd byte."""
+@pytest.mark.parametrize("B,H,L,D,bq,bk,keep,cached,route", ROUTES)
+def test_dealt_rows_and_work_list_agree(B, H, L, D, bq, bk, keep, cached, route):
+    """The one-shot call deals few rows out by workgroup number or sorts them in its workgroups, and decodes them in place;
+    beyond, and in a stored plan, they go through the work list.  Same rows, same bits; the symbols start at an odd byte."""
     print(f"[case] routes B={B} H={H} L={L} D={D} {bq}x{bk} keep={keep} cached={cached}", flush=True)
     w = synth.random_case(synth.BASE_SEED + 120 + L, B, H, L, D, bq, bk, keep=1.0 if keep is None else keep,
                           cached_frac=cached, with_cache_tensor=True)
@@ -181,6 +189,7 @@ def test_dealt_rows_and_work_list_agree(B, H, L, D, bq, bk, keep, cached):
         odd.copy_(case.mask)
         case.mask = odd
     got = case.run()
+    assert prepass_ran(case) == (route == "list")
     plan = pkg.SparseAttnPlan(case.flags, case.mask, w.B, w.H, w.L, bq, bk)
     for rep in range(3):
         O = fresh_O(w)
@@ -274,17 +283,19 @@ def test_symbols_decoded_in_front_of_the_queues(n):
     assert empty.any() and (down_bits(O)[empty] == 0).all()
 
 
-@pytest.mark.parametrize("D,bk", [(64, 64), (128, 128)])
-def test_skewed_rows_of_64_row_blocks(D, bk):
+@pytest.mark.parametrize("D,bk,L", [(64, 64, 2900), (128, 128, 2900),       # 1104 rows: sorted by the workgroups
+                                    (64, 64, 5500), (128, 128, 5500)])      # 2064: work list
+def test_skewed_rows_of_64_row_blocks(D, bk, L):
     """A tenth of the rows keeps nine tenths of the key blocks, the others 5 %: long rows, fine buckets and a queue whose
     grid has four workgroups per CU.  Every block once, same bits as the plan's."""
-    B, H, L, bq = 1, 24, 2900, 64                                  # 1104 rows: work list
+    B, H, bq = 1, 24, 64
     w = synth.random_case(synth.BASE_SEED + 360 + D, B, H, L, D, bq, bk, keep=1.0, cached_frac=0.1)
     rng = np.random.default_rng(synth.BASE_SEED + 361 + D)
     p = np.where(rng.random((B, H, w.M_s.shape[2], 1)) < 0.1, 0.9, 0.05)
     w.M_s = (rng.random(w.M_s.shape) < p).astype(w.M_s.dtype)
     case = DeviceCase(w)
     got = case.run()
+    assert prepass_ran(case) == (L == 5500)
     plan = pkg.SparseAttnPlan(case.flags, case.mask, B, H, L, bq, bk)
     O = fresh_O(w)
     plan.run(case.Q, case.K, case.V, case.Oc, O)

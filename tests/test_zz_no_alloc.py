@@ -9,7 +9,7 @@ import torch
 
 import paper_2509_25401_amd as pkg
 from paper_2509_25401_amd import synth
-from gpu_utils import DeviceCase, dev, down_bits, oracle_full, check_against_oracle
+from gpu_utils import DeviceCase, dev, down_bits, oracle_full, check_against_oracle, prepass_ran
 
 pytestmark = pytest.mark.gpu
 
@@ -35,10 +35,12 @@ def _fresh(w, fill):
 
 def test_no_alloc_entry_point_matches_the_allocating_one_twice_in_a_row():
     lib = pkg.load_library()
-    big = synth.random_case(synth.BASE_SEED + 701, 2, 3, 1664, 128, 128, 128, keep=0.4, cached_frac=0.3)
-    small = synth.random_case(synth.BASE_SEED + 702, 1, 2, 600, 64, 64, 128, keep=0.6, cached_frac=0.25)
+    big = synth.random_case(synth.BASE_SEED + 701, 2, 4, 8833, 64, 64, 64, keep=0.05, cached_frac=0.3)    # 1112 rows of five words
+    small = synth.random_case(synth.BASE_SEED + 702, 1, 17, 4300, 64, 128, 128, cached_frac=0.5)           # 578 rows, flags alone
+    small.M_s = None
     for label, w in (("first call", big), ("second, smaller call", small)):
         case = DeviceCase(w)
+        assert prepass_ran(case), "the call does without scratch memory"
         want = _call(lib.sparse_attn_fwd_stream, case, _fresh(w, 0x4242))
         got = _call(lib.sparse_attn_fwd_noalloc, case, _fresh(w, 0x4242))
         assert (got == want).all(), f"{label}: output differs from sparse_attn_fwd_stream"
