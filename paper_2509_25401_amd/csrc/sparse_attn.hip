@@ -10,7 +10,7 @@
 //               its K/V stream through one L2): rows that are a large part of a workgroup's
 //               share first (longest first), the others head by head and heaviest first inside a
 //               head (55 kept-count buckets), cached rows (plain copies) last;
-//   attn        a persistent grid that fills the CUs (two workgroups of 128 query rows each) pulls items
+//   attn        a persistent grid that fills the CUs (two workgroups of 128 query rows each, three with 64 channels) pulls items
 //               from its XCD's queue and steals from the others when that is drained.  A compute item is one query block:
 //               Q lives in registers as stored (the 1/sqrt(D) scale is applied to the fp32 score),
 //               the reduction-axis symbol is walked with scalar find-first-set on the decoded words, and only kept
@@ -458,7 +458,8 @@ __device__ __forceinline__ unsigned sa_lane0_atomic_inc_wrap(uint32_t* counter, 
   return value;
 }
 // The lane number, formed where it is needed: offsets that follow from it are then not computed once, in front of the item
-// loop, to occupy registers for the whole kernel (the headline instance: 240 vector registers -> 224).
+// loop, to occupy registers for the whole kernel (the instance for 33024 tokens of 128 channels takes 229 vector registers; with the
+// lane number computed once it takes all 256 and spills 13).
 __device__ __forceinline__ int sa_fresh_lane() {
   int ln;
   asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
