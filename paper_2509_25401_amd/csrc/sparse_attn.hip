@@ -94,7 +94,7 @@ constexpr int kSortLds = kSortRows * 4 * 2 + kSortRows * kSortWords * 4 + 16;   
 // Wavefronts per SIMD that the registers are laid out for.  64 channels leave room for three (168 registers, no spill), which
 // 128-row blocks use (three workgroups of 32 KiB LDS per CU; 24 heads, us, two / three: 9001 tokens dense 577 / 552, 33024
 // tokens at 25 % keep 1745 / 1681; in sorted calls see `W`); of the 64-row workgroups LDS holds four, two wavefronts per SIMD,
-// either way.  Dealt instances take up to 170 registers and would spill.
+// either way.  Dealt instances take up to 172 registers and would spill.
 constexpr int attn_waves_per_simd(int D, int mode) { return D == 64 && mode != kDealt ? 3 : 2; }
 constexpr int kLongBuckets = 8;       // kept-count buckets of the long rows of a queue (longest first, across heads)
 constexpr int kFineBuckets = 55;      // ... of its other rows (head by head); with the bucket of cached rows: 64,
@@ -1588,13 +1588,14 @@ int run(const void* Q, const void* K, const void* V, const uint8_t* cache_flags,
   // all rows are equally long, so with up to two per workgroup dealing them out by number does as well.  Every
   // workgroup then decodes its own rows (at most 64 words each).  512 tokens, two heads of 64: 20.1 -> 12.3 us; 4608
   // tokens, 24 heads, dense: 273 -> 261 us.
-  // None either where the rows differ and there are between one per CU and two and a quarter per workgroup (two waves on a SIMD): the workgroups
-  // sort them.  24 heads, us, queues or dealt / sorted: 4608 tokens, 30 % keep, 56 % cached 56.1 / 50.5; 64 channels, 64-row
-  // blocks, 40 % cached 48.4 / 37.2; 6000 tokens (1128 rows on 512 workgroups), 20 % keep 106 / 99, 70 % 312 / 300; 1200
-  // tokens in 64-row blocks (456 rows) 18.0 / 16.3; 16 heads of 777 tokens (208 rows) 12.4 / 13.6.  Beyond, tickets and stealing
-  // balance better (7500 tokens, 1416 rows, 40 % keep, 30 % cached 199 / 203; 10500 tokens, 60 % cached 190 / 200), and so they
-  // do without a mask, where a row too many for the workgroups of one XCD is a whole row (64 channels, 4608 tokens, 40 % cached
-  // 127 / 140; with a mask at 90 % keep 114 / 122, at 50 % 79 / 70).
+  // None either where the rows differ and there are between one per CU and two and a quarter per workgroup (counted with two
+  // waves on a SIMD): the workgroups sort them.  24 heads, us, queues or dealt / sorted: 4608 tokens, 30 % keep, 56 % cached
+  // 56.1 / 50.5; 64 channels, 64-row blocks, 40 % cached 48.4 / 37.2; 6000 tokens (1128 rows on 512 workgroups), 20 % keep
+  // 106 / 99, 70 % 312 / 300; 1200 tokens in 64-row blocks (456 rows) 18.0 / 16.3; 16 heads of 777 tokens (208 rows) 12.4 /
+  // 13.6.  Beyond, tickets and stealing balance better (7500 tokens, 1416 rows, 40 % keep, 30 % cached 199 / 203; 10500 tokens,
+  // 60 % cached 190 / 200), and so they do without a mask, where a row too many for the workgroups of one XCD is a whole row (64
+  // channels, 4608 tokens, 40 % cached 127 / 140).  Measured before the last round was turned around (early_of); with it none of
+  // 60 calls over the range was slower sorted than through the list.
   const bool symbols = cache_flags != nullptr || kv_mask != nullptr;
   int mode = kQueues;
   if (!plan && kv_mask && s.nw32 <= kSortWords && s.N > cus && s.N <= kXcds * kSortRows && 4LL * s.N <= 9LL * std::min(room(kSorted), 8 * cus / (bq / 32)))
