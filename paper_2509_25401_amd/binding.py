@@ -116,7 +116,7 @@ def _raise(code):
 # The calls below are a few microseconds of argument marshalling each, which is what a short call costs: addresses go
 # to ctypes as plain integers, devices are compared as objects, and the current stream is asked for without building a
 # Stream object (512-token attention call: 8 us of Python, then 4).  The one-shot attention call first takes its arguments
-# for valid (_fwd_args_valid: 2.6 us in all; call after call 8.6 -> 7.2 us, of which the launch is 2.4).
+# for valid (_fwd_args_valid: 3.4 -> 2.0 us; call after call 8.0 -> 6.6 us on the same machine, of which the launch is 2.4).
 def _dev_ptr(t, name, allow_none=False):
     if t is None:
         if allow_none:
