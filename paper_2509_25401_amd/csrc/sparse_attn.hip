@@ -93,7 +93,8 @@ constexpr int kSortLds = kSortRows * 4 * 2 + kSortRows * kSortWords * 4 + 16;   
 
 // Wavefronts per SIMD that the registers are laid out for.  64 channels leave room for three (168 registers, no spill), which
 // 128-row blocks use (three workgroups of 32 KiB LDS per CU; 24 heads, us, two / three: 9001 tokens dense 577 / 552, 33024
-// tokens at 25 % keep 1745 / 1681; in sorted calls see `W`); of the 64-row workgroups LDS holds four, two wavefronts per SIMD,
+// tokens at 25 % keep 1745 / 1681; sorted calls, 4608 tokens, 90 % keep 148 / 135, 30 % 53 / 48; 8 heads of 12544 tokens, 90 % keep,
+// 388 / 345; 24 calls of 97 to 141 rows per XCD: none slower); of the 64-row workgroups LDS holds four, two wavefronts per SIMD,
 // either way.  Dealt instances take up to 172 registers and would spill.
 constexpr int attn_waves_per_simd(int D, int mode) { return D == 64 && mode != kDealt ? 3 : 2; }
 constexpr int kLongBuckets = 8;       // kept-count buckets of the long rows of a queue (longest first, across heads)
@@ -540,7 +541,6 @@ __device__ __forceinline__ int v_swizzle(int row) {
 template <int D, int BQ, int BK, int KEYS, bool RAGGED, int MODE>
 __global__ void __launch_bounds__(BQ * 2, attn_waves_per_simd(D, MODE)) attn_kernel(const AttnParams p) {
   constexpr bool DEALT = MODE == kDealt, SORTED = MODE == kSorted;
-  constexpr bool kThreePerCu = SORTED && BQ == 128 && attn_waves_per_simd(D, kSorted) == 3;
   constexpr int NWAVES = BQ / 32;
   constexpr int NT = NWAVES * 64;
   constexpr int SUB = BK / KEYS;           // LDS sub-tiles per symbol bit
@@ -625,7 +625,7 @@ __global__ void __launch_bounds__(BQ * 2, attn_waves_per_simd(D, MODE)) attn_ker
     const bool back = (slot / kCusPerXcd) % 2 == 0 && chunk + kCusPerXcd <= nwg(q0);
     return back ? 2 * chunk + kCusPerXcd - 1 - slot : slot;
   };
-  int W = 0;                           // SORTED: workgroups of this XCD that take rows
+  int W = 0;                           // SORTED: workgroups of this XCD
   // SORTED.  After the first round the rows go to the workgroups from the end, the shortest row's first, except in a last round
   // that does not reach all of them: there to those launched first, whose waves issue first and which are done first, while the
   // others still run.  Of four two-wave workgroups on a CU each shares a SIMD with the one launched before it and one with the one
@@ -688,17 +688,9 @@ __global__ void __launch_bounds__(BQ * 2, attn_waves_per_simd(D, MODE)) attn_ker
     __syncthreads();
     n_list = rows;
     n_computed = __builtin_amdgcn_readfirstlane((int)*sort_computed);
-    // Three workgroups on a CU as long as none has a second row, else two, where the second round is fuller (64 channels,
-    // 128-row blocks, 24 heads, us, two / three: 4000 tokens, 90 % keep 115 / 102; 4608, 90 % and 40 % cached 116 / 98; 90 % and none
-    // cached 146 / 152; 6000, 70 % 183 / 192).
     W = nwg(q0);
-    if constexpr (kThreePerCu) {
-      if (n_computed > W) W = min(W, 2 * kCusPerXcd);
-    }
     list_at = first_of(q0, slot);
-    if (slot >= W) {
-      list_at = rest_at = rows;
-    } else if (p.n_terms > 0 || p.do_copy) {
+    if (p.n_terms > 0 || p.do_copy) {
       // Cached rows: workgroups without a computed one take some each, as many as fit beside the longest computed row; the others
       // are dealt to all.  Moving a row is taken to last as long as three blocks of one; a call's time is the same for one to
       // three and grows beyond (24 heads, us, 1 / 3 / 6 / 12 blocks: 4608 tokens, 30 % keep, 56 % cached 50.8 / 50.9 / 50.7 / 54.7; 6000,
@@ -1594,8 +1586,8 @@ int run(const void* Q, const void* K, const void* V, const uint8_t* cache_flags,
   // 106 / 99, 70 % 312 / 300; 1200 tokens in 64-row blocks (456 rows) 18.0 / 16.3; 16 heads of 777 tokens (208 rows) 12.4 /
   // 13.6.  Beyond, tickets and stealing balance better (7500 tokens, 1416 rows, 40 % keep, 30 % cached 199 / 203; 10500 tokens,
   // 60 % cached 190 / 200), and so they do without a mask, where a row too many for the workgroups of one XCD is a whole row (64
-  // channels, 4608 tokens, 40 % cached 127 / 140).  Measured before the last round was turned around (early_of); with it none of
-  // 60 calls over the range was slower sorted than through the list.
+  // channels, 4608 tokens, 40 % cached 127 / 140).  Measured before the last round was turned around (early_of); with it, 60 calls
+  // of 65 to 249 rows per XCD, 10 to 90 % keep, up to 90 % cached and both channel counts take 0.67 to 1.002 of the list's time.
   const bool symbols = cache_flags != nullptr || kv_mask != nullptr;
   int mode = kQueues;
   if (!plan && kv_mask && s.nw32 <= kSortWords && s.N > cus && s.N <= kXcds * kSortRows && 4LL * s.N <= 9LL * std::min(room(kSorted), 8 * cus / (bq / 32)))

@@ -22,8 +22,8 @@ pytestmark = pytest.mark.gpu
     (128, 64, 128, 2, 11, 2049, 0.5, 0.9),      # one token in the last block, nearly everything cached
     (64, 128, 64, 1, 20, 4000, 0.3, 0.1),
     (64, 128, 128, 1, 24, 4000, 0.3, 0.0),      # 96 rows per XCD: one for each of three workgroups per CU
-    (64, 128, 128, 1, 24, 4608, 0.3, 0.04),     # some 104 computed rows: two workgroups per CU, the third ones take no cached rows
-    (64, 128, 64, 1, 24, 6000, 0.2, 0.0),       # 141 rows on 64 workgroups: the last of three rounds is a part
+    (64, 128, 128, 1, 24, 4608, 0.3, 0.04),     # some 104 computed rows: the first eight or so workgroups have a second one
+    (64, 128, 64, 1, 24, 6000, 0.2, 0.0),       # 141 rows: nearly half of the 96 have a second one
     (64, 64, 128, 1, 24, 3584, 0.3, 0.0),       # 168 rows on 128 workgroups: the last round on the first and third of a CU
     (64, 64, 64, 1, 24, 4608, 0.2, 0.0),        # 216 rows: the last round from the end
     (128, 64, 64, 1, 24, 3584, 0.3, 0.0),
