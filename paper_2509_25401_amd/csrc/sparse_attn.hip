@@ -1587,7 +1587,7 @@ int run(const void* Q, const void* K, const void* V, const uint8_t* cache_flags,
   // 13.6.  Beyond, tickets and stealing balance better (7500 tokens, 1416 rows, 40 % keep, 30 % cached 199 / 203; 10500 tokens,
   // 60 % cached 190 / 200), and so they do without a mask, where a row too many for the workgroups of one XCD is a whole row (64
   // channels, 4608 tokens, 40 % cached 127 / 140).  Measured before the last round was turned around (early_of); with it, 60 calls
-  // of 65 to 249 rows per XCD, 10 to 90 % keep, up to 90 % cached and both channel counts take 0.67 to 1.002 of the list's time.
+  // of 39 to 250 rows per XCD, 10 to 90 % keep, up to 90 % cached and both channel counts take 0.67 to 1.002 of the list's time.
   const bool symbols = cache_flags != nullptr || kv_mask != nullptr;
   int mode = kQueues;
   if (!plan && kv_mask && s.nw32 <= kSortWords && s.N > cus && s.N <= kXcds * kSortRows && 4LL * s.N <= 9LL * std::min(room(kSorted), 8 * cus / (bq / 32)))
